@@ -480,7 +480,7 @@ static kt_status resolve_weights(const kt_plan *p, const float *weights, int K, 
 // Shared by pack and unpack: validate, build [tensor ptrs | bucket ptrs], stage.
 static kt_status prepare_tensor_call(kt_plan *p, int bucket, const void *const *tensor_ptrs,
                                      const void *const *bucket_bufs, const char *who, hipStream_t stream,
-                                     int64_t *tile0, int64_t *ntiles, bool *vector_ok, PtrSlot **slot)
+                                     int64_t *tile0, int64_t *ntiles, PtrSlot **slot)
 {
     if (!p) { kt_set_error("%s: NULL plan", who); return KT_EINVAL; }
     int b0, b1;
@@ -497,12 +497,10 @@ static kt_status prepare_tensor_call(kt_plan *p, int bucket, const void *const *
     std::vector<uint64_t> &vals = call_table(T + nb);
     for (size_t t = 0; t < T; ++t) vals[t] = reinterpret_cast<uintptr_t>(tensor_ptrs[t]);
     for (size_t b = 0; b < nb; ++b) vals[T + b] = reinterpret_cast<uintptr_t>(bucket_bufs[b]);
-    bool vec = hp.align_bytes % KT_VEC_BYTES == 0;
     for (int b = b0; b < b1; ++b) {
         const uintptr_t bp = reinterpret_cast<uintptr_t>(bucket_bufs[b]);
         if (hp.b_elems[b] > 0 && !bp) { kt_set_error("%s: NULL buffer for bucket %d", who, b); return KT_EINVAL; }
         if (bp & emask) { kt_set_error("%s: bucket %d buffer not aligned to the element size", who, b); return KT_EALIGN; }
-        if (bp & (KT_VEC_BYTES - 1)) vec = false;
         for (int t = hp.b_first[b]; t < hp.b_first[b] + hp.b_count[b]; ++t) {
             const uintptr_t tp = reinterpret_cast<uintptr_t>(tensor_ptrs[t]);
             if (hp.t_numel[t] > 0 && !tp) { kt_set_error("%s: NULL pointer for tensor %d", who, t); return KT_EINVAL; }
@@ -512,7 +510,6 @@ static kt_status prepare_tensor_call(kt_plan *p, int bucket, const void *const *
             if (tn && tp < bp + bn && bp < tp + tn) { kt_set_error("%s: tensor %d overlaps bucket %d", who, t, b); return KT_EINVAL; }
         }
     }
-    *vector_ok = vec;
     st = ensure_device(p, stream);
     if (st != KT_OK) return st;
     return stage_pointers(p, vals.data(), vals.size(), stream, slot);
@@ -526,14 +523,13 @@ extern "C" kt_status kt_bucket_pack(kt_plan *p, int bucket, const void *const *t
     std::lock_guard<std::mutex> lock(p->mu);
     hipStream_t s = static_cast<hipStream_t>(stream);
     int64_t tile0 = 0, ntiles = 0;
-    bool vec = false;
     PtrSlot *slot = nullptr;
-    kt_status st = prepare_tensor_call(p, bucket, tensor_ptrs, bucket_bufs, "kt_bucket_pack", s, &tile0, &ntiles, &vec, &slot);
+    kt_status st = prepare_tensor_call(p, bucket, tensor_ptrs, bucket_bufs, "kt_bucket_pack", s, &tile0, &ntiles, &slot);
     if (st != KT_OK || ntiles == 0) return st;
     const size_t T = p->hp.t_numel.size();
     const void *const *d_t = static_cast<const void *const *>(slot->dev);
     void *const *d_b = reinterpret_cast<void *const *>(static_cast<uint64_t *>(slot->dev) + T);
-    int e = kt_launch_pack(p->tb, p->hp.dt, tile0, ntiles, d_t, d_b, vec, stream);
+    int e = kt_launch_pack(p->tb, p->hp.dt, tile0, ntiles, d_t, d_b, stream);
     if (e != 0) return hip_fail("kt_bucket_pack: launch", (hipError_t)e);
     return mark_used(p, slot, s);
     KT_GUARD_END("kt_bucket_pack")
@@ -547,14 +543,13 @@ extern "C" kt_status kt_bucket_unpack_scale(kt_plan *p, int bucket, const void *
     std::lock_guard<std::mutex> lock(p->mu);
     hipStream_t s = static_cast<hipStream_t>(stream);
     int64_t tile0 = 0, ntiles = 0;
-    bool vec = false;
     PtrSlot *slot = nullptr;
-    kt_status st = prepare_tensor_call(p, bucket, tensor_ptrs, bucket_bufs, "kt_bucket_unpack_scale", s, &tile0, &ntiles, &vec, &slot);
+    kt_status st = prepare_tensor_call(p, bucket, tensor_ptrs, bucket_bufs, "kt_bucket_unpack_scale", s, &tile0, &ntiles, &slot);
     if (st != KT_OK || ntiles == 0) return st;
     const size_t T = p->hp.t_numel.size();
     void *const *d_t = static_cast<void *const *>(slot->dev);
     const void *const *d_b = reinterpret_cast<const void *const *>(static_cast<uint64_t *>(slot->dev) + T);
-    int e = kt_launch_unpack(p->tb, p->hp.dt, tile0, ntiles, d_b, scale, d_t, vec, stream);
+    int e = kt_launch_unpack(p->tb, p->hp.dt, tile0, ntiles, d_b, scale, d_t, stream);
     if (e != 0) return hip_fail("kt_bucket_unpack_scale: launch", (hipError_t)e);
     return mark_used(p, slot, s);
     KT_GUARD_END("kt_bucket_unpack_scale")

@@ -19,6 +19,13 @@
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+// The same vectors at any element address (2 bytes for bf16, 4 for binary32).  The HSA runtime
+// runs kernels in unaligned access mode, so one such access is one global_load/store_dwordx4 at
+// any address: a copy loses 1 % (4-byte) to 3.5 % (2-byte) to misaligned loads and 4 % to stores
+// that do not start on a 64-byte boundary (512 MiB copied: 6.45 TB/s aligned), where one element
+// per lane loses more than half.
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
+typedef u32x2 u32x2_any __attribute__((aligned(2)));
 
 namespace {
 
@@ -33,9 +40,9 @@ template <> struct Elem<uint16_t> { static constexpr int VE = 8; };
 
 __device__ __forceinline__ u32x4 ld_vec(const void *p)
 {
-    const KT_GLOBAL u32x4 *g = (const KT_GLOBAL u32x4 *)p;
+    const KT_GLOBAL u32x4_any *g = (const KT_GLOBAL u32x4_any *)p;
 #if KT_NT_LOAD == 2
-    return *(const volatile KT_GLOBAL u32x4 *)g;      // system scope (sc0 sc1), for measurement
+    return *(const volatile KT_GLOBAL u32x4_any *)g;      // system scope (sc0 sc1), for measurement
 #elif KT_NT_LOAD
     return __builtin_nontemporal_load(g);
 #else
@@ -45,9 +52,9 @@ __device__ __forceinline__ u32x4 ld_vec(const void *p)
 
 __device__ __forceinline__ void st_vec(void *p, u32x4 v)
 {
-    KT_GLOBAL u32x4 *g = (KT_GLOBAL u32x4 *)p;
+    KT_GLOBAL u32x4_any *g = (KT_GLOBAL u32x4_any *)p;
 #if KT_NT_STORE == 2
-    *(volatile KT_GLOBAL u32x4 *)g = v;                // system scope (sc0 sc1), for measurement
+    *(volatile KT_GLOBAL u32x4_any *)g = v;                // system scope (sc0 sc1), for measurement
 #elif KT_NT_STORE
     __builtin_nontemporal_store(v, g);
 #else
@@ -68,12 +75,61 @@ template <bool WT> __device__ __forceinline__ void st_vec_copy(void *p, u32x4 v)
 {
 #if KT_WT_STORE && KT_NT_STORE == 1
     if (WT) {
-        *(volatile KT_GLOBAL u32x4 *)p = v;
+        *(volatile KT_GLOBAL u32x4_any *)p = v;
         return;
     }
 #endif
     st_vec(p, v);
 }
+// The system-scope store of a tile's vectors as a buffer store (descriptor of `bytes` bytes from a
+// uniform base): unlike the volatile store it is not waited for, so a wavefront that has stored
+// ends at once and its place goes to the next.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(void *base, int bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(base, 0, bytes, 0x00020000);
+}
+__device__ __forceinline__ void st_tile_wt(__amdgpu_buffer_rsrc_t rs, int at, u32x4 v)
+{
+#if KT_WT_STORE && KT_NT_STORE == 1
+    __builtin_amdgcn_raw_buffer_store_b128(v, rs, at, 0, 1 | 16);       // sc0 sc1
+#else
+    __builtin_amdgcn_raw_buffer_store_b128(v, rs, at, 0, 2);            // nt
+#endif
+}
+// The same choice at run time.  The system-scope store wants whole 64-byte pieces: where a
+// wavefront's stores start elsewhere it costs 11 % of a copy's rate (5.8 TB/s against 6.58
+// aligned), the non-temporal store 4 % (6.28 against 6.45).
+__device__ __forceinline__ void st_vec_pick(void *p, u32x4 v, bool wt)
+{
+    if (wt) st_vec_copy<true>(p, v); else st_vec(p, v);
+}
+
+// ---- whole tiles at any address ------------------------------------------------
+// The vectors of a full tile are laid out from the destination's 64-byte boundary at or below
+// the tile's first byte, so that every store but the first and last of the tile fills whole
+// 64-byte pieces wherever the tensor lies; the loads then sit at any address, which costs far
+// less (see u32x4_any).  `pos` is a vector's byte position from that boundary and `o` the tile's
+// first byte (0..63): positions below `o` belong to the end of the tile, BYTES further on, which
+// keeps one vector per lane and the lane numbering.  Where `o` is no multiple of 16 one vector is
+// cut in two by the tile's ends; its VE elements are taken one by one (edge_elem).
+struct RotVec {
+    int at;       // byte offset of the vector from the tile's first byte
+    bool whole;   // false: the vector cut in two (`at` is then 0, in bounds)
+};
+template <int BYTES> __device__ __forceinline__ RotVec rot_vec(int pos, int o)
+{
+    RotVec r;
+    r.whole = pos >= o || pos + KT_VEC_BYTES <= o;
+    r.at = r.whole ? (pos >= o ? pos - o : pos + BYTES - o) : 0;
+    return r;
+}
+// Element q (0 <= q < 16 / es) of the cut vector as a byte offset from the tile's first byte.
+template <int BYTES> __device__ __forceinline__ int edge_elem(int q, int es, int o)
+{
+    const int pos = (o & ~(KT_VEC_BYTES - 1)) + q * es;
+    return pos >= o ? pos - o : pos + BYTES - o;
+}
+__device__ __forceinline__ int off64(const void *p) { return (int)(reinterpret_cast<uintptr_t>(p) & 63u); }
 
 // Holds a wave back until the store window opens (KtWindow).  Bounded twice over: the clock
 // always advances, so the condition comes true within one period (about 12 us), and the
@@ -130,18 +186,32 @@ template <> __device__ __forceinline__ u32x4 scale_vec<uint16_t>(u32x4 v, float 
     return r;
 }
 
+// The tables are constant while a kernel runs and every index into them is uniform over the
+// workgroup: read through the constant address space they are scalar loads whatever the compiler
+// can prove about the stores around them.
+#define KT_CONST __attribute__((address_space(4)))
+template <typename P> __device__ __forceinline__ P ld_table(const P *p) { return *(const KT_CONST P *)p; }
+__device__ __forceinline__ KtTile ld_tile(const KtTile *p)
+{
+    const u32x4 v = *(const KT_CONST u32x4 *)p;
+    return KtTile{(int32_t)v[0], v[1], (int32_t)v[2], (int32_t)v[3]};
+}
+// Makes a value exist in scalar registers at this point, so that the table loads of a tile are
+// issued together and waited for once: the way from the tile record to the first data load is
+// two dependent scalar loads (record; lengths and pointers) instead of four.
+__device__ __forceinline__ void pin(uint64_t a, uint64_t b, uint64_t c, uint64_t d) { asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d)); }
+
 struct TileGeom {
     int bucket;
     int64_t start;   // first element of the tile inside the bucket
     int64_t end;     // one past the last element (clipped to the bucket length)
 };
 
-__device__ __forceinline__ TileGeom tile_geom(const KtTile &tl, const int64_t *b_elems, int64_t tile_elems)
+__device__ __forceinline__ TileGeom tile_geom(const KtTile &tl, int64_t n, int64_t tile_elems)
 {
     TileGeom g;
     g.bucket = tl.bucket;
     g.start = (int64_t)tl.tile_in_bucket * tile_elems;
-    int64_t n = b_elems[tl.bucket];
     g.end = g.start + tile_elems < n ? g.start + tile_elems : n;
     return g;
 }
@@ -180,6 +250,67 @@ template <typename V> __device__ __forceinline__ int find_owner_v(const V &tv, i
         if (tv.off[mid] <= e) lo = mid + 1; else hi = mid;
     }
     return lo - 1;
+}
+
+// Calls f(q, i, r) for every element e0 + q (0 <= q < N) below `lim` that belongs to a tensor:
+// element r of the tile's i-th tensor.  `i` is the owner of e0 (find_owner_v).  Only the owner
+// search of successive elements depends on the one before; loads issued by f stay in flight.
+template <int N, typename V, typename F>
+__device__ __forceinline__ void each_owned(const V &tv, int nt, int i, int64_t e0, int64_t lim, F f)
+{
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+        const int64_t e = e0 + q;
+        while (i + 1 < nt && tv.off[i + 1] <= e) ++i;
+        if (i >= 0 && e < lim) {
+            const int64_t r = e - tv.off[i];
+            if (r < tv.numel[i]) f(q, i, r);
+        }
+    }
+}
+
+// VE elements held one per register <-> a 16-byte vector
+__device__ __forceinline__ u32x4 join(const float *x)
+{
+    return u32x4{__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(x[2]), __float_as_uint(x[3])};
+}
+__device__ __forceinline__ u32x4 join(const uint16_t *x)
+{
+    u32x4 r;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) r[c] = (uint32_t)x[2 * c] | ((uint32_t)x[2 * c + 1] << 16);
+    return r;
+}
+template <typename T> __device__ __forceinline__ T elem_of(u32x4 v, int q);
+template <> __device__ __forceinline__ float elem_of<float>(u32x4 v, int q) { return __uint_as_float(v[q]); }
+template <> __device__ __forceinline__ uint16_t elem_of<uint16_t>(u32x4 v, int q)
+{
+    return (uint16_t)(v[q >> 1] >> (16 * (q & 1)));
+}
+
+// The elements [e0, e0 + VE) of a vector that is not wholly inside one tensor, 0 where none owns one.
+template <typename T, typename V>
+__device__ __forceinline__ u32x4 gather_vec(const V &tv, int nt, int i, int64_t e0, int64_t lim)
+{
+    constexpr int VE = Elem<T>::VE;
+    T x[VE];
+#pragma unroll
+    for (int q = 0; q < VE; ++q) x[q] = 0;
+    each_owned<VE>(tv, nt, i, e0, lim, [&](int q, int t, int64_t r) { x[q] = ld_elem(reinterpret_cast<const T *>(tv.ptr[t]) + r); });
+    return join(x);
+}
+// A bucket's vector at e0 (bucket base b): whole, or, at the end of a densely packed bucket, its `lim - e0` elements.
+template <typename T> __device__ __forceinline__ u32x4 ld_bucket_vec(const T *b, int64_t e0, int64_t lim)
+{
+    constexpr int VE = Elem<T>::VE;
+    if (e0 + VE <= lim) return ld_vec(b + e0);
+    T x[VE];
+#pragma unroll
+    for (int q = 0; q < VE; ++q) {
+        x[q] = 0;
+        if (e0 + q < lim) x[q] = ld_elem(b + e0 + q);
+    }
+    return join(x);
 }
 
 // `second` may be NULL for kernels with one tensor set (ptr2 then mirrors ptr).

@@ -104,7 +104,7 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_kernel(KtDeviceTables tb, i
 
     const int part = SPLIT == 1 ? 0 : (int)(blockIdx.x % SPLIT);
     const KtTile tl = tb.tiles[tile0 + blockIdx.x / SPLIT];
-    const TileGeom g = tile_geom(tl, tb.b_elems, TILE_ELEMS);
+    const TileGeom g = tile_geom(tl, tb.b_elems[tl.bucket], TILE_ELEMS);
     const int tid = threadIdx.x;
 
     const T *x[KP];   // peers 1..K-1, already advanced to the tile start
@@ -227,7 +227,7 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_manyk_kernel(KtDeviceTables
     __shared__ LdsTable lds;
 
     const KtTile tl = tb.tiles[tile0 + blockIdx.x];
-    const TileGeom g = tile_geom(tl, tb.b_elems, TILE_ELEMS);
+    const TileGeom g = tile_geom(tl, tb.b_elems[tl.bucket], TILE_ELEMS);
     const int tid = threadIdx.x;
     const void *const *pp = peer_ptrs + (int64_t)g.bucket * (K - 1);   // peers 1..K-1 of this bucket
 
@@ -270,7 +270,7 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_elem_kernel(KtDeviceTables 
     constexpr int VE = Elem<T>::VE;
     constexpr int64_t TILE_ELEMS = (int64_t)KT_TILE_VECS * VE;
     const KtTile tl = tb.tiles[tile0 + blockIdx.x];
-    const TileGeom g = tile_geom(tl, tb.b_elems, TILE_ELEMS);
+    const TileGeom g = tile_geom(tl, tb.b_elems[tl.bucket], TILE_ELEMS);
     const int nt = tl.nt == 0 ? 1 : tl.nt;
     const GlobalView tv = global_view(tb, local_ptrs, reinterpret_cast<const void *const *>(out_ptrs), tl.t0);
     const void *const *pp = peer_ptrs + (int64_t)g.bucket * (K - 1);

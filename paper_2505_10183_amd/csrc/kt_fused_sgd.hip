@@ -275,7 +275,7 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_kernel(KtDeviceTables t
     const KtSgd a = resolve_sgd(a_in);
     const int part = SPLIT == 1 ? 0 : (int)(blockIdx.x % SPLIT);
     const KtTile tl = tb.tiles[tile0 + blockIdx.x / SPLIT];
-    const TileGeom g = tile_geom(tl, tb.b_elems, TILE_ELEMS);
+    const TileGeom g = tile_geom(tl, tb.b_elems[tl.bucket], TILE_ELEMS);
     const int tid = threadIdx.x;
     const void *const *pp = f.peer_ptrs + (int64_t)g.bucket * (K - 1);   // peers 1..K-1 of this bucket
 
@@ -328,7 +328,7 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_any_kernel(KtDeviceTabl
 
     const KtSgd a = resolve_sgd(a_in);
     const KtTile tl = tb.tiles[tile0 + blockIdx.x];
-    const TileGeom g = tile_geom(tl, tb.b_elems, TILE_ELEMS);
+    const TileGeom g = tile_geom(tl, tb.b_elems[tl.bucket], TILE_ELEMS);
     const int tid = threadIdx.x;
     const void *const *pp = f.peer_ptrs + (int64_t)g.bucket * (K - 1);
 

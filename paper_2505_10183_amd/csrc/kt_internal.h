@@ -64,11 +64,10 @@ struct KtDeviceTables {
 // All return a hipError_t cast to int.
 int kt_launch_pack(const KtDeviceTables &tb, kt_dtype dt, int64_t tile0,
                    int64_t ntiles, const void *const *d_tensor_ptrs,
-                   void *const *d_bucket_ptrs, bool vector_ok, void *stream);
+                   void *const *d_bucket_ptrs, void *stream);
 int kt_launch_unpack(const KtDeviceTables &tb, kt_dtype dt, int64_t tile0,
                      int64_t ntiles, const void *const *d_bucket_ptrs,
-                     float scale, void *const *d_tensor_ptrs, bool vector_ok,
-                     void *stream);
+                     float scale, void *const *d_tensor_ptrs, void *stream);
 // Store window of the read-dominated kernels (reduce, fused pass) on large launches: every wave
 // holds its finished results back until the device-wide constant-rate clock, masked to a period
 // of about 10 us, is inside the first `width` ticks, so that the whole chip alternates between

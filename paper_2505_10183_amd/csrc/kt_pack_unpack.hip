@@ -1,7 +1,7 @@
 // HIP kernels for gfx950: multi-tensor pack and unpack-scale driven by the device-side
 // tile + tensor-offset table.  Streaming, zero-reuse, HBM-bound: workgroups of 256 lanes
-// (4 wavefronts), four to a 16 KiB tile, 16-byte vectors (non-temporal loads, system-scope
-// stores), all loads of a lane in flight before its first store.
+// (4 wavefronts), four to a 16 KiB tile, 16-byte vectors at any element address (non-temporal
+// loads, system-scope stores), all loads of a lane in flight before its first store.
 #include "kt_device.h"
 
 // The copy kernels do best with little work per workgroup (unlike the
@@ -10,6 +10,12 @@
 // KT_TILE_VECS / KT_BLOCK / KT_COPY_SPLIT vectors per lane.  With one vector
 // per lane and workgroup (the default: 4 workgroups per 16 KiB tile) pack runs
 // at 84 % of 8 TB/s on 1.3 G bf16 elements against 76 % with one workgroup per tile.
+// That is the rate of a plain copy; a wavefront lives for little more than one memory latency,
+// so the scalar loads ahead of its data load count: with one more dependent load on the way
+// pack took 841 us instead of 785 and unpack 945 instead of 795.
+// Tensors and buckets may lie at any element address.  24.4 M bf16 elements in 400 tensors of odd
+// sizes, dense layout, gradients as views: pack 47 -> 20.5 us and unpack 48 -> 20 us against one
+// element per lane, which misaligned addresses took before.
 #ifndef KT_COPY_SPLIT
 #define KT_COPY_SPLIT (KT_TILE_VECS / KT_BLOCK)
 #endif
@@ -22,29 +28,10 @@ static_assert(COPY_VPT >= 1 && COPY_VPT * COPY_SPLIT * KT_BLOCK == KT_TILE_VECS,
 
 // ---- pack ----------------------------------------------------------------
 
-// One vector of a mixed tile, element by element: tensor tails, padding,
-// misaligned sources, vectors straddling tensors, the last partial vector of a
-// densely packed bucket.
-template <typename T, typename V>
-__device__ __forceinline__ void pack_slow(const V &tv, int nt, int64_t e0, int64_t b_n, T *dst)
-{
-    constexpr int VE = Elem<T>::VE;
-    int i = find_owner_v(tv, nt, e0);
-#pragma unroll 1
-    for (int q = 0; q < VE; ++q) {
-        const int64_t e = e0 + q;
-        if (e >= b_n) break;
-        while (i + 1 < nt && tv.off[i + 1] <= e) ++i;
-        T x = 0;
-        if (i >= 0 && e - tv.off[i] < tv.numel[i])
-            x = ld_elem(reinterpret_cast<const T *>(tv.ptr[i]) + (e - tv.off[i]));
-        st_elem(dst + e, x);
-    }
-}
-
-// Mixed tile, 16-byte path.  Two phases so that the loads of all of a lane's
-// vectors are in flight together: (1) find each vector's owner in the staged
-// table and issue its load, (2) store; stragglers go element by element.
+// Mixed tile: (1) find each vector's owner in the staged table and issue its load, (2) store.
+// A vector that is not wholly inside one tensor (tensor ends, padding) gathers its elements, all
+// loads in flight together, so that a tile's few such vectors cost one memory latency more and
+// not one per element.
 template <typename T, typename V>
 __device__ __forceinline__ void pack_mixed(const V &tv, int nt, const TileGeom &g, int64_t b_n, T *dst, int part)
 {
@@ -52,49 +39,36 @@ __device__ __forceinline__ void pack_mixed(const V &tv, int nt, const TileGeom &
     constexpr int VPT = COPY_VPT;
     const int nvec = (int)((g.end - g.start + VE - 1) / VE);
     u32x4 val[VPT];
-    int how[VPT];      // 0 = nothing, 1 = whole vector loaded, 2 = element-wise
 #pragma unroll
     for (int j = 0; j < VPT; ++j) {
         const int v = (part * VPT + j) * KT_BLOCK + threadIdx.x;
-        how[j] = 0;
         if (v < nvec) {
             const int64_t e0 = g.start + (int64_t)v * VE;
-            how[j] = 2;
             const int i = find_owner_v(tv, nt, e0);
-            if (i >= 0 && e0 + VE <= b_n) {
-                const int64_t r = e0 - tv.off[i];
-                if (r + VE <= tv.numel[i]) {
-                    const uintptr_t p = tv.ptr[i] + (uintptr_t)r * sizeof(T);
-                    if ((p & 15u) == 0) {
-                        val[j] = ld_vec(reinterpret_cast<const void *>(p));
-                        how[j] = 1;
-                    }
-                }
+            const int64_t r = i >= 0 ? e0 - tv.off[i] : -1;
+            if (r >= 0 && r + VE <= tv.numel[i] && e0 + VE <= b_n)
+                val[j] = ld_vec(reinterpret_cast<const T *>(tv.ptr[i]) + r);
+            else
+                val[j] = gather_vec<T>(tv, nt, i, e0, b_n);
+        }
+    }
+    const bool wt = off64(dst) == 0;
+#pragma unroll
+    for (int j = 0; j < VPT; ++j) {
+        const int v = (part * VPT + j) * KT_BLOCK + threadIdx.x;
+        if (v < nvec) {
+            const int64_t e0 = g.start + (int64_t)v * VE;
+            if (e0 + VE <= b_n) st_vec_pick(dst + e0, val[j], wt);
+            else {                    // the last, partial vector of a densely packed bucket
+#pragma unroll
+                for (int q = 0; q < VE; ++q)
+                    if (e0 + q < b_n) st_elem(dst + e0 + q, elem_of<T>(val[j], q));
             }
         }
     }
-#pragma unroll
-    for (int j = 0; j < VPT; ++j) {
-        const int64_t e0 = g.start + (int64_t)((part * VPT + j) * KT_BLOCK + threadIdx.x) * VE;
-        if (how[j] == 1) st_vec_copy<true>(dst + e0, val[j]);
-        else if (how[j] == 2) pack_slow<T>(tv, nt, e0, b_n, dst);
-    }
 }
 
-// Any alignment: one element per lane per step, coalesced.
-template <typename T, typename V>
-__device__ __forceinline__ void pack_elems(const V &tv, int nt, const TileGeom &g, T *dst, int part)
-{
-    for (int64_t e = g.start + part * KT_BLOCK + threadIdx.x; e < g.end; e += COPY_SPLIT * KT_BLOCK) {
-        const int i = find_owner_v(tv, nt, e);
-        T x = 0;
-        if (i >= 0 && e - tv.off[i] < tv.numel[i])
-            x = ld_elem(reinterpret_cast<const T *>(tv.ptr[i]) + (e - tv.off[i]));
-        st_elem(dst + e, x);
-    }
-}
-
-template <typename T, bool VEC>
+template <typename T>
 __global__ __launch_bounds__(KT_BLOCK) void kt_pack_kernel(KtDeviceTables tb, int64_t tile0,
                                                            const void *const *tensor_ptrs,
                                                            void *const *bucket_ptrs)
@@ -105,111 +79,88 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_pack_kernel(KtDeviceTables tb, in
     __shared__ LdsTable lds;
 
     const int part = COPY_SPLIT == 1 ? 0 : (int)(blockIdx.x % COPY_SPLIT);
-    const KtTile tl = tb.tiles[tile0 + blockIdx.x / COPY_SPLIT];
-    const TileGeom g = tile_geom(tl, tb.b_elems, TILE_ELEMS);
-    T *dst = reinterpret_cast<T *>(bucket_ptrs[g.bucket]);
+    const KtTile tl = ld_tile(tb.tiles + tile0 + blockIdx.x / COPY_SPLIT);
+    const int64_t b_n = ld_table(tb.b_elems + tl.bucket), t_off = ld_table(tb.t_off + tl.t0);
+    T *dst = reinterpret_cast<T *>(ld_table(bucket_ptrs + tl.bucket));
+    const T *src = reinterpret_cast<const T *>(ld_table(tensor_ptrs + tl.t0));
+    pin(b_n, t_off, (uint64_t)dst, (uint64_t)src);
+    const TileGeom g = tile_geom(tl, b_n, TILE_ELEMS);
     const int tid = threadIdx.x;
 
-    if (VEC && tl.nt == 0) {
-        // Solid tile: one tensor owns everything; straight 16-byte copy when
-        // the source address is 16-byte aligned.
-        const T *src = reinterpret_cast<const T *>(tensor_ptrs[tl.t0]) + (g.start - tb.t_off[tl.t0]);
-        if ((reinterpret_cast<uintptr_t>(src) & 15u) == 0) {
-            const u32x4 *s4 = reinterpret_cast<const u32x4 *>(src);
-            u32x4 *d4 = reinterpret_cast<u32x4 *>(dst + g.start);
-            const int nvec = (int)((g.end - g.start) / VE);
-            if (nvec == KT_TILE_VECS) {
-                u32x4 r[VPT];
+    if (tl.nt == 0) {
+        // Solid tile: one tensor owns everything; straight 16-byte copy at any address.
+        src += g.start - t_off;
+        T *d = dst + g.start;
+        const int o = off64(d);
+        const int nvec = (int)((g.end - g.start) / VE);
+        if (nvec == KT_TILE_VECS) {
+            u32x4 r[VPT];
+            RotVec rv[VPT];
 #pragma unroll
-                for (int j = 0; j < VPT; ++j) r[j] = ld_vec(s4 + (part * VPT + j) * KT_BLOCK + tid);
-#pragma unroll
-                for (int j = 0; j < VPT; ++j) st_vec_copy<true>(d4 + (part * VPT + j) * KT_BLOCK + tid, r[j]);
-            } else {
-#pragma unroll 1
-                for (int v = part * KT_BLOCK + tid; v < nvec; v += COPY_SPLIT * KT_BLOCK) st_vec_copy<true>(d4 + v, ld_vec(s4 + v));
+            for (int j = 0; j < VPT; ++j) {
+                rv[j] = rot_vec<KT_TILE_BYTES>(((part * VPT + j) * KT_BLOCK + tid) * KT_VEC_BYTES, o);
+                r[j] = ld_vec(reinterpret_cast<const char *>(src) + rv[j].at);
             }
-            return;
+            const __amdgpu_buffer_rsrc_t rs = tile_rsrc(d, KT_TILE_BYTES);
+#pragma unroll
+            for (int j = 0; j < VPT; ++j)
+                if (rv[j].whole) st_tile_wt(rs, rv[j].at, r[j]);
+            if ((o & (KT_VEC_BYTES - 1)) && part == 0 && tid < VE) {
+                const int e = edge_elem<KT_TILE_BYTES>(tid, sizeof(T), o) / (int)sizeof(T);
+                st_elem(d + e, ld_elem(src + e));
+            }
+        } else {
+#pragma unroll 1
+            for (int v = part * KT_BLOCK + tid; v < nvec; v += COPY_SPLIT * KT_BLOCK)
+                st_vec_pick(d + (int64_t)v * VE, ld_vec(src + (int64_t)v * VE), o == 0);
         }
+        return;
     }
 
     // a short last tile leaves the later workgroups of the tile without vectors
-    if (VEC && (int64_t)part * VPT * KT_BLOCK * VE >= g.end - g.start) return;
-    const int nt = tl.nt == 0 ? 1 : tl.nt;
-    const int64_t b_n = tb.b_elems[g.bucket];
-    if (nt <= KT_LDS_TENSORS) {
-        const LdsView tv = stage_lds(lds, tb, tensor_ptrs, nullptr, tl.t0, nt);
-        if (VEC) pack_mixed<T>(tv, nt, g, b_n, dst, part); else pack_elems<T>(tv, nt, g, dst, part);
+    if ((int64_t)part * VPT * KT_BLOCK * VE >= g.end - g.start) return;
+    if (tl.nt <= KT_LDS_TENSORS) {
+        const LdsView tv = stage_lds(lds, tb, tensor_ptrs, nullptr, tl.t0, tl.nt);
+        pack_mixed<T>(tv, tl.nt, g, b_n, dst, part);
     } else {
         const GlobalView tv = global_view(tb, tensor_ptrs, nullptr, tl.t0);
-        if (VEC) pack_mixed<T>(tv, nt, g, b_n, dst, part); else pack_elems<T>(tv, nt, g, dst, part);
+        pack_mixed<T>(tv, tl.nt, g, b_n, dst, part);
     }
 }
 
 // ---- unpack with scale ----------------------------------------------------
 
+// Mixed tile.  The bucket's vectors (`val`) were loaded before the table was staged: their
+// addresses do not depend on it.
 template <typename T, typename V>
-__device__ __forceinline__ void unpack_slow(const V &tv, int nt, int64_t e0, int64_t b_n, const T *src, float scale)
-{
-    constexpr int VE = Elem<T>::VE;
-    int i = find_owner_v(tv, nt, e0);
-#pragma unroll 1
-    for (int q = 0; q < VE; ++q) {
-        const int64_t e = e0 + q;
-        if (e >= b_n) break;
-        while (i + 1 < nt && tv.off[i + 1] <= e) ++i;
-        if (i >= 0 && e - tv.off[i] < tv.numel[i])
-            st_elem(reinterpret_cast<T *>(tv.ptr[i]) + (e - tv.off[i]), scale_elem(ld_elem(src + e), scale));
-    }
-}
-
-template <typename T, typename V>
-__device__ __forceinline__ void unpack_mixed(const V &tv, int nt, const TileGeom &g, int64_t b_n, const T *src,
+__device__ __forceinline__ void unpack_mixed(const V &tv, int nt, const TileGeom &g, int64_t b_n, const u32x4 *val,
                                              float scale, int part)
 {
     constexpr int VE = Elem<T>::VE;
     constexpr int VPT = COPY_VPT;
     const int nvec = (int)((g.end - g.start + VE - 1) / VE);
-    u32x4 val[VPT];
-    uintptr_t where[VPT];   // destination of a whole vector, 0 = none, 1 = element-wise
 #pragma unroll
     for (int j = 0; j < VPT; ++j) {
         const int v = (part * VPT + j) * KT_BLOCK + threadIdx.x;
-        where[j] = 0;
         if (v < nvec) {
             const int64_t e0 = g.start + (int64_t)v * VE;
-            where[j] = 1;
             const int i = find_owner_v(tv, nt, e0);
-            if (i >= 0 && e0 + VE <= b_n) {
-                const int64_t r = e0 - tv.off[i];
-                if (r + VE <= tv.numel[i]) {
-                    const uintptr_t p = tv.ptr[i] + (uintptr_t)r * sizeof(T);
-                    if ((p & 15u) == 0) {
-                        val[j] = ld_vec(src + e0);
-                        where[j] = p;
-                    }
-                }
+            const int64_t r = i >= 0 ? e0 - tv.off[i] : -1;
+            const u32x4 x = scale_vec<T>(val[j], scale);
+            if (r >= 0 && r + VE <= tv.numel[i] && e0 + VE <= b_n) {
+                T *p = reinterpret_cast<T *>(tv.ptr[i]) + r;
+                // whole 64-byte pieces per wavefront: the address of the lane that starts the piece
+                st_vec_pick(p, x, off64(reinterpret_cast<char *>(p) - (size_t)(threadIdx.x & 3) * KT_VEC_BYTES) == 0);
+            } else {
+                each_owned<VE>(tv, nt, i, e0, b_n, [&](int q, int t, int64_t rr) {
+                    st_elem(reinterpret_cast<T *>(tv.ptr[t]) + rr, elem_of<T>(x, q));
+                });
             }
         }
     }
-#pragma unroll
-    for (int j = 0; j < VPT; ++j) {
-        if (where[j] > 1) st_vec_copy<true>(reinterpret_cast<void *>(where[j]), scale_vec<T>(val[j], scale));
-        else if (where[j] == 1)
-            unpack_slow<T>(tv, nt, g.start + (int64_t)((part * VPT + j) * KT_BLOCK + threadIdx.x) * VE, b_n, src, scale);
-    }
 }
 
-template <typename T, typename V>
-__device__ __forceinline__ void unpack_elems(const V &tv, int nt, const TileGeom &g, const T *src, float scale, int part)
-{
-    for (int64_t e = g.start + part * KT_BLOCK + threadIdx.x; e < g.end; e += COPY_SPLIT * KT_BLOCK) {
-        const int i = find_owner_v(tv, nt, e);
-        if (i >= 0 && e - tv.off[i] < tv.numel[i])
-            st_elem(reinterpret_cast<T *>(tv.ptr[i]) + (e - tv.off[i]), scale_elem(ld_elem(src + e), scale));
-    }
-}
-
-template <typename T, bool VEC>
+template <typename T>
 __global__ __launch_bounds__(KT_BLOCK) void kt_unpack_kernel(KtDeviceTables tb, int64_t tile0,
                                                              const void *const *bucket_ptrs, float scale,
                                                              void *const *tensor_ptrs)
@@ -220,42 +171,57 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_unpack_kernel(KtDeviceTables tb, 
     __shared__ LdsTable lds;
 
     const int part = COPY_SPLIT == 1 ? 0 : (int)(blockIdx.x % COPY_SPLIT);
-    const KtTile tl = tb.tiles[tile0 + blockIdx.x / COPY_SPLIT];
-    const TileGeom g = tile_geom(tl, tb.b_elems, TILE_ELEMS);
-    const T *src = reinterpret_cast<const T *>(bucket_ptrs[g.bucket]);
+    const KtTile tl = ld_tile(tb.tiles + tile0 + blockIdx.x / COPY_SPLIT);
+    const int64_t b_n = ld_table(tb.b_elems + tl.bucket), t_off = ld_table(tb.t_off + tl.t0);
+    const T *src = reinterpret_cast<const T *>(ld_table(bucket_ptrs + tl.bucket));
+    T *dst = reinterpret_cast<T *>(ld_table(tensor_ptrs + tl.t0));
+    pin(b_n, t_off, (uint64_t)dst, (uint64_t)src);
+    const TileGeom g = tile_geom(tl, b_n, TILE_ELEMS);
     const int tid = threadIdx.x;
 
-    if (VEC && tl.nt == 0) {
-        T *dst = reinterpret_cast<T *>(tensor_ptrs[tl.t0]) + (g.start - tb.t_off[tl.t0]);
-        if ((reinterpret_cast<uintptr_t>(dst) & 15u) == 0) {
-            const u32x4 *s4 = reinterpret_cast<const u32x4 *>(src + g.start);
-            u32x4 *d4 = reinterpret_cast<u32x4 *>(dst);
-            const int nvec = (int)((g.end - g.start) / VE);
-            if (nvec == KT_TILE_VECS) {
-                u32x4 r[VPT];
+    if (tl.nt == 0) {
+        dst += g.start - t_off;
+        const T *s = src + g.start;
+        const int o = off64(dst);
+        const int nvec = (int)((g.end - g.start) / VE);
+        if (nvec == KT_TILE_VECS) {
+            u32x4 r[VPT];
+            RotVec rv[VPT];
 #pragma unroll
-                for (int j = 0; j < VPT; ++j) r[j] = ld_vec(s4 + (part * VPT + j) * KT_BLOCK + tid);
-#pragma unroll
-                for (int j = 0; j < VPT; ++j) st_vec_copy<true>(d4 + (part * VPT + j) * KT_BLOCK + tid, scale_vec<T>(r[j], scale));
-            } else {
-#pragma unroll 1
-                for (int v = part * KT_BLOCK + tid; v < nvec; v += COPY_SPLIT * KT_BLOCK)
-                    st_vec_copy<true>(d4 + v, scale_vec<T>(ld_vec(s4 + v), scale));
+            for (int j = 0; j < VPT; ++j) {
+                rv[j] = rot_vec<KT_TILE_BYTES>(((part * VPT + j) * KT_BLOCK + tid) * KT_VEC_BYTES, o);
+                r[j] = ld_vec(reinterpret_cast<const char *>(s) + rv[j].at);
             }
-            return;
+            const __amdgpu_buffer_rsrc_t rs = tile_rsrc(dst, KT_TILE_BYTES);
+#pragma unroll
+            for (int j = 0; j < VPT; ++j)
+                if (rv[j].whole) st_tile_wt(rs, rv[j].at, scale_vec<T>(r[j], scale));
+            if ((o & (KT_VEC_BYTES - 1)) && part == 0 && tid < VE) {
+                const int e = edge_elem<KT_TILE_BYTES>(tid, sizeof(T), o) / (int)sizeof(T);
+                st_elem(dst + e, scale_elem(ld_elem(s + e), scale));
+            }
+        } else {
+#pragma unroll 1
+            for (int v = part * KT_BLOCK + tid; v < nvec; v += COPY_SPLIT * KT_BLOCK)
+                st_vec_pick(dst + (int64_t)v * VE, scale_vec<T>(ld_vec(s + (int64_t)v * VE), scale), o == 0);
         }
+        return;
     }
 
-    if (VEC && (int64_t)part * VPT * KT_BLOCK * VE >= g.end - g.start) return;
-    const int nt = tl.nt == 0 ? 1 : tl.nt;
-    const int64_t b_n = tb.b_elems[g.bucket];
+    if ((int64_t)part * VPT * KT_BLOCK * VE >= g.end - g.start) return;
+    u32x4 val[VPT];
+#pragma unroll
+    for (int j = 0; j < VPT; ++j) {
+        const int64_t e0 = g.start + (int64_t)((part * VPT + j) * KT_BLOCK + tid) * VE;
+        val[j] = ld_bucket_vec(src, e0, b_n);      // nothing is read at or past b_n
+    }
     const void *const *tp = reinterpret_cast<const void *const *>(tensor_ptrs);
-    if (nt <= KT_LDS_TENSORS) {
-        const LdsView tv = stage_lds(lds, tb, tp, nullptr, tl.t0, nt);
-        if (VEC) unpack_mixed<T>(tv, nt, g, b_n, src, scale, part); else unpack_elems<T>(tv, nt, g, src, scale, part);
+    if (tl.nt <= KT_LDS_TENSORS) {
+        const LdsView tv = stage_lds(lds, tb, tp, nullptr, tl.t0, tl.nt);
+        unpack_mixed<T>(tv, tl.nt, g, b_n, val, scale, part);
     } else {
         const GlobalView tv = global_view(tb, tp, nullptr, tl.t0);
-        if (VEC) unpack_mixed<T>(tv, nt, g, b_n, src, scale, part); else unpack_elems<T>(tv, nt, g, src, scale, part);
+        unpack_mixed<T>(tv, tl.nt, g, b_n, val, scale, part);
     }
 }
 
@@ -275,34 +241,23 @@ template <typename F> static int launch_in_chunks(int64_t tile0, int64_t ntiles,
 }
 
 int kt_launch_pack(const KtDeviceTables &tb, kt_dtype dt, int64_t tile0, int64_t ntiles,
-                   const void *const *d_tensor_ptrs, void *const *d_bucket_ptrs, bool vector_ok, void *stream)
+                   const void *const *d_tensor_ptrs, void *const *d_bucket_ptrs, void *stream)
 {
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const dim3 block(KT_BLOCK);
     return launch_in_chunks(tile0, ntiles, [&](int64_t t0, dim3 grid) {
-        if (dt == KT_F32) {
-            if (vector_ok) kt_pack_kernel<float, true><<<grid, block, 0, s>>>(tb, t0, d_tensor_ptrs, d_bucket_ptrs);
-            else kt_pack_kernel<float, false><<<grid, block, 0, s>>>(tb, t0, d_tensor_ptrs, d_bucket_ptrs);
-        } else {
-            if (vector_ok) kt_pack_kernel<uint16_t, true><<<grid, block, 0, s>>>(tb, t0, d_tensor_ptrs, d_bucket_ptrs);
-            else kt_pack_kernel<uint16_t, false><<<grid, block, 0, s>>>(tb, t0, d_tensor_ptrs, d_bucket_ptrs);
-        }
+        if (dt == KT_F32) kt_pack_kernel<float><<<grid, block, 0, s>>>(tb, t0, d_tensor_ptrs, d_bucket_ptrs);
+        else kt_pack_kernel<uint16_t><<<grid, block, 0, s>>>(tb, t0, d_tensor_ptrs, d_bucket_ptrs);
     });
 }
 
 int kt_launch_unpack(const KtDeviceTables &tb, kt_dtype dt, int64_t tile0, int64_t ntiles,
-                     const void *const *d_bucket_ptrs, float scale, void *const *d_tensor_ptrs, bool vector_ok,
-                     void *stream)
+                     const void *const *d_bucket_ptrs, float scale, void *const *d_tensor_ptrs, void *stream)
 {
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const dim3 block(KT_BLOCK);
     return launch_in_chunks(tile0, ntiles, [&](int64_t t0, dim3 grid) {
-        if (dt == KT_F32) {
-            if (vector_ok) kt_unpack_kernel<float, true><<<grid, block, 0, s>>>(tb, t0, d_bucket_ptrs, scale, d_tensor_ptrs);
-            else kt_unpack_kernel<float, false><<<grid, block, 0, s>>>(tb, t0, d_bucket_ptrs, scale, d_tensor_ptrs);
-        } else {
-            if (vector_ok) kt_unpack_kernel<uint16_t, true><<<grid, block, 0, s>>>(tb, t0, d_bucket_ptrs, scale, d_tensor_ptrs);
-            else kt_unpack_kernel<uint16_t, false><<<grid, block, 0, s>>>(tb, t0, d_bucket_ptrs, scale, d_tensor_ptrs);
-        }
+        if (dt == KT_F32) kt_unpack_kernel<float><<<grid, block, 0, s>>>(tb, t0, d_bucket_ptrs, scale, d_tensor_ptrs);
+        else kt_unpack_kernel<uint16_t><<<grid, block, 0, s>>>(tb, t0, d_bucket_ptrs, scale, d_tensor_ptrs);
     });
 }

@@ -75,7 +75,7 @@ __global__ __launch_bounds__(KT_BLOCK) KT_REDUCE_OCC void kt_reduce_kernel(KtDev
     constexpr int VPT = KT_TILE_VECS / KT_BLOCK;   // vectors per lane, K loads each, all in flight at once
 
     const KtTile tl = tb.tiles[tile0 + reduce_tile_index()];
-    const TileGeom g = tile_geom(tl, tb.b_elems, TILE_ELEMS);
+    const TileGeom g = tile_geom(tl, tb.b_elems[tl.bucket], TILE_ELEMS);
     const int tid = threadIdx.x;
 
     const T *x[K];
@@ -189,7 +189,7 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_reduce_manyk_kernel(KtDeviceTable
     constexpr int64_t TILE_ELEMS = (int64_t)KT_TILE_VECS * VE;
     constexpr int VPT = KT_TILE_VECS / KT_BLOCK;
     const KtTile tl = tb.tiles[tile0 + blockIdx.x];
-    const TileGeom g = tile_geom(tl, tb.b_elems, TILE_ELEMS);
+    const TileGeom g = tile_geom(tl, tb.b_elems[tl.bucket], TILE_ELEMS);
     const int tid = threadIdx.x;
     const void *const *pp = peer_ptrs + (int64_t)g.bucket * K;
     T *out = reinterpret_cast<T *>(out_ptrs[g.bucket]) + g.start;
@@ -233,7 +233,7 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_reduce_elem_kernel(KtDeviceTables
     constexpr int VE = Elem<T>::VE;
     constexpr int64_t TILE_ELEMS = (int64_t)KT_TILE_VECS * VE;
     const KtTile tl = tb.tiles[tile0 + blockIdx.x];
-    const TileGeom g = tile_geom(tl, tb.b_elems, TILE_ELEMS);
+    const TileGeom g = tile_geom(tl, tb.b_elems[tl.bucket], TILE_ELEMS);
     const void *const *pp = peer_ptrs + (int64_t)g.bucket * K;
     T *out = reinterpret_cast<T *>(out_ptrs[g.bucket]);
     for (int64_t e = g.start + threadIdx.x; e < g.end; e += KT_BLOCK) {

@@ -134,7 +134,7 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_unpack_sgd_kernel(KtDeviceTables 
 
     const int part = SPLIT == 1 ? 0 : (int)(blockIdx.x % SPLIT);
     const KtTile tl = tb.tiles[tile0 + blockIdx.x / SPLIT];
-    const TileGeom g = tile_geom(tl, tb.b_elems, TILE_ELEMS);
+    const TileGeom g = tile_geom(tl, tb.b_elems[tl.bucket], TILE_ELEMS);
     const T *src = reinterpret_cast<const T *>(bucket_ptrs[g.bucket]);
     const int tid = threadIdx.x;
 

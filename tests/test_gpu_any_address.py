@@ -1,0 +1,83 @@
+"""Tensors and buckets at every kind of element address: a full tile's vectors are laid out from a
+64-byte boundary of the destination, so the byte offset of the destination from that boundary (0 to
+62) decides which vector wraps to the tile's end and which elements go one by one.  Every element
+against the CPU checker's binary32 step mode (bit-identical), with guard elements around every output."""
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2505_10183_amd as kt
+from paper_2505_10183_amd import workloads as wl
+from test_gpu_parity import DEV, host, raw, tdtype
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def announce(request):
+    print("\n[gpu-case] %s" % request.node.nodeid, file=sys.stderr, flush=True)
+    yield
+    torch.cuda.synchronize()
+
+
+GUARD = 64
+
+
+class Guarded:
+    """Views of n elements each that start `shift` bytes past a 64-byte boundary, between guard elements."""
+
+    def __init__(self, sizes, dtype, shift, fill):
+        es = torch.empty((), dtype=dtype).element_size()
+        assert shift % es == 0
+        self.fill = fill
+        self.at = GUARD + shift // es       # the allocator's blocks start on 512-byte boundaries
+        self.whole = [torch.full((n + self.at + GUARD,), fill, dtype=dtype, device=DEV) for n in sizes]
+        self.views = [t[self.at:self.at + n] for t, n in zip(self.whole, sizes)]
+
+    def check_guards(self, what):
+        for i, (t, v) in enumerate(zip(self.whole, self.views)):
+            assert bool((t[:self.at] == self.fill).all()) and bool((t[self.at + v.numel():] == self.fill).all()), (what, i)
+
+
+def same(got, want, what):
+    for t, (a, b) in enumerate(zip(got, want)):
+        assert raw(host(a)).tobytes() == raw(b).tobytes(), (what, t)
+
+
+def case(dtype, align, K):
+    es = 4 if dtype == "f32" else 2
+    tile = 16384 // es
+    # several full tiles from an odd start, one element, a tile and its neighbours, a short last tile
+    numels = [5, 3 * tile + 7, 1, tile, tile - 1, tile + 1, 2 * tile, 9, 4097, 2 * tile + 333]
+    w = wl.Workload("any", dtype, tuple((n,) for n in numels), tuple(1.0 - 0.04 * k for k in range(K)), 1024,
+                    7 * 16384, 1e-3, 77)
+    plan = kt.Plan(numels, dtype, w.bucket_cap_bytes, align)
+    layout = oracle.assign_buckets(numels, es, w.bucket_cap_bytes, align)
+    shares, weights = kt.kt_plan_shares(w.throughputs, w.global_batch)
+    return w, plan, layout, weights, oracle.share_weights(shares, w.global_batch)
+
+
+@pytest.mark.parametrize("dtype,shift", [("f32", s) for s in (0, 4, 12, 16, 36, 48, 60)] +
+                         [("bf16", s) for s in (0, 2, 14, 16, 34, 48, 62)])
+@pytest.mark.parametrize("dense", [True, False])
+def test_pack_unpack(dtype, shift, dense):
+    w, plan, layout, _, _ = case(dtype, (4 if dtype == "f32" else 2) if dense else 16, 1)
+    td = tdtype(dtype)
+    grads = Guarded(w.numels, td, shift, 3.0)
+    for v, g in zip(grads.views, wl.gradient_set(w, 0, DEV)):
+        v.copy_(g.reshape(-1))
+    hg = [host(v) for v in grads.views]
+    want = oracle.pack(layout, hg, dtype)
+    for bshift in (0, 64 - shift if shift else 32):
+        buckets = Guarded(plan.bucket_elems(), td, bshift, 5.0)
+        out = Guarded(w.numels, td, shift, 7.0)
+        plan.kt_bucket_pack(-1, grads.views, buckets.views)
+        plan.kt_bucket_unpack_scale(-1, buckets.views, 0.37, out.views)
+        torch.cuda.synchronize()
+        same(buckets.views, want, "pack")
+        same(out.views, oracle.unpack_scale(layout, want, w.numels, 0.37, dtype, "S"), "unpack")
+        buckets.check_guards("pack")
+        out.check_guards("unpack")
