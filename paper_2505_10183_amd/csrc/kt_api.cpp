@@ -578,18 +578,15 @@ extern "C" kt_status kt_weighted_reduce(kt_plan *p, int bucket, const void *cons
     std::vector<uint64_t> &vals = call_table(nb * K + nb);
     for (size_t i = 0; i < nb * K; ++i) vals[i] = reinterpret_cast<uintptr_t>(peer_bufs[i]);
     for (size_t b = 0; b < nb; ++b) vals[nb * K + b] = reinterpret_cast<uintptr_t>(out_bufs[b]);
-    bool vec = true;
     for (int b = b0; b < b1; ++b) {
         const uintptr_t bytes = (uintptr_t)hp.b_elems[b] * hp.elem_size;
         const uintptr_t op = reinterpret_cast<uintptr_t>(out_bufs[b]);
         if (bytes && !op) { kt_set_error("%s: NULL output for bucket %d", who, b); return KT_EINVAL; }
         if (op & emask) { kt_set_error("%s: output %d not aligned to the element size", who, b); return KT_EALIGN; }
-        if (op & (KT_VEC_BYTES - 1)) vec = false;
         for (int k = 0; k < K; ++k) {
             const uintptr_t pp = reinterpret_cast<uintptr_t>(peer_bufs[(size_t)b * K + k]);
             if (bytes && !pp) { kt_set_error("%s: NULL peer %d of bucket %d", who, k, b); return KT_EINVAL; }
             if (pp & emask) { kt_set_error("%s: peer %d of bucket %d not aligned to the element size", who, k, b); return KT_EALIGN; }
-            if (pp & (KT_VEC_BYTES - 1)) vec = false;
             // the output may be exactly one of the inputs (in place), never a partial overlap
             if (bytes && pp != op && pp < op + bytes && op < pp + bytes) {
                 kt_set_error("%s: output of bucket %d partially overlaps peer %d", who, b, k);
@@ -604,7 +601,7 @@ extern "C" kt_status kt_weighted_reduce(kt_plan *p, int bucket, const void *cons
     if (st != KT_OK) return st;
     const void *const *d_p = static_cast<const void *const *>(slot->dev);
     void *const *d_o = reinterpret_cast<void *const *>(static_cast<uint64_t *>(slot->dev) + nb * K);
-    int e = kt_launch_reduce(p->tb, hp.dt, tile0, ntiles, d_p, K, w, d_o, vec, stream);
+    int e = kt_launch_reduce(p->tb, hp.dt, tile0, ntiles, d_p, K, w, d_o, stream);
     if (e != 0) return hip_fail("kt_weighted_reduce: launch", (hipError_t)e);
     return mark_used(p, slot, s);
     KT_GUARD_END("kt_weighted_reduce")

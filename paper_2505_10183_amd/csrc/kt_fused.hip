@@ -236,9 +236,10 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_manyk_kernel(KtDeviceTables
         const T *src = reinterpret_cast<const T *>(local_ptrs[tl.t0]) + rel;
         T *dst = reinterpret_cast<T *>(out_ptrs[tl.t0]) + rel;
         if (((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) & 15u) == 0) {
+            const TileVecs<false> at(tid, 0);
             Acc<T> acc[VPT];
             sum_in_chunks<T, DEVW>(acc, [&](int k) { return k == 0 ? src : reinterpret_cast<const T *>(pp[k - 1]) + g.start; },
-                             wts, K, tid);
+                             wts, K, at);
             u32x4 res[VPT];
 #pragma unroll
             for (int u = 0; u < VPT; ++u) res[u] = scale_vec<T>(acc[u].finish(), scale);

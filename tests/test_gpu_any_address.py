@@ -81,3 +81,26 @@ def test_pack_unpack(dtype, shift, dense):
         same(out.views, oracle.unpack_scale(layout, want, w.numels, 0.37, dtype, "S"), "unpack")
         buckets.check_guards("pack")
         out.check_guards("unpack")
+
+
+@pytest.mark.parametrize("dtype,shift", [("f32", s) for s in (0, 4, 12, 16, 36, 48, 60)] +
+                         [("bf16", s) for s in (0, 2, 14, 16, 34, 48, 62)])
+@pytest.mark.parametrize("K", [1, 3, 8, 11])
+def test_reduce(dtype, shift, K):
+    w, plan, layout, weights, wts = case(dtype, 4 if dtype == "f32" else 2, K)
+    nb = plan.num_buckets
+    td = tdtype(dtype)
+    # every copy at another address, then the output beside them and over the first copy
+    peers = [Guarded(plan.bucket_elems(), td, (shift + 4 * k) % 64, 3.0) for k in range(K)]
+    for k in range(K):
+        for b, v in enumerate(peers[k].views):
+            v.copy_(wl.flat_normal(v.numel(), dtype, 1e-3, 100 * k + b, DEV))
+    want = [oracle.weighted_reduce([host(peers[k].views[b]) for k in range(K)], wts, dtype, "S") for b in range(nb)]
+    flat = [peers[k].views[b] for b in range(nb) for k in range(K)]
+    out = Guarded(plan.bucket_elems(), td, (64 - shift) % 64, 5.0)
+    plan.kt_weighted_reduce(-1, flat, K, weights, out.views)
+    plan.kt_weighted_reduce(-1, flat, K, weights, peers[0].views)
+    torch.cuda.synchronize()
+    for dst in (out, peers[0]):
+        same(dst.views, want, "reduce")
+        dst.check_guards("reduce")
