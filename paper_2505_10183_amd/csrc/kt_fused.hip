@@ -298,7 +298,7 @@ hipError_t launch_fused_t(const KtDeviceTables &tb, int64_t tile0, int64_t ntile
         return hipGetLastError();
     }
     // the window assumes one workgroup per tile (the time a generation of workgroups reads for)
-    const KtWindow win = FUSED_SPLIT == 1 ? kt_store_window(K, ntiles, KT_WINDOW_MIN_TILES_FUSED) : KtWindow{0, 0};
+    const KtWindow win = FUSED_SPLIT == 1 ? kt_store_window(K, ntiles, (KT_WINDOW_MIN_READS_FUSED + K - 1) / K) : KtWindow{0, 0};
     if (K > 8) {
         kt_fused_manyk_kernel<T, DEVW><<<grid, block, 0, s>>>(tb, tile0, locals, peers, K, w, scale, outs, win);
         return hipGetLastError();

@@ -92,14 +92,22 @@ KtWindow kt_store_window(int K, int64_t ntiles, int64_t min_tiles);
 #ifndef KT_WINDOW_OPEN_PCT
 #define KT_WINDOW_OPEN_PCT 10
 #endif
-// Smallest launches that use the window.  The fused pass is a step of its own and gains from
-// 16 Ki tiles (256 MiB per copy) on; the reduce inside the chained step (between pack and
-// unpack) measured 2 % slower with the window at 21 Ki tiles and 5 % faster at 160 Ki.
-#ifndef KT_WINDOW_MIN_TILES_FUSED
-#define KT_WINDOW_MIN_TILES_FUSED 16384
+// Smallest launches that use the window, in tiles read (tiles x copies) or, for the reduce of up to
+// 8 copies, in tiles.  The fused pass is a step of its own and gains from 65 536 tiles read on
+// (K = 8: 8 192 tiles 205 -> 200 us; K = 16: 8 192 tiles 399 -> 371 us, 4 096 tiles 212 -> 199 us)
+// and is even at K = 4, 16 384 tiles.  The reduce stands between pack and unpack, which lose part
+// of what the caches held for them: inside the step K = 8 is 1-3 % slower with the window up to
+// 32 768 tiles and 2-4 % faster from 65 536 on.  With more copies that share shrinks: from 262 144
+// tiles read on the step is even or faster (K = 16, 32 768 tiles: 1 927 -> 1 888 us fp32, 1 952 ->
+// 1 862 bf16) and the reduce alone gains 6-10 % (K = 16, 21 135 tiles: 1 040 -> 983 us, 1 032 -> 943).
+#ifndef KT_WINDOW_MIN_READS_FUSED
+#define KT_WINDOW_MIN_READS_FUSED 65536
 #endif
 #ifndef KT_WINDOW_MIN_TILES_REDUCE
 #define KT_WINDOW_MIN_TILES_REDUCE 65536
+#endif
+#ifndef KT_WINDOW_MIN_READS_REDUCE_MANYK
+#define KT_WINDOW_MIN_READS_REDUCE_MANYK 262144
 #endif
 
 // The K weights of a launch travel in the kernel-argument block (`w`), unless

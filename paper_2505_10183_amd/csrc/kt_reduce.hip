@@ -148,7 +148,7 @@ hipError_t launch_reduce_t(const KtDeviceTables &tb, int64_t tile0, int64_t ntil
                            int K, const KtWeights &w, void *const *outs, hipStream_t s)
 {
     dim3 grid((unsigned)ntiles), block(KT_BLOCK);
-    const KtWindow win = kt_store_window(K, ntiles, KT_WINDOW_MIN_TILES_REDUCE);
+    const KtWindow win = kt_store_window(K, ntiles, K <= 8 ? KT_WINDOW_MIN_TILES_REDUCE : (KT_WINDOW_MIN_READS_REDUCE_MANYK + K - 1) / K);
     switch (K) {
 #define KT_CASE(KK) \
     case KK: kt_reduce_kernel<T, KK, DEVW><<<grid, block, 0, s>>>(tb, tile0, peers, w, outs, win); break;
