@@ -688,7 +688,7 @@ extern "C" kt_status kt_plan_set_sgd(kt_plan *p, float scale, float lr, float mo
 kt_status kt_fused_prepare(const kt_plan *p, int bucket, const void *const *local_tensor_ptrs,
                            const void *const *peer_bufs, int K, const float *weights,
                            void *const *out_tensor_ptrs, const char *who, std::vector<uint64_t> &vals,
-                           KtWeights *w, int64_t *tile0, int64_t *ntiles, bool *vector_ok)
+                           KtWeights *w, int64_t *tile0, int64_t *ntiles)
 {
     *ntiles = 0;
     if (!p) { kt_set_error("%s: NULL plan", who); return KT_EINVAL; }
@@ -709,14 +709,12 @@ kt_status kt_fused_prepare(const kt_plan *p, int bucket, const void *const *loca
         vals[T + t] = reinterpret_cast<uintptr_t>(out_tensor_ptrs[t]);
     }
     for (size_t i = 0; i < nb * KP; ++i) vals[2 * T + i] = reinterpret_cast<uintptr_t>(peer_bufs[i]);
-    bool vec = hp.align_bytes % KT_VEC_BYTES == 0;
     for (int b = b0; b < b1; ++b) {
         const uintptr_t bbytes = (uintptr_t)hp.b_elems[b] * hp.elem_size;
         for (size_t k = 0; k < KP; ++k) {
             const uintptr_t pp = vals[2 * T + (size_t)b * KP + k];
             if (bbytes && !pp) { kt_set_error("%s: NULL peer %zu of bucket %d", who, k + 1, b); return KT_EINVAL; }
             if (pp & emask) { kt_set_error("%s: peer %zu of bucket %d not aligned to the element size", who, k + 1, b); return KT_EALIGN; }
-            if (pp & (KT_VEC_BYTES - 1)) vec = false;
         }
         for (int t = hp.b_first[b]; t < hp.b_first[b] + hp.b_count[b]; ++t) {
             const uintptr_t lp = vals[t], op = vals[T + t];
@@ -731,7 +729,6 @@ kt_status kt_fused_prepare(const kt_plan *p, int bucket, const void *const *loca
             }
         }
     }
-    *vector_ok = vec;
     return KT_OK;
 }
 
@@ -745,11 +742,10 @@ extern "C" kt_status kt_fused_step(kt_plan *p, int bucket, const void *const *lo
     std::lock_guard<std::mutex> lock(p->mu);
     hipStream_t s = static_cast<hipStream_t>(stream);
     int64_t tile0 = 0, ntiles = 0;
-    bool vec = false;
     KtWeights w;
     std::vector<uint64_t> &vals = call_table(0);
     kt_status st = kt_fused_prepare(p, bucket, local_tensor_ptrs, peer_bufs, K, weights, out_tensor_ptrs, who, vals, &w,
-                                    &tile0, &ntiles, &vec);
+                                    &tile0, &ntiles);
     if (st != KT_OK || ntiles == 0) return st;
     const size_t T = p->hp.t_numel.size();
     st = ensure_device(p, s);
@@ -760,7 +756,7 @@ extern "C" kt_status kt_fused_step(kt_plan *p, int bucket, const void *const *lo
     const uint64_t *d = static_cast<const uint64_t *>(slot->dev);
     int e = kt_launch_fused(p->tb, p->hp.dt, tile0, ntiles, reinterpret_cast<const void *const *>(d),
                             reinterpret_cast<const void *const *>(d + 2 * T), K, w, scale,
-                            reinterpret_cast<void *const *>(const_cast<uint64_t *>(d + T)), vec, stream);
+                            reinterpret_cast<void *const *>(const_cast<uint64_t *>(d + T)), stream);
     if (e != 0) return hip_fail("kt_fused_step: launch", (hipError_t)e);
     return mark_used(p, slot, s);
     KT_GUARD_END("kt_fused_step")

@@ -129,36 +129,6 @@ template <int BYTES> __device__ __forceinline__ int edge_elem(int q, int es, int
     const int pos = (o & ~(KT_VEC_BYTES - 1)) + q * es;
     return pos >= o ? pos - o : pos + BYTES - o;
 }
-// A lane's vectors of a full tile that one workgroup takes whole.  ROT: laid out from the
-// destination's 64-byte boundary, else from the tile's first byte (the destination lies on the
-// boundary).  Two instantiations: with the offsets held in registers the 32 loads of the K = 8
-// reduce issue back to back, which inside the store windows measured 3 % slower (3.89 ms against
-// 3.77 on the 1.3B set) than with the address arithmetic between them.
-template <bool ROT> struct TileVecs {
-    uint32_t at[KT_TILE_VECS / KT_BLOCK];
-    bool whole0;      // only the lane's first vector can be the cut one
-    int tid;
-    __device__ __forceinline__ TileVecs(int tid_, int o) : whole0(true), tid(tid_)
-    {
-        if (ROT) {
-            const RotVec v = rot_vec<KT_TILE_BYTES>(tid * KT_VEC_BYTES, o);
-            at[0] = (uint32_t)v.at;
-            whole0 = v.whole;
-#pragma unroll
-            for (int u = 1; u < KT_TILE_VECS / KT_BLOCK; ++u) at[u] = (uint32_t)((u * KT_BLOCK + tid) * KT_VEC_BYTES - o);
-        }
-    }
-    template <typename T> __device__ __forceinline__ u32x4 load(const T *p, int u) const
-    {
-        if (ROT) return ld_vec(reinterpret_cast<const char *>(p) + at[u]);
-        return ld_vec(reinterpret_cast<const u32x4 *>(p) + u * KT_BLOCK + tid);
-    }
-    template <typename T> __device__ __forceinline__ void store(T *p, int u, u32x4 v) const
-    {
-        if (!ROT) st_vec(reinterpret_cast<u32x4 *>(p) + u * KT_BLOCK + tid, v);
-        else if (u > 0 || whole0) st_vec(reinterpret_cast<char *>(p) + at[u], v);
-    }
-};
 __device__ __forceinline__ int off64(const void *p) { return (int)(reinterpret_cast<uintptr_t>(p) & 63u); }
 
 // Holds a wave back until the store window opens (KtWindow).  Bounded twice over: the clock
@@ -299,6 +269,25 @@ __device__ __forceinline__ void each_owned(const V &tv, int nt, int i, int64_t e
     }
 }
 
+// Calls f(i, r, e) for every element of the tile (length `len`, at bucket element `start`) that lies
+// in a vector not wholly inside one tensor: the elements of each tensor before its first whole
+// vector of the tile and after its last.  `i` is the tensor, `r` the element in it, `e` the element
+// in the tile.  One element per lane and call, so that the few cut vectors of a tile cost one
+// memory latency and little code; `first` and `stride` share the work out over the lanes.
+template <int VE, typename V, typename F>
+__device__ __forceinline__ void each_cut_elem(const V &tv, int nt, int64_t start, int len, int first, int stride, F f)
+{
+    for (int idx = first; idx < nt * 2 * VE; idx += stride) {
+        const int i = idx / (2 * VE), slot = idx % (2 * VE);
+        const int64_t rel = tv.off[i] - start, last = rel + tv.numel[i];
+        const int a = rel > 0 ? (int)(rel < len ? rel : len) : 0;             // the tensor's part of the tile: [a, b)
+        const int b = last > 0 ? (int)(last < len ? last : len) : 0;
+        const int body = (a + VE - 1) / VE * VE;
+        const int e = slot < VE ? a + slot : b / VE * VE + slot - VE;
+        if (e < b && (slot < VE ? e < body : e >= body)) f(i, (int64_t)e - rel, e);
+    }
+}
+
 // VE elements held one per register <-> a 16-byte vector
 __device__ __forceinline__ u32x4 join(const float *x)
 {
@@ -329,20 +318,6 @@ __device__ __forceinline__ u32x4 gather_vec(const V &tv, int nt, int i, int64_t 
     each_owned<VE>(tv, nt, i, e0, lim, [&](int q, int t, int64_t r) { x[q] = ld_elem(reinterpret_cast<const T *>(tv.ptr[t]) + r); });
     return join(x);
 }
-// A bucket's vector at e0 (bucket base b): whole, or, at the end of a densely packed bucket, its `lim - e0` elements.
-template <typename T> __device__ __forceinline__ u32x4 ld_bucket_vec(const T *b, int64_t e0, int64_t lim)
-{
-    constexpr int VE = Elem<T>::VE;
-    if (e0 + VE <= lim) return ld_vec(b + e0);
-    T x[VE];
-#pragma unroll
-    for (int q = 0; q < VE; ++q) {
-        x[q] = 0;
-        if (e0 + q < lim) x[q] = ld_elem(b + e0 + q);
-    }
-    return join(x);
-}
-
 // `second` may be NULL for kernels with one tensor set (ptr2 then mirrors ptr).
 __device__ __forceinline__ LdsView stage_lds(LdsTable &lds, const KtDeviceTables &tb, const void *const *first,
                                              const void *const *second, int t0, int nt)
@@ -440,21 +415,21 @@ template <> struct Acc<uint16_t> {
 // lane still has (vectors per lane) x (chunk) loads in flight at a time and the
 // per-element order of operations is the one of the definition (product for
 // k = 0, then one fused multiply-add per peer in ascending k).  `ptr(k)` gives
-// peer k's data at the tile start, `at` the lane's places in it.
+// peer k's data at the tile start.
 template <typename T> struct Chunk;
 template <> struct Chunk<float> { static constexpr int N = 8; };       // 148 VGPRs, 3 waves per SIMD
 template <> struct Chunk<uint16_t> { static constexpr int N = 6; };    // 8 accumulators per vector: 6 keeps 3 waves per SIMD
 
-template <typename T, int KC, bool DEVW, typename P, typename TV>
-__device__ __forceinline__ void sum_chunk(Acc<T> *acc, P ptr, const KtWeights &wts, int k0, const TV &at)
+template <typename T, int KC, bool DEVW, typename P>
+__device__ __forceinline__ void sum_chunk(Acc<T> *acc, P ptr, const KtWeights &wts, int k0, int tid)
 {
     constexpr int VPT = KT_TILE_VECS / KT_BLOCK;
     u32x4 r[VPT][KC];
 #pragma unroll
     for (int j = 0; j < KC; ++j) {
-        const T *x = ptr(k0 + j);
+        const u32x4 *x = reinterpret_cast<const u32x4 *>(ptr(k0 + j));
 #pragma unroll
-        for (int u = 0; u < VPT; ++u) r[u][j] = at.load(x, u);
+        for (int u = 0; u < VPT; ++u) r[u][j] = ld_vec(x + u * KT_BLOCK + tid);
     }
 #pragma unroll
     for (int j = 0; j < KC; ++j) {
@@ -467,21 +442,21 @@ __device__ __forceinline__ void sum_chunk(Acc<T> *acc, P ptr, const KtWeights &w
 }
 
 // acc[u] = sum over all K peers of vector u of a full tile.
-template <typename T, bool DEVW, typename P, typename TV>
-__device__ __forceinline__ void sum_in_chunks(Acc<T> *acc, P ptr, const KtWeights &wts, int K, const TV &at)
+template <typename T, bool DEVW, typename P>
+__device__ __forceinline__ void sum_in_chunks(Acc<T> *acc, P ptr, const KtWeights &wts, int K, int tid)
 {
     constexpr int CH = Chunk<T>::N;
     int k0 = 0;
 #pragma unroll 1
-    for (; k0 + CH <= K; k0 += CH) sum_chunk<T, CH, DEVW>(acc, ptr, wts, k0, at);
+    for (; k0 + CH <= K; k0 += CH) sum_chunk<T, CH, DEVW>(acc, ptr, wts, k0, tid);
     switch (K - k0) {      // the last, shorter chunk (uniform over the grid)
-    case 1: sum_chunk<T, 1, DEVW>(acc, ptr, wts, k0, at); break;
-    case 2: sum_chunk<T, 2, DEVW>(acc, ptr, wts, k0, at); break;
-    case 3: sum_chunk<T, 3, DEVW>(acc, ptr, wts, k0, at); break;
-    case 4: sum_chunk<T, 4, DEVW>(acc, ptr, wts, k0, at); break;
-    case 5: sum_chunk<T, 5, DEVW>(acc, ptr, wts, k0, at); break;
-    case 6: if (CH > 6) sum_chunk<T, 6, DEVW>(acc, ptr, wts, k0, at); break;
-    case 7: if (CH > 7) sum_chunk<T, 7, DEVW>(acc, ptr, wts, k0, at); break;
+    case 1: sum_chunk<T, 1, DEVW>(acc, ptr, wts, k0, tid); break;
+    case 2: sum_chunk<T, 2, DEVW>(acc, ptr, wts, k0, tid); break;
+    case 3: sum_chunk<T, 3, DEVW>(acc, ptr, wts, k0, tid); break;
+    case 4: sum_chunk<T, 4, DEVW>(acc, ptr, wts, k0, tid); break;
+    case 5: sum_chunk<T, 5, DEVW>(acc, ptr, wts, k0, tid); break;
+    case 6: if (CH > 6) sum_chunk<T, 6, DEVW>(acc, ptr, wts, k0, tid); break;
+    case 7: if (CH > 7) sum_chunk<T, 7, DEVW>(acc, ptr, wts, k0, tid); break;
     default: break;
     }
 }

@@ -334,10 +334,9 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_any_kernel(KtDeviceTabl
 
     const SolidTile<T> st = solid_tile<T>(tb, tl, g, f, vec_ok);
     if (st.ok) {
-        const TileVecs<false> at(tid, 0);
         Acc<T> acc[VPT];
         sum_in_chunks<T, DEVW>(acc, [&](int k) { return k == 0 ? st.src : reinterpret_cast<const T *>(pp[k - 1]) + g.start; },
-                               wts, K, at);
+                               wts, K, tid);
         u32x4 red[VPT];
 #pragma unroll
         for (int u = 0; u < VPT; ++u) red[u] = acc[u].finish();

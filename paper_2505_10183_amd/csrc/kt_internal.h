@@ -123,8 +123,7 @@ int kt_launch_reduce(const KtDeviceTables &tb, kt_dtype dt, int64_t tile0,
 int kt_launch_fused(const KtDeviceTables &tb, kt_dtype dt, int64_t tile0,
                     int64_t ntiles, const void *const *d_local_ptrs,
                     const void *const *d_peer_ptrs, int K, const KtWeights &w,
-                    float scale, void *const *d_out_ptrs, bool vector_ok,
-                    void *stream);
+                    float scale, void *const *d_out_ptrs, void *stream);
 
 struct KtSgd {
     float scale, lr, mu, wd;
@@ -161,6 +160,6 @@ uint64_t kt_plan_serial(const kt_plan *p);
 kt_status kt_fused_prepare(const kt_plan *p, int bucket, const void *const *local_tensor_ptrs,
                            const void *const *peer_bufs, int K, const float *weights,
                            void *const *out_tensor_ptrs, const char *who, std::vector<uint64_t> &vals,
-                           KtWeights *w, int64_t *tile0, int64_t *ntiles, bool *vector_ok);
+                           KtWeights *w, int64_t *tile0, int64_t *ntiles);
 
 #endif

@@ -131,14 +131,15 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_pack_kernel(KtDeviceTables tb, in
 // ---- unpack with scale ----------------------------------------------------
 
 // Mixed tile.  The bucket's vectors (`val`) were loaded before the table was staged: their
-// addresses do not depend on it.
+// addresses do not depend on it.  The elements of vectors that are not wholly inside one tensor go
+// one per lane (each_cut_elem).
 template <typename T, typename V>
-__device__ __forceinline__ void unpack_mixed(const V &tv, int nt, const TileGeom &g, int64_t b_n, const u32x4 *val,
+__device__ __forceinline__ void unpack_mixed(const V &tv, int nt, const TileGeom &g, const u32x4 *val, const T *src,
                                              float scale, int part)
 {
     constexpr int VE = Elem<T>::VE;
     constexpr int VPT = COPY_VPT;
-    const int nvec = (int)((g.end - g.start + VE - 1) / VE);
+    const int nvec = (int)((g.end - g.start) / VE);
 #pragma unroll
     for (int j = 0; j < VPT; ++j) {
         const int v = (part * VPT + j) * KT_BLOCK + threadIdx.x;
@@ -146,18 +147,17 @@ __device__ __forceinline__ void unpack_mixed(const V &tv, int nt, const TileGeom
             const int64_t e0 = g.start + (int64_t)v * VE;
             const int i = find_owner_v(tv, nt, e0);
             const int64_t r = i >= 0 ? e0 - tv.off[i] : -1;
-            const u32x4 x = scale_vec<T>(val[j], scale);
-            if (r >= 0 && r + VE <= tv.numel[i] && e0 + VE <= b_n) {
+            if (r >= 0 && r + VE <= tv.numel[i]) {
                 T *p = reinterpret_cast<T *>(tv.ptr[i]) + r;
                 // whole 64-byte pieces per wavefront: the address of the lane that starts the piece
-                st_vec_pick(p, x, off64(reinterpret_cast<char *>(p) - (size_t)(threadIdx.x & 3) * KT_VEC_BYTES) == 0);
-            } else {
-                each_owned<VE>(tv, nt, i, e0, b_n, [&](int q, int t, int64_t rr) {
-                    st_elem(reinterpret_cast<T *>(tv.ptr[t]) + rr, elem_of<T>(x, q));
-                });
+                st_vec_pick(p, scale_vec<T>(val[j], scale), off64(reinterpret_cast<char *>(p) - (size_t)(threadIdx.x & 3) * KT_VEC_BYTES) == 0);
             }
         }
     }
+    each_cut_elem<VE>(tv, nt, g.start, (int)(g.end - g.start), part * KT_BLOCK + threadIdx.x, COPY_SPLIT * KT_BLOCK,
+                      [&](int i, int64_t r, int e) {
+                          st_elem(reinterpret_cast<T *>(tv.ptr[i]) + r, scale_elem(ld_elem(src + g.start + e), scale));
+                      });
 }
 
 template <typename T>
@@ -208,20 +208,20 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_unpack_kernel(KtDeviceTables tb, 
         return;
     }
 
-    if ((int64_t)part * VPT * KT_BLOCK * VE >= g.end - g.start) return;
+    if ((int64_t)part * VPT * KT_BLOCK * VE >= g.end - g.start && part * KT_BLOCK >= tl.nt * 2 * VE) return;
     u32x4 val[VPT];
 #pragma unroll
     for (int j = 0; j < VPT; ++j) {
         const int64_t e0 = g.start + (int64_t)((part * VPT + j) * KT_BLOCK + tid) * VE;
-        val[j] = ld_bucket_vec(src, e0, b_n);      // nothing is read at or past b_n
+        if (e0 + VE <= g.end) val[j] = ld_vec(src + e0);
     }
     const void *const *tp = reinterpret_cast<const void *const *>(tensor_ptrs);
     if (tl.nt <= KT_LDS_TENSORS) {
         const LdsView tv = stage_lds(lds, tb, tp, nullptr, tl.t0, tl.nt);
-        unpack_mixed<T>(tv, tl.nt, g, b_n, val, scale, part);
+        unpack_mixed<T>(tv, tl.nt, g, val, src, scale, part);
     } else {
         const GlobalView tv = global_view(tb, tp, nullptr, tl.t0);
-        unpack_mixed<T>(tv, tl.nt, g, b_n, val, scale, part);
+        unpack_mixed<T>(tv, tl.nt, g, val, src, scale, part);
     }
 }
 

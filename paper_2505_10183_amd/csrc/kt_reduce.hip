@@ -4,42 +4,12 @@
 
 namespace {
 
-// A full tile of one workgroup: every load of the lane before its arithmetic, the stores last.
-template <typename T, int K, bool ROT>
-__device__ __forceinline__ void reduce_tile(const T *const *x, const float *w, T *out, int o, int tid, const KtWindow &win)
-{
-    constexpr int VPT = KT_TILE_VECS / KT_BLOCK;   // vectors per lane, K loads each, all in flight at once
-    const TileVecs<ROT> at(tid, o);
-    u32x4 r[VPT][K];
-#pragma unroll
-    for (int u = 0; u < VPT; ++u)
-#pragma unroll
-        for (int k = 0; k < K; ++k) r[u][k] = at.load(x[k], u);
-    u32x4 res[VPT];
-#pragma unroll
-    for (int u = 0; u < VPT; ++u) {
-        Acc<T> acc;
-        acc.first(r[u][0], w[0]);
-#pragma unroll
-        for (int k = 1; k < K; ++k) acc.add(r[u][k], w[k]);
-        res[u] = acc.finish();
-    }
-    kt_wait_store_window(win);     // large launches: the chip writes in bursts (KtWindow)
-#pragma unroll
-    for (int u = 0; u < VPT; ++u) at.store(out, u, res[u]);
-    if (ROT && (o & (KT_VEC_BYTES - 1)) && tid < Elem<T>::VE) {
-        const int e = edge_elem<KT_TILE_BYTES>(tid, sizeof(T), o) / (int)sizeof(T);
-        float a = __fmul_rn(w[0], widen(ld_elem(x[0] + e)));
-#pragma unroll
-        for (int k = 1; k < K; ++k) a = __fmaf_rn(w[k], widen(ld_elem(x[k] + e)), a);
-        st_elem(out + e, narrow<T>(a));
-    }
-}
-
 // One workgroup per 16 KiB tile.  A full tile keeps all K copies of the lane's 4 vectors in flight
 // together (32 loads at K = 8): the kernel is bound by what the memory system sustains for reads
-// with one written line in K + 1.  Copies and output may lie at any element address: the vectors
-// of a full tile are laid out from a 64-byte boundary of the output (rot_vec).
+// with one written line in K + 1.  Copies and output may lie at any element address.  The stores
+// are not moved to 64-byte boundaries as pack and unpack do: with the offsets in registers the
+// loads issue back to back, which inside the store windows lost 3-10 % (1.3B set 3.77 -> 3.89 ms),
+// more than the 3 % of a misaligned non-temporal store stream.
 template <typename T, int K, bool DEVW>
 __global__ __launch_bounds__(KT_BLOCK) void kt_reduce_kernel(KtDeviceTables tb, int64_t tile0,
                                                              const void *const *peer_ptrs, KtWeights wts,
@@ -47,6 +17,7 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_reduce_kernel(KtDeviceTables tb, 
 {
     constexpr int VE = Elem<T>::VE;
     constexpr int64_t TILE_ELEMS = (int64_t)KT_TILE_VECS * VE;
+    constexpr int VPT = KT_TILE_VECS / KT_BLOCK;   // vectors per lane, K loads each, all in flight at once
 
     const KtTile tl = ld_tile(tb.tiles + tile0 + blockIdx.x);
     const int64_t b_n = ld_table(tb.b_elems + tl.bucket);
@@ -68,9 +39,23 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_reduce_kernel(KtDeviceTables tb, 
     const int nvec = (int)(n / VE);
 
     if (nvec == KT_TILE_VECS) {
-        const int o = off64(out);
-        if (o == 0) reduce_tile<T, K, false>(x, w, out, o, tid, win);
-        else reduce_tile<T, K, true>(x, w, out, o, tid, win);
+        u32x4 r[VPT][K];
+#pragma unroll
+        for (int u = 0; u < VPT; ++u)
+#pragma unroll
+            for (int k = 0; k < K; ++k) r[u][k] = ld_vec(reinterpret_cast<const u32x4 *>(x[k]) + u * KT_BLOCK + tid);
+        u32x4 res[VPT];
+#pragma unroll
+        for (int u = 0; u < VPT; ++u) {
+            Acc<T> acc;
+            acc.first(r[u][0], w[0]);
+#pragma unroll
+            for (int k = 1; k < K; ++k) acc.add(r[u][k], w[k]);
+            res[u] = acc.finish();
+        }
+        kt_wait_store_window(win);     // large launches: the chip writes in bursts (KtWindow)
+#pragma unroll
+        for (int u = 0; u < VPT; ++u) st_vec(reinterpret_cast<u32x4 *>(out) + u * KT_BLOCK + tid, res[u]);
     } else {
         for (int v = tid; v < nvec; v += KT_BLOCK) {
             u32x4 r[K];
@@ -110,25 +95,15 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_reduce_manyk_kernel(KtDeviceTable
     T *out = reinterpret_cast<T *>(ld_table(out_ptrs + g.bucket)) + g.start;
     const int64_t n = g.end - g.start;
     const int nvec = (int)(n / VE);
-    auto element = [&](int64_t e) {
-        float a = __fmul_rn(kt_weight<DEVW>(wts, 0), widen(ld_elem(peer(0) + e)));
-        for (int k = 1; k < K; ++k) a = __fmaf_rn(kt_weight<DEVW>(wts, k), widen(ld_elem(peer(k) + e)), a);
-        st_elem(out + e, narrow<T>(a));
-    };
     if (nvec == KT_TILE_VECS) {
-        const int o = off64(out);
-        auto whole = [&](const auto &at) {
-            Acc<T> acc[VPT];
-            sum_in_chunks<T, DEVW>(acc, peer, wts, K, at);
-            u32x4 res[VPT];
+        Acc<T> acc[VPT];
+        sum_in_chunks<T, DEVW>(acc, peer, wts, K, tid);
+        u32x4 res[VPT];
 #pragma unroll
-            for (int u = 0; u < VPT; ++u) res[u] = acc[u].finish();
-            kt_wait_store_window(win);
+        for (int u = 0; u < VPT; ++u) res[u] = acc[u].finish();
+        kt_wait_store_window(win);
 #pragma unroll
-            for (int u = 0; u < VPT; ++u) at.store(out, u, res[u]);
-        };
-        if (o == 0) whole(TileVecs<false>(tid, o)); else whole(TileVecs<true>(tid, o));
-        if ((o & (KT_VEC_BYTES - 1)) && tid < VE) element(edge_elem<KT_TILE_BYTES>(tid, sizeof(T), o) / (int)sizeof(T));
+        for (int u = 0; u < VPT; ++u) st_vec(reinterpret_cast<u32x4 *>(out) + u * KT_BLOCK + tid, res[u]);
         return;
     }
     // the ragged last tile of a bucket: one vector at a time
@@ -140,7 +115,11 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_reduce_manyk_kernel(KtDeviceTable
         st_vec(out + (int64_t)v * VE, acc.finish());
     }
     const int64_t e = (int64_t)nvec * VE + tid;
-    if (e < n) element(e);
+    if (e < n) {
+        float a = __fmul_rn(kt_weight<DEVW>(wts, 0), widen(ld_elem(peer(0) + e)));
+        for (int k = 1; k < K; ++k) a = __fmaf_rn(kt_weight<DEVW>(wts, k), widen(ld_elem(peer(k) + e)), a);
+        st_elem(out + e, narrow<T>(a));
+    }
 }
 
 template <typename T, bool DEVW>

@@ -55,10 +55,9 @@ extern "C" kt_status kt_fused_step_noalloc(kt_plan *p, int bucket, const void *c
     static thread_local std::vector<uint64_t> vals;
     try {
         int64_t tile0 = 0, ntiles = 0;
-        bool vec = false;
         KtWeights w;
         kt_status st = kt_fused_prepare(p, bucket, local_tensor_ptrs, peer_bufs, K, weights, out_tensor_ptrs, who, vals,
-                                        &w, &tile0, &ntiles, &vec);
+                                        &w, &tile0, &ntiles);
         if (st != KT_OK || ntiles == 0) return st;
 
         // layout inside the array: [tiles | tensor offsets | tensor sizes | bucket lengths | pointer table]
@@ -134,7 +133,7 @@ extern "C" kt_status kt_fused_step_noalloc(kt_plan *p, int bucket, const void *c
         const uint64_t *dp = reinterpret_cast<const uint64_t *>(base + o_ptrs);
         int le = kt_launch_fused(tb, hp.dt, tile0, ntiles, reinterpret_cast<const void *const *>(dp),
                                  reinterpret_cast<const void *const *>(dp + 2 * T), K, w, scale,
-                                 reinterpret_cast<void *const *>(const_cast<uint64_t *>(dp + T)), vec, stream);
+                                 reinterpret_cast<void *const *>(const_cast<uint64_t *>(dp + T)), stream);
         if (le != 0) return fail("launch", (hipError_t)le);
         return KT_OK;
     } catch (const std::bad_alloc &) {

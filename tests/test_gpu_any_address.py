@@ -104,3 +104,29 @@ def test_reduce(dtype, shift, K):
     for dst in (out, peers[0]):
         same(dst.views, want, "reduce")
         dst.check_guards("reduce")
+
+
+@pytest.mark.parametrize("dtype,shift", [("f32", s) for s in (0, 4, 12, 16, 36, 48, 60)] +
+                         [("bf16", s) for s in (0, 2, 14, 16, 34, 48, 62)])
+@pytest.mark.parametrize("K,dense", [(1, True), (4, True), (8, False), (8, True), (11, True)])
+def test_fused(dtype, shift, K, dense):
+    w, plan, layout, weights, wts = case(dtype, (4 if dtype == "f32" else 2) if dense else 16, K)
+    nb = plan.num_buckets
+    td = tdtype(dtype)
+    sets = [wl.gradient_set(w, k, DEV) for k in range(K)]
+    grads = Guarded(w.numels, td, shift, 3.0)
+    for v, g in zip(grads.views, sets[0]):
+        v.copy_(g.reshape(-1))
+    hg = [[host(t.reshape(-1)) for t in s] for s in sets]
+    peers = [Guarded(plan.bucket_elems(), td, (shift + 4 * k) % 64, 5.0) for k in range(1, K)]
+    for k in range(1, K):
+        plan.kt_bucket_pack(-1, sets[k], peers[k - 1].views)
+    flat = [peers[k - 1].views[b] for b in range(nb) for k in range(1, K)]
+    want = oracle.direct(hg, wts, 0.37, dtype, "S")
+    out = Guarded(w.numels, td, (64 - shift) % 64, 7.0)
+    plan.kt_fused_step(-1, grads.views, flat, K, weights, 0.37, out.views)
+    plan.kt_fused_step(-1, grads.views, flat, K, weights, 0.37, grads.views)     # over the local gradients
+    torch.cuda.synchronize()
+    for dst in (out, grads):
+        same(dst.views, want, "fused")
+        dst.check_guards("fused")
