@@ -148,15 +148,35 @@ __device__ __forceinline__ void kt_wait_store_window(const KtWindow &w)
 template <typename T> __device__ __forceinline__ T ld_elem(const T *p) { return *(const KT_GLOBAL T *)p; }
 template <typename T> __device__ __forceinline__ void st_elem(T *p, T v) { *(KT_GLOBAL T *)p = v; }
 
-// bf16 <-> binary32.  Widening is exact (the bits become the upper half);
-// narrowing is round-to-nearest-even on the bit pattern, NaN stays quiet NaN.
+// bf16 <-> binary32.  Widening is exact (the bits become the upper half); narrowing is
+// round-to-nearest-even, NaN stays quiet NaN with its upper payload bits: two values per
+// v_cvt_pk_bf16_f32, which gives the bits of (u + 0x7FFF + ((u >> 16) & 1)) >> 16 for each of the
+// 2^32 binary32 patterns (NaN: (u >> 16) | 0x40), in one instruction where the integer form took
+// twelve and a branch and made the bf16 kernels three times the size.
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
-__device__ __forceinline__ uint32_t f32_to_bf16(float f)
+__device__ __forceinline__ uint32_t f32_to_bf16x2(float lo, float hi)
 {
-    uint32_t u = __float_as_uint(f);
+    const f32x2 v = {lo, hi};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+__device__ __forceinline__ uint32_t f32_to_bf16(float f) { return f32_to_bf16x2(f, f) & 0xFFFFu; }
+// INT: the same bits in integer instructions.  Only for full tiles of the reduce (6 to 8 copies)
+// and of the fused pass (6 or more), whose large launches run inside the store windows: there the
+// longer way from the last load to the store spaces the workgroups out and is 1-4 % faster (1.3B
+// set: reduce 3.77 ms against 3.82, fused 3.85 ms against 3.91; fused K = 6, 65 536 tiles 1 245 us
+// against 1 292).
+__device__ __forceinline__ uint32_t f32_to_bf16_int(float f)
+{
+    const uint32_t u = __float_as_uint(f);
     if ((u & 0x7FFFFFFFu) > 0x7F800000u) return (u >> 16) | 0x40u;
     return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
+}
+template <bool INT> __device__ __forceinline__ uint32_t narrow_x2(float lo, float hi)
+{
+    return INT ? f32_to_bf16_int(lo) | (f32_to_bf16_int(hi) << 16) : f32_to_bf16x2(lo, hi);
 }
 
 // scale * x for one element of either storage type
@@ -166,22 +186,15 @@ __device__ __forceinline__ uint16_t scale_elem(uint16_t x, float s)
     return (uint16_t)f32_to_bf16(__fmul_rn(s, __uint_as_float((uint32_t)x << 16)));
 }
 
-template <typename T> __device__ __forceinline__ u32x4 scale_vec(u32x4 v, float s);
-template <> __device__ __forceinline__ u32x4 scale_vec<float>(u32x4 v, float s)
+template <typename T, bool INT = false> __device__ __forceinline__ u32x4 scale_vec(u32x4 v, float s)
 {
     u32x4 r;
+    if constexpr (sizeof(T) == 4) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) r[c] = __float_as_uint(__fmul_rn(s, __uint_as_float(v[c])));
-    return r;
-}
-template <> __device__ __forceinline__ u32x4 scale_vec<uint16_t>(u32x4 v, float s)
-{
-    u32x4 r;
+        for (int c = 0; c < 4; ++c) r[c] = __float_as_uint(__fmul_rn(s, __uint_as_float(v[c])));
+    } else {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        uint32_t lo = f32_to_bf16(__fmul_rn(s, bf16_lo(v[c])));
-        uint32_t hi = f32_to_bf16(__fmul_rn(s, bf16_hi(v[c])));
-        r[c] = lo | (hi << 16);
+        for (int c = 0; c < 4; ++c) r[c] = narrow_x2<INT>(__fmul_rn(s, bf16_lo(v[c])), __fmul_rn(s, bf16_hi(v[c])));
     }
     return r;
 }
@@ -374,7 +387,7 @@ template <> struct Acc<float> {
 #pragma unroll
         for (int c = 0; c < 4; ++c) a[c] = __fmaf_rn(w, __uint_as_float(x[c]), a[c]);
     }
-    __device__ __forceinline__ u32x4 finish() const
+    template <bool INT = false> __device__ __forceinline__ u32x4 finish() const
     {
         u32x4 r;
 #pragma unroll
@@ -400,11 +413,11 @@ template <> struct Acc<uint16_t> {
             a[2 * c + 1] = __fmaf_rn(w, bf16_hi(x[c]), a[2 * c + 1]);
         }
     }
-    __device__ __forceinline__ u32x4 finish() const
+    template <bool INT = false> __device__ __forceinline__ u32x4 finish() const
     {
         u32x4 r;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) r[c] = f32_to_bf16(a[2 * c]) | (f32_to_bf16(a[2 * c + 1]) << 16);
+        for (int c = 0; c < 4; ++c) r[c] = narrow_x2<INT>(a[2 * c], a[2 * c + 1]);
         return r;
     }
 };

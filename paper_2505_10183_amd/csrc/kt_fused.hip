@@ -124,7 +124,7 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_kernel(KtDeviceTables tb, i
                 acc.first(r[u][0], w[0]);
 #pragma unroll
                 for (int k = 1; k < K; ++k) acc.add(r[u][k], w[k]);
-                res[u] = scale_vec<T>(acc.finish(), scale);
+                res[u] = scale_vec<T, (K >= 6)>(acc.template finish<(K >= 6)>(), scale);
             }
             kt_wait_store_window(win);     // large launches: the chip writes in bursts (KtWindow)
 #pragma unroll
@@ -214,7 +214,7 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_manyk_kernel(KtDeviceTables
                          wts, K, tid);
         u32x4 res[VPT];
 #pragma unroll
-        for (int u = 0; u < VPT; ++u) res[u] = scale_vec<T>(acc[u].finish(), scale);
+        for (int u = 0; u < VPT; ++u) res[u] = scale_vec<T, true>(acc[u].template finish<true>(), scale);
         kt_wait_store_window(win);
 #pragma unroll
         for (int u = 0; u < VPT; ++u) st_vec(reinterpret_cast<u32x4 *>(dst) + u * KT_BLOCK + tid, res[u]);
@@ -237,7 +237,7 @@ hipError_t launch_fused_t(const KtDeviceTables &tb, int64_t tile0, int64_t ntile
                           hipStream_t s)
 {
     const dim3 grid((unsigned)ntiles), block(KT_BLOCK);
-    const KtWindow win = kt_store_window(K, ntiles, (KT_WINDOW_MIN_READS_FUSED + K - 1) / K);
+    const KtWindow win = kt_store_window(K, ntiles, (KT_WINDOW_MIN_READS_FUSED + K - 1) / K, sizeof(T) == 4 && K >= 8);
     switch (K) {
 #define KT_CASE(KK) \
     case KK: kt_fused_kernel<T, KK, DEVW><<<grid, block, 0, s>>>(tb, tile0, locals, peers, w, scale, outs, win); break;

@@ -83,14 +83,24 @@ struct KtWindow {
 // The window for a launch of `ntiles` tiles with K peers on the current device (host); none
 // below `min_tiles` tiles: a launch of a few generations of workgroups only pays for the waits
 // of its first and last one.
-KtWindow kt_store_window(int K, int64_t ntiles, int64_t min_tiles);
-// KT_WINDOW_NS: period in nanoseconds (0 switches the window off); KT_WINDOW_OPEN_PCT: the share
-// of the period in which stores are issued.
+// `late` takes the longer period and the narrower opening.
+KtWindow kt_store_window(int K, int64_t ntiles, int64_t min_tiles, bool late);
+// The period in nanoseconds (0 switches the window off) and the share of it, in per cent, in which
+// stores are issued.  `late`: the fp32 reduce (K = 8, 65 536 tiles 1.59 -> 1.57 ms against 12 us /
+// 10 %; K = 16 3.03 -> 2.98 ms) and the fp32 fused pass of 8 and more copies (K = 8 1.60 -> 1.57 ms);
+// bf16 (reduce K = 12 2.19 ms, 2.32 late; fused 1.3B set 3.86 ms, 4.01 late) and the fused pass of
+// fewer copies (fp32 K = 4, 21 135 tiles 289 us, 293 late) stay with the shorter one.
 #ifndef KT_WINDOW_NS
 #define KT_WINDOW_NS 12000
 #endif
 #ifndef KT_WINDOW_OPEN_PCT
 #define KT_WINDOW_OPEN_PCT 10
+#endif
+#ifndef KT_WINDOW_LATE_NS
+#define KT_WINDOW_LATE_NS 14000
+#endif
+#ifndef KT_WINDOW_LATE_OPEN_PCT
+#define KT_WINDOW_LATE_OPEN_PCT 6
 #endif
 // Smallest launches that use the window, in tiles read (tiles x copies) or, for the reduce of up to
 // 8 copies, in tiles.  The fused pass is a step of its own and gains from 65 536 tiles read on

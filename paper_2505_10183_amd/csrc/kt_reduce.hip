@@ -51,7 +51,7 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_reduce_kernel(KtDeviceTables tb, 
             acc.first(r[u][0], w[0]);
 #pragma unroll
             for (int k = 1; k < K; ++k) acc.add(r[u][k], w[k]);
-            res[u] = acc.finish();
+            res[u] = acc.template finish<(K >= 6)>();
         }
         kt_wait_store_window(win);     // large launches: the chip writes in bursts (KtWindow)
 #pragma unroll
@@ -127,7 +127,8 @@ hipError_t launch_reduce_t(const KtDeviceTables &tb, int64_t tile0, int64_t ntil
                            int K, const KtWeights &w, void *const *outs, hipStream_t s)
 {
     dim3 grid((unsigned)ntiles), block(KT_BLOCK);
-    const KtWindow win = kt_store_window(K, ntiles, K <= 8 ? KT_WINDOW_MIN_TILES_REDUCE : (KT_WINDOW_MIN_READS_REDUCE_MANYK + K - 1) / K);
+    const KtWindow win = kt_store_window(K, ntiles, K <= 8 ? KT_WINDOW_MIN_TILES_REDUCE : (KT_WINDOW_MIN_READS_REDUCE_MANYK + K - 1) / K,
+                                         sizeof(T) == 4);
     switch (K) {
 #define KT_CASE(KK) \
     case KK: kt_reduce_kernel<T, KK, DEVW><<<grid, block, 0, s>>>(tb, tile0, peers, w, outs, win); break;

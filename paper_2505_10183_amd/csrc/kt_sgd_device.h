@@ -69,8 +69,8 @@ __device__ __forceinline__ void sgd_quad(const Quad<uint16_t> &g, u32x4 &p, u32x
 template <bool SYS = false> __device__ __forceinline__ void st_model_quad(void *m, u32x4 p)
 {
     u32x2 o;
-    o[0] = f32_to_bf16(__uint_as_float(p[0])) | (f32_to_bf16(__uint_as_float(p[1])) << 16);
-    o[1] = f32_to_bf16(__uint_as_float(p[2])) | (f32_to_bf16(__uint_as_float(p[3])) << 16);
+    o[0] = f32_to_bf16x2(__uint_as_float(p[0]), __uint_as_float(p[1]));
+    o[1] = f32_to_bf16x2(__uint_as_float(p[2]), __uint_as_float(p[3]));
 #if KT_WT_STORE && KT_NT_STORE == 1
     if (SYS) {
         *(volatile KT_GLOBAL u32x2 *)m = o;
