@@ -901,14 +901,12 @@ static kt_status fused_sgd_impl(kt_plan *p, int bucket, const void *const *local
     const size_t P0 = 3 * T + M;
     for (size_t i = 0; i < nb * KP; ++i) vals[P0 + i] = reinterpret_cast<uintptr_t>(peer_bufs[i]);
     auto overlap = [](uintptr_t a, uintptr_t an, uintptr_t b, uintptr_t bn) { return an && bn && a < b + bn && b < a + an; };
-    bool vec = hp.align_bytes % KT_VEC_BYTES == 0;
     for (int b = b0; b < b1; ++b) {
         const uintptr_t bbytes = (uintptr_t)hp.b_elems[b] * hp.elem_size;
         for (size_t k = 0; k < KP; ++k) {
             const uintptr_t pp = vals[P0 + (size_t)b * KP + k];
             if (bbytes && !pp) { kt_set_error("%s: NULL peer %zu of bucket %d", who, k + 1, b); return KT_EINVAL; }
             if (pp & emask) { kt_set_error("%s: peer %zu of bucket %d not aligned to the element size", who, k + 1, b); return KT_EALIGN; }
-            if (pp & (KT_VEC_BYTES - 1)) vec = false;
         }
         for (int t = hp.b_first[b]; t < hp.b_first[b] + hp.b_count[b]; ++t) {
             const uintptr_t lp = vals[t], pa = vals[T + t], va = vals[2 * T + t], ma = master ? vals[3 * T + t] : 0;
@@ -942,7 +940,7 @@ static kt_status fused_sgd_impl(kt_plan *p, int bucket, const void *const *local
     int e = kt_launch_fused_sgd(p->tb, hp.dt, tile0, ntiles, reinterpret_cast<const void *const *>(d),
                                 reinterpret_cast<const void *const *>(d + P0), K, w,
                                 reinterpret_cast<void *const *>(d + T), reinterpret_cast<void *const *>(d + 2 * T),
-                                master ? reinterpret_cast<void *const *>(d + 3 * T) : nullptr, a, vec, stream);
+                                master ? reinterpret_cast<void *const *>(d + 3 * T) : nullptr, a, stream);
     if (e != 0) { kt_set_error("%s: launch: %s", who, hipGetErrorString((hipError_t)e)); return KT_EHIP; }
     return mark_used(p, slot, s);
     KT_GUARD_END(who)

@@ -152,7 +152,7 @@ int kt_launch_fused_sgd(const KtDeviceTables &tb, kt_dtype dt, int64_t tile0,
                         const void *const *d_peer_ptrs, int K, const KtWeights &w,
                         void *const *d_param_ptrs, void *const *d_mom_ptrs,
                         void *const *d_model_ptrs /* NULL: no bf16 model copy */,
-                        const KtSgd &a, bool vector_ok, void *stream);
+                        const KtSgd &a, void *stream);
 
 // ---- shared between the C ABI (kt_api.cpp) and the entry point that
 // allocates nothing (kt_static.hip) ------------------------------------------

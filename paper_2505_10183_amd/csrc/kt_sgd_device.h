@@ -34,7 +34,7 @@ __device__ __forceinline__ Quad<float> ld_quad(const Quad<float> *p)
 }
 __device__ __forceinline__ Quad<uint16_t> ld_quad(const Quad<uint16_t> *p)
 {
-    const u32x2 t = __builtin_nontemporal_load((const KT_GLOBAL u32x2 *)p);
+    const u32x2 t = __builtin_nontemporal_load((const KT_GLOBAL u32x2_any *)p);
     Quad<uint16_t> q;
     q.d[0] = t[0];
     q.d[1] = t[1];
@@ -73,11 +73,11 @@ template <bool SYS = false> __device__ __forceinline__ void st_model_quad(void *
     o[1] = f32_to_bf16x2(__uint_as_float(p[2]), __uint_as_float(p[3]));
 #if KT_WT_STORE && KT_NT_STORE == 1
     if (SYS) {
-        *(volatile KT_GLOBAL u32x2 *)m = o;
+        *(volatile KT_GLOBAL u32x2_any *)m = o;
         return;
     }
 #endif
-    __builtin_nontemporal_store(o, (KT_GLOBAL u32x2 *)m);
+    __builtin_nontemporal_store(o, (KT_GLOBAL u32x2_any *)m);
 }
 
 // one 16-byte gradient vector against its 4 (fp32) or 8 (bf16) parameters

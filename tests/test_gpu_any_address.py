@@ -130,3 +130,40 @@ def test_fused(dtype, shift, K, dense):
     for dst in (out, grads):
         same(dst.views, want, "fused")
         dst.check_guards("fused")
+
+
+@pytest.mark.parametrize("dtype,shift", [("f32", s) for s in (0, 4, 12, 16, 36, 48, 60)] +
+                         [("bf16", s) for s in (0, 4, 12, 16, 36, 48, 60)])
+@pytest.mark.parametrize("K,dense,master", [(1, True, False), (4, True, True), (8, False, True), (8, True, False), (11, True, True)])
+def test_fused_sgd(dtype, shift, K, dense, master):
+    w, plan, layout, weights, wts = case(dtype, (4 if dtype == "f32" else 2) if dense else 16, K)
+    nb = plan.num_buckets
+    td = tdtype(dtype)
+    sets = [wl.gradient_set(w, k, DEV) for k in range(K)]
+    grads = Guarded(w.numels, td, shift, 3.0)
+    for v, g in zip(grads.views, sets[0]):
+        v.copy_(g.reshape(-1))
+    peers = [Guarded(plan.bucket_elems(), td, (shift + 4 * k) % 64, 5.0) for k in range(1, K)]
+    for k in range(1, K):
+        plan.kt_bucket_pack(-1, sets[k], peers[k - 1].views)
+    flat = [peers[k - 1].views[b] for b in range(nb) for k in range(1, K)]
+    p, v = Guarded(w.numels, torch.float32, (64 - shift) % 64, 7.0), Guarded(w.numels, torch.float32, shift, 9.0)
+    m = Guarded(w.numels, torch.bfloat16, shift // 2, 11.0)
+    for t in range(len(w.numels)):
+        p.views[t].copy_(wl.flat_normal(w.numels[t], "f32", 1.0, 300 + t, DEV))
+        v.views[t].fill_(float("nan"))          # a first step does not use the momentum
+    hp, hv = [host(t) for t in p.views], [host(t) for t in v.views]
+    hb = [oracle.weighted_reduce([oracle.pack(layout, [host(t.reshape(-1)) for t in s], dtype)[b] for s in sets], wts, dtype, "S")
+          for b in range(nb)]
+    for step in range(2):
+        plan.kt_fused_step_sgd(-1, grads.views, flat, K, weights, 0.37, p.views, v.views, m.views if master else None,
+                               0.1, 0.9, 5e-4, step == 0)
+        torch.cuda.synchronize()
+        hp, hv = oracle.unpack_sgd(layout, hb, w.numels, 0.37, hp, hv, 0.1, 0.9, 5e-4, step == 0, dtype, "S")
+        same(p.views, hp, "p")
+        same(v.views, hv, "v")
+        for t in range(len(w.numels)):
+            if master:
+                assert bool((m.views[t] == p.views[t].bfloat16()).all()), ("model", step, t)
+    for g, what in ((p, "p"), (v, "v"), (m, "model")):
+        g.check_guards(what)
