@@ -795,12 +795,10 @@ static kt_status unpack_sgd_impl(kt_plan *p, int bucket, const void *const *buck
         if (master) vals[2 * T + t] = reinterpret_cast<uintptr_t>(model_ptrs[t]);
     }
     for (size_t b = 0; b < nb; ++b) vals[2 * T + M + b] = reinterpret_cast<uintptr_t>(bucket_bufs[b]);
-    bool vec = hp.align_bytes % KT_VEC_BYTES == 0;
     for (int b = b0; b < b1; ++b) {
         const uintptr_t bp = vals[2 * T + M + b], bn = (uintptr_t)hp.b_elems[b] * hp.elem_size;
         if (bn && !bp) { kt_set_error("%s: NULL buffer for bucket %d", who, b); return KT_EINVAL; }
         if (bp & ((uintptr_t)hp.elem_size - 1)) { kt_set_error("%s: bucket %d buffer not aligned to the element size", who, b); return KT_EALIGN; }
-        if (bp & (KT_VEC_BYTES - 1)) vec = false;
         for (int t = hp.b_first[b]; t < hp.b_first[b] + hp.b_count[b]; ++t) {
             const uintptr_t pp = vals[t], vp = vals[T + t], tn = (uintptr_t)hp.t_numel[t] * 4;
             if (tn && (!pp || !vp)) { kt_set_error("%s: NULL parameter or momentum pointer for tensor %d", who, t); return KT_EINVAL; }
@@ -829,7 +827,7 @@ static kt_status unpack_sgd_impl(kt_plan *p, int bucket, const void *const *buck
     KtSgd a{scale, lr, momentum, weight_decay, first_step ? 1 : 0, resident ? p->dev_sgd : nullptr};
     int e = kt_launch_unpack_sgd(p->tb, hp.dt, tile0, ntiles, reinterpret_cast<const void *const *>(d + 2 * T + M),
                                  reinterpret_cast<void *const *>(d), reinterpret_cast<void *const *>(d + T),
-                                 master ? reinterpret_cast<void *const *>(d + 2 * T) : nullptr, a, vec, stream);
+                                 master ? reinterpret_cast<void *const *>(d + 2 * T) : nullptr, a, stream);
     if (e != 0) { kt_set_error("%s: launch: %s", who, hipGetErrorString((hipError_t)e)); return KT_EHIP; }
     return mark_used(p, slot, s);
     KT_GUARD_END(who)

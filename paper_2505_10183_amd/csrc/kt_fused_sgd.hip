@@ -320,7 +320,8 @@ constexpr unsigned FSGD_LDS_2 = 40960, FSGD_LDS_4 = 24576;
 // Bytes in flight and store scope by the size of the launch:
 //   bf16    2 workgroups per CU (96 KiB in flight at K = 8) from 256 tiles on: 1.3B set 7.38 -> 7.08 ms
 //           against 8 workgroups (with the model copy 7.97 -> 7.60), K = 4, 21 135 tiles 791 -> 745 us,
-//           K = 2, 512 tiles 22.9 -> 18.9 us
+//           K = 2, 512 tiles 22.9 -> 18.9 us.  8 copies and 32 768 tiles or more also with
+//           system-scope stores (65 536 tiles 3 116 -> 3 062 us); fewer lose 3-20 % with them
 //   fp32    up to 4 096 tiles (128 MiB of p and v written) system-scope stores: what is written stays
 //           in the last-level cache, 2 729 tiles K = 4 57.0 -> 53.5 us; above that they lose up to 15 %
 //           beyond: 2 workgroups per CU for 4 and more copies (K = 8, 21 135 tiles 716 -> 687 us,
@@ -331,7 +332,7 @@ struct FsgdLaunch {
 };
 template <typename T> FsgdLaunch fsgd_launch(int K, int64_t ntiles)
 {
-    if (sizeof(T) == 2) return FsgdLaunch{ntiles > 256 ? FSGD_LDS_2 : 0u, false};
+    if (sizeof(T) == 2) return FsgdLaunch{ntiles > 256 ? FSGD_LDS_2 : 0u, K >= 8 && ntiles >= 32768};
     if (ntiles <= 4096) return FsgdLaunch{0u, true};
     return FsgdLaunch{K >= 4 ? FSGD_LDS_2 : FSGD_LDS_4, false};
 }
@@ -346,7 +347,6 @@ hipError_t launch_fused_sgd_t(const KtDeviceTables &tb, int64_t tile0, int64_t n
         return hipGetLastError();
     }
     const FsgdLaunch how = fsgd_launch<T>(K, ntiles);
-    constexpr bool MAY_SYS = sizeof(T) == 4;
     // SPLIT workgroups per tile; a grid may not hold 2^32 or more lanes: very large plans go in several launches
     constexpr int SPLIT = FsgdShape<T>::SPLIT;
     const int64_t per_launch = (((int64_t)1 << 32) / KT_BLOCK - 1) / SPLIT;
@@ -357,7 +357,7 @@ hipError_t launch_fused_sgd_t(const KtDeviceTables &tb, int64_t tile0, int64_t n
         switch (K) {
 #define KT_CASE(KK) \
     case KK:                                                                                                     \
-        if (MAY_SYS && how.sys) kt_fused_sgd_kernel<T, KK, DEVW, MAY_SYS><<<g2, block, how.lds, s>>>(tb, t0, f, w, a); \
+        if (how.sys) kt_fused_sgd_kernel<T, KK, DEVW, sizeof(T) == 4 || KK >= 8><<<g2, block, how.lds, s>>>(tb, t0, f, w, a); \
         else kt_fused_sgd_kernel<T, KK, DEVW, false><<<g2, block, how.lds, s>>>(tb, t0, f, w, a);                \
         break;
             KT_CASE(1) KT_CASE(2) KT_CASE(3) KT_CASE(4) KT_CASE(5) KT_CASE(6) KT_CASE(7) KT_CASE(8)

@@ -167,3 +167,33 @@ def test_fused_sgd(dtype, shift, K, dense, master):
                 assert bool((m.views[t] == p.views[t].bfloat16()).all()), ("model", step, t)
     for g, what in ((p, "p"), (v, "v"), (m, "model")):
         g.check_guards(what)
+
+
+@pytest.mark.parametrize("dtype,shift", [("f32", s) for s in (0, 4, 12, 16, 36, 48, 60)] +
+                         [("bf16", s) for s in (0, 4, 12, 16, 36, 48, 60)])
+@pytest.mark.parametrize("dense,master", [(True, False), (True, True), (False, True)])
+def test_unpack_sgd(dtype, shift, dense, master):
+    w, plan, layout, _, _ = case(dtype, (4 if dtype == "f32" else 2) if dense else 16, 1)
+    buckets = Guarded(plan.bucket_elems(), tdtype(dtype), (shift + 4) % 64, 5.0)
+    for b, t in enumerate(buckets.views):
+        t.copy_(wl.flat_normal(t.numel(), dtype, 1e-3, 500 + b, DEV))
+    p, v = Guarded(w.numels, torch.float32, shift, 7.0), Guarded(w.numels, torch.float32, (shift if dense else 8), 9.0)
+    m = Guarded(w.numels, torch.bfloat16, shift // 2, 11.0)
+    for t in range(len(w.numels)):
+        p.views[t].copy_(wl.flat_normal(w.numels[t], "f32", 1.0, 300 + t, DEV))
+        v.views[t].fill_(float("nan"))          # a first step does not use the momentum
+    hp, hv, hb = [host(t) for t in p.views], [host(t) for t in v.views], [host(t) for t in buckets.views]
+    for step in range(2):
+        if master:
+            plan.kt_bucket_unpack_sgd_master(-1, buckets.views, 0.37, p.views, v.views, m.views, 0.1, 0.9, 5e-4, step == 0)
+        else:
+            plan.kt_bucket_unpack_sgd(-1, buckets.views, 0.37, p.views, v.views, 0.1, 0.9, 5e-4, step == 0)
+        torch.cuda.synchronize()
+        hp, hv = oracle.unpack_sgd(layout, hb, w.numels, 0.37, hp, hv, 0.1, 0.9, 5e-4, step == 0, dtype, "S")
+        same(p.views, hp, "p")
+        same(v.views, hv, "v")
+        for t in range(len(w.numels)):
+            if master:
+                assert bool((m.views[t] == p.views[t].bfloat16()).all()), ("model", step, t)
+    for g, what in ((p, "p"), (v, "v"), (m, "model")):
+        g.check_guards(what)
