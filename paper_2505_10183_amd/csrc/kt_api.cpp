@@ -88,7 +88,7 @@ KtWindow kt_store_window(int K, int64_t ntiles, int64_t min_tiles, bool late)
     KtWindow off{0, 0};
     long ns = window_ns();
     if (ns < 0) ns = late ? KT_WINDOW_LATE_NS : KT_WINDOW_NS;
-    if (ns == 0 || K < 4 || ntiles < min_tiles) return off;
+    if (ns == 0 || K < 5 || ntiles < min_tiles) return off;
     // rate of the device-wide constant clock in kHz, looked up once per device
     static std::atomic<int> rate_khz[64];
     int dev = -1;

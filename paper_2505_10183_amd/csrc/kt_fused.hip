@@ -238,9 +238,10 @@ hipError_t launch_fused_t(const KtDeviceTables &tb, int64_t tile0, int64_t ntile
 {
     const dim3 grid((unsigned)ntiles), block(KT_BLOCK);
     const KtWindow win = kt_store_window(K, ntiles, (KT_WINDOW_MIN_READS_FUSED + K - 1) / K, sizeof(T) == 4 && K >= 8);
+    const unsigned lds = kt_mix_lds(win, K, ntiles, 2048, (unsigned)sizeof(LdsTable));
     switch (K) {
 #define KT_CASE(KK) \
-    case KK: kt_fused_kernel<T, KK, DEVW><<<grid, block, 0, s>>>(tb, tile0, locals, peers, w, scale, outs, win); break;
+    case KK: kt_fused_kernel<T, KK, DEVW><<<grid, block, lds, s>>>(tb, tile0, locals, peers, w, scale, outs, win); break;
         KT_CASE(1) KT_CASE(2) KT_CASE(3) KT_CASE(4) KT_CASE(5) KT_CASE(6) KT_CASE(7) KT_CASE(8)
 #undef KT_CASE
     default: kt_fused_manyk_kernel<T, DEVW><<<grid, block, 0, s>>>(tb, tile0, locals, peers, K, w, scale, outs, win); break;

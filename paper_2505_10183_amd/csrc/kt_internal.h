@@ -74,7 +74,7 @@ int kt_launch_unpack(const KtDeviceTables &tb, kt_dtype dt, int64_t tile0,
 // reading and writing instead of sprinkling one written line among eight read ones.  Measured on
 // 8 peers: 72-73 % -> 77-78 % of 8 TB/s, flat for periods of 9-18 us, and a steep loss once the
 // period exceeds the time the resident workgroups need for their loads (about 14-19 us), which
-// is why it is used only where that time is known to be longer (K >= 4, many tiles).
+// is why it is used only where that time is known to be longer (K >= 5, many tiles).
 // width == 0: no window.
 struct KtWindow {
     uint32_t period;  // clock ticks
@@ -89,7 +89,7 @@ KtWindow kt_store_window(int K, int64_t ntiles, int64_t min_tiles, bool late);
 // stores are issued.  `late`: the fp32 reduce (K = 8, 65 536 tiles 1.59 -> 1.57 ms against 12 us /
 // 10 %; K = 16 3.03 -> 2.98 ms) and the fp32 fused pass of 8 and more copies (K = 8 1.60 -> 1.57 ms);
 // bf16 (reduce K = 12 2.19 ms, 2.32 late; fused 1.3B set 3.86 ms, 4.01 late) and the fused pass of
-// fewer copies (fp32 K = 4, 21 135 tiles 289 us, 293 late) stay with the shorter one.
+// fewer copies stay with the shorter one.
 #ifndef KT_WINDOW_NS
 #define KT_WINDOW_NS 12000
 #endif
@@ -104,8 +104,8 @@ KtWindow kt_store_window(int K, int64_t ntiles, int64_t min_tiles, bool late);
 #endif
 // Smallest launches that use the window, in tiles read (tiles x copies) or, for the reduce of up to
 // 8 copies, in tiles.  The fused pass is a step of its own and gains from 65 536 tiles read on
-// (K = 8: 8 192 tiles 205 -> 200 us; K = 16: 8 192 tiles 399 -> 371 us, 4 096 tiles 212 -> 199 us)
-// and is even at K = 4, 16 384 tiles.  The reduce stands between pack and unpack, which lose part
+// (K = 8: 8 192 tiles 205 -> 200 us; K = 16: 8 192 tiles 399 -> 371 us, 4 096 tiles 212 -> 199 us).
+// The reduce stands between pack and unpack, which lose part
 // of what the caches held for them: inside the step K = 8 is 1-3 % slower with the window up to
 // 32 768 tiles and 2-4 % faster from 65 536 on.  With more copies that share shrinks: from 262 144
 // tiles read on the step is even or faster (K = 16, 32 768 tiles: 1 927 -> 1 888 us fp32, 1 952 ->
@@ -119,6 +119,17 @@ KtWindow kt_store_window(int K, int64_t ntiles, int64_t min_tiles, bool late);
 #ifndef KT_WINDOW_MIN_READS_REDUCE_MANYK
 #define KT_WINDOW_MIN_READS_REDUCE_MANYK 262144
 #endif
+
+// LDS asked for by reduce and fused launches of 3 to 5 copies that do not use the window, to hold 3
+// workgroups on a CU (160 KiB; registers allow 4 to 7): fewer reads in flight mix better with the
+// writes (18 000 tiles, K = 4: fused 245 -> 237 us fp32, 244 -> 234 bf16; reduce 240 -> 235 us, 242 ->
+// 234; K = 3, 65 536 tiles 705 -> 690 us), and better than the window does at K = 4.  Two copies or
+// less gain nothing; the reduce loses 1-2 % below 4 096 tiles, the fused pass is even at 2 048 and
+// gains from there (2 729 tiles, K = 4: 38.0 -> 37.7 us).  `own`: the kernel's own LDS.
+inline unsigned kt_mix_lds(const KtWindow &w, int K, int64_t ntiles, int64_t min_tiles, unsigned own)
+{
+    return w.width == 0 && K >= 3 && K <= 5 && ntiles >= min_tiles ? 54272u - own : 0u;
+}
 
 // The K weights of a launch travel in the kernel-argument block (`w`), unless
 // `dev` is set: then the kernels read them from that device array when they

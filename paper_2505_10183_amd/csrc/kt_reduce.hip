@@ -129,9 +129,10 @@ hipError_t launch_reduce_t(const KtDeviceTables &tb, int64_t tile0, int64_t ntil
     dim3 grid((unsigned)ntiles), block(KT_BLOCK);
     const KtWindow win = kt_store_window(K, ntiles, K <= 8 ? KT_WINDOW_MIN_TILES_REDUCE : (KT_WINDOW_MIN_READS_REDUCE_MANYK + K - 1) / K,
                                          sizeof(T) == 4);
+    const unsigned lds = kt_mix_lds(win, K, ntiles, 4096, 0);
     switch (K) {
 #define KT_CASE(KK) \
-    case KK: kt_reduce_kernel<T, KK, DEVW><<<grid, block, 0, s>>>(tb, tile0, peers, w, outs, win); break;
+    case KK: kt_reduce_kernel<T, KK, DEVW><<<grid, block, lds, s>>>(tb, tile0, peers, w, outs, win); break;
         KT_CASE(1) KT_CASE(2) KT_CASE(3) KT_CASE(4) KT_CASE(5) KT_CASE(6) KT_CASE(7) KT_CASE(8)
 #undef KT_CASE
     default: kt_reduce_manyk_kernel<T, DEVW><<<grid, block, 0, s>>>(tb, tile0, peers, K, w, outs, win); break;
