@@ -759,7 +759,7 @@ def main():
                                   res["buckets"], w.bucket_cap_bytes >> 20),
                    "launch": "one batched launch per kernel over all buckets; reduce %s"
                              % ("into its own output buffers" if args.out_of_place else "in place over peer slot 0")
-                             + ("; buckets misaligned by one element (element-wise kernels)" if args.misalign else "")
+                             + ("; buckets misaligned by one element" if args.misalign else "")
                              + ("; tensors aligned to %d bytes inside the buckets" % args.align if args.align != 16 else ""),
                    "bytes_per_element": "(K+5)*s = %d" % ((w.K + 5) * w.elem_size)},
         "pct_of_hbm_peak": round(100.0 * res["step_GBps"] / HBM_PEAK_GBS, 2),

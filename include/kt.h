@@ -250,8 +250,8 @@ KT_API kt_status kt_plan_tile_info(const kt_plan *plan, int64_t i, int *bucket,
  *                          tensor id; entries of zero-size tensors may be NULL.
  *   bucket_bufs  host, in: device pointers by bucket; only selected buckets
  *                          are written on the device.
- * Pointers must be aligned to the element size (KT_EALIGN otherwise); 16-byte
- * aligned pointers take the vector path, others a slower correct one.
+ * Pointers must be aligned to the element size (KT_EALIGN otherwise); every
+ * such address takes the vector path.
  * Tensors and buckets must not overlap.
  */
 KT_API kt_status kt_bucket_pack(kt_plan *plan, int bucket,
@@ -373,9 +373,8 @@ KT_API kt_status kt_bucket_unpack_sgd(kt_plan *plan, int bucket,
  *
  *   master_ptrs, momentum_ptrs host, in: T device pointers each, binary32.
  *   model_ptrs                 host, in: T device pointers, bf16, numel[t]
- *                                        elements, 2-byte aligned (8-byte
- *                                        alignment gives the vector path);
- *                                        written only.
+ *                                        elements, 2-byte aligned; written
+ *                                        only.
  * Master parameters, momentum, model parameters and buckets must not overlap.
  */
 KT_API kt_status kt_bucket_unpack_sgd_master(kt_plan *plan, int bucket,
@@ -438,8 +437,7 @@ KT_API kt_status kt_bucket_unpack_sgd_resident(kt_plan *plan, int bucket,
  *                               receive every updated parameter rounded to
  *                               nearest-even (mixed precision).
  * Gradients, parameters, momentum, model parameters and peer buckets must not
- * overlap.  16-byte aligned addresses (8 for the model copy) take the vector
- * path.  kt_fused_step_sgd_resident reads the weights (kt_plan_set_weights) and
+ * overlap.  kt_fused_step_sgd_resident reads the weights (kt_plan_set_weights) and
  * scale, lr, momentum, weight_decay (kt_plan_set_sgd) from the plan's device
  * memory when the kernel runs, for recorded graphs; KT_EINVAL if either was not
  * set.  A first step is refused under stream capture (KT_EUNSUPPORTED).
