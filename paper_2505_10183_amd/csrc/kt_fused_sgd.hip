@@ -266,7 +266,12 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_kernel(KtDeviceTables t
             red[u] = acc.finish();
         }
         update_quads<VPT>(red, lds.red, pr, vr, a, T(0));
-        st_quads<QPL, SYS>(p4, v4, t.m ? reinterpret_cast<u32x2 *>(t.m) + q0 : nullptr, pr, vr);
+        u32x2 *m2 = t.m ? reinterpret_cast<u32x2 *>(t.m) + q0 : nullptr;
+        // system-scope stores want whole 64-byte pieces: a tile that starts elsewhere in any of the three
+        // takes the others (48 831 tiles, K = 8, tensors at 16-byte steps, with the model copy: 2.57 ms,
+        // 2.85 with system-scope stores throughout, 2.54 with none)
+        if (SYS && (sizeof(T) == 4 || off64(t.p) + off64(t.v) + off64(t.m) == 0)) st_quads<QPL, SYS>(p4, v4, m2, pr, vr);
+        else st_quads<QPL, false>(p4, v4, m2, pr, vr);
         return;
     }
     fsgd_other_tile<T, K, DEVW>(lds.table, tb, tl, g, f, pp, K, wts, a, part, SPLIT);
