@@ -270,7 +270,7 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_kernel(KtDeviceTables t
         // system-scope stores want whole 64-byte pieces: a tile that starts elsewhere in any of the three
         // takes the others (48 831 tiles, K = 8, tensors at 16-byte steps, with the model copy: 2.57 ms,
         // 2.85 with system-scope stores throughout, 2.54 with none)
-        if (SYS && (sizeof(T) == 4 || off64(t.p) + off64(t.v) + off64(t.m) == 0)) st_quads<QPL, SYS>(p4, v4, m2, pr, vr);
+        if (SYS && off64(t.p) + off64(t.v) + off64(t.m) == 0) st_quads<QPL, SYS>(p4, v4, m2, pr, vr);
         else st_quads<QPL, false>(p4, v4, m2, pr, vr);
         return;
     }
@@ -327,10 +327,11 @@ constexpr unsigned FSGD_LDS_2 = 40960, FSGD_LDS_4 = 24576;
 //           against 8 workgroups (with the model copy 7.97 -> 7.60), K = 4, 21 135 tiles 791 -> 745 us,
 //           K = 2, 512 tiles 22.9 -> 18.9 us.  8 copies and 32 768 tiles or more also with
 //           system-scope stores (65 536 tiles 3 116 -> 3 062 us); fewer lose 3-20 % with them
-//   fp32    up to 4 096 tiles (128 MiB of p and v written) system-scope stores: what is written stays
-//           in the last-level cache, 2 729 tiles K = 4 57.0 -> 53.5 us; above that they lose up to 15 %
-//           beyond: 2 workgroups per CU for 4 and more copies (K = 8, 21 135 tiles 716 -> 687 us,
-//           K = 4, 8 192 tiles 181 -> 179 us), 4 for fewer (K = 2, 21 135 tiles 340 -> 336 us)
+//   fp32    above 4 096 tiles 2 workgroups per CU for 4 and more copies (K = 8, 21 135 tiles 716 -> 687 us,
+//           K = 4, 8 192 tiles 181 -> 179 us), 4 for fewer (K = 2, 21 135 tiles 340 -> 336 us).  Non-temporal
+//           stores throughout: system-scope ones gain 2-10 % up to 4 096 tiles where a call finds p and v
+//           of the call before in the last-level cache and lose 2-5 % (64-byte aligned) to 13 % (odd
+//           addresses, 2 700 tiles) where it does not, which is the state a training step is called in
 struct FsgdLaunch {
     unsigned lds;
     bool sys;
@@ -338,7 +339,7 @@ struct FsgdLaunch {
 template <typename T> FsgdLaunch fsgd_launch(int K, int64_t ntiles)
 {
     if (sizeof(T) == 2) return FsgdLaunch{ntiles > 256 ? FSGD_LDS_2 : 0u, K >= 8 && ntiles >= 32768};
-    if (ntiles <= 4096) return FsgdLaunch{0u, true};
+    if (ntiles <= 4096) return FsgdLaunch{0u, false};
     return FsgdLaunch{K >= 4 ? FSGD_LDS_2 : FSGD_LDS_4, false};
 }
 
@@ -362,7 +363,7 @@ hipError_t launch_fused_sgd_t(const KtDeviceTables &tb, int64_t tile0, int64_t n
         switch (K) {
 #define KT_CASE(KK) \
     case KK:                                                                                                     \
-        if (how.sys) kt_fused_sgd_kernel<T, KK, DEVW, sizeof(T) == 4 || KK >= 8><<<g2, block, how.lds, s>>>(tb, t0, f, w, a); \
+        if (how.sys) kt_fused_sgd_kernel<T, KK, DEVW, sizeof(T) == 2 && KK >= 8><<<g2, block, how.lds, s>>>(tb, t0, f, w, a); \
         else kt_fused_sgd_kernel<T, KK, DEVW, false><<<g2, block, how.lds, s>>>(tb, t0, f, w, a);                \
         break;
             KT_CASE(1) KT_CASE(2) KT_CASE(3) KT_CASE(4) KT_CASE(5) KT_CASE(6) KT_CASE(7) KT_CASE(8)
