@@ -323,12 +323,15 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_manyk_kernel(KtDeviceTa
 constexpr unsigned FSGD_LDS_2 = 40960, FSGD_LDS_4 = 24576;
 
 // Bytes in flight and store scope by the size of the launch:
-//   bf16    2 workgroups per CU (96 KiB in flight at K = 8) from 256 tiles on: 1.3B set 7.38 -> 7.08 ms
-//           against 8 workgroups (with the model copy 7.97 -> 7.60), K = 4, 21 135 tiles 791 -> 745 us,
-//           K = 2, 512 tiles 22.9 -> 18.9 us.  8 copies and 32 768 tiles or more also with
-//           system-scope stores (65 536 tiles 3 116 -> 3 062 us); fewer lose 3-20 % with them
+//   bf16    2 workgroups per CU (96 KiB in flight at K = 8) above 2 048 tiles, above 1 024 for one and
+//           two copies: 1.3B set 7.38 -> 7.08 ms against 8 workgroups (with the model copy 7.97 -> 7.60),
+//           K = 4, 21 135 tiles 791 -> 745 us.  Below, the chip is not full long enough to gain
+//           (300 to 1 200 tiles, K = 1 to 6: 1-6 % slower with it on aligned sets).  8 copies and
+//           32 768 tiles or more also with system-scope stores (65 536 tiles 3 116 -> 3 062 us); fewer
+//           lose 3-20 % with them
 //   fp32    above 4 096 tiles 2 workgroups per CU for 4 and more copies (K = 8, 21 135 tiles 716 -> 687 us,
-//           K = 4, 8 192 tiles 181 -> 179 us), 4 for fewer (K = 2, 21 135 tiles 340 -> 336 us).  Non-temporal
+//           K = 4, 8 192 tiles 181 -> 179 us), 4 for fewer (K = 2, 21 135 tiles 340 -> 336 us); 6 and more
+//           copies from 2 048 tiles on (K = 8, 3 700 tiles 2-5 % over none).  Non-temporal
 //           stores throughout: system-scope ones gain 2-10 % up to 4 096 tiles where a call finds p and v
 //           of the call before in the last-level cache and lose 2-5 % (64-byte aligned) to 13 % (odd
 //           addresses, 2 700 tiles) where it does not, which is the state a training step is called in
@@ -338,8 +341,8 @@ struct FsgdLaunch {
 };
 template <typename T> FsgdLaunch fsgd_launch(int K, int64_t ntiles)
 {
-    if (sizeof(T) == 2) return FsgdLaunch{ntiles > 256 ? FSGD_LDS_2 : 0u, K >= 8 && ntiles >= 32768};
-    if (ntiles <= 4096) return FsgdLaunch{0u, false};
+    if (sizeof(T) == 2) return FsgdLaunch{ntiles > (K <= 2 ? 1024 : 2048) ? FSGD_LDS_2 : 0u, K >= 8 && ntiles >= 32768};
+    if (ntiles <= (K >= 6 ? 2048 : 4096)) return FsgdLaunch{0u, false};
     return FsgdLaunch{K >= 4 ? FSGD_LDS_2 : FSGD_LDS_4, false};
 }
 

@@ -1,0 +1,98 @@
+"""Which launches hold back workgroups per CU (they ask for LDS beyond the kernel's own): read from
+the kernel nodes of a recorded graph, around the limits of the launch rules."""
+import ctypes
+import sys
+
+import pytest
+import torch
+
+import paper_2505_10183_amd as kt
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.fixture(autouse=True)
+def announce(request):
+    print("\n[gpu-case] %s" % request.node.nodeid, file=sys.stderr, flush=True)
+    yield
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+
+
+class Dim3(ctypes.Structure):
+    _fields_ = [("x", ctypes.c_uint32), ("y", ctypes.c_uint32), ("z", ctypes.c_uint32)]
+
+
+class KernelNodeParams(ctypes.Structure):      # hipKernelNodeParams
+    _fields_ = [("blockDim", Dim3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("gridDim", Dim3),
+                ("kernelParams", ctypes.c_void_p), ("sharedMemBytes", ctypes.c_uint)]
+
+
+def hip():
+    kt.binding.lib()
+    return ctypes.CDLL("libamdhip64.so")       # the runtime the process already holds
+
+
+def recorded_lds(call):
+    """The dynamic LDS of the one kernel that `call(stream)` launches (its tables are on the device already)."""
+    h, s = hip(), torch.cuda.Stream()
+    graph = ctypes.c_void_p()
+    assert h.hipStreamBeginCapture(ctypes.c_void_p(s.cuda_stream), 0) == 0
+    try:
+        call(s)
+    finally:
+        assert h.hipStreamEndCapture(ctypes.c_void_p(s.cuda_stream), ctypes.byref(graph)) == 0
+    n = ctypes.c_size_t(0)
+    assert h.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert h.hipGraphGetNodes(graph, nodes, ctypes.byref(n)) == 0
+    got = []
+    for node in nodes:
+        kind = ctypes.c_int(-1)
+        assert h.hipGraphNodeGetType(ctypes.c_void_p(node), ctypes.byref(kind)) == 0
+        if kind.value == 0:                    # hipGraphNodeTypeKernel
+            p = KernelNodeParams()
+            assert h.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
+            assert p.blockDim.x == 256
+            got.append(p.sharedMemBytes)
+    assert h.hipGraphDestroy(graph) == 0
+    assert len(got) == 1, got
+    return got[0]
+
+
+def dynamic_lds(op, dtype, K, tiles):
+    es, td = (4, torch.float32) if dtype == "f32" else (2, torch.bfloat16)
+    numels = [tiles * (16384 // es)]
+    plan = kt.Plan(numels, dtype, 0, 16)
+    assert plan.num_tiles == tiles
+    mk = plan.marshal
+    keep = [torch.zeros(numels[0], dtype=td, device=DEV) for _ in range(K + 1)]
+    state = [torch.zeros(numels[0], device=DEV) for _ in range(2)] if op in ("sgd", "fused_sgd") else []
+    grads, out, others, copies = mk(keep[:1]), mk(keep[K:]), mk(keep[1:K]), mk(keep[:K])
+    w = [1.0 / K] * K
+
+    def call(stream=None):
+        if op == "reduce":
+            plan.kt_weighted_reduce(-1, copies, K, w, out, stream=stream)
+        elif op == "fused":
+            plan.kt_fused_step(-1, grads, others, K, w, 1.0, out, stream=stream)
+        elif op == "sgd":
+            plan.kt_bucket_unpack_sgd(-1, grads, 1.0, mk(state[:1]), mk(state[1:]), 0.1, 0.9, 0.0, False, stream=stream)
+        else:
+            plan.kt_fused_step_sgd(-1, grads, others, K, w, 1.0, mk(state[:1]), mk(state[1:]), None, 0.1, 0.9, 0.0, False,
+                                   stream=stream)
+
+    call()
+    torch.cuda.synchronize()
+    return recorded_lds(call)
+
+
+@pytest.mark.parametrize("op,dtype,K,least", [
+    ("fused_sgd", "bf16", 1, 1024), ("fused_sgd", "bf16", 2, 1024), ("fused_sgd", "bf16", 4, 2048),
+    ("fused_sgd", "bf16", 8, 2048), ("fused_sgd", "f32", 2, 4096), ("fused_sgd", "f32", 4, 4096),
+    ("fused_sgd", "f32", 8, 2048),
+])
+def test_workgroups_are_held_above_a_launch_size_only(op, dtype, K, least):
+    assert dynamic_lds(op, dtype, K, least) == 0
+    assert dynamic_lds(op, dtype, K, least + 1) > 0
