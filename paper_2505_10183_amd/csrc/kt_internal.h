@@ -125,10 +125,12 @@ KtWindow kt_store_window(int K, int64_t ntiles, int64_t min_tiles, bool late);
 // writes (18 000 tiles, K = 4: fused 245 -> 237 us fp32, 244 -> 234 bf16; reduce 240 -> 235 us, 242 ->
 // 234; K = 3, 65 536 tiles 705 -> 690 us), and better than the window does at K = 4.  Two copies or
 // less gain nothing; the reduce loses 1-2 % below 4 096 tiles, the fused pass is even at 2 048 and
-// gains from there (2 729 tiles, K = 4: 38.0 -> 37.7 us).  `own`: the kernel's own LDS.
+// gains from there (2 729 tiles, K = 4: 38.0 -> 37.7 us).  Three copies gain from 8 192 tiles on only
+// (fp32 fused, aligned: 2 500 tiles 4-7 % slower, 5 000 1 %, 7 000 even, 10 000 1 % faster).  `own`: the
+// kernel's own LDS.
 inline unsigned kt_mix_lds(const KtWindow &w, int K, int64_t ntiles, int64_t min_tiles, unsigned own)
 {
-    return w.width == 0 && K >= 3 && K <= 5 && ntiles >= min_tiles ? 54272u - own : 0u;
+    return w.width == 0 && K >= 3 && K <= 5 && ntiles >= (K == 3 ? 8192 : min_tiles) ? 54272u - own : 0u;
 }
 
 // The K weights of a launch travel in the kernel-argument block (`w`), unless

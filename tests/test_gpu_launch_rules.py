@@ -91,7 +91,9 @@ def dynamic_lds(op, dtype, K, tiles):
 @pytest.mark.parametrize("op,dtype,K,least", [
     ("fused_sgd", "bf16", 1, 1024), ("fused_sgd", "bf16", 2, 1024), ("fused_sgd", "bf16", 4, 2048),
     ("fused_sgd", "bf16", 8, 2048), ("fused_sgd", "f32", 2, 4096), ("fused_sgd", "f32", 4, 4096),
-    ("fused_sgd", "f32", 8, 2048),
+    ("fused_sgd", "f32", 8, 2048), ("reduce", "f32", 3, 8191), ("reduce", "bf16", 4, 4095),
+    ("fused", "f32", 3, 8191), ("fused", "bf16", 3, 8191), ("fused", "f32", 4, 2047), ("fused", "bf16", 5, 2047),
+    ("sgd", "f32", 1, 4095), ("sgd", "bf16", 1, 4095),
 ])
 def test_workgroups_are_held_above_a_launch_size_only(op, dtype, K, least):
     assert dynamic_lds(op, dtype, K, least) == 0
