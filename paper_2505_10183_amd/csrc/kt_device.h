@@ -164,10 +164,13 @@ __device__ __forceinline__ uint32_t f32_to_bf16x2(float lo, float hi)
 }
 __device__ __forceinline__ uint32_t f32_to_bf16(float f) { return f32_to_bf16x2(f, f) & 0xFFFFu; }
 // INT: the same bits in integer instructions.  Only for full tiles of the reduce (6 to 8 copies)
-// and of the fused pass (6 or more), whose large launches run inside the store windows: there the
-// longer way from the last load to the store spaces the workgroups out and is 1-4 % faster (1.3B
-// set: reduce 3.77 ms against 3.82, fused 3.85 ms against 3.91; fused K = 6, 65 536 tiles 1 245 us
-// against 1 292).
+// and of the fused pass (one copy, 6 or more): the longer way from the last load to the store spaces
+// the workgroups out.  With 6 and more copies it is 1-4 % faster in launches inside the store
+// windows (1.3B set: reduce 3.77 ms against 3.82, fused 3.85 ms against 3.91; fused K = 6, 65 536
+// tiles 1 245 us against 1 292); with one, 2-5 % faster from 20 000 tiles on (40 034 tiles of odd
+// tensors 224 us against 233).  The choice is by the number of copies only, so that launches of 300 to
+// 5 000 tiles pay 1-10 % for it (fused K = 6, 900 tiles); made while the kernel runs, by a branch
+// on the window, it took 5-14 % from the large launches.
 __device__ __forceinline__ uint32_t f32_to_bf16_int(float f)
 {
     const uint32_t u = __float_as_uint(f);

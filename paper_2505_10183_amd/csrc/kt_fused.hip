@@ -85,6 +85,7 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_kernel(KtDeviceTables tb, i
     constexpr int64_t TILE_ELEMS = (int64_t)KT_TILE_VECS * VE;
     constexpr int VPT = KT_TILE_VECS / KT_BLOCK;
     constexpr int KP = K > 1 ? K - 1 : 1;
+    constexpr bool INT = K == 1 || K >= 6;         // narrowing in integer instructions (f32_to_bf16_int)
     __shared__ LdsTable lds;
 
     const KtTile tl = ld_tile(tb.tiles + tile0 + blockIdx.x);
@@ -124,7 +125,7 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_kernel(KtDeviceTables tb, i
                 acc.first(r[u][0], w[0]);
 #pragma unroll
                 for (int k = 1; k < K; ++k) acc.add(r[u][k], w[k]);
-                res[u] = scale_vec<T, (K >= 6)>(acc.template finish<(K >= 6)>(), scale);
+                res[u] = scale_vec<T, INT>(acc.template finish<INT>(), scale);
             }
             kt_wait_store_window(win);     // large launches: the chip writes in bursts (KtWindow)
 #pragma unroll
