@@ -290,9 +290,30 @@ __device__ __forceinline__ void each_owned(const V &tv, int nt, int i, int64_t e
 // vector of the tile and after its last.  `i` is the tensor, `r` the element in it, `e` the element
 // in the tile.  One element per lane and call, so that the few cut vectors of a tile cost one
 // memory latency and little code; `first` and `stride` share the work out over the lanes.
+// Every tensor takes 2 * VE places that way, whatever its size.  Where these take more turns than
+// going through the tile's vectors element by element would (tensors of a few elements: 512 and
+// more in a full tile) the vectors are gone through instead.  8 000 tensors of one element, bf16,
+// dense: unpack 49 us by places, 10 by vectors; fused pass 236, 43; one-pass SGD 98, 16.
 template <int VE, typename V, typename F>
 __device__ __forceinline__ void each_cut_elem(const V &tv, int nt, int64_t start, int len, int first, int stride, F f)
 {
+    const int nvec = (len + VE - 1) / VE;
+    if ((nt * 2 * VE + stride - 1) / stride >= VE * ((nvec + stride - 1) / stride)) {
+#pragma unroll 1
+        for (int v = first; v < nvec; v += stride) {
+            const int64_t e0 = start + (int64_t)v * VE;
+            int i = find_owner_v(tv, nt, e0);
+            if (i >= 0 && e0 - tv.off[i] + VE <= tv.numel[i]) continue;
+#pragma unroll 1
+            for (int e = v * VE; e < len && e < v * VE + VE; ++e) {
+                while (i + 1 < nt && tv.off[i + 1] <= start + e) ++i;
+                if (i < 0) continue;
+                const int64_t r = start + e - tv.off[i];
+                if (r < tv.numel[i]) f(i, r, e);
+            }
+        }
+        return;
+    }
     for (int idx = first; idx < nt * 2 * VE; idx += stride) {
         const int i = idx / (2 * VE), slot = idx % (2 * VE);
         const int64_t rel = tv.off[i] - start, last = rel + tv.numel[i];

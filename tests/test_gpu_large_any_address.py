@@ -1,7 +1,7 @@
 """Launches large enough for the choices that depend on the launch size (workgroups held per CU,
 store windows, store scope), with tensors and buckets away from 64-byte boundaries: every kernel,
 every element against the CPU checker's binary32 step mode (bit-identical), with guard elements
-around every output."""
+around every output.  Then the same for tiles that hold hundreds of very small tensors."""
 import sys
 from concurrent.futures import ThreadPoolExecutor
 
@@ -41,14 +41,31 @@ def equal(dev, want, what):
     ("f32", 8192, 3, 60, True),
     ("bf16", 8192, 3, 16, False),
 ])
-def test_every_kernel(dtype, tiles, K, shift, dense):
+def test_large_launches(dtype, tiles, K, shift, dense):
+    n = -(-tiles * (16384 // (4 if dtype == "f32" else 2)) // 24) | 1
+    plan = every_kernel([n + 2 * t for t in range(24)], dtype, (25 if dtype == "f32" else 64) << 20, K, shift, dense)
+    assert plan.num_tiles > tiles
+
+
+# 512 and more tensors in a full tile, or too many in a short one, take another way through the
+# elements (each_cut_elem).
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("sizes,count,dense", [
+    ((1,), 1500, True), ((1,), 1500, False), ((0, 1, 2, 0, 3), 1800, True), ((3, 1, 0, 9), 1400, False),
+    ((7,), 1300, True), ((1,), 40, True), ((9,), 513, False),
+])
+@pytest.mark.parametrize("K", [1, 4, 11])
+def test_many_small_tensors(dtype, sizes, count, dense, K):
+    numels = [sizes[t % len(sizes)] for t in range(count)]
+    numels.insert(count // 2, 20011)           # a tensor of several tiles between them
+    every_kernel(numels, dtype, 0, K, 4, dense)
+
+
+def every_kernel(numels, dtype, cap, K, shift, dense):
     td, es = tdtype(dtype), 4 if dtype == "f32" else 2
-    n = -(-tiles * (16384 // es) // 24) | 1
-    numels = [n + 2 * t for t in range(24)]
-    cap, align = (25 if dtype == "f32" else 64) << 20, es if dense else 16
+    align = es if dense else 16
     plan = kt.Plan(numels, dtype, cap, align)
     L = oracle.assign_buckets(numels, es, cap, align)
-    assert plan.num_tiles > tiles
     thr = [1.0 - 0.04 * k for k in range(K)]
     shares, weights = kt.kt_plan_shares(thr, 1024)
     wts = oracle.share_weights(shares, 1024)
@@ -56,8 +73,9 @@ def test_every_kernel(dtype, tiles, K, shift, dense):
 
     def filled(sizes, dt, sh, seed, sigma=1e-3):
         g = Guarded(sizes, dt, sh, 3.0)
-        for i, v in enumerate(g.views):
-            v.copy_(wl.flat_normal(v.numel(), "f32" if dt == torch.float32 else "bf16", sigma, seed + i, DEV))
+        values = wl.flat_normal(sum(sizes), "f32" if dt == torch.float32 else "bf16", sigma, seed, DEV)
+        for v, x in zip(g.views, values.split(list(sizes))):
+            v.copy_(x)
         return g
 
     grads = filled(numels, td, shift, 1000)
@@ -102,3 +120,4 @@ def test_every_kernel(dtype, tiles, K, shift, dense):
     for g, what in ((slot0, "slot0"), (other, "reduced"), (out, "out"), (fout, "fused"), (p, "p"), (v, "v"), (m, "m"),
                     (fp, "one pass p"), (fv, "one pass v"), (fm, "one pass m")):
         g.check_guards(what)
+    return plan
