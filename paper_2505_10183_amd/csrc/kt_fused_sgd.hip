@@ -210,9 +210,10 @@ __device__ __forceinline__ void fsgd_other_tile(LdsTable &lds, const KtDeviceTab
 }
 
 // K = 1..8.  SPLIT workgroups share a tile; on a full solid tile the loads of all copies, of p and
-// of v are in flight together.  The kernel reads 24 to 40 bytes and writes 8 to 10 per element, and
-// what bounds it is how well the memory system mixes the two: the fewer bytes the chip has in
-// flight beyond what hides the latency the better (FsgdLaunch).  SYS: system-scope stores.
+// of v are in flight together.  The kernel reads K * s + 8 bytes (24 and 40 at K = 8) and writes
+// 8 or 10 per element, and what bounds it is how well the memory system mixes the two: the fewer
+// bytes the chip has in flight beyond what hides the latency the better (FsgdLaunch).  SYS:
+// system-scope stores.
 template <typename T, int K, bool DEVW, bool SYS>
 __global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_kernel(KtDeviceTables tb, int64_t tile0, FsgdArgs f,
                                                                 KtWeights wts, KtSgd a_in)
@@ -318,9 +319,9 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_manyk_kernel(KtDeviceTa
     fsgd_other_tile<T, 0, DEVW>(lds.table, tb, tl, g, f, pp, K, wts, a, 0, 1);
 }
 
-// Bytes of LDS asked for beyond the kernel's own 16 KiB, to hold the number of workgroups per CU
-// (160 KiB of LDS) at 2, 3 or 4; without, registers allow 7 or 8.
-constexpr unsigned FSGD_LDS_2 = 40960, FSGD_LDS_4 = 24576;
+// Bytes of LDS asked for beyond the kernel's own, to hold the number of workgroups per CU at 2 or 4;
+// without, registers allow 7 or 8.
+constexpr unsigned FSGD_LDS_2 = kt_hold_lds(2, sizeof(FsgdLds)), FSGD_LDS_4 = kt_hold_lds(4, sizeof(FsgdLds));
 
 // Bytes in flight and store scope by the size of the launch:
 //   bf16    2 workgroups per CU (96 KiB in flight at K = 8) above 2 048 tiles, above 1 024 for one and

@@ -120,17 +120,34 @@ KtWindow kt_store_window(int K, int64_t ntiles, int64_t min_tiles, bool late);
 #define KT_WINDOW_MIN_READS_REDUCE_MANYK 262144
 #endif
 
-// LDS asked for by reduce and fused launches of 3 to 5 copies that do not use the window, to hold 3
-// workgroups on a CU (160 KiB; registers allow 4 to 7): fewer reads in flight mix better with the
+// LDS to ask for beyond a kernel's own `own` bytes, so that `wgs` workgroups share a CU: the smallest
+// request of which one more does not fit.  A CU has 160 KiB and gives it out in granules of 1 280 bytes
+// (workgroups counted while they run: 53 760 bytes hold 3, 54 272 hold 2; the runtime's occupancy
+// query rounds to less and says 3 for both).
+constexpr unsigned KT_CU_LDS = 163840, KT_LDS_GRANULE = 1280;
+constexpr unsigned kt_hold_lds(unsigned wgs, unsigned own)
+{
+    return (KT_CU_LDS / (wgs + 1) / KT_LDS_GRANULE + 1) * KT_LDS_GRANULE - own;
+}
+constexpr bool kt_holds(unsigned wgs)
+{
+    const unsigned bytes = kt_hold_lds(wgs, 0);
+    return bytes % KT_LDS_GRANULE == 0 && bytes <= 65536 && KT_CU_LDS / bytes == wgs;
+}
+static_assert(kt_holds(2) && kt_holds(4) && kt_holds(5), "the counts that launches ask for");
+
+// LDS asked for by reduce and fused launches of 3 to 5 copies that do not use the window, to hold 2
+// workgroups on a CU (registers allow 4 to 7): fewer reads in flight mix better with the
 // writes (18 000 tiles, K = 4: fused 245 -> 237 us fp32, 244 -> 234 bf16; reduce 240 -> 235 us, 242 ->
-// 234; K = 3, 65 536 tiles 705 -> 690 us), and better than the window does at K = 4.  Two copies or
+// 234; K = 3, 65 536 tiles 705 -> 690 us), and better than the window does at K = 4.  Three are no
+// better than without.  Two copies or
 // less gain nothing; the reduce loses 1-2 % below 4 096 tiles, the fused pass is even at 2 048 and
 // gains from there (2 729 tiles, K = 4: 38.0 -> 37.7 us).  Three copies gain from 8 192 tiles on only
 // (fp32 fused, aligned: 2 500 tiles 4-7 % slower, 5 000 1 %, 7 000 even, 10 000 1 % faster).  `own`: the
 // kernel's own LDS.
 inline unsigned kt_mix_lds(const KtWindow &w, int K, int64_t ntiles, int64_t min_tiles, unsigned own)
 {
-    return w.width == 0 && K >= 3 && K <= 5 && ntiles >= (K == 3 ? 8192 : min_tiles) ? 54272u - own : 0u;
+    return w.width == 0 && K >= 3 && K <= 5 && ntiles >= (K == 3 ? 8192 : min_tiles) ? kt_hold_lds(2, own) : 0u;
 }
 
 // The K weights of a launch travel in the kernel-argument block (`w`), unless

@@ -150,15 +150,15 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_unpack_sgd_kernel(KtDeviceTables 
     }
 }
 
-// LDS asked for beyond the kernel's own 16 KiB, to hold the number of workgroups per CU (160 KiB of
-// LDS; 8 without) and with it the reads in flight: fewer mix better with the writes.  bf16: 6 (1.3B
-// set 3.78 -> 3.47 ms, with the model copy 4.30 -> 3.92); fp32: 5 (ViT-B/16 0.281 -> 0.269 ms,
+// LDS asked for beyond the kernel's own, to hold the number of workgroups per CU (8 without) and
+// with it the reads in flight: fewer mix better with the writes.  bf16: 5 (1.3B
+// set 3.78 -> 3.47 ms, with the model copy 4.30 -> 3.92); fp32: 4 (ViT-B/16 0.281 -> 0.269 ms,
 // 65 536 tiles 0.914 -> 0.835 ms).  Launches of less than 64 MiB of gradient do not fill the chip
 // long enough to gain (2 729 tiles fp32 36 us either way) and go without.
 static unsigned sgd_lds(kt_dtype dt, int64_t ntiles)
 {
     if (ntiles < 4096) return 0;
-    return dt == KT_F32 ? 16000 : 10800;
+    return kt_hold_lds(dt == KT_F32 ? 4 : 5, (unsigned)sizeof(LdsTable));
 }
 
 }  // namespace

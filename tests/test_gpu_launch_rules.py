@@ -98,3 +98,13 @@ def dynamic_lds(op, dtype, K, tiles):
 def test_workgroups_are_held_above_a_launch_size_only(op, dtype, K, least):
     assert dynamic_lds(op, dtype, K, least) == 0
     assert dynamic_lds(op, dtype, K, least + 1) > 0
+
+
+@pytest.mark.parametrize("op,dtype,K,own,count", [
+    ("reduce", "f32", 4, 0, 2), ("fused", "bf16", 5, 16384, 2), ("sgd", "f32", 1, 16384, 4), ("sgd", "bf16", 1, 16384, 5),
+    ("fused_sgd", "bf16", 8, 16384, 2), ("fused_sgd", "f32", 2, 16384, 4), ("fused_sgd", "f32", 8, 16384, 2),
+])
+def test_held_workgroups_per_cu(op, dtype, K, own, count):
+    """160 KiB of LDS in granules of 1280 bytes; `own` is the kernel's static LDS."""
+    granules = -(-(own + dynamic_lds(op, dtype, K, 4200)) // 1280)
+    assert 163840 // 1280 // granules == count
