@@ -70,7 +70,8 @@ static bool capturing(hipStream_t s)
 // ---- store window ------------------------------------------------------------
 
 // The period in nanoseconds: what the environment variable KT_STORE_WINDOW_NS says (read once;
-// 0 switches the windows off, e.g. when other work shares the GPU), or -1: the built-in ones.
+// 0, for callers whose other work shares the GPU, switches the windows and kt_hold_lds off), or -1: the
+// built-in ones.
 static long window_ns()
 {
     static const long ns = [] {
@@ -82,6 +83,8 @@ static long window_ns()
     }();
     return ns;
 }
+
+bool kt_may_hold() { return window_ns() != 0; }
 
 KtWindow kt_store_window(int K, int64_t ntiles, int64_t min_tiles, bool late)
 {

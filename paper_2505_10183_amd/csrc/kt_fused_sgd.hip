@@ -356,7 +356,8 @@ hipError_t launch_fused_sgd_t(const KtDeviceTables &tb, int64_t tile0, int64_t n
         kt_fused_sgd_manyk_kernel<T, DEVW><<<grid, block, 0, s>>>(tb, tile0, f, K, w, a);
         return hipGetLastError();
     }
-    const FsgdLaunch how = fsgd_launch<T>(K, ntiles);
+    FsgdLaunch how = fsgd_launch<T>(K, ntiles);
+    if (!kt_may_hold()) how.lds = 0;
     // SPLIT workgroups per tile; a grid may not hold 2^32 or more lanes: very large plans go in several launches
     constexpr int SPLIT = FsgdShape<T>::SPLIT;
     const int64_t per_launch = (((int64_t)1 << 32) / KT_BLOCK - 1) / SPLIT;

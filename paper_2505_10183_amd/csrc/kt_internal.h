@@ -70,11 +70,12 @@ int kt_launch_unpack(const KtDeviceTables &tb, kt_dtype dt, int64_t tile0,
                      float scale, void *const *d_tensor_ptrs, void *stream);
 // Store window of the read-dominated kernels (reduce, fused pass) on large launches: every wave
 // holds its finished results back until the device-wide constant-rate clock, masked to a period
-// of about 10 us, is inside the first `width` ticks, so that the whole chip alternates between
+// of 12 or 14 us, is inside the first `width` ticks, so that the whole chip alternates between
 // reading and writing instead of sprinkling one written line among eight read ones.  Measured on
-// 8 peers: 72-73 % -> 77-78 % of 8 TB/s, flat for periods of 9-18 us, and a steep loss once the
-// period exceeds the time the resident workgroups need for their loads (about 14-19 us), which
-// is why it is used only where that time is known to be longer (K >= 5, many tiles).
+// 8 peers: 72-73 % -> 77-78 % of 8 TB/s, the same within a point for periods of 10-14 us, and a steep
+// loss once the period exceeds the time the resident workgroups need for their loads (about 14-19 us
+// at K = 8; the 14 us period leaves 0-5 us, the 12 us one 2-7), which is why it is used only where
+// that time is known to be longer (K >= 5, many tiles).
 // width == 0: no window.
 struct KtWindow {
     uint32_t period;  // clock ticks
@@ -85,8 +86,8 @@ struct KtWindow {
 // of its first and last one.
 // `late` takes the longer period and the narrower opening.
 KtWindow kt_store_window(int K, int64_t ntiles, int64_t min_tiles, bool late);
-// The period in nanoseconds (0 switches the window off) and the share of it, in per cent, in which
-// stores are issued.  `late`: the fp32 reduce (K = 8, 65 536 tiles 1.59 -> 1.57 ms against 12 us /
+// The period in nanoseconds (0 switches the window off; KT_STORE_WINDOW_NS sets one period for both
+// kinds) and the share of it, in per cent, in which stores are issued.  `late`: the fp32 reduce (K = 8, 65 536 tiles 1.59 -> 1.57 ms against 12 us /
 // 10 %; K = 16 3.03 -> 2.98 ms) and the fp32 fused pass of 8 and more copies (K = 8 1.60 -> 1.57 ms);
 // bf16 (reduce K = 12 2.19 ms, 2.32 late; fused 1.3B set 3.86 ms, 4.01 late) and the fused pass of
 // fewer copies stay with the shorter one.
@@ -136,6 +137,10 @@ constexpr bool kt_holds(unsigned wgs)
 }
 static_assert(kt_holds(2) && kt_holds(4) && kt_holds(5), "the counts that launches ask for");
 
+// false where the caller shares the GPU (KT_STORE_WINDOW_NS=0): held workgroups keep the LDS of every
+// CU from kernels that run beside them.
+bool kt_may_hold();
+
 // LDS asked for by reduce and fused launches of 3 to 5 copies that do not use the window, to hold 2
 // workgroups on a CU (registers allow 4 to 7): fewer reads in flight mix better with the
 // writes (18 000 tiles, K = 4: fused 245 -> 237 us fp32, 244 -> 234 bf16; reduce 240 -> 235 us, 242 ->
@@ -147,7 +152,7 @@ static_assert(kt_holds(2) && kt_holds(4) && kt_holds(5), "the counts that launch
 // kernel's own LDS.
 inline unsigned kt_mix_lds(const KtWindow &w, int K, int64_t ntiles, int64_t min_tiles, unsigned own)
 {
-    return w.width == 0 && K >= 3 && K <= 5 && ntiles >= (K == 3 ? 8192 : min_tiles) ? kt_hold_lds(2, own) : 0u;
+    return w.width == 0 && K >= 3 && K <= 5 && ntiles >= (K == 3 ? 8192 : min_tiles) && kt_may_hold() ? kt_hold_lds(2, own) : 0u;
 }
 
 // The K weights of a launch travel in the kernel-argument block (`w`), unless

@@ -157,7 +157,7 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_unpack_sgd_kernel(KtDeviceTables 
 // long enough to gain (2 729 tiles fp32 36 us either way) and go without.
 static unsigned sgd_lds(kt_dtype dt, int64_t ntiles)
 {
-    if (ntiles < 4096) return 0;
+    if (ntiles < 4096 || !kt_may_hold()) return 0;
     return kt_hold_lds(dt == KT_F32 ? 4 : 5, (unsigned)sizeof(LdsTable));
 }
 

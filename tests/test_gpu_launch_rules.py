@@ -1,6 +1,8 @@
 """Which launches hold back workgroups per CU (they ask for LDS beyond the kernel's own): read from
 the kernel nodes of a recorded graph, around the limits of the launch rules."""
 import ctypes
+import os
+import subprocess
 import sys
 
 import pytest
@@ -108,3 +110,20 @@ def test_held_workgroups_per_cu(op, dtype, K, own, count):
     """160 KiB of LDS in granules of 1280 bytes; `own` is the kernel's static LDS."""
     granules = -(-(own + dynamic_lds(op, dtype, K, 4200)) // 1280)
     assert 163840 // 1280 // granules == count
+
+
+LARGE = [("reduce", "f32", 4), ("reduce", "bf16", 5), ("fused", "bf16", 4), ("sgd", "f32", 1), ("sgd", "bf16", 1),
+         ("fused_sgd", "bf16", 8), ("fused_sgd", "f32", 2)]
+
+
+@pytest.mark.parametrize("op,dtype,K", LARGE)
+def test_nothing_held_where_the_gpu_is_shared(op, dtype, K):
+    """KT_STORE_WINDOW_NS=0 (read once per process, hence a child): no LDS beyond the kernel's own."""
+    assert dynamic_lds(op, dtype, K, 4200) > 0
+    env = dict(os.environ, KT_STORE_WINDOW_NS="0")
+    here = os.path.dirname(os.path.abspath(__file__))
+    code = "import sys; sys.path[:0] = [%r, %r]; import test_gpu_launch_rules as t; print('LDS', t.dynamic_lds(%r, %r, %d, 4200))" \
+        % (os.path.dirname(here), here, op, dtype, K)
+    r = subprocess.run([sys.executable, "-c", code], env=env, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0, r.stderr[-2000:]
+    assert "LDS 0" in r.stdout.splitlines(), r.stdout
