@@ -501,16 +501,14 @@ def test_pointer_churn_and_streams():
         assert all(bool((t == float(r)).all()) for t in o2)
 
 
-@pytest.mark.parametrize("dtype,K", [("f32", 5), ("bf16", 4)])
-def test_reduce_large_launch_with_store_windows(dtype, K):
-    """A launch large enough (65 536 tiles, K >= 4) for the reduce to hold its stores back until the
-    chip-wide store window: every element of every bucket against the checker's strict mode, in place
-    and into separate outputs."""
-    w = wl.get("sized_%s_65536" % dtype)
+def check_large_reduce(dtype, K, tiles):
+    """Every element of every bucket against the checker's strict mode, in place and into separate outputs."""
+    from concurrent.futures import ThreadPoolExecutor
+    w = wl.get("sized_%s_%d" % (dtype, tiles))
     plan = kt.Plan(w.numels, dtype, w.bucket_cap_bytes, 16)
     nb, elems = plan.num_buckets, plan.bucket_elems()
-    assert plan.num_tiles >= 65536
-    thr = w.throughputs[:K]
+    assert plan.num_tiles >= tiles
+    thr = [1.0 - 0.04 * k for k in range(K)]
     shares, weights = kt.kt_plan_shares(thr, 1024)
     wts = oracle.share_weights(oracle.plan_shares(thr, 1024), 1024)
     peers = [[wl.flat_normal(n, dtype, 1e-3, 3000 + 50 * k + b, DEV) for b, n in enumerate(elems)] for k in range(K)]
@@ -520,10 +518,28 @@ def test_reduce_large_launch_with_store_windows(dtype, K):
     plan.kt_weighted_reduce(-1, flat, K, weights, outs)
     plan.kt_weighted_reduce(-1, flat, K, weights, peers[0])          # in place over peer 0
     torch.cuda.synchronize()
-    for b in range(nb):
+
+    def bucket(b):
         want = oracle.weighted_reduce([hp0[b]] + [host(peers[k][b]) for k in range(1, K)], wts, dtype, "S")
         assert raw(host(outs[b])).tobytes() == raw(want).tobytes(), ("own output", b)
         assert raw(host(peers[0][b])).tobytes() == raw(want).tobytes(), ("in place", b)
+
+    with ThreadPoolExecutor(8) as pool:
+        list(pool.map(bucket, range(nb)))
+
+
+# the reduce holds its stores back until the chip-wide store window from 65 536 tiles on with 5 to 8
+# copies and from 262 144 tiles read on with more
+@pytest.mark.parametrize("dtype,K,tiles", [("f32", 5, 65536), ("bf16", 6, 65536), ("f32", 16, 16384), ("bf16", 16, 16384)])
+def test_reduce_large_launch_with_store_windows(dtype, K, tiles):
+    assert K >= 5 and (tiles >= 65536 if K <= 8 else tiles * K >= 262144)
+    check_large_reduce(dtype, K, tiles)
+
+
+@pytest.mark.parametrize("dtype,K", [("f32", 3), ("bf16", 4)])
+def test_reduce_large_launch_with_held_workgroups(dtype, K):
+    """Three to five copies without a window: two workgroups per CU."""
+    check_large_reduce(dtype, K, 16384)
 
 
 def test_two_host_threads_share_a_plan():
