@@ -32,8 +32,8 @@ HBM_PEAK_GBS = 8000.0
 # sources the figure is reported as null until the counters are taken again.
 KERNEL_SOURCES = ("kt_internal.h", "kt_device.h", "kt_sgd_device.h", "kt_pack_unpack.hip", "kt_reduce.hip", "kt_fused.hip",
                   "kt_sgd.hip", "kt_fused_sgd.hip")
-TRAFFIC_SOURCES_SHA = "380d6c1e6ad918bb"
-TRAFFIC_BYTES = {"decoder_1p3b": 23705640787, "vit_b16": 3119150390}
+TRAFFIC_SOURCES_SHA = "37e082aea58e3388"
+TRAFFIC_BYTES = {"decoder_1p3b": 23705645761, "vit_b16": 3119138757}
 
 
 def measured_traffic(workload):
@@ -649,8 +649,7 @@ def main():
                     help="align_bytes of the bucket plan (16 as in the workload definitions; 16384 puts every "
                          "tensor on a tile boundary)")
     ap.add_argument("--misalign", action="store_true",
-                    help="offset every bucket buffer by one element: the library then takes its "
-                         "element-wise (4-byte / 2-byte) kernels instead of the 16-byte ones")
+                    help="offset every bucket buffer by one element (16-byte accesses at 4- or 2-byte addresses)")
     ap.add_argument("--ab", default="", help="interleaved comparison of library builds: comma list of name=path "
                                              "(see ab_compare); prints a table instead of the JSON line")
     ap.add_argument("--kernels", default="reduce,fused,sgd", help="kernels compared by --ab")

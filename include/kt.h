@@ -56,10 +56,10 @@
  *    every 14 us in the binary32 reduce and the binary32 fused pass of 8 and
  *    more copies.
  *  - Other large launches ask for more LDS than they use, so that only 2 to 5 of
- *    their workgroups share a CU (23 to 53 KiB of its LDS stay free):
- *    kt_fused_step and kt_weighted_reduce of 3 to 5 copies from 32 to 128 MiB
- *    per copy, unpack fused with SGD from 64 MiB, kt_fused_step_sgd of up to 8
- *    copies above 16 to 64 MiB.
+ *    their workgroups share a CU (22 to 52 KiB of its LDS stay free):
+ *    kt_fused_step and kt_weighted_reduce of 3 to 5 copies without bursts from
+ *    32 to 128 MiB per copy on, unpack fused with SGD from 64 MiB, and
+ *    kt_fused_step_sgd of up to 8 copies above 16 to 64 MiB.
  *  - The environment variable KT_STORE_WINDOW_NS, read once per process, sets the
  *    period of the bursts in nanoseconds; 0, for programs whose other kernels
  *    run beside these calls, switches both the bursts and the LDS requests off.

@@ -67,7 +67,8 @@ __device__ __forceinline__ void st_vec(void *p, u32x4 v)
 // the L2 writes through at once instead of holding the line, measured 1-4 points of 8 TB/s
 // better there than the non-temporal store, and 1-3 points worse in the kernels that write a
 // quarter of their bytes or less (reduce, fused pass, K copies -> parameters), which keep
-// st_vec.  KT_WT_STORE=0 builds these kernels with st_vec as well, for measurement.
+// st_vec (the last one but for large bf16 launches, FsgdLaunch).  KT_WT_STORE=0 builds these
+// kernels with st_vec as well, for measurement.
 #ifndef KT_WT_STORE
 #define KT_WT_STORE 1
 #endif

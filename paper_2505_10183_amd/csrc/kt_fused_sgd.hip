@@ -325,11 +325,13 @@ constexpr unsigned FSGD_LDS_2 = kt_hold_lds(2, sizeof(FsgdLds)), FSGD_LDS_4 = kt
 
 // Bytes in flight and store scope by the size of the launch:
 //   bf16    2 workgroups per CU (96 KiB in flight at K = 8) above 2 048 tiles, above 1 024 for one and
-//           two copies: 1.3B set 7.38 -> 7.08 ms against 8 workgroups (with the model copy 7.97 -> 7.60),
-//           K = 4, 21 135 tiles 791 -> 745 us.  Below, the chip is not full long enough to gain
-//           (300 to 1 200 tiles, K = 1 to 6: 1-6 % slower with it on aligned sets).  8 copies and
-//           32 768 tiles or more also with system-scope stores (65 536 tiles 3 116 -> 3 062 us); fewer
-//           lose 3-20 % with them
+//           two copies: 1.3B set 7.38 -> 7.08 ms against 8 workgroups, with the model copy 7.97 -> 7.60
+//           (which depends on where the tensors lie: three sets of 46 GB in turn, 24 arrangements,
+//           7.45-7.94 ms without, 7.47-7.77 with, 7.45-7.65 with system-scope stores as well); K = 4,
+//           21 135 tiles 791 -> 745 us.  Below, the chip is not full long enough to gain (300 to 1 200
+//           tiles, K = 1 to 6: 1-6 % slower with it on aligned sets).  8 copies and 32 768 tiles or
+//           more also with system-scope stores (65 536 tiles 3 116 -> 3 062 us); fewer lose 3-20 % with
+//           them.  Buffer stores, which are not waited for, are slower there (1.3B set 7.74 ms, 7.54)
 //   fp32    above 4 096 tiles 2 workgroups per CU for 4 and more copies (K = 8, 21 135 tiles 716 -> 687 us,
 //           K = 4, 8 192 tiles 181 -> 179 us), 4 for fewer (K = 2, 21 135 tiles 340 -> 336 us); 6 and more
 //           copies from 2 048 tiles on (K = 8, 3 700 tiles 2-5 % over none).  Non-temporal

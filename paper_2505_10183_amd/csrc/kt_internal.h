@@ -142,7 +142,7 @@ static_assert(kt_holds(2) && kt_holds(4) && kt_holds(5), "the counts that launch
 bool kt_may_hold();
 
 // LDS asked for by reduce and fused launches of 3 to 5 copies that do not use the window, to hold 2
-// workgroups on a CU (registers allow 4 to 7): fewer reads in flight mix better with the
+// workgroups on a CU (registers allow 5 to 8): fewer reads in flight mix better with the
 // writes (18 000 tiles, K = 4: fused 245 -> 237 us fp32, 244 -> 234 bf16; reduce 240 -> 235 us, 242 ->
 // 234; K = 3, 65 536 tiles 705 -> 690 us), and better than the window does at K = 4.  Three are no
 // better than without.  Two copies or
