@@ -357,12 +357,12 @@ __device__ __forceinline__ u32x4 gather_vec(const V &tv, int nt, int i, int64_t 
     return join(x);
 }
 // `second` may be NULL for kernels with one tensor set (ptr2 then mirrors ptr).
-__device__ __forceinline__ LdsView stage_lds(LdsTable &lds, const KtDeviceTables &tb, const void *const *first,
-                                             const void *const *second, int t0, int nt)
+__device__ __forceinline__ LdsView stage_lds(LdsTable &lds, const int64_t *t_off, const int64_t *t_numel,
+                                             const void *const *first, const void *const *second, int t0, int nt)
 {
     for (int i = threadIdx.x; i < nt; i += KT_BLOCK) {
-        lds.off[i] = tb.t_off[t0 + i];
-        lds.numel[i] = tb.t_numel[t0 + i];
+        lds.off[i] = t_off[t0 + i];
+        lds.numel[i] = t_numel[t0 + i];
         lds.ptr[i] = reinterpret_cast<uintptr_t>(first[t0 + i]);
         lds.ptr2[i] = reinterpret_cast<uintptr_t>(second ? second[t0 + i] : first[t0 + i]);
     }
@@ -375,22 +375,35 @@ __device__ __forceinline__ LdsView stage_lds(LdsTable &lds, const KtDeviceTables
     return v;
 }
 
-__device__ __forceinline__ GlobalView global_view(const KtDeviceTables &tb, const void *const *first,
-                                                  const void *const *second, int t0)
+__device__ __forceinline__ GlobalView global_view(const int64_t *t_off, const int64_t *t_numel,
+                                                  const void *const *first, const void *const *second, int t0)
 {
     GlobalView v;
-    v.off = (const KT_GLOBAL int64_t *)(tb.t_off + t0);
-    v.numel = (const KT_GLOBAL int64_t *)(tb.t_numel + t0);
+    v.off = (const KT_GLOBAL int64_t *)(t_off + t0);
+    v.numel = (const KT_GLOBAL int64_t *)(t_numel + t0);
     v.ptr = (const KT_GLOBAL uintptr_t *)(reinterpret_cast<const uintptr_t *>(first) + t0);
     v.ptr2 = (const KT_GLOBAL uintptr_t *)(reinterpret_cast<const uintptr_t *>(second ? second : first) + t0);
     return v;
 }
 
+// The weights as a kernel argument.  Kernels for up to 8 copies take 8 of them: a launch copies its
+// argument block to the device, and 340 bytes of it cost the host 3.4 us a launch against 2.8 for 48.
+template <int N> struct WeightArgs {
+    float w[N];
+    const float *dev;
+    explicit WeightArgs(const KtWeights &f) : dev(f.dev)
+    {
+        for (int k = 0; k < N; ++k) w[k] = f.w[k];
+    }
+};
+using FewWeights = WeightArgs<8>;
+using AllWeights = WeightArgs<KT_MAX_PEERS>;
+
 // Weight of peer k: from the kernel-argument block, or, when the caller asked for
 // the plan's device-resident weights, from device memory (uniform scalar reads).
 // (a template parameter, so that launches with weights by value run exactly the code they
 // would without this choice.)
-template <bool DEVW> __device__ __forceinline__ float kt_weight(const KtWeights &wts, int k)
+template <bool DEVW, typename W> __device__ __forceinline__ float kt_weight(const W &wts, int k)
 {
     if (DEVW) return ld_table(wts.dev + k);
     return wts.w[k];
@@ -459,7 +472,7 @@ template <> struct Chunk<float> { static constexpr int N = 8; };       // 148 VG
 template <> struct Chunk<uint16_t> { static constexpr int N = 6; };    // 8 accumulators per vector: 6 keeps 3 waves per SIMD
 
 template <typename T, int KC, bool DEVW, typename P>
-__device__ __forceinline__ void sum_chunk(Acc<T> *acc, P ptr, const KtWeights &wts, int k0, int tid)
+__device__ __forceinline__ void sum_chunk(Acc<T> *acc, P ptr, const AllWeights &wts, int k0, int tid)
 {
     constexpr int VPT = KT_TILE_VECS / KT_BLOCK;
     u32x4 r[VPT][KC];
@@ -481,7 +494,7 @@ __device__ __forceinline__ void sum_chunk(Acc<T> *acc, P ptr, const KtWeights &w
 
 // acc[u] = sum over all K peers of vector u of a full tile.
 template <typename T, bool DEVW, typename P>
-__device__ __forceinline__ void sum_in_chunks(Acc<T> *acc, P ptr, const KtWeights &wts, int K, int tid)
+__device__ __forceinline__ void sum_in_chunks(Acc<T> *acc, P ptr, const AllWeights &wts, int K, int tid)
 {
     constexpr int CH = Chunk<T>::N;
     int k0 = 0;

@@ -76,10 +76,11 @@ __device__ __forceinline__ void fused_mixed(const V &tv, int nt, const TileGeom 
 }
 
 template <typename T, int K, bool DEVW>
-__global__ __launch_bounds__(KT_BLOCK) void kt_fused_kernel(KtDeviceTables tb, int64_t tile0,
-                                                            const void *const *local_ptrs,
-                                                            const void *const *peer_ptrs, KtWeights wts,
-                                                            float scale, void *const *out_ptrs, KtWindow win)
+__global__ __launch_bounds__(KT_BLOCK) void kt_fused_kernel(const KtTile *tiles, const int64_t *b_elems,
+                                                            const int64_t *t_offs, const void *const *local_ptrs,
+                                                            const void *const *peer_ptrs, void *const *out_ptrs,
+                                                            float scale, KtWindow win,
+                                                            const int64_t *t_numel, FewWeights wts)
 {
     constexpr int VE = Elem<T>::VE;
     constexpr int64_t TILE_ELEMS = (int64_t)KT_TILE_VECS * VE;
@@ -88,8 +89,8 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_kernel(KtDeviceTables tb, i
     constexpr bool INT = K == 1 || K >= 6;         // narrowing in integer instructions (f32_to_bf16_int)
     __shared__ LdsTable lds;
 
-    const KtTile tl = ld_tile(tb.tiles + tile0 + blockIdx.x);
-    const int64_t b_n = ld_table(tb.b_elems + tl.bucket), t_off = ld_table(tb.t_off + tl.t0);
+    const KtTile tl = ld_tile(tiles + blockIdx.x);
+    const int64_t b_n = ld_table(b_elems + tl.bucket), t_off = ld_table(t_offs + tl.t0);
     const T *src = reinterpret_cast<const T *>(ld_table(local_ptrs + tl.t0));
     T *dst = reinterpret_cast<T *>(ld_table(out_ptrs + tl.t0));
     const T *x[KP];   // peers 1..K-1
@@ -146,10 +147,10 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_kernel(KtDeviceTables tb, i
     // mixed tile: stage (offset, size, source, destination) of its tensors in LDS
     const void *const *op = reinterpret_cast<const void *const *>(out_ptrs);
     if (tl.nt <= KT_LDS_TENSORS) {
-        const LdsView tv = stage_lds(lds, tb, local_ptrs, op, tl.t0, tl.nt);
+        const LdsView tv = stage_lds(lds, t_offs, t_numel, local_ptrs, op, tl.t0, tl.nt);
         fused_mixed<T, K>(tv, tl.nt, g, x, w, scale);
     } else {
-        const GlobalView tv = global_view(tb, local_ptrs, op, tl.t0);
+        const GlobalView tv = global_view(t_offs, t_numel, local_ptrs, op, tl.t0);
         fused_mixed<T, K>(tv, tl.nt, g, x, w, scale);
     }
 }
@@ -159,7 +160,7 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_kernel(KtDeviceTables tb, i
 // vector by vector with a loop over the peers.
 template <typename T, bool DEVW, typename V>
 __device__ __forceinline__ void fused_mixed_manyk(const V &tv, int nt, const TileGeom &g,
-                                                  const void *const *pp, int K, const KtWeights &wts, float scale)
+                                                  const void *const *pp, int K, const AllWeights &wts, float scale)
 {
     constexpr int VE = Elem<T>::VE;
     const int nvec = (int)((g.end - g.start + VE - 1) / VE);
@@ -187,19 +188,19 @@ __device__ __forceinline__ void fused_mixed_manyk(const V &tv, int nt, const Til
 }
 
 template <typename T, bool DEVW>
-__global__ __launch_bounds__(KT_BLOCK) void kt_fused_manyk_kernel(KtDeviceTables tb, int64_t tile0,
-                                                                  const void *const *local_ptrs,
-                                                                  const void *const *peer_ptrs, int K,
-                                                                  KtWeights wts, float scale, void *const *out_ptrs,
-                                                                  KtWindow win)
+__global__ __launch_bounds__(KT_BLOCK) void kt_fused_manyk_kernel(const KtTile *tiles, const int64_t *b_elems,
+                                                                  const int64_t *t_offs, const void *const *local_ptrs,
+                                                                  const void *const *peer_ptrs, void *const *out_ptrs,
+                                                                  float scale, int K, KtWindow win,
+                                                                  const int64_t *t_numel, AllWeights wts)
 {
     constexpr int VE = Elem<T>::VE;
     constexpr int64_t TILE_ELEMS = (int64_t)KT_TILE_VECS * VE;
     constexpr int VPT = KT_TILE_VECS / KT_BLOCK;
     __shared__ LdsTable lds;
 
-    const KtTile tl = ld_tile(tb.tiles + tile0 + blockIdx.x);
-    const int64_t b_n = ld_table(tb.b_elems + tl.bucket), t_off = ld_table(tb.t_off + tl.t0);
+    const KtTile tl = ld_tile(tiles + blockIdx.x);
+    const int64_t b_n = ld_table(b_elems + tl.bucket), t_off = ld_table(t_offs + tl.t0);
     const T *src = reinterpret_cast<const T *>(ld_table(local_ptrs + tl.t0));
     T *dst = reinterpret_cast<T *>(ld_table(out_ptrs + tl.t0));
     pin(b_n, t_off, (uint64_t)src, (uint64_t)dst);
@@ -224,10 +225,10 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_manyk_kernel(KtDeviceTables
     const int nt = tl.nt == 0 ? 1 : tl.nt;
     const void *const *op = reinterpret_cast<const void *const *>(out_ptrs);
     if (nt <= KT_LDS_TENSORS) {
-        const LdsView tv = stage_lds(lds, tb, local_ptrs, op, tl.t0, nt);
+        const LdsView tv = stage_lds(lds, t_offs, t_numel, local_ptrs, op, tl.t0, nt);
         fused_mixed_manyk<T, DEVW>(tv, nt, g, pp, K, wts, scale);
     } else {
-        const GlobalView tv = global_view(tb, local_ptrs, op, tl.t0);
+        const GlobalView tv = global_view(t_offs, t_numel, local_ptrs, op, tl.t0);
         fused_mixed_manyk<T, DEVW>(tv, nt, g, pp, K, wts, scale);
     }
 }
@@ -238,14 +239,15 @@ hipError_t launch_fused_t(const KtDeviceTables &tb, int64_t tile0, int64_t ntile
                           hipStream_t s)
 {
     const dim3 grid((unsigned)ntiles), block(KT_BLOCK);
+    const KtTile *tiles = tb.tiles + tile0;
     const KtWindow win = kt_store_window(K, ntiles, (KT_WINDOW_MIN_READS_FUSED + K - 1) / K, sizeof(T) == 4 && K >= 8);
     const unsigned lds = kt_mix_lds(win, K, ntiles, 2048, (unsigned)sizeof(LdsTable));
     switch (K) {
 #define KT_CASE(KK) \
-    case KK: kt_fused_kernel<T, KK, DEVW><<<grid, block, lds, s>>>(tb, tile0, locals, peers, w, scale, outs, win); break;
+    case KK: kt_fused_kernel<T, KK, DEVW><<<grid, block, lds, s>>>(tiles, tb.b_elems, tb.t_off, locals, peers, outs, scale, win, tb.t_numel, FewWeights(w)); break;
         KT_CASE(1) KT_CASE(2) KT_CASE(3) KT_CASE(4) KT_CASE(5) KT_CASE(6) KT_CASE(7) KT_CASE(8)
 #undef KT_CASE
-    default: kt_fused_manyk_kernel<T, DEVW><<<grid, block, 0, s>>>(tb, tile0, locals, peers, K, w, scale, outs, win); break;
+    default: kt_fused_manyk_kernel<T, DEVW><<<grid, block, 0, s>>>(tiles, tb.b_elems, tb.t_off, locals, peers, outs, scale, K, win, tb.t_numel, AllWeights(w)); break;
     }
     return hipGetLastError();
 }

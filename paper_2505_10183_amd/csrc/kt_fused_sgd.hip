@@ -119,9 +119,9 @@ template <typename T> struct FsgdShape {
 // the others one per lane (each_cut_elem).  tv.ptr = local gradients, tv.ptr2 = parameters;
 // momentum and model pointers come from the global pointer table (mom, model: already advanced to
 // the tile's first tensor).  KC: K at compile time, or 0.
-template <typename T, int KC, bool DEVW, typename V>
+template <typename T, int KC, bool DEVW, typename V, typename W>
 __device__ __forceinline__ void fsgd_mixed(const V &tv, int nt, const TileGeom &g, const void *const *pp, int K_,
-                                           const KtWeights &wts, const KtSgd &a, void *const *mom, void *const *model,
+                                           const W &wts, const KtSgd &a, void *const *mom, void *const *model,
                                            int part, int parts)
 {
     constexpr int VE = Elem<T>::VE;
@@ -191,20 +191,20 @@ union FsgdLds {
     u32x4 red[KT_TILE_VECS];
 };
 
-template <typename T, int KC, bool DEVW>
-__device__ __forceinline__ void fsgd_other_tile(LdsTable &lds, const KtDeviceTables &tb, const KtTile &tl,
+template <typename T, int KC, bool DEVW, typename W>
+__device__ __forceinline__ void fsgd_other_tile(LdsTable &lds, const int64_t *t_offs, const int64_t *t_numel, const KtTile &tl,
                                                 const TileGeom &g, const FsgdArgs &f, const void *const *pp, int K,
-                                                const KtWeights &wts, const KtSgd &a, int part, int parts)
+                                                const W &wts, const KtSgd &a, int part, int parts)
 {
     const int nt = tl.nt == 0 ? 1 : tl.nt;
     const void *const *prm = reinterpret_cast<const void *const *>(f.param_ptrs);
     void *const *mom = f.mom_ptrs + tl.t0;
     void *const *model = f.model_ptrs ? f.model_ptrs + tl.t0 : nullptr;
     if (nt <= KT_LDS_TENSORS) {
-        const LdsView tv = stage_lds(lds, tb, f.local_ptrs, prm, tl.t0, nt);
+        const LdsView tv = stage_lds(lds, t_offs, t_numel, f.local_ptrs, prm, tl.t0, nt);
         fsgd_mixed<T, KC, DEVW>(tv, nt, g, pp, K, wts, a, mom, model, part, parts);
     } else {
-        const GlobalView tv = global_view(tb, f.local_ptrs, prm, tl.t0);
+        const GlobalView tv = global_view(t_offs, t_numel, f.local_ptrs, prm, tl.t0);
         fsgd_mixed<T, KC, DEVW>(tv, nt, g, pp, K, wts, a, mom, model, part, parts);
     }
 }
@@ -215,9 +215,14 @@ __device__ __forceinline__ void fsgd_other_tile(LdsTable &lds, const KtDeviceTab
 // bytes the chip has in flight beyond what hides the latency the better (FsgdLaunch).  SYS:
 // system-scope stores.
 template <typename T, int K, bool DEVW, bool SYS>
-__global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_kernel(KtDeviceTables tb, int64_t tile0, FsgdArgs f,
-                                                                KtWeights wts, KtSgd a_in)
+__global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_kernel(const KtTile *tiles, const int64_t *b_elems,
+                                                                const int64_t *t_offs, const void *const *local_ptrs,
+                                                                const void *const *peer_ptrs, void *const *param_ptrs,
+                                                                void *const *mom_ptrs, void *const *model_ptrs,
+                                                                const int64_t *t_numel, KtSgd a_in,
+                                                                FewWeights wts)
 {
+    const FsgdArgs f{local_ptrs, peer_ptrs, param_ptrs, mom_ptrs, model_ptrs};
     constexpr int VE = Elem<T>::VE;
     constexpr int64_t TILE_ELEMS = (int64_t)KT_TILE_VECS * VE;
     constexpr int VPT = FsgdShape<T>::VPT, SPLIT = FsgdShape<T>::SPLIT, QPL = VPT * FsgdShape<T>::QPV;
@@ -225,8 +230,8 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_kernel(KtDeviceTables t
     __shared__ FsgdLds lds;
 
     const int part = SPLIT == 1 ? 0 : (int)(blockIdx.x % SPLIT);
-    const KtTile tl = ld_tile(tb.tiles + tile0 + blockIdx.x / SPLIT);
-    const int64_t b_n = ld_table(tb.b_elems + tl.bucket), t_off = ld_table(tb.t_off + tl.t0);
+    const KtTile tl = ld_tile(tiles + blockIdx.x / SPLIT);
+    const int64_t b_n = ld_table(b_elems + tl.bucket), t_off = ld_table(t_offs + tl.t0);
     const void *const *pp = f.peer_ptrs + (int64_t)tl.bucket * (K - 1);   // peers 1..K-1 of this bucket
     const T *x[KP];
 #pragma unroll
@@ -275,22 +280,27 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_kernel(KtDeviceTables t
         else st_quads<QPL, false>(p4, v4, m2, pr, vr);
         return;
     }
-    fsgd_other_tile<T, K, DEVW>(lds.table, tb, tl, g, f, pp, K, wts, a, part, SPLIT);
+    fsgd_other_tile<T, K, DEVW>(lds.table, t_offs, t_numel, tl, g, f, pp, K, wts, a, part, SPLIT);
 }
 
 // K = 9..64: full solid tiles take the peers in chunks with the accumulators in registers, one
 // workgroup per tile; every other tile as above.
 template <typename T, bool DEVW>
-__global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_manyk_kernel(KtDeviceTables tb, int64_t tile0, FsgdArgs f,
-                                                                      int K, KtWeights wts, KtSgd a_in)
+__global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_manyk_kernel(const KtTile *tiles, const int64_t *b_elems,
+                                                                      const int64_t *t_offs, const void *const *local_ptrs,
+                                                                      const void *const *peer_ptrs, void *const *param_ptrs,
+                                                                      void *const *mom_ptrs, void *const *model_ptrs,
+                                                                      int K, const int64_t *t_numel, KtSgd a_in,
+                                                                      AllWeights wts)
 {
+    const FsgdArgs f{local_ptrs, peer_ptrs, param_ptrs, mom_ptrs, model_ptrs};
     constexpr int VE = Elem<T>::VE;
     constexpr int64_t TILE_ELEMS = (int64_t)KT_TILE_VECS * VE;
     constexpr int VPT = KT_TILE_VECS / KT_BLOCK, QPL = VPT * FsgdShape<T>::QPV;
     __shared__ FsgdLds lds;
 
-    const KtTile tl = ld_tile(tb.tiles + tile0 + blockIdx.x);
-    const int64_t b_n = ld_table(tb.b_elems + tl.bucket), t_off = ld_table(tb.t_off + tl.t0);
+    const KtTile tl = ld_tile(tiles + blockIdx.x);
+    const int64_t b_n = ld_table(b_elems + tl.bucket), t_off = ld_table(t_offs + tl.t0);
     TensorSide<T> t(f, tl.t0);
     const KtSgd a = resolve_sgd(a_in);
     const TileGeom g = tile_geom(tl, b_n, TILE_ELEMS);
@@ -316,7 +326,7 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_manyk_kernel(KtDeviceTa
         st_quads<QPL, false>(p4, v4, t.m ? reinterpret_cast<u32x2 *>(t.m) + tid : nullptr, pr, vr);
         return;
     }
-    fsgd_other_tile<T, 0, DEVW>(lds.table, tb, tl, g, f, pp, K, wts, a, 0, 1);
+    fsgd_other_tile<T, 0, DEVW>(lds.table, t_offs, t_numel, tl, g, f, pp, K, wts, a, 0, 1);
 }
 
 // Bytes of LDS asked for beyond the kernel's own, to hold the number of workgroups per CU at 2 or 4;
@@ -355,7 +365,8 @@ hipError_t launch_fused_sgd_t(const KtDeviceTables &tb, int64_t tile0, int64_t n
 {
     const dim3 grid((unsigned)ntiles), block(KT_BLOCK);
     if (K > 8) {
-        kt_fused_sgd_manyk_kernel<T, DEVW><<<grid, block, 0, s>>>(tb, tile0, f, K, w, a);
+        kt_fused_sgd_manyk_kernel<T, DEVW><<<grid, block, 0, s>>>(tb.tiles + tile0, tb.b_elems, tb.t_off, f.local_ptrs, f.peer_ptrs,
+                                                                      f.param_ptrs, f.mom_ptrs, f.model_ptrs, K, tb.t_numel, a, AllWeights(w));
         return hipGetLastError();
     }
     FsgdLaunch how = fsgd_launch<T>(K, ntiles);
@@ -366,15 +377,18 @@ hipError_t launch_fused_sgd_t(const KtDeviceTables &tb, int64_t tile0, int64_t n
     for (int64_t done = 0; done < ntiles; done += per_launch) {
         const int64_t now = ntiles - done < per_launch ? ntiles - done : per_launch;
         const dim3 g2((unsigned)(now * SPLIT));
-        const int64_t t0 = tile0 + done;
+        const KtTile *tiles = tb.tiles + tile0 + done;
+#define KT_ARGS \
+    tiles, tb.b_elems, tb.t_off, f.local_ptrs, f.peer_ptrs, f.param_ptrs, f.mom_ptrs, f.model_ptrs, tb.t_numel, a, FewWeights(w)
         switch (K) {
 #define KT_CASE(KK) \
     case KK:                                                                                                     \
-        if (how.sys) kt_fused_sgd_kernel<T, KK, DEVW, sizeof(T) == 2 && KK >= 8><<<g2, block, how.lds, s>>>(tb, t0, f, w, a); \
-        else kt_fused_sgd_kernel<T, KK, DEVW, false><<<g2, block, how.lds, s>>>(tb, t0, f, w, a);                \
+        if (how.sys) kt_fused_sgd_kernel<T, KK, DEVW, sizeof(T) == 2 && KK >= 8><<<g2, block, how.lds, s>>>(KT_ARGS); \
+        else kt_fused_sgd_kernel<T, KK, DEVW, false><<<g2, block, how.lds, s>>>(KT_ARGS);                     \
         break;
             KT_CASE(1) KT_CASE(2) KT_CASE(3) KT_CASE(4) KT_CASE(5) KT_CASE(6) KT_CASE(7) KT_CASE(8)
 #undef KT_CASE
+#undef KT_ARGS
         default: return hipErrorInvalidValue;
         }
         const hipError_t e = hipGetLastError();

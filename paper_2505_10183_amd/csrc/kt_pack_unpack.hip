@@ -69,9 +69,9 @@ __device__ __forceinline__ void pack_mixed(const V &tv, int nt, const TileGeom &
 }
 
 template <typename T>
-__global__ __launch_bounds__(KT_BLOCK) void kt_pack_kernel(KtDeviceTables tb, int64_t tile0,
-                                                           const void *const *tensor_ptrs,
-                                                           void *const *bucket_ptrs)
+__global__ __launch_bounds__(KT_BLOCK) void kt_pack_kernel(const KtTile *tiles, const int64_t *b_elems,
+                                                           const int64_t *t_offs, const void *const *tensor_ptrs,
+                                                           void *const *bucket_ptrs, const int64_t *t_numel)
 {
     constexpr int VE = Elem<T>::VE;
     constexpr int64_t TILE_ELEMS = (int64_t)KT_TILE_VECS * VE;
@@ -79,8 +79,8 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_pack_kernel(KtDeviceTables tb, in
     __shared__ LdsTable lds;
 
     const int part = COPY_SPLIT == 1 ? 0 : (int)(blockIdx.x % COPY_SPLIT);
-    const KtTile tl = ld_tile(tb.tiles + tile0 + blockIdx.x / COPY_SPLIT);
-    const int64_t b_n = ld_table(tb.b_elems + tl.bucket), t_off = ld_table(tb.t_off + tl.t0);
+    const KtTile tl = ld_tile(tiles + blockIdx.x / COPY_SPLIT);
+    const int64_t b_n = ld_table(b_elems + tl.bucket), t_off = ld_table(t_offs + tl.t0);
     T *dst = reinterpret_cast<T *>(ld_table(bucket_ptrs + tl.bucket));
     const T *src = reinterpret_cast<const T *>(ld_table(tensor_ptrs + tl.t0));
     pin(b_n, t_off, (uint64_t)dst, (uint64_t)src);
@@ -120,10 +120,10 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_pack_kernel(KtDeviceTables tb, in
     // a short last tile leaves the later workgroups of the tile without vectors
     if ((int64_t)part * VPT * KT_BLOCK * VE >= g.end - g.start) return;
     if (tl.nt <= KT_LDS_TENSORS) {
-        const LdsView tv = stage_lds(lds, tb, tensor_ptrs, nullptr, tl.t0, tl.nt);
+        const LdsView tv = stage_lds(lds, t_offs, t_numel, tensor_ptrs, nullptr, tl.t0, tl.nt);
         pack_mixed<T>(tv, tl.nt, g, b_n, dst, part);
     } else {
-        const GlobalView tv = global_view(tb, tensor_ptrs, nullptr, tl.t0);
+        const GlobalView tv = global_view(t_offs, t_numel, tensor_ptrs, nullptr, tl.t0);
         pack_mixed<T>(tv, tl.nt, g, b_n, dst, part);
     }
 }
@@ -161,9 +161,10 @@ __device__ __forceinline__ void unpack_mixed(const V &tv, int nt, const TileGeom
 }
 
 template <typename T>
-__global__ __launch_bounds__(KT_BLOCK) void kt_unpack_kernel(KtDeviceTables tb, int64_t tile0,
-                                                             const void *const *bucket_ptrs, float scale,
-                                                             void *const *tensor_ptrs)
+__global__ __launch_bounds__(KT_BLOCK) void kt_unpack_kernel(const KtTile *tiles, const int64_t *b_elems,
+                                                             const int64_t *t_offs, const void *const *bucket_ptrs,
+                                                             void *const *tensor_ptrs, float scale,
+                                                             const int64_t *t_numel)
 {
     constexpr int VE = Elem<T>::VE;
     constexpr int64_t TILE_ELEMS = (int64_t)KT_TILE_VECS * VE;
@@ -171,8 +172,8 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_unpack_kernel(KtDeviceTables tb, 
     __shared__ LdsTable lds;
 
     const int part = COPY_SPLIT == 1 ? 0 : (int)(blockIdx.x % COPY_SPLIT);
-    const KtTile tl = ld_tile(tb.tiles + tile0 + blockIdx.x / COPY_SPLIT);
-    const int64_t b_n = ld_table(tb.b_elems + tl.bucket), t_off = ld_table(tb.t_off + tl.t0);
+    const KtTile tl = ld_tile(tiles + blockIdx.x / COPY_SPLIT);
+    const int64_t b_n = ld_table(b_elems + tl.bucket), t_off = ld_table(t_offs + tl.t0);
     const T *src = reinterpret_cast<const T *>(ld_table(bucket_ptrs + tl.bucket));
     T *dst = reinterpret_cast<T *>(ld_table(tensor_ptrs + tl.t0));
     pin(b_n, t_off, (uint64_t)dst, (uint64_t)src);
@@ -217,10 +218,10 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_unpack_kernel(KtDeviceTables tb, 
     }
     const void *const *tp = reinterpret_cast<const void *const *>(tensor_ptrs);
     if (tl.nt <= KT_LDS_TENSORS) {
-        const LdsView tv = stage_lds(lds, tb, tp, nullptr, tl.t0, tl.nt);
+        const LdsView tv = stage_lds(lds, t_offs, t_numel, tp, nullptr, tl.t0, tl.nt);
         unpack_mixed<T>(tv, tl.nt, g, val, src, scale, part);
     } else {
-        const GlobalView tv = global_view(tb, tp, nullptr, tl.t0);
+        const GlobalView tv = global_view(t_offs, t_numel, tp, nullptr, tl.t0);
         unpack_mixed<T>(tv, tl.nt, g, val, src, scale, part);
     }
 }
@@ -228,12 +229,12 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_unpack_kernel(KtDeviceTables tb, 
 }  // namespace
 
 // A grid may not hold 2^32 or more lanes: very large plans go in several launches.
-template <typename F> static int launch_in_chunks(int64_t tile0, int64_t ntiles, F launch)
+template <typename F> static int launch_in_chunks(const KtTile *tiles, int64_t ntiles, F launch)
 {
     const int64_t per_launch = (((int64_t)1 << 32) / KT_BLOCK - 1) / COPY_SPLIT;
     for (int64_t done = 0; done < ntiles; done += per_launch) {
         const int64_t now = ntiles - done < per_launch ? ntiles - done : per_launch;
-        launch(tile0 + done, dim3((unsigned)(now * COPY_SPLIT)));
+        launch(tiles + done, dim3((unsigned)(now * COPY_SPLIT)));
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return (int)e;
     }
@@ -245,9 +246,9 @@ int kt_launch_pack(const KtDeviceTables &tb, kt_dtype dt, int64_t tile0, int64_t
 {
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const dim3 block(KT_BLOCK);
-    return launch_in_chunks(tile0, ntiles, [&](int64_t t0, dim3 grid) {
-        if (dt == KT_F32) kt_pack_kernel<float><<<grid, block, 0, s>>>(tb, t0, d_tensor_ptrs, d_bucket_ptrs);
-        else kt_pack_kernel<uint16_t><<<grid, block, 0, s>>>(tb, t0, d_tensor_ptrs, d_bucket_ptrs);
+    return launch_in_chunks(tb.tiles + tile0, ntiles, [&](const KtTile *tiles, dim3 grid) {
+        if (dt == KT_F32) kt_pack_kernel<float><<<grid, block, 0, s>>>(tiles, tb.b_elems, tb.t_off, d_tensor_ptrs, d_bucket_ptrs, tb.t_numel);
+        else kt_pack_kernel<uint16_t><<<grid, block, 0, s>>>(tiles, tb.b_elems, tb.t_off, d_tensor_ptrs, d_bucket_ptrs, tb.t_numel);
     });
 }
 
@@ -256,8 +257,8 @@ int kt_launch_unpack(const KtDeviceTables &tb, kt_dtype dt, int64_t tile0, int64
 {
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const dim3 block(KT_BLOCK);
-    return launch_in_chunks(tile0, ntiles, [&](int64_t t0, dim3 grid) {
-        if (dt == KT_F32) kt_unpack_kernel<float><<<grid, block, 0, s>>>(tb, t0, d_bucket_ptrs, scale, d_tensor_ptrs);
-        else kt_unpack_kernel<uint16_t><<<grid, block, 0, s>>>(tb, t0, d_bucket_ptrs, scale, d_tensor_ptrs);
+    return launch_in_chunks(tb.tiles + tile0, ntiles, [&](const KtTile *tiles, dim3 grid) {
+        if (dt == KT_F32) kt_unpack_kernel<float><<<grid, block, 0, s>>>(tiles, tb.b_elems, tb.t_off, d_bucket_ptrs, d_tensor_ptrs, scale, tb.t_numel);
+        else kt_unpack_kernel<uint16_t><<<grid, block, 0, s>>>(tiles, tb.b_elems, tb.t_off, d_bucket_ptrs, d_tensor_ptrs, scale, tb.t_numel);
     });
 }

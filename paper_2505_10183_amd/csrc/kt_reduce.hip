@@ -11,16 +11,16 @@ namespace {
 // loads issue back to back, which inside the store windows lost 3-10 % (1.3B set 3.77 -> 3.89 ms),
 // more than the 3 % of a misaligned non-temporal store stream.
 template <typename T, int K, bool DEVW>
-__global__ __launch_bounds__(KT_BLOCK) void kt_reduce_kernel(KtDeviceTables tb, int64_t tile0,
-                                                             const void *const *peer_ptrs, KtWeights wts,
-                                                             void *const *out_ptrs, KtWindow win)
+__global__ __launch_bounds__(KT_BLOCK) void kt_reduce_kernel(const KtTile *tiles, const int64_t *b_elems,
+                                                             const void *const *peer_ptrs, void *const *out_ptrs,
+                                                             KtWindow win, FewWeights wts)
 {
     constexpr int VE = Elem<T>::VE;
     constexpr int64_t TILE_ELEMS = (int64_t)KT_TILE_VECS * VE;
     constexpr int VPT = KT_TILE_VECS / KT_BLOCK;   // vectors per lane, K loads each, all in flight at once
 
-    const KtTile tl = ld_tile(tb.tiles + tile0 + blockIdx.x);
-    const int64_t b_n = ld_table(tb.b_elems + tl.bucket);
+    const KtTile tl = ld_tile(tiles + blockIdx.x);
+    const int64_t b_n = ld_table(b_elems + tl.bucket);
     T *out = reinterpret_cast<T *>(ld_table(out_ptrs + tl.bucket));
     const T *x[K];
 #pragma unroll
@@ -80,15 +80,15 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_reduce_kernel(KtDeviceTables tb, 
 
 // K > 8: peers in chunks, accumulators in registers across chunks (sum_in_chunks).
 template <typename T, bool DEVW>
-__global__ __launch_bounds__(KT_BLOCK) void kt_reduce_manyk_kernel(KtDeviceTables tb, int64_t tile0,
-                                                                   const void *const *peer_ptrs, int K,
-                                                                   KtWeights wts, void *const *out_ptrs, KtWindow win)
+__global__ __launch_bounds__(KT_BLOCK) void kt_reduce_manyk_kernel(const KtTile *tiles, const int64_t *b_elems,
+                                                                   const void *const *peer_ptrs, void *const *out_ptrs,
+                                                                   int K, KtWindow win, AllWeights wts)
 {
     constexpr int VE = Elem<T>::VE;
     constexpr int64_t TILE_ELEMS = (int64_t)KT_TILE_VECS * VE;
     constexpr int VPT = KT_TILE_VECS / KT_BLOCK;
-    const KtTile tl = ld_tile(tb.tiles + tile0 + blockIdx.x);
-    const TileGeom g = tile_geom(tl, ld_table(tb.b_elems + tl.bucket), TILE_ELEMS);
+    const KtTile tl = ld_tile(tiles + blockIdx.x);
+    const TileGeom g = tile_geom(tl, ld_table(b_elems + tl.bucket), TILE_ELEMS);
     const int tid = threadIdx.x;
     const void *const *pp = peer_ptrs + (int64_t)g.bucket * K;
     auto peer = [&](int k) { return reinterpret_cast<const T *>(ld_table(pp + k)) + g.start; };
@@ -127,15 +127,16 @@ hipError_t launch_reduce_t(const KtDeviceTables &tb, int64_t tile0, int64_t ntil
                            int K, const KtWeights &w, void *const *outs, hipStream_t s)
 {
     dim3 grid((unsigned)ntiles), block(KT_BLOCK);
+    const KtTile *tiles = tb.tiles + tile0;
     const KtWindow win = kt_store_window(K, ntiles, K <= 8 ? KT_WINDOW_MIN_TILES_REDUCE : (KT_WINDOW_MIN_READS_REDUCE_MANYK + K - 1) / K,
                                          sizeof(T) == 4);
     const unsigned lds = kt_mix_lds(win, K, ntiles, 4096, 0);
     switch (K) {
 #define KT_CASE(KK) \
-    case KK: kt_reduce_kernel<T, KK, DEVW><<<grid, block, lds, s>>>(tb, tile0, peers, w, outs, win); break;
+    case KK: kt_reduce_kernel<T, KK, DEVW><<<grid, block, lds, s>>>(tiles, tb.b_elems, peers, outs, win, FewWeights(w)); break;
         KT_CASE(1) KT_CASE(2) KT_CASE(3) KT_CASE(4) KT_CASE(5) KT_CASE(6) KT_CASE(7) KT_CASE(8)
 #undef KT_CASE
-    default: kt_reduce_manyk_kernel<T, DEVW><<<grid, block, 0, s>>>(tb, tile0, peers, K, w, outs, win); break;
+    default: kt_reduce_manyk_kernel<T, DEVW><<<grid, block, 0, s>>>(tiles, tb.b_elems, peers, outs, K, win, AllWeights(w)); break;
     }
     return hipGetLastError();
 }

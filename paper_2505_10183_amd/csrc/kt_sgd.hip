@@ -71,10 +71,11 @@ __device__ __forceinline__ void sgd_mixed(const V &tv, int nt, const TileGeom &g
 // a learning-rate schedule.  A separate instantiation: launches with scalars by value run the
 // code they always ran.
 template <typename T, bool MASTER, bool DEVS>
-__global__ __launch_bounds__(KT_BLOCK) void kt_unpack_sgd_kernel(KtDeviceTables tb, int64_t tile0,
-                                                                 const void *const *bucket_ptrs,
+__global__ __launch_bounds__(KT_BLOCK) void kt_unpack_sgd_kernel(const KtTile *tiles, const int64_t *b_elems,
+                                                                 const int64_t *t_offs, const void *const *bucket_ptrs,
                                                                  void *const *param_ptrs, void *const *mom_ptrs,
-                                                                 void *const *model_ptrs, KtSgd a)
+                                                                 void *const *model_ptrs, KtSgd a,
+                                                                 const int64_t *t_numel)
 {
     constexpr int VE = Elem<T>::VE;
     constexpr int64_t TILE_ELEMS = (int64_t)KT_TILE_VECS * VE;
@@ -82,8 +83,8 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_unpack_sgd_kernel(KtDeviceTables 
     __shared__ LdsTable lds;
 
     const int part = SPLIT == 1 ? 0 : (int)(blockIdx.x % SPLIT);
-    const KtTile tl = ld_tile(tb.tiles + tile0 + blockIdx.x / SPLIT);
-    const int64_t b_n = ld_table(tb.b_elems + tl.bucket), t_off = ld_table(tb.t_off + tl.t0);
+    const KtTile tl = ld_tile(tiles + blockIdx.x / SPLIT);
+    const int64_t b_n = ld_table(b_elems + tl.bucket), t_off = ld_table(t_offs + tl.t0);
     const T *src = reinterpret_cast<const T *>(ld_table(bucket_ptrs + tl.bucket));
     float *p = reinterpret_cast<float *>(ld_table(param_ptrs + tl.t0));
     float *v = reinterpret_cast<float *>(ld_table(mom_ptrs + tl.t0));
@@ -142,10 +143,10 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_unpack_sgd_kernel(KtDeviceTables 
     const void *const *mp = reinterpret_cast<const void *const *>(mom_ptrs);
     void *const *model = MASTER ? model_ptrs + tl.t0 : nullptr;
     if (tl.nt <= KT_LDS_TENSORS) {
-        const LdsView tv = stage_lds(lds, tb, pp, mp, tl.t0, tl.nt);
+        const LdsView tv = stage_lds(lds, t_offs, t_numel, pp, mp, tl.t0, tl.nt);
         sgd_mixed<T, MASTER>(tv, tl.nt, g, src, a, part, model);
     } else {
-        const GlobalView tv = global_view(tb, pp, mp, tl.t0);
+        const GlobalView tv = global_view(t_offs, t_numel, pp, mp, tl.t0);
         sgd_mixed<T, MASTER>(tv, tl.nt, g, src, a, part, model);
     }
 }
@@ -176,15 +177,15 @@ int kt_launch_unpack_sgd(const KtDeviceTables &tb, kt_dtype dt, int64_t tile0, i
     for (int64_t done = 0; done < ntiles; done += per_launch) {
         const int64_t now = ntiles - done < per_launch ? ntiles - done : per_launch;
         const dim3 grid((unsigned)(now * split));
-        const int64_t t0 = tile0 + done;
+        const KtTile *tiles = tb.tiles + tile0 + done;
 #define KT_SGD_LAUNCH(TT, MM)                                                                                        \
     do {                                                                                                            \
         if (a.dev)                                                                                                  \
-            kt_unpack_sgd_kernel<TT, MM, true><<<grid, block, lds, s>>>(tb, t0, d_bucket_ptrs, d_param_ptrs, d_mom_ptrs, \
-                                                                      d_model_ptrs, a);                            \
+            kt_unpack_sgd_kernel<TT, MM, true><<<grid, block, lds, s>>>(tiles, tb.b_elems, tb.t_off, d_bucket_ptrs, d_param_ptrs, \
+                                                                      d_mom_ptrs, d_model_ptrs, a, tb.t_numel);                            \
         else                                                                                                        \
-            kt_unpack_sgd_kernel<TT, MM, false><<<grid, block, lds, s>>>(tb, t0, d_bucket_ptrs, d_param_ptrs, d_mom_ptrs, \
-                                                                       d_model_ptrs, a);                           \
+            kt_unpack_sgd_kernel<TT, MM, false><<<grid, block, lds, s>>>(tiles, tb.b_elems, tb.t_off, d_bucket_ptrs, d_param_ptrs, \
+                                                                       d_mom_ptrs, d_model_ptrs, a, tb.t_numel);                           \
     } while (0)
         if (dt == KT_F32) {
             if (d_model_ptrs) KT_SGD_LAUNCH(float, true); else KT_SGD_LAUNCH(float, false);
