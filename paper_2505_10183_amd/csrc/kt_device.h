@@ -164,14 +164,12 @@ __device__ __forceinline__ uint32_t f32_to_bf16x2(float lo, float hi)
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 __device__ __forceinline__ uint32_t f32_to_bf16(float f) { return f32_to_bf16x2(f, f) & 0xFFFFu; }
-// INT: the same bits in integer instructions.  Only for full tiles of the reduce (6 to 8 copies)
-// and of the fused pass (one copy, 6 or more): the longer way from the last load to the store spaces
-// the workgroups out.  With 6 and more copies it is 1-4 % faster in launches inside the store
-// windows (1.3B set: reduce 3.77 ms against 3.82, fused 3.85 ms against 3.91; fused K = 6, 65 536
-// tiles 1 245 us against 1 292); with one, 2-5 % faster from 20 000 tiles on (40 034 tiles of odd
-// tensors 224 us against 233).  The choice is by the number of copies only, so that launches of 300 to
-// 5 000 tiles pay 1-10 % for it (fused K = 6, 900 tiles); made while the kernel runs, by a branch
-// on the window, it took 5-14 % from the large launches.
+// INT: the same bits in integer instructions.  Only for full tiles of the reduce and the fused pass: the
+// longer way from the last load to the store spaces the workgroups out.  Launches of 6 and more
+// copies that hold their workgroups or use the store window gain 1-5 % (fused, two half tiles per CU: K = 8,
+// 21 099 tiles 518 us against 493; K = 6, 24 394 tiles 455 against 431; reduce of the 1.3B set inside the
+// windows 3.82 against 3.77 ms), those of whole tiles below 2 048 lose 3-6 %; the fused pass of one
+// copy gains 2-5 % from 20 000 tiles on (40 034 tiles of odd tensors 233 us against 224).
 __device__ __forceinline__ uint32_t f32_to_bf16_int(float f)
 {
     const uint32_t u = __float_as_uint(f);
@@ -517,6 +515,20 @@ __device__ __forceinline__ float widen(uint16_t x) { return __uint_as_float((uin
 template <typename T> __device__ __forceinline__ T narrow(float a);
 template <> __device__ __forceinline__ float narrow<float>(float a) { return a; }
 template <> __device__ __forceinline__ uint16_t narrow<uint16_t>(float a) { return (uint16_t)f32_to_bf16(a); }
+
+// A grid may not hold 2^32 or more lanes: very large plans go in several launches.  `split`
+// workgroups share a tile; launch(tiles, grid) launches one part.
+template <typename F> hipError_t launch_in_chunks(const KtTile *tiles, int64_t ntiles, int split, F launch)
+{
+    const int64_t per_launch = (((int64_t)1 << 32) / KT_BLOCK - 1) / split;
+    for (int64_t done = 0; done < ntiles; done += per_launch) {
+        const int64_t now = ntiles - done < per_launch ? ntiles - done : per_launch;
+        launch(tiles + done, dim3((unsigned)(now * split)));
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
 
 }  // namespace
 

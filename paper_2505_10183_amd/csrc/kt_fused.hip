@@ -10,8 +10,8 @@ namespace {
 // type, then one multiplication), so the results are bit-identical to the
 // chained path while moving (K+1) instead of (K+5) element sizes per element.
 //
-// One workgroup per 16 KiB tile; bound, like the reduce, by what the memory
-// system sustains for K reads and one write.  Tensors and buckets may lie at any
+// SPLIT workgroups per 16 KiB tile (fused_shape); bound, like the reduce, by how well the memory
+// system takes K reads and one write.  Tensors and buckets may lie at any
 // element address (stores as in the reduce, at the tile's own offsets).  77.2 M fp32 elements, K = 4, odd
 // tensor sizes in the dense layout: 652 us with one element per lane, which every
 // dense plan and misaligned bucket took before, against 265 us.
@@ -34,18 +34,18 @@ __device__ __forceinline__ void fused_elem(const T *src, T *dst, const T *const 
 // are not wholly inside one tensor go one per lane (each_cut_elem).
 template <typename T, int K, typename V>
 __device__ __forceinline__ void fused_mixed(const V &tv, int nt, const TileGeom &g,
-                                            const T *const *x, const float *w, float scale)
+                                            const T *const *x, const float *w, float scale, int part, int parts)
 {
     constexpr int VE = Elem<T>::VE;
     constexpr int MB = K <= 4 ? 4 : 2;
     const int nvec = (int)((g.end - g.start + VE - 1) / VE);
 #pragma unroll 1
-    for (int v0 = threadIdx.x; v0 < nvec; v0 += MB * KT_BLOCK) {
+    for (int v0 = part * KT_BLOCK + threadIdx.x; v0 < nvec; v0 += MB * parts * KT_BLOCK) {
         u32x4 r[MB][K];
         uintptr_t where[MB];      // destination of a whole vector, 0 = none
 #pragma unroll
         for (int j = 0; j < MB; ++j) {
-            const int v = v0 + j * KT_BLOCK;
+            const int v = v0 + j * parts * KT_BLOCK;
             where[j] = 0;
             if (v < nvec) {
                 const int64_t e0 = g.start + (int64_t)v * VE;
@@ -70,12 +70,12 @@ __device__ __forceinline__ void fused_mixed(const V &tv, int nt, const TileGeom 
             }
         }
     }
-    each_cut_elem<VE>(tv, nt, g.start, (int)(g.end - g.start), threadIdx.x, KT_BLOCK, [&](int i, int64_t r, int e) {
+    each_cut_elem<VE>(tv, nt, g.start, (int)(g.end - g.start), part * KT_BLOCK + threadIdx.x, parts * KT_BLOCK, [&](int i, int64_t r, int e) {
         fused_elem<T, K>(reinterpret_cast<const T *>(tv.ptr[i]) + r, reinterpret_cast<T *>(tv.ptr2[i]) + r, x, e, w, scale);
     });
 }
 
-template <typename T, int K, bool DEVW>
+template <typename T, int K, bool DEVW, int SPLIT, bool INT>
 __global__ __launch_bounds__(KT_BLOCK) void kt_fused_kernel(const KtTile *tiles, const int64_t *b_elems,
                                                             const int64_t *t_offs, const void *const *local_ptrs,
                                                             const void *const *peer_ptrs, void *const *out_ptrs,
@@ -84,12 +84,12 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_kernel(const KtTile *tiles,
 {
     constexpr int VE = Elem<T>::VE;
     constexpr int64_t TILE_ELEMS = (int64_t)KT_TILE_VECS * VE;
-    constexpr int VPT = KT_TILE_VECS / KT_BLOCK;
+    constexpr int VPT = KT_TILE_VECS / KT_BLOCK / SPLIT;
     constexpr int KP = K > 1 ? K - 1 : 1;
-    constexpr bool INT = K == 1 || K >= 6;         // narrowing in integer instructions (f32_to_bf16_int)
     __shared__ LdsTable lds;
 
-    const KtTile tl = ld_tile(tiles + blockIdx.x);
+    const int part = SPLIT == 1 ? 0 : (int)(blockIdx.x % SPLIT);
+    const KtTile tl = ld_tile(tiles + blockIdx.x / SPLIT);
     const int64_t b_n = ld_table(b_elems + tl.bucket), t_off = ld_table(t_offs + tl.t0);
     const T *src = reinterpret_cast<const T *>(ld_table(local_ptrs + tl.t0));
     T *dst = reinterpret_cast<T *>(ld_table(out_ptrs + tl.t0));
@@ -111,13 +111,14 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_kernel(const KtTile *tiles,
         dst += g.start - t_off;
         const int nvec = (int)((g.end - g.start) / VE);
         if (nvec == KT_TILE_VECS) {
+            const int v0 = part * VPT * KT_BLOCK + tid;        // the lane's first vector in the tile
             u32x4 r[VPT][K];
 #pragma unroll
             for (int u = 0; u < VPT; ++u) {
-                r[u][0] = ld_vec(reinterpret_cast<const u32x4 *>(src) + u * KT_BLOCK + tid);
+                r[u][0] = ld_vec(reinterpret_cast<const u32x4 *>(src) + u * KT_BLOCK + v0);
 #pragma unroll
                 for (int k = 1; k < K; ++k)
-                    r[u][k] = ld_vec(reinterpret_cast<const u32x4 *>(x[k - 1]) + u * KT_BLOCK + tid);
+                    r[u][k] = ld_vec(reinterpret_cast<const u32x4 *>(x[k - 1]) + u * KT_BLOCK + v0);
             }
             u32x4 res[VPT];
 #pragma unroll
@@ -128,12 +129,12 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_kernel(const KtTile *tiles,
                 for (int k = 1; k < K; ++k) acc.add(r[u][k], w[k]);
                 res[u] = scale_vec<T, INT>(acc.template finish<INT>(), scale);
             }
-            kt_wait_store_window(win);     // large launches: the chip writes in bursts (KtWindow)
+            if (SPLIT == 1) kt_wait_store_window(win);     // large launches: the chip writes in bursts (KtWindow)
 #pragma unroll
-            for (int u = 0; u < VPT; ++u) st_vec(reinterpret_cast<u32x4 *>(dst) + u * KT_BLOCK + tid, res[u]);
+            for (int u = 0; u < VPT; ++u) st_vec(reinterpret_cast<u32x4 *>(dst) + u * KT_BLOCK + v0, res[u]);
         } else {
 #pragma unroll 1
-            for (int v = tid; v < nvec; v += KT_BLOCK) {
+            for (int v = part * KT_BLOCK + tid; v < nvec; v += SPLIT * KT_BLOCK) {
                 Acc<T> acc;
                 acc.first(ld_vec(reinterpret_cast<const u32x4 *>(src) + v), w[0]);
 #pragma unroll
@@ -148,10 +149,10 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_kernel(const KtTile *tiles,
     const void *const *op = reinterpret_cast<const void *const *>(out_ptrs);
     if (tl.nt <= KT_LDS_TENSORS) {
         const LdsView tv = stage_lds(lds, t_offs, t_numel, local_ptrs, op, tl.t0, tl.nt);
-        fused_mixed<T, K>(tv, tl.nt, g, x, w, scale);
+        fused_mixed<T, K>(tv, tl.nt, g, x, w, scale, part, SPLIT);
     } else {
         const GlobalView tv = global_view(t_offs, t_numel, local_ptrs, op, tl.t0);
-        fused_mixed<T, K>(tv, tl.nt, g, x, w, scale);
+        fused_mixed<T, K>(tv, tl.nt, g, x, w, scale, part, SPLIT);
     }
 }
 
@@ -233,22 +234,80 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_manyk_kernel(const KtTile *
     }
 }
 
+// Workgroups per tile and per CU, as for the reduce (before: whole tiles, two per CU for 3 to 5
+// copies, the store window from 65 536 tiles read on):
+//   K   fp32 (quarter tiles)                              bf16 (half tiles, two per CU)
+//   4   91 562 tiles 1 246 -> 1 186 us, 7 052 even        42 502 tiles 562 -> 553 us, 18 043 even
+//   5   7 052 tiles 114.2 -> 111.9 us, 3 563 2 % slower   5 393 tiles 89.9 -> 87.6 us, 3 526 2 % slower
+//   6   12 206 tiles 236.4 -> 222.2 us, 2 367 2 % slower  4 727 tiles 93.2 -> 86.3 us, 85 285 1 612 -> 1 582
+//   7   42 203 tiles 917 -> 894 us, 84 997 even           18 043 tiles 390 -> 368 us
+//   8   7 052 tiles 174.3 -> 165.2 us (two per CU),       7 117 tiles 181.8 -> 163.3 us, 85 285 2 089 -> 2 046,
+//       20 623 even with the window, 84 997 4 % slower    158 564 tiles 1 % slower than with the window
+// Quarter tiles of bf16 and half tiles of fp32 are 1-3 % behind on most sizes.  bf16 launches of a few rounds
+// (below 1 024 tiles) take half tiles as well, not held (551 tiles: K = 8 18.4 -> 15.4 us against 17.1
+// for whole tiles, K = 4 11.6 -> 9.4 against 10.5); fp32 ones quarter tiles where whole ones are uneven
+// (828 tiles, K = 4: 14.5 -> 12.9 against 13.4).
+template <typename T> struct FusedSplit { static constexpr int N = 4; };
+template <> struct FusedSplit<uint16_t> { static constexpr int N = 2; };
+
+template <typename T> KtShape fused_shape(int K, int64_t nt)
+{
+    constexpr int S = FusedSplit<T>::N;
+    if (sizeof(T) == 2) {
+        if (K >= 6) return {S, nt >= 1024 ? 2u : 0u};
+        if (K >= 4 && nt < 1024) return {S, 0};
+        if (nt >= (K == 4 ? 32768 : 5120) && K >= 4) return {S, 2};
+    } else {
+        if (K == 4 && nt >= 8192) return {S, 3};
+        if (K == 5 && nt >= 6144) return {S, 3};
+        if (K >= 6 && nt >= 4096) return {S, K == 8 ? 2u : 3u};
+        if (K >= 4 && kt_uneven(nt)) return {S, 0};
+    }
+    // whole tiles, two per CU for 3 to 5 copies (2 729 tiles, K = 4: 38.0 -> 37.7 us against none held; 3 copies,
+    // fp32, aligned: 2 500 tiles 4-7 % slower, 7 000 even, 10 000 1 % faster)
+    return {1, K >= 3 && K <= 5 && nt >= (K == 3 ? 8192 : 2048) ? 2u : 0u};
+}
+
+template <typename T, int K, bool DEVW>
+hipError_t launch_fused_k(const KtDeviceTables &tb, const KtTile *tiles, int64_t nt, const void *const *locals,
+                          const void *const *peers, const KtWeights &w, float scale, void *const *outs, hipStream_t s)
+{
+    const dim3 block(KT_BLOCK);
+#define KT_ARGS(TILES, WIN) TILES, tb.b_elems, tb.t_off, locals, peers, outs, scale, WIN, tb.t_numel, FewWeights(w)
+    if constexpr (K >= 7) {
+        const int64_t least = sizeof(T) == 2 ? 131072 : K == 8 ? KT_WINDOW_MIN_TILES_FUSED : KT_WINDOW_MIN_TILES_REDUCE;
+        const KtWindow win = kt_store_window(K, nt, least, sizeof(T) == 4 && K == 8);
+        if (win.width) {
+            kt_fused_kernel<T, K, DEVW, 1, sizeof(T) == 2><<<dim3((unsigned)nt), block, 0, s>>>(KT_ARGS(tiles, win));
+            return hipGetLastError();
+        }
+    }
+    const KtShape sh = fused_shape<T>(K, nt);
+    const unsigned lds = kt_shape_lds(sh, (unsigned)sizeof(LdsTable));
+    const KtWindow off{0, 0};
+    return launch_in_chunks(tiles, nt, sh.split, [&](const KtTile *t, dim3 grid) {
+        if constexpr (K >= 4) {
+            if (sh.split > 1) { kt_fused_kernel<T, K, DEVW, FusedSplit<T>::N, (sizeof(T) == 2 && K >= 6)><<<grid, block, lds, s>>>(KT_ARGS(t, off)); return; }
+        }
+        if constexpr (K < 6 || sizeof(T) == 4) kt_fused_kernel<T, K, DEVW, 1, (sizeof(T) == 2 && K == 1)><<<grid, block, lds, s>>>(KT_ARGS(t, off));
+    });
+#undef KT_ARGS
+}
+
 template <typename T, bool DEVW>
-hipError_t launch_fused_t(const KtDeviceTables &tb, int64_t tile0, int64_t ntiles, const void *const *locals,
+hipError_t launch_fused_t(const KtDeviceTables &tb, int64_t tile0, int64_t nt, const void *const *locals,
                           const void *const *peers, int K, const KtWeights &w, float scale, void *const *outs,
                           hipStream_t s)
 {
-    const dim3 grid((unsigned)ntiles), block(KT_BLOCK);
     const KtTile *tiles = tb.tiles + tile0;
-    const KtWindow win = kt_store_window(K, ntiles, (KT_WINDOW_MIN_READS_FUSED + K - 1) / K, sizeof(T) == 4 && K >= 8);
-    const unsigned lds = kt_mix_lds(win, K, ntiles, 2048, (unsigned)sizeof(LdsTable));
     switch (K) {
-#define KT_CASE(KK) \
-    case KK: kt_fused_kernel<T, KK, DEVW><<<grid, block, lds, s>>>(tiles, tb.b_elems, tb.t_off, locals, peers, outs, scale, win, tb.t_numel, FewWeights(w)); break;
+#define KT_CASE(KK) case KK: return launch_fused_k<T, KK, DEVW>(tb, tiles, nt, locals, peers, w, scale, outs, s);
         KT_CASE(1) KT_CASE(2) KT_CASE(3) KT_CASE(4) KT_CASE(5) KT_CASE(6) KT_CASE(7) KT_CASE(8)
 #undef KT_CASE
-    default: kt_fused_manyk_kernel<T, DEVW><<<grid, block, 0, s>>>(tiles, tb.b_elems, tb.t_off, locals, peers, outs, scale, K, win, tb.t_numel, AllWeights(w)); break;
     }
+    const KtWindow win = kt_store_window(K, nt, (KT_WINDOW_MIN_READS_FUSED + K - 1) / K, sizeof(T) == 4);
+    kt_fused_manyk_kernel<T, DEVW><<<dim3((unsigned)nt), dim3(KT_BLOCK), 0, s>>>(tiles, tb.b_elems, tb.t_off, locals, peers, outs,
+                                                                                 scale, K, win, tb.t_numel, AllWeights(w));
     return hipGetLastError();
 }
 

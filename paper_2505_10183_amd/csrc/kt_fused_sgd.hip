@@ -363,38 +363,28 @@ template <typename T, bool DEVW>
 hipError_t launch_fused_sgd_t(const KtDeviceTables &tb, int64_t tile0, int64_t ntiles, const FsgdArgs &f, int K,
                               const KtWeights &w, const KtSgd &a, hipStream_t s)
 {
-    const dim3 grid((unsigned)ntiles), block(KT_BLOCK);
+    const dim3 block(KT_BLOCK);
     if (K > 8) {
-        kt_fused_sgd_manyk_kernel<T, DEVW><<<grid, block, 0, s>>>(tb.tiles + tile0, tb.b_elems, tb.t_off, f.local_ptrs, f.peer_ptrs,
+        kt_fused_sgd_manyk_kernel<T, DEVW><<<dim3((unsigned)ntiles), block, 0, s>>>(tb.tiles + tile0, tb.b_elems, tb.t_off, f.local_ptrs, f.peer_ptrs,
                                                                       f.param_ptrs, f.mom_ptrs, f.model_ptrs, K, tb.t_numel, a, AllWeights(w));
         return hipGetLastError();
     }
     FsgdLaunch how = fsgd_launch<T>(K, ntiles);
     if (!kt_may_hold()) how.lds = 0;
-    // SPLIT workgroups per tile; a grid may not hold 2^32 or more lanes: very large plans go in several launches
-    constexpr int SPLIT = FsgdShape<T>::SPLIT;
-    const int64_t per_launch = (((int64_t)1 << 32) / KT_BLOCK - 1) / SPLIT;
-    for (int64_t done = 0; done < ntiles; done += per_launch) {
-        const int64_t now = ntiles - done < per_launch ? ntiles - done : per_launch;
-        const dim3 g2((unsigned)(now * SPLIT));
-        const KtTile *tiles = tb.tiles + tile0 + done;
+    return launch_in_chunks(tb.tiles + tile0, ntiles, FsgdShape<T>::SPLIT, [&](const KtTile *tiles, dim3 grid) {
 #define KT_ARGS \
     tiles, tb.b_elems, tb.t_off, f.local_ptrs, f.peer_ptrs, f.param_ptrs, f.mom_ptrs, f.model_ptrs, tb.t_numel, a, FewWeights(w)
         switch (K) {
-#define KT_CASE(KK) \
-    case KK:                                                                                                     \
-        if (how.sys) kt_fused_sgd_kernel<T, KK, DEVW, sizeof(T) == 2 && KK >= 8><<<g2, block, how.lds, s>>>(KT_ARGS); \
-        else kt_fused_sgd_kernel<T, KK, DEVW, false><<<g2, block, how.lds, s>>>(KT_ARGS);                     \
+#define KT_CASE(KK)                                                                                                     \
+    case KK:                                                                                                            \
+        if (how.sys) kt_fused_sgd_kernel<T, KK, DEVW, sizeof(T) == 2 && KK >= 8><<<grid, block, how.lds, s>>>(KT_ARGS); \
+        else kt_fused_sgd_kernel<T, KK, DEVW, false><<<grid, block, how.lds, s>>>(KT_ARGS);                             \
         break;
             KT_CASE(1) KT_CASE(2) KT_CASE(3) KT_CASE(4) KT_CASE(5) KT_CASE(6) KT_CASE(7) KT_CASE(8)
 #undef KT_CASE
 #undef KT_ARGS
-        default: return hipErrorInvalidValue;
         }
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    });
 }
 
 }  // namespace

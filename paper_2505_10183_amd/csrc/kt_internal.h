@@ -75,7 +75,8 @@ int kt_launch_unpack(const KtDeviceTables &tb, kt_dtype dt, int64_t tile0,
 // 8 peers: 72-73 % -> 77-78 % of 8 TB/s, the same within a point for periods of 10-14 us, and a steep
 // loss once the period exceeds the time the resident workgroups need for their loads (about 14-19 us
 // at K = 8; the 14 us period leaves 0-5 us, the 12 us one 2-7), which is why it is used only where
-// that time is known to be longer (K >= 5, many tiles).
+// that time is known to be longer (K >= 5, many tiles).  Launches of 7 and 8 copies below the limits
+// here, and all of fewer, do better with few workgroups per CU that share tiles (KtShape).
 // width == 0: no window.
 struct KtWindow {
     uint32_t period;  // clock ticks
@@ -104,15 +105,18 @@ KtWindow kt_store_window(int K, int64_t ntiles, int64_t min_tiles, bool late);
 #define KT_WINDOW_LATE_OPEN_PCT 6
 #endif
 // Smallest launches that use the window, in tiles read (tiles x copies) or, for the reduce of up to
-// 8 copies, in tiles.  The fused pass is a step of its own and gains from 65 536 tiles read on
-// (K = 8: 8 192 tiles 205 -> 200 us; K = 16: 8 192 tiles 399 -> 371 us, 4 096 tiles 212 -> 199 us).
-// The reduce stands between pack and unpack, which lose part
-// of what the caches held for them: inside the step K = 8 is 1-3 % slower with the window up to
-// 32 768 tiles and 2-4 % faster from 65 536 on.  With more copies that share shrinks: from 262 144
+// 8 copies, in tiles.  The fused pass of more copies gains from 65 536 tiles read on
+// (K = 16: 8 192 tiles 399 -> 371 us, 4 096 tiles 212 -> 199 us), the fp32 one of 8 is even with quarter
+// tiles from 10 331 to 20 623 tiles and better above (39 522 tiles 923 us, 935), the bf16 one from 131 072 on.  The reduce of 7 and 8 copies
+// is 6-9 % slower with the window at 40 000 tiles and 2-5 % faster at 85 000 (K = 8, fp32 1 984 us against
+// 2 066, bf16 2 016 against 2 075).  With more copies, in the step between pack and unpack, from 262 144
 // tiles read on the step is even or faster (K = 16, 32 768 tiles: 1 927 -> 1 888 us fp32, 1 952 ->
 // 1 862 bf16) and the reduce alone gains 6-10 % (K = 16, 21 135 tiles: 1 040 -> 983 us, 1 032 -> 943).
 #ifndef KT_WINDOW_MIN_READS_FUSED
 #define KT_WINDOW_MIN_READS_FUSED 65536
+#endif
+#ifndef KT_WINDOW_MIN_TILES_FUSED
+#define KT_WINDOW_MIN_TILES_FUSED 16384
 #endif
 #ifndef KT_WINDOW_MIN_TILES_REDUCE
 #define KT_WINDOW_MIN_TILES_REDUCE 65536
@@ -135,25 +139,22 @@ constexpr bool kt_holds(unsigned wgs)
     const unsigned bytes = kt_hold_lds(wgs, 0);
     return bytes % KT_LDS_GRANULE == 0 && bytes <= 65536 && KT_CU_LDS / bytes == wgs;
 }
-static_assert(kt_holds(2) && kt_holds(4) && kt_holds(5), "the counts that launches ask for");
+static_assert(kt_holds(2) && kt_holds(3) && kt_holds(4) && kt_holds(5), "the counts that launches ask for");
 
 // false where the caller shares the GPU (KT_STORE_WINDOW_NS=0): held workgroups keep the LDS of every
 // CU from kernels that run beside them.
 bool kt_may_hold();
 
-// LDS asked for by reduce and fused launches of 3 to 5 copies that do not use the window, to hold 2
-// workgroups on a CU (registers allow 5 to 8): fewer reads in flight mix better with the
-// writes (18 000 tiles, K = 4: fused 245 -> 237 us fp32, 244 -> 234 bf16; reduce 240 -> 235 us, 242 ->
-// 234; K = 3, 65 536 tiles 705 -> 690 us), and better than the window does at K = 4.  Three are no
-// better than without.  Two copies or
-// less gain nothing; the reduce loses 1-2 % below 4 096 tiles, the fused pass is even at 2 048 and
-// gains from there (2 729 tiles, K = 4: 38.0 -> 37.7 us).  Three copies gain from 8 192 tiles on only
-// (fp32 fused, aligned: 2 500 tiles 4-7 % slower, 5 000 1 %, 7 000 even, 10 000 1 % faster).  `own`: the
-// kernel's own LDS.
-inline unsigned kt_mix_lds(const KtWindow &w, int K, int64_t ntiles, int64_t min_tiles, unsigned own)
-{
-    return w.width == 0 && K >= 3 && K <= 5 && ntiles >= (K == 3 ? 8192 : min_tiles) && kt_may_hold() ? kt_hold_lds(2, own) : 0u;
-}
+// How a launch of the reduce or the fused pass is laid out: workgroups that share a tile, and
+// workgroups per CU that it is held to by asking for LDS (0: as many as fit).  `own`: the kernel's own LDS.
+struct KtShape {
+    int split;
+    unsigned wgs;
+};
+inline unsigned kt_shape_lds(const KtShape &s, unsigned own) { return s.wgs && kt_may_hold() ? kt_hold_lds(s.wgs, own) : 0u; }
+
+// Launches of two to four rounds over the 256 CUs, a tile each, whose last round is more than a sixth empty.
+inline bool kt_uneven(int64_t ntiles) { return ntiles > 256 && ntiles < 1024 && 5 * ((ntiles + 255) / 256 * 256) > 6 * ntiles; }
 
 // The K weights of a launch travel in the kernel-argument block (`w`), unless
 // `dev` is set: then the kernels read them from that device array when they

@@ -228,25 +228,12 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_unpack_kernel(const KtTile *tiles
 
 }  // namespace
 
-// A grid may not hold 2^32 or more lanes: very large plans go in several launches.
-template <typename F> static int launch_in_chunks(const KtTile *tiles, int64_t ntiles, F launch)
-{
-    const int64_t per_launch = (((int64_t)1 << 32) / KT_BLOCK - 1) / COPY_SPLIT;
-    for (int64_t done = 0; done < ntiles; done += per_launch) {
-        const int64_t now = ntiles - done < per_launch ? ntiles - done : per_launch;
-        launch(tiles + done, dim3((unsigned)(now * COPY_SPLIT)));
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return (int)e;
-    }
-    return (int)hipSuccess;
-}
-
 int kt_launch_pack(const KtDeviceTables &tb, kt_dtype dt, int64_t tile0, int64_t ntiles,
                    const void *const *d_tensor_ptrs, void *const *d_bucket_ptrs, void *stream)
 {
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const dim3 block(KT_BLOCK);
-    return launch_in_chunks(tb.tiles + tile0, ntiles, [&](const KtTile *tiles, dim3 grid) {
+    return (int)launch_in_chunks(tb.tiles + tile0, ntiles, COPY_SPLIT, [&](const KtTile *tiles, dim3 grid) {
         if (dt == KT_F32) kt_pack_kernel<float><<<grid, block, 0, s>>>(tiles, tb.b_elems, tb.t_off, d_tensor_ptrs, d_bucket_ptrs, tb.t_numel);
         else kt_pack_kernel<uint16_t><<<grid, block, 0, s>>>(tiles, tb.b_elems, tb.t_off, d_tensor_ptrs, d_bucket_ptrs, tb.t_numel);
     });
@@ -257,7 +244,7 @@ int kt_launch_unpack(const KtDeviceTables &tb, kt_dtype dt, int64_t tile0, int64
 {
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     const dim3 block(KT_BLOCK);
-    return launch_in_chunks(tb.tiles + tile0, ntiles, [&](const KtTile *tiles, dim3 grid) {
+    return (int)launch_in_chunks(tb.tiles + tile0, ntiles, COPY_SPLIT, [&](const KtTile *tiles, dim3 grid) {
         if (dt == KT_F32) kt_unpack_kernel<float><<<grid, block, 0, s>>>(tiles, tb.b_elems, tb.t_off, d_bucket_ptrs, d_tensor_ptrs, scale, tb.t_numel);
         else kt_unpack_kernel<uint16_t><<<grid, block, 0, s>>>(tiles, tb.b_elems, tb.t_off, d_bucket_ptrs, d_tensor_ptrs, scale, tb.t_numel);
     });

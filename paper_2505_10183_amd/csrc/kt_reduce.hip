@@ -4,22 +4,26 @@
 
 namespace {
 
-// One workgroup per 16 KiB tile.  A full tile keeps all K copies of the lane's 4 vectors in flight
-// together (32 loads at K = 8): the kernel is bound by what the memory system sustains for reads
-// with one written line in K + 1.  Copies and output may lie at any element address.  The stores
-// are not moved to 64-byte boundaries as pack and unpack do: with the offsets in registers the
-// loads issue back to back, which inside the store windows lost 3-10 % (1.3B set 3.77 -> 3.89 ms),
-// more than the 3 % of a misaligned non-temporal store stream.
-template <typename T, int K, bool DEVW>
+// SPLIT workgroups share a 16 KiB tile, each with KT_TILE_VECS / KT_BLOCK / SPLIT vectors of all K copies per
+// lane in flight together.  The kernel is bound by how well the memory system takes K read streams and
+// one write stream: few bytes in flight (48-96 KB per CU), in workgroups that the dispatcher starts
+// in order, so that the chip sweeps every stream over a narrow front, do best (reduce_shape); persistent
+// workgroups with the same bytes in flight lose 5-10 %.  Copies and output may lie at any element
+// address; the stores are not moved to 64-byte boundaries as pack and unpack do: it costs more
+// than the 3 % of a misaligned non-temporal store stream.  INT: bf16 narrowing in integer instructions
+// (f32_to_bf16_int).  Whole tiles test the window's width whether it is zero or not: without
+// that test between loads and stores they are 1-3 % slower.
+template <typename T, int K, bool DEVW, int SPLIT, bool INT>
 __global__ __launch_bounds__(KT_BLOCK) void kt_reduce_kernel(const KtTile *tiles, const int64_t *b_elems,
                                                              const void *const *peer_ptrs, void *const *out_ptrs,
                                                              KtWindow win, FewWeights wts)
 {
     constexpr int VE = Elem<T>::VE;
     constexpr int64_t TILE_ELEMS = (int64_t)KT_TILE_VECS * VE;
-    constexpr int VPT = KT_TILE_VECS / KT_BLOCK;   // vectors per lane, K loads each, all in flight at once
+    constexpr int VPT = KT_TILE_VECS / KT_BLOCK / SPLIT;   // vectors per lane, K loads each, all in flight at once
 
-    const KtTile tl = ld_tile(tiles + blockIdx.x);
+    const int part = SPLIT == 1 ? 0 : (int)(blockIdx.x % SPLIT);
+    const KtTile tl = ld_tile(tiles + blockIdx.x / SPLIT);
     const int64_t b_n = ld_table(b_elems + tl.bucket);
     T *out = reinterpret_cast<T *>(ld_table(out_ptrs + tl.bucket));
     const T *x[K];
@@ -39,11 +43,12 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_reduce_kernel(const KtTile *tiles
     const int nvec = (int)(n / VE);
 
     if (nvec == KT_TILE_VECS) {
+        const int v0 = part * VPT * KT_BLOCK + tid;        // the lane's first vector in the tile
         u32x4 r[VPT][K];
 #pragma unroll
         for (int u = 0; u < VPT; ++u)
 #pragma unroll
-            for (int k = 0; k < K; ++k) r[u][k] = ld_vec(reinterpret_cast<const u32x4 *>(x[k]) + u * KT_BLOCK + tid);
+            for (int k = 0; k < K; ++k) r[u][k] = ld_vec(reinterpret_cast<const u32x4 *>(x[k]) + u * KT_BLOCK + v0);
         u32x4 res[VPT];
 #pragma unroll
         for (int u = 0; u < VPT; ++u) {
@@ -51,13 +56,13 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_reduce_kernel(const KtTile *tiles
             acc.first(r[u][0], w[0]);
 #pragma unroll
             for (int k = 1; k < K; ++k) acc.add(r[u][k], w[k]);
-            res[u] = acc.template finish<(K >= 6)>();
+            res[u] = acc.template finish<INT>();
         }
-        kt_wait_store_window(win);     // large launches: the chip writes in bursts (KtWindow)
+        if (SPLIT == 1) kt_wait_store_window(win);     // large launches: the chip writes in bursts (KtWindow)
 #pragma unroll
-        for (int u = 0; u < VPT; ++u) st_vec(reinterpret_cast<u32x4 *>(out) + u * KT_BLOCK + tid, res[u]);
+        for (int u = 0; u < VPT; ++u) st_vec(reinterpret_cast<u32x4 *>(out) + u * KT_BLOCK + v0, res[u]);
     } else {
-        for (int v = tid; v < nvec; v += KT_BLOCK) {
+        for (int v = part * KT_BLOCK + tid; v < nvec; v += SPLIT * KT_BLOCK) {
             u32x4 r[K];
 #pragma unroll
             for (int k = 0; k < K; ++k) r[k] = ld_vec(x[k] + (int64_t)v * VE);
@@ -69,7 +74,7 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_reduce_kernel(const KtTile *tiles
         }
         // tail of a densely packed bucket (fewer than VE elements)
         const int64_t e = (int64_t)nvec * VE + tid;
-        if (e < n) {
+        if (part == 0 && e < n) {
             float a = __fmul_rn(w[0], widen(ld_elem(x[0] + e)));
 #pragma unroll
             for (int k = 1; k < K; ++k) a = __fmaf_rn(w[k], widen(ld_elem(x[k] + e)), a);
@@ -122,22 +127,69 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_reduce_manyk_kernel(const KtTile 
     }
 }
 
-template <typename T, bool DEVW>
-hipError_t launch_reduce_t(const KtDeviceTables &tb, int64_t tile0, int64_t ntiles, const void *const *peers,
-                           int K, const KtWeights &w, void *const *outs, hipStream_t s)
+// Workgroups per tile and per CU (0: as many as fit) by type, copies and tiles, where no store window
+// is open.  Quarter tiles held at 2 to 5 workgroups per CU (40-96 KB in flight) against whole tiles as
+// the launches had them before (two per CU for 3 to 5 copies), flat out:
+//   K   fp32                                             bf16
+//   2   23 912 tiles 187.7 -> 180.0 us, 14 767 even (not held; held at 3 to 5: 2-10 % slower)   60 883 tiles 487 -> 463 us
+//   3   23 912 tiles 250.5 -> 244.2 us                   18 043 tiles 191.8 -> 185.7 us
+//   4   36 090 tiles 485 -> 467 us, 7 052 even           11 956 tiles 156.1 -> 153.3 us, 9 081 1 % slower
+//   5   7 052 tiles 113.8 -> 109.7 us, 3 563 2 % slower  18 043 tiles 291.7 -> 280.2 us, 3 526 2 % slower
+//   6   42 203 tiles 832 -> 761 us, 1 957 even           42 502 tiles 837 -> 741 us, 1 528 1 % slower
+//   7   42 203 tiles 958 -> 889 us, 1 957 4 % slower     18 043 tiles 407 -> 375 us, 2 055 even
+//   8   39 522 tiles 1 006 -> 920 us, 1 957 1 % slower   39 961 tiles 1 020 -> 942 us, 2 055 55.7 -> 50.5 us
+//       (two per CU; three: 931 us)
+// Below, a launch is a few rounds of workgroups: quarter tiles only where whole ones would leave a sixth of
+// the last round idle (551 tiles of bf16: K = 8 17.8 -> 15.4 us against 16.3, K = 4 10.5 -> 8.9 against
+// 9.3; 491 tiles, 96 % of two rounds: whole tiles 4-8 % faster).
+template <typename T> KtShape reduce_shape(int K, int64_t nt)
 {
-    dim3 grid((unsigned)ntiles), block(KT_BLOCK);
-    const KtTile *tiles = tb.tiles + tile0;
-    const KtWindow win = kt_store_window(K, ntiles, K <= 8 ? KT_WINDOW_MIN_TILES_REDUCE : (KT_WINDOW_MIN_READS_REDUCE_MANYK + K - 1) / K,
-                                         sizeof(T) == 4);
-    const unsigned lds = kt_mix_lds(win, K, ntiles, 4096, 0);
+    const bool half = sizeof(T) == 2;
     switch (K) {
-#define KT_CASE(KK) \
-    case KK: kt_reduce_kernel<T, KK, DEVW><<<grid, block, lds, s>>>(tiles, tb.b_elems, peers, outs, win, FewWeights(w)); break;
+    case 1: break;
+    case 2: if (nt >= 12288) return {4, 0}; break;
+    case 3: if (nt >= 8192) return {4, 5}; break;
+    case 4: if (nt >= 4096) return nt >= (half ? 12288 : 8192) ? KtShape{4, 3} : KtShape{1, 2}; break;
+    case 5: if (nt >= 4096) return {4, 3}; break;
+    case 6: if (nt >= 2048) return {4, 3}; break;
+    case 7: if (nt >= (half ? 2048 : 4096)) return {4, 3}; break;
+    default: if (nt >= (half ? 2048 : 3072)) return {4, half ? 3u : 2u}; break;
+    }
+    return {K >= 2 && kt_uneven(nt) ? 4 : 1, 0};
+}
+
+template <typename T, int K, bool DEVW>
+hipError_t launch_reduce_k(const KtTile *tiles, const int64_t *b_elems, int64_t nt, const void *const *peers,
+                           const KtWeights &w, void *const *outs, hipStream_t s)
+{
+    const dim3 block(KT_BLOCK);
+    if constexpr (K >= 7) {
+        const KtWindow win = kt_store_window(K, nt, KT_WINDOW_MIN_TILES_REDUCE, sizeof(T) == 4);
+        if (win.width) {
+            kt_reduce_kernel<T, K, DEVW, 1, sizeof(T) == 2><<<dim3((unsigned)nt), block, 0, s>>>(tiles, b_elems, peers, outs, win, FewWeights(w));
+            return hipGetLastError();
+        }
+    }
+    const KtShape sh = reduce_shape<T>(K, nt);
+    const unsigned lds = kt_shape_lds(sh, 0);
+    return launch_in_chunks(tiles, nt, sh.split, [&](const KtTile *t, dim3 grid) {
+        if (sh.split == 1) kt_reduce_kernel<T, K, DEVW, 1, false><<<grid, block, lds, s>>>(t, b_elems, peers, outs, KtWindow{0, 0}, FewWeights(w));
+        else if constexpr (K > 1) kt_reduce_kernel<T, K, DEVW, 4, (sizeof(T) == 2 && K >= 6)><<<grid, block, lds, s>>>(t, b_elems, peers, outs, KtWindow{0, 0}, FewWeights(w));
+    });
+}
+
+template <typename T, bool DEVW>
+hipError_t launch_reduce_t(const KtDeviceTables &tb, int64_t tile0, int64_t nt, const void *const *peers, int K,
+                           const KtWeights &w, void *const *outs, hipStream_t s)
+{
+    const KtTile *tiles = tb.tiles + tile0;
+    switch (K) {
+#define KT_CASE(KK) case KK: return launch_reduce_k<T, KK, DEVW>(tiles, tb.b_elems, nt, peers, w, outs, s);
         KT_CASE(1) KT_CASE(2) KT_CASE(3) KT_CASE(4) KT_CASE(5) KT_CASE(6) KT_CASE(7) KT_CASE(8)
 #undef KT_CASE
-    default: kt_reduce_manyk_kernel<T, DEVW><<<grid, block, 0, s>>>(tiles, tb.b_elems, peers, outs, K, win, AllWeights(w)); break;
     }
+    const KtWindow win = kt_store_window(K, nt, (KT_WINDOW_MIN_READS_REDUCE_MANYK + K - 1) / K, sizeof(T) == 4);
+    kt_reduce_manyk_kernel<T, DEVW><<<dim3((unsigned)nt), dim3(KT_BLOCK), 0, s>>>(tiles, tb.b_elems, peers, outs, K, win, AllWeights(w));
     return hipGetLastError();
 }
 

@@ -172,29 +172,17 @@ int kt_launch_unpack_sgd(const KtDeviceTables &tb, kt_dtype dt, int64_t tile0, i
     dim3 block(KT_BLOCK);
     const int split = dt == KT_F32 ? SgdShape<float>::SPLIT : SgdShape<uint16_t>::SPLIT;
     const unsigned lds = sgd_lds(dt, ntiles);
-    // a grid may not hold 2^32 or more lanes: very large plans go in several launches
-    const int64_t per_launch = (((int64_t)1 << 32) / KT_BLOCK - 1) / split;
-    for (int64_t done = 0; done < ntiles; done += per_launch) {
-        const int64_t now = ntiles - done < per_launch ? ntiles - done : per_launch;
-        const dim3 grid((unsigned)(now * split));
-        const KtTile *tiles = tb.tiles + tile0 + done;
-#define KT_SGD_LAUNCH(TT, MM)                                                                                        \
-    do {                                                                                                            \
-        if (a.dev)                                                                                                  \
-            kt_unpack_sgd_kernel<TT, MM, true><<<grid, block, lds, s>>>(tiles, tb.b_elems, tb.t_off, d_bucket_ptrs, d_param_ptrs, \
-                                                                      d_mom_ptrs, d_model_ptrs, a, tb.t_numel);                            \
-        else                                                                                                        \
-            kt_unpack_sgd_kernel<TT, MM, false><<<grid, block, lds, s>>>(tiles, tb.b_elems, tb.t_off, d_bucket_ptrs, d_param_ptrs, \
-                                                                       d_mom_ptrs, d_model_ptrs, a, tb.t_numel);                           \
-    } while (0)
+    return (int)launch_in_chunks(tb.tiles + tile0, ntiles, split, [&](const KtTile *tiles, dim3 grid) {
+#define KT_SGD_LAUNCH(TT, MM, DD)                                                                                    \
+    kt_unpack_sgd_kernel<TT, MM, DD><<<grid, block, lds, s>>>(tiles, tb.b_elems, tb.t_off, d_bucket_ptrs, d_param_ptrs, \
+                                                              d_mom_ptrs, d_model_ptrs, a, tb.t_numel)
         if (dt == KT_F32) {
-            if (d_model_ptrs) KT_SGD_LAUNCH(float, true); else KT_SGD_LAUNCH(float, false);
+            if (d_model_ptrs) { if (a.dev) KT_SGD_LAUNCH(float, true, true); else KT_SGD_LAUNCH(float, true, false); }
+            else { if (a.dev) KT_SGD_LAUNCH(float, false, true); else KT_SGD_LAUNCH(float, false, false); }
         } else {
-            if (d_model_ptrs) KT_SGD_LAUNCH(uint16_t, true); else KT_SGD_LAUNCH(uint16_t, false);
+            if (d_model_ptrs) { if (a.dev) KT_SGD_LAUNCH(uint16_t, true, true); else KT_SGD_LAUNCH(uint16_t, true, false); }
+            else { if (a.dev) KT_SGD_LAUNCH(uint16_t, false, true); else KT_SGD_LAUNCH(uint16_t, false, false); }
         }
 #undef KT_SGD_LAUNCH
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return (int)e;
-    }
-    return (int)hipSuccess;
+    });
 }
