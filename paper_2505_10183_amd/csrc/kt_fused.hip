@@ -157,16 +157,17 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_kernel(const KtTile *tiles,
 }
 
 // K > 8: full solid tiles take the peers in chunks with the accumulators in
-// registers (sum_in_chunks; peer 0 is the local tensor); every other tile goes
+// registers (sum_in_chunks, quarter tiles sum_rolling; peer 0 is the local tensor); every other tile goes
 // vector by vector with a loop over the peers.
 template <typename T, bool DEVW, typename V>
 __device__ __forceinline__ void fused_mixed_manyk(const V &tv, int nt, const TileGeom &g,
-                                                  const void *const *pp, int K, const AllWeights &wts, float scale)
+                                                  const void *const *pp, int K, const AllWeights &wts, float scale,
+                                                  int part, int parts)
 {
     constexpr int VE = Elem<T>::VE;
     const int nvec = (int)((g.end - g.start + VE - 1) / VE);
 #pragma unroll 1
-    for (int v = threadIdx.x; v < nvec; v += KT_BLOCK) {
+    for (int v = part * KT_BLOCK + threadIdx.x; v < nvec; v += parts * KT_BLOCK) {
         const int64_t e0 = g.start + (int64_t)v * VE;
         const int i = find_owner_v(tv, nt, e0);
         const int64_t r = i >= 0 ? e0 - tv.off[i] : -1;
@@ -179,7 +180,7 @@ __device__ __forceinline__ void fused_mixed_manyk(const V &tv, int nt, const Til
             st_vec(reinterpret_cast<T *>(tv.ptr2[i]) + r, scale_vec<T>(acc.finish(), scale));
         }
     }
-    each_cut_elem<VE>(tv, nt, g.start, (int)(g.end - g.start), threadIdx.x, KT_BLOCK, [&](int i, int64_t r, int e) {
+    each_cut_elem<VE>(tv, nt, g.start, (int)(g.end - g.start), part * KT_BLOCK + threadIdx.x, parts * KT_BLOCK, [&](int i, int64_t r, int e) {
         float a = __fmul_rn(kt_weight<DEVW>(wts, 0), widen(ld_elem(reinterpret_cast<const T *>(tv.ptr[i]) + r)));
 #pragma unroll 4
         for (int k = 1; k < K; ++k)
@@ -188,7 +189,7 @@ __device__ __forceinline__ void fused_mixed_manyk(const V &tv, int nt, const Til
     });
 }
 
-template <typename T, bool DEVW>
+template <typename T, bool DEVW, int SPLIT>
 __global__ __launch_bounds__(KT_BLOCK) void kt_fused_manyk_kernel(const KtTile *tiles, const int64_t *b_elems,
                                                                   const int64_t *t_offs, const void *const *local_ptrs,
                                                                   const void *const *peer_ptrs, void *const *out_ptrs,
@@ -197,10 +198,11 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_manyk_kernel(const KtTile *
 {
     constexpr int VE = Elem<T>::VE;
     constexpr int64_t TILE_ELEMS = (int64_t)KT_TILE_VECS * VE;
-    constexpr int VPT = KT_TILE_VECS / KT_BLOCK;
+    constexpr int VPT = KT_TILE_VECS / KT_BLOCK / SPLIT;
     __shared__ LdsTable lds;
 
-    const KtTile tl = ld_tile(tiles + blockIdx.x);
+    const int part = SPLIT == 1 ? 0 : (int)(blockIdx.x % SPLIT);
+    const KtTile tl = ld_tile(tiles + blockIdx.x / SPLIT);
     const int64_t b_n = ld_table(b_elems + tl.bucket), t_off = ld_table(t_offs + tl.t0);
     const T *src = reinterpret_cast<const T *>(ld_table(local_ptrs + tl.t0));
     T *dst = reinterpret_cast<T *>(ld_table(out_ptrs + tl.t0));
@@ -212,25 +214,27 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_manyk_kernel(const KtTile *
     if (tl.nt == 0 && g.end - g.start == TILE_ELEMS) {
         src += g.start - t_off;
         dst += g.start - t_off;
+        const int v0 = part * VPT * KT_BLOCK + tid;
         Acc<T> acc[VPT];
-        sum_in_chunks<T, DEVW>(acc, [&](int k) { return k == 0 ? src : reinterpret_cast<const T *>(ld_table(pp + k - 1)) + g.start; },
-                         wts, K, tid);
+        auto copy = [&](int k) { return k == 0 ? src : reinterpret_cast<const T *>(ld_table(pp + k - 1)) + g.start; };
+        if constexpr (VPT == 1) sum_rolling<T, DEVW>(acc[0], copy, wts, K, v0);
+        else sum_in_chunks<T, VPT, DEVW>(acc, copy, wts, K, v0);
         u32x4 res[VPT];
 #pragma unroll
-        for (int u = 0; u < VPT; ++u) res[u] = scale_vec<T, true>(acc[u].template finish<true>(), scale);
-        kt_wait_store_window(win);
+        for (int u = 0; u < VPT; ++u) res[u] = scale_vec<T, SPLIT == 1>(acc[u].template finish<SPLIT == 1>(), scale);
+        if (SPLIT == 1) kt_wait_store_window(win);
 #pragma unroll
-        for (int u = 0; u < VPT; ++u) st_vec(reinterpret_cast<u32x4 *>(dst) + u * KT_BLOCK + tid, res[u]);
+        for (int u = 0; u < VPT; ++u) st_vec(reinterpret_cast<u32x4 *>(dst) + u * KT_BLOCK + v0, res[u]);
         return;
     }
     const int nt = tl.nt == 0 ? 1 : tl.nt;
     const void *const *op = reinterpret_cast<const void *const *>(out_ptrs);
     if (nt <= KT_LDS_TENSORS) {
         const LdsView tv = stage_lds(lds, t_offs, t_numel, local_ptrs, op, tl.t0, nt);
-        fused_mixed_manyk<T, DEVW>(tv, nt, g, pp, K, wts, scale);
+        fused_mixed_manyk<T, DEVW>(tv, nt, g, pp, K, wts, scale, part, SPLIT);
     } else {
         const GlobalView tv = global_view(t_offs, t_numel, local_ptrs, op, tl.t0);
-        fused_mixed_manyk<T, DEVW>(tv, nt, g, pp, K, wts, scale);
+        fused_mixed_manyk<T, DEVW>(tv, nt, g, pp, K, wts, scale, part, SPLIT);
     }
 }
 
@@ -267,6 +271,12 @@ template <typename T> KtShape fused_shape(int K, int64_t nt)
     // fp32, aligned: 2 500 tiles 4-7 % slower, 7 000 even, 10 000 1 % faster)
     return {1, K >= 3 && K <= 5 && nt >= (K == 3 ? 8192 : 2048) ? 2u : 0u};
 }
+
+// 9 and more copies outside the store window: quarter tiles, whose mixed tiles are shared too (a vector with a
+// serial loop over the copies decides small launches: K = 16 fp32 29 tiles 18.3 -> 6.3 us, 222 tiles 22.1 -> 13.0, 763 tiles
+// 41 -> 37.5, bf16 508 tiles 32.6 -> 27.2), held at two per CU above 1 152 (K = 12 fp32 2 713 tiles 5 % faster than whole
+// ones, 1 200 to 1 800 tiles within 2 %; K = 9 there up to 4 % behind).
+inline KtShape fused_manyk_shape(int64_t nt) { return {4, nt > 1152 ? 2u : 0u}; }
 
 template <typename T, int K, bool DEVW>
 hipError_t launch_fused_k(const KtDeviceTables &tb, const KtTile *tiles, int64_t nt, const void *const *locals,
@@ -306,9 +316,14 @@ hipError_t launch_fused_t(const KtDeviceTables &tb, int64_t tile0, int64_t nt, c
 #undef KT_CASE
     }
     const KtWindow win = kt_store_window(K, nt, (KT_WINDOW_MIN_READS_FUSED + K - 1) / K, sizeof(T) == 4);
-    kt_fused_manyk_kernel<T, DEVW><<<dim3((unsigned)nt), dim3(KT_BLOCK), 0, s>>>(tiles, tb.b_elems, tb.t_off, locals, peers, outs,
-                                                                                 scale, K, win, tb.t_numel, AllWeights(w));
-    return hipGetLastError();
+    const KtShape sh = win.width ? KtShape{1, 0} : fused_manyk_shape(nt);
+    const unsigned lds = kt_shape_lds(sh, (unsigned)sizeof(LdsTable));
+    return launch_in_chunks(tiles, nt, sh.split, [&](const KtTile *t, dim3 grid) {
+#define KT_ARGS t, tb.b_elems, tb.t_off, locals, peers, outs, scale, K, win, tb.t_numel, AllWeights(w)
+        if (sh.split == 1) kt_fused_manyk_kernel<T, DEVW, 1><<<grid, dim3(KT_BLOCK), lds, s>>>(KT_ARGS);
+        else kt_fused_manyk_kernel<T, DEVW, 4><<<grid, dim3(KT_BLOCK), lds, s>>>(KT_ARGS);
+#undef KT_ARGS
+    });
 }
 
 }  // namespace

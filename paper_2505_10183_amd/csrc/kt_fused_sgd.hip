@@ -283,9 +283,10 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_kernel(const KtTile *ti
     fsgd_other_tile<T, K, DEVW>(lds.table, t_offs, t_numel, tl, g, f, pp, K, wts, a, part, SPLIT);
 }
 
-// K = 9..64: full solid tiles take the peers in chunks with the accumulators in registers, one
-// workgroup per tile; every other tile as above.
-template <typename T, bool DEVW>
+// K = 9..64: full solid tiles take the peers in chunks with the accumulators in registers; every other
+// tile as above.  SPLIT workgroups share a tile (fsgd_manyk_shape).  Chunks, not sum_rolling, on quarter tiles: p and
+// v are in flight beside them, and the rolling form is 1-5 % slower (K = 9 fp32 19 874 tiles 672 us, 695).
+template <typename T, bool DEVW, int SPLIT>
 __global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_manyk_kernel(const KtTile *tiles, const int64_t *b_elems,
                                                                       const int64_t *t_offs, const void *const *local_ptrs,
                                                                       const void *const *peer_ptrs, void *const *param_ptrs,
@@ -296,10 +297,11 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_manyk_kernel(const KtTi
     const FsgdArgs f{local_ptrs, peer_ptrs, param_ptrs, mom_ptrs, model_ptrs};
     constexpr int VE = Elem<T>::VE;
     constexpr int64_t TILE_ELEMS = (int64_t)KT_TILE_VECS * VE;
-    constexpr int VPT = KT_TILE_VECS / KT_BLOCK, QPL = VPT * FsgdShape<T>::QPV;
+    constexpr int VPT = KT_TILE_VECS / KT_BLOCK / SPLIT, QPL = VPT * FsgdShape<T>::QPV;
     __shared__ FsgdLds lds;
 
-    const KtTile tl = ld_tile(tiles + blockIdx.x);
+    const int part = SPLIT == 1 ? 0 : (int)(blockIdx.x % SPLIT);
+    const KtTile tl = ld_tile(tiles + blockIdx.x / SPLIT);
     const int64_t b_n = ld_table(b_elems + tl.bucket), t_off = ld_table(t_offs + tl.t0);
     TensorSide<T> t(f, tl.t0);
     const KtSgd a = resolve_sgd(a_in);
@@ -309,24 +311,30 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_manyk_kernel(const KtTi
 
     if (tl.nt == 0 && g.end - g.start == TILE_ELEMS) {
         t.advance(g.start - t_off);
-        Acc<T> acc[VPT];
-        sum_in_chunks<T, DEVW>(acc, [&](int k) { return k == 0 ? t.src : reinterpret_cast<const T *>(ld_table(pp + k - 1)) + g.start; },
-                               wts, K, tid);
+        const int v0 = part * VPT * KT_BLOCK + tid;       // the lane's first vector in the tile
+        const int q0 = part * QPL * KT_BLOCK + tid;       // and its first quad of p, v and the model copy
         u32x4 red[VPT], pr[QPL], vr[QPL];
+        u32x4 *p4 = reinterpret_cast<u32x4 *>(t.p) + q0, *v4 = reinterpret_cast<u32x4 *>(t.v) + q0;
+        u32x4 *vs = a.first ? p4 : v4;
+        auto load_state = [&] {
+#pragma unroll
+            for (int j = 0; j < QPL; ++j) {
+                pr[j] = ld_vec(p4 + j * KT_BLOCK);
+                vr[j] = ld_vec(vs + j * KT_BLOCK);
+            }
+        };
+        if (SPLIT > 1) load_state();                      // in flight with the first copies
+        Acc<T> acc[VPT];
+        sum_in_chunks<T, VPT, DEVW>(acc, [&](int k) { return k == 0 ? t.src : reinterpret_cast<const T *>(ld_table(pp + k - 1)) + g.start; },
+                              wts, K, v0);
 #pragma unroll
         for (int u = 0; u < VPT; ++u) red[u] = acc[u].finish();
-        u32x4 *p4 = reinterpret_cast<u32x4 *>(t.p) + tid, *v4 = reinterpret_cast<u32x4 *>(t.v) + tid;
-        u32x4 *vs = a.first ? p4 : v4;
-#pragma unroll
-        for (int j = 0; j < QPL; ++j) {
-            pr[j] = ld_vec(p4 + j * KT_BLOCK);
-            vr[j] = ld_vec(vs + j * KT_BLOCK);
-        }
+        if (SPLIT == 1) load_state();
         update_quads<VPT>(red, lds.red, pr, vr, a, T(0));
-        st_quads<QPL, false>(p4, v4, t.m ? reinterpret_cast<u32x2 *>(t.m) + tid : nullptr, pr, vr);
+        st_quads<QPL, false>(p4, v4, t.m ? reinterpret_cast<u32x2 *>(t.m) + q0 : nullptr, pr, vr);
         return;
     }
-    fsgd_other_tile<T, 0, DEVW>(lds.table, t_offs, t_numel, tl, g, f, pp, K, wts, a, 0, 1);
+    fsgd_other_tile<T, 0, DEVW>(lds.table, t_offs, t_numel, tl, g, f, pp, K, wts, a, part, SPLIT);
 }
 
 // Bytes of LDS asked for beyond the kernel's own, to hold the number of workgroups per CU at 2 or 4;
@@ -359,15 +367,31 @@ template <typename T> FsgdLaunch fsgd_launch(int K, int64_t ntiles)
     return FsgdLaunch{K >= 4 ? FSGD_LDS_2 : FSGD_LDS_4, false};
 }
 
+// 9 and more copies.  Small launches take quarter tiles (K = 16: 29 tiles fp32 18.9 -> 6.6 us, 249 tiles bf16
+// 27.8 -> 19.2, 597 tiles fp32 42.5 -> 36.4; nearly one round of four whole tiles per CU does better with these: K = 9
+// from 640 tiles on, K = 12 even at 900), large ones quarter tiles held at two per CU (K = 12 bf16 2 700 tiles
+// even, 7 900 tiles 458 -> 422 us, 20 449 tiles 1 208 -> 1 104; K = 16 fp32 20 749 tiles 1 232 -> 1 169).
+inline KtShape fsgd_manyk_shape(int K, int64_t nt)
+{
+    if (nt >= 2560) return {4, 2};
+    return {nt <= (K < 12 ? 640 : 896) ? 4 : 1, 0};
+}
+
 template <typename T, bool DEVW>
 hipError_t launch_fused_sgd_t(const KtDeviceTables &tb, int64_t tile0, int64_t ntiles, const FsgdArgs &f, int K,
                               const KtWeights &w, const KtSgd &a, hipStream_t s)
 {
     const dim3 block(KT_BLOCK);
     if (K > 8) {
-        kt_fused_sgd_manyk_kernel<T, DEVW><<<dim3((unsigned)ntiles), block, 0, s>>>(tb.tiles + tile0, tb.b_elems, tb.t_off, f.local_ptrs, f.peer_ptrs,
-                                                                      f.param_ptrs, f.mom_ptrs, f.model_ptrs, K, tb.t_numel, a, AllWeights(w));
-        return hipGetLastError();
+        const KtShape sh = fsgd_manyk_shape(K, ntiles);
+        const unsigned lds = kt_shape_lds(sh, (unsigned)sizeof(FsgdLds));
+        return launch_in_chunks(tb.tiles + tile0, ntiles, sh.split, [&](const KtTile *tiles, dim3 grid) {
+#define KT_ARGS \
+    tiles, tb.b_elems, tb.t_off, f.local_ptrs, f.peer_ptrs, f.param_ptrs, f.mom_ptrs, f.model_ptrs, K, tb.t_numel, a, AllWeights(w)
+            if (sh.split == 1) kt_fused_sgd_manyk_kernel<T, DEVW, 1><<<grid, block, lds, s>>>(KT_ARGS);
+            else kt_fused_sgd_manyk_kernel<T, DEVW, 4><<<grid, block, lds, s>>>(KT_ARGS);
+#undef KT_ARGS
+        });
     }
     FsgdLaunch how = fsgd_launch<T>(K, ntiles);
     if (!kt_may_hold()) how.lds = 0;

@@ -83,16 +83,18 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_reduce_kernel(const KtTile *tiles
     }
 }
 
-// K > 8: peers in chunks, accumulators in registers across chunks (sum_in_chunks).
-template <typename T, bool DEVW>
+// K > 8: peers in chunks, accumulators in registers across chunks (whole tiles: sum_in_chunks; quarter tiles, SPLIT 4:
+// sum_rolling).
+template <typename T, bool DEVW, int SPLIT>
 __global__ __launch_bounds__(KT_BLOCK) void kt_reduce_manyk_kernel(const KtTile *tiles, const int64_t *b_elems,
                                                                    const void *const *peer_ptrs, void *const *out_ptrs,
                                                                    int K, KtWindow win, AllWeights wts)
 {
     constexpr int VE = Elem<T>::VE;
     constexpr int64_t TILE_ELEMS = (int64_t)KT_TILE_VECS * VE;
-    constexpr int VPT = KT_TILE_VECS / KT_BLOCK;
-    const KtTile tl = ld_tile(tiles + blockIdx.x);
+    constexpr int VPT = KT_TILE_VECS / KT_BLOCK / SPLIT;
+    const int part = SPLIT == 1 ? 0 : (int)(blockIdx.x % SPLIT);
+    const KtTile tl = ld_tile(tiles + blockIdx.x / SPLIT);
     const TileGeom g = tile_geom(tl, ld_table(b_elems + tl.bucket), TILE_ELEMS);
     const int tid = threadIdx.x;
     const void *const *pp = peer_ptrs + (int64_t)g.bucket * K;
@@ -101,18 +103,20 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_reduce_manyk_kernel(const KtTile 
     const int64_t n = g.end - g.start;
     const int nvec = (int)(n / VE);
     if (nvec == KT_TILE_VECS) {
+        const int v0 = part * VPT * KT_BLOCK + tid;
         Acc<T> acc[VPT];
-        sum_in_chunks<T, DEVW>(acc, peer, wts, K, tid);
+        if constexpr (VPT == 1) sum_rolling<T, DEVW>(acc[0], peer, wts, K, v0);
+        else sum_in_chunks<T, VPT, DEVW>(acc, peer, wts, K, v0);
         u32x4 res[VPT];
 #pragma unroll
         for (int u = 0; u < VPT; ++u) res[u] = acc[u].finish();
-        kt_wait_store_window(win);
+        if (SPLIT == 1) kt_wait_store_window(win);
 #pragma unroll
-        for (int u = 0; u < VPT; ++u) st_vec(reinterpret_cast<u32x4 *>(out) + u * KT_BLOCK + tid, res[u]);
+        for (int u = 0; u < VPT; ++u) st_vec(reinterpret_cast<u32x4 *>(out) + u * KT_BLOCK + v0, res[u]);
         return;
     }
     // the ragged last tile of a bucket: one vector at a time
-    for (int v = tid; v < nvec; v += KT_BLOCK) {
+    for (int v = part * KT_BLOCK + tid; v < nvec; v += SPLIT * KT_BLOCK) {
         Acc<T> acc;
         acc.first(ld_vec(peer(0) + (int64_t)v * VE), kt_weight<DEVW>(wts, 0));
 #pragma unroll 4
@@ -120,7 +124,7 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_reduce_manyk_kernel(const KtTile 
         st_vec(out + (int64_t)v * VE, acc.finish());
     }
     const int64_t e = (int64_t)nvec * VE + tid;
-    if (e < n) {
+    if (part == 0 && e < n) {
         float a = __fmul_rn(kt_weight<DEVW>(wts, 0), widen(ld_elem(peer(0) + e)));
         for (int k = 1; k < K; ++k) a = __fmaf_rn(kt_weight<DEVW>(wts, k), widen(ld_elem(peer(k) + e)), a);
         st_elem(out + e, narrow<T>(a));
@@ -158,6 +162,17 @@ template <typename T> KtShape reduce_shape(int K, int64_t nt)
     return {K >= 2 && kt_uneven(nt) ? 4 : 1, 0};
 }
 
+// 9 and more copies outside the store window.  Up to one tile per CU, and where whole tiles would leave a sixth of
+// two or three rounds idle, quarter tiles (K = 16: 29 tiles fp32 8.6 -> 5.6 us, 111 tiles bf16 14.2 -> 8.0, 577 tiles
+// bf16 28.9 -> 23.7; a workgroup's serial chunks and its own table reads are a quarter); even or 2-10 % slower
+// than whole tiles on full rounds.  From 2 560 tiles on quarter tiles held at two per CU (64 KB in flight; K = 12 fp32
+// 2 713 tiles even, 4 149 tiles 4 % faster, 20 749 tiles 769 -> 704 us; bf16 K = 16 7 896 tiles 378 -> 361).
+inline KtShape reduce_manyk_shape(int64_t nt)
+{
+    if (nt >= 2560) return {4, 2};
+    return {nt <= 256 || (nt <= 640 && kt_uneven(nt)) ? 4 : 1, 0};
+}
+
 template <typename T, int K, bool DEVW>
 hipError_t launch_reduce_k(const KtTile *tiles, const int64_t *b_elems, int64_t nt, const void *const *peers,
                            const KtWeights &w, void *const *outs, hipStream_t s)
@@ -189,8 +204,12 @@ hipError_t launch_reduce_t(const KtDeviceTables &tb, int64_t tile0, int64_t nt, 
 #undef KT_CASE
     }
     const KtWindow win = kt_store_window(K, nt, (KT_WINDOW_MIN_READS_REDUCE_MANYK + K - 1) / K, sizeof(T) == 4);
-    kt_reduce_manyk_kernel<T, DEVW><<<dim3((unsigned)nt), dim3(KT_BLOCK), 0, s>>>(tiles, tb.b_elems, peers, outs, K, win, AllWeights(w));
-    return hipGetLastError();
+    const KtShape sh = win.width ? KtShape{1, 0} : reduce_manyk_shape(nt);
+    const unsigned lds = kt_shape_lds(sh, 0);
+    return launch_in_chunks(tiles, nt, sh.split, [&](const KtTile *t, dim3 grid) {
+        if (sh.split == 1) kt_reduce_manyk_kernel<T, DEVW, 1><<<grid, dim3(KT_BLOCK), lds, s>>>(t, tb.b_elems, peers, outs, K, win, AllWeights(w));
+        else kt_reduce_manyk_kernel<T, DEVW, 4><<<grid, dim3(KT_BLOCK), lds, s>>>(t, tb.b_elems, peers, outs, K, win, AllWeights(w));
+    });
 }
 
 }  // namespace
