@@ -86,12 +86,12 @@ static long window_ns()
 
 bool kt_may_hold() { return window_ns() != 0; }
 
-KtWindow kt_store_window(int K, int64_t ntiles, int64_t min_tiles, bool late)
+KtWindow kt_store_window(KtPeriod kind, int64_t ntiles, int64_t min_tiles)
 {
     KtWindow off{0, 0};
     long ns = window_ns();
-    if (ns < 0) ns = late ? KT_WINDOW_LATE_NS : KT_WINDOW_NS;
-    if (ns == 0 || K < 5 || ntiles < min_tiles) return off;
+    if (ns < 0) ns = kind.ns;
+    if (ns == 0 || ntiles < min_tiles) return off;
     // rate of the device-wide constant clock in kHz, looked up once per device
     static std::atomic<int> rate_khz[64];
     int dev = -1;
@@ -105,7 +105,7 @@ KtWindow kt_store_window(int K, int64_t ntiles, int64_t min_tiles, bool late)
     }
     if (r <= 0) { (void)hipGetLastError(); return off; }
     const uint64_t period = (uint64_t)r * (uint64_t)ns / 1000000;     // ticks
-    const uint64_t width = period * (late ? KT_WINDOW_LATE_OPEN_PCT : KT_WINDOW_OPEN_PCT) / 100;
+    const uint64_t width = period * (uint64_t)kind.pct / 100;
     if (period < 64 || period > (1u << 30) || width < 1) return off;
     return KtWindow{(uint32_t)period, (uint32_t)width};
 }

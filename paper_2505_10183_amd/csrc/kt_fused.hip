@@ -286,7 +286,7 @@ hipError_t launch_fused_k(const KtDeviceTables &tb, const KtTile *tiles, int64_t
 #define KT_ARGS(TILES, WIN) TILES, tb.b_elems, tb.t_off, locals, peers, outs, scale, WIN, tb.t_numel, FewWeights(w)
     if constexpr (K >= 7) {
         const int64_t least = sizeof(T) == 2 ? 131072 : K == 8 ? KT_WINDOW_MIN_TILES_FUSED : KT_WINDOW_MIN_TILES_REDUCE;
-        const KtWindow win = kt_store_window(K, nt, least, sizeof(T) == 4 && K == 8);
+        const KtWindow win = kt_store_window(sizeof(T) == 4 && K == 8 ? KT_PERIOD_14 : KT_PERIOD_12, nt, least);
         if (win.width) {
             kt_fused_kernel<T, K, DEVW, 1, sizeof(T) == 2><<<dim3((unsigned)nt), block, 0, s>>>(KT_ARGS(tiles, win));
             return hipGetLastError();
@@ -315,7 +315,7 @@ hipError_t launch_fused_t(const KtDeviceTables &tb, int64_t tile0, int64_t nt, c
         KT_CASE(1) KT_CASE(2) KT_CASE(3) KT_CASE(4) KT_CASE(5) KT_CASE(6) KT_CASE(7) KT_CASE(8)
 #undef KT_CASE
     }
-    const KtWindow win = kt_store_window(K, nt, (KT_WINDOW_MIN_READS_FUSED + K - 1) / K, sizeof(T) == 4);
+    const KtWindow win = kt_manyk_window(sizeof(T) == 2, K, nt, KT_WINDOW_MIN_READS_FUSED);
     const KtShape sh = win.width ? KtShape{1, 0} : fused_manyk_shape(nt);
     const unsigned lds = kt_shape_lds(sh, (unsigned)sizeof(LdsTable));
     return launch_in_chunks(tiles, nt, sh.split, [&](const KtTile *t, dim3 grid) {

@@ -292,7 +292,7 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_manyk_kernel(const KtTi
                                                                       const void *const *peer_ptrs, void *const *param_ptrs,
                                                                       void *const *mom_ptrs, void *const *model_ptrs,
                                                                       int K, const int64_t *t_numel, KtSgd a_in,
-                                                                      AllWeights wts)
+                                                                      KtWindow win, AllWeights wts)
 {
     const FsgdArgs f{local_ptrs, peer_ptrs, param_ptrs, mom_ptrs, model_ptrs};
     constexpr int VE = Elem<T>::VE;
@@ -331,6 +331,7 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_manyk_kernel(const KtTi
         for (int u = 0; u < VPT; ++u) red[u] = acc[u].finish();
         if (SPLIT == 1) load_state();
         update_quads<VPT>(red, lds.red, pr, vr, a, T(0));
+        if (SPLIT == 1) kt_wait_store_window(win);
         st_quads<QPL, false>(p4, v4, t.m ? reinterpret_cast<u32x2 *>(t.m) + q0 : nullptr, pr, vr);
         return;
     }
@@ -377,17 +378,30 @@ inline KtShape fsgd_manyk_shape(int K, int64_t nt)
     return {nt <= (K < 12 ? 640 : 896) ? 4 : 1, 0};
 }
 
+// Large launches of many copies write little enough (fp32, K = 16: 10 % of the bytes) for the store window of the reduce
+// and the fused pass: fp32 from 11 copies on (20 000 tiles: K = 12 924 -> 883 us against held quarter tiles, K = 16
+// 1 157 -> 1 066, start 1 221; K = 10 710 us, 740 in the window), bf16 from 14 on with the longest period (K = 16
+// with the model copy 1 472 -> 1 411, K = 13 1 262 us against 1 248), smaller ones even or better without (7 900 tiles:
+// fp32 K = 12 333 us, 348 in the window, K = 16 429 against 411; bf16 K = 16 561 against 573).
+template <typename T> KtWindow fsgd_manyk_window(int K, int64_t nt)
+{
+    if (K < (sizeof(T) == 2 ? 14 : 11)) return KtWindow{0, 0};
+    const int64_t reads = sizeof(T) == 2 ? 196608 : 98304;
+    return kt_store_window(sizeof(T) == 2 ? KT_PERIOD_24 : kt_manyk_period(false, K + 2), nt, (reads + K - 1) / K);
+}
+
 template <typename T, bool DEVW>
 hipError_t launch_fused_sgd_t(const KtDeviceTables &tb, int64_t tile0, int64_t ntiles, const FsgdArgs &f, int K,
                               const KtWeights &w, const KtSgd &a, hipStream_t s)
 {
     const dim3 block(KT_BLOCK);
     if (K > 8) {
-        const KtShape sh = fsgd_manyk_shape(K, ntiles);
+        const KtWindow win = fsgd_manyk_window<T>(K, ntiles);
+        const KtShape sh = win.width ? KtShape{1, 0} : fsgd_manyk_shape(K, ntiles);
         const unsigned lds = kt_shape_lds(sh, (unsigned)sizeof(FsgdLds));
         return launch_in_chunks(tb.tiles + tile0, ntiles, sh.split, [&](const KtTile *tiles, dim3 grid) {
 #define KT_ARGS \
-    tiles, tb.b_elems, tb.t_off, f.local_ptrs, f.peer_ptrs, f.param_ptrs, f.mom_ptrs, f.model_ptrs, K, tb.t_numel, a, AllWeights(w)
+    tiles, tb.b_elems, tb.t_off, f.local_ptrs, f.peer_ptrs, f.param_ptrs, f.mom_ptrs, f.model_ptrs, K, tb.t_numel, a, win, AllWeights(w)
             if (sh.split == 1) kt_fused_sgd_manyk_kernel<T, DEVW, 1><<<grid, block, lds, s>>>(KT_ARGS);
             else kt_fused_sgd_manyk_kernel<T, DEVW, 4><<<grid, block, lds, s>>>(KT_ARGS);
 #undef KT_ARGS

@@ -82,28 +82,28 @@ struct KtWindow {
     uint32_t period;  // clock ticks
     uint32_t width;   // ticks at the start of each period in which stores are issued
 };
-// The window for a launch of `ntiles` tiles with K peers on the current device (host); none
-// below `min_tiles` tiles: a launch of a few generations of workgroups only pays for the waits
-// of its first and last one.
-// `late` takes the longer period and the narrower opening.
-KtWindow kt_store_window(int K, int64_t ntiles, int64_t min_tiles, bool late);
-// The period in nanoseconds (0 switches the window off; KT_STORE_WINDOW_NS sets one period for both
-// kinds) and the share of it, in per cent, in which stores are issued.  `late`: the fp32 reduce (K = 8, 65 536 tiles 1.59 -> 1.57 ms against 12 us /
-// 10 %; K = 16 3.03 -> 2.98 ms) and the fp32 fused pass of 8 and more copies (K = 8 1.60 -> 1.57 ms);
-// bf16 (reduce K = 12 2.19 ms, 2.32 late; fused 1.3B set 3.86 ms, 4.01 late) and the fused pass of
-// fewer copies stay with the shorter one.
-#ifndef KT_WINDOW_NS
-#define KT_WINDOW_NS 12000
-#endif
-#ifndef KT_WINDOW_OPEN_PCT
-#define KT_WINDOW_OPEN_PCT 10
-#endif
-#ifndef KT_WINDOW_LATE_NS
-#define KT_WINDOW_LATE_NS 14000
-#endif
-#ifndef KT_WINDOW_LATE_OPEN_PCT
-#define KT_WINDOW_LATE_OPEN_PCT 6
-#endif
+// The period in nanoseconds and the share of it, in per cent, in which stores are issued.  The best
+// period grows with the time that the resident workgroups need for their loads, hence with the copies:
+//   up to 8    12 us / 10 %; the fp32 reduce and the fp32 fused pass of 8 copies 14 us / 6 % (K = 8, 65 536 tiles 1.59 -> 1.57 ms and
+//              1.60 -> 1.57 ms against 12 us; bf16 fused 1.3B set 3.86 ms, 4.01 with 14 us)
+//   more, fp32 14 us up to 12 copies, 18 us up to 15, 24 us above (reduce and fused pass, 20 000 tiles: K = 12 692 us
+//              against 703 with 12 us, 698 with 18; K = 15 800 against 817 with 14; K = 16 889 against 923;
+//              K = 20 1 028 against 1 058); one-pass SGD, which reads p and v as well, as two copies more
+//   more, bf16 12 us / 10 % up to 13 copies, 14 us up to 16, 18 us above (chunks of 6 copies; fused pass K = 12
+//              664 us, 756 with 14; K = 15 793 against 818 with 12, 936 with 18; K = 20 1 037 against 1 054 with 14)
+struct KtPeriod {
+    int ns, pct;
+};
+constexpr KtPeriod KT_PERIOD_12{12000, 10}, KT_PERIOD_14{14000, 6}, KT_PERIOD_18{18000, 6}, KT_PERIOD_24{24000, 6};
+inline KtPeriod kt_manyk_period(bool half, int K)
+{
+    if (half) return K < 14 ? KT_PERIOD_12 : K <= 16 ? KT_PERIOD_14 : KT_PERIOD_18;
+    return K <= 12 ? KT_PERIOD_14 : K < 16 ? KT_PERIOD_18 : KT_PERIOD_24;
+}
+// The window for a launch of `ntiles` tiles on the current device (host); none below `min_tiles` tiles: a
+// launch of a few generations of workgroups only pays for the waits of its first and last one.
+// KT_STORE_WINDOW_NS sets one period for all (0: no windows).
+KtWindow kt_store_window(KtPeriod period, int64_t ntiles, int64_t min_tiles);
 // Smallest launches that use the window, in tiles read (tiles x copies) or, for the reduce of up to
 // 8 copies, in tiles.  The fused pass of more copies gains from 65 536 tiles read on
 // (K = 16: 8 192 tiles 399 -> 371 us, 4 096 tiles 212 -> 199 us), the fp32 one of 8 is even with quarter
@@ -124,6 +124,15 @@ KtWindow kt_store_window(int K, int64_t ntiles, int64_t min_tiles, bool late);
 #ifndef KT_WINDOW_MIN_READS_REDUCE_MANYK
 #define KT_WINDOW_MIN_READS_REDUCE_MANYK 262144
 #endif
+
+// The window of the reduce and the fused pass of 9 and more copies, from `min_reads` tiles read on.  9 copies (bf16: and
+// 10) do better with held quarter tiles (20 000 tiles, K = 9: bf16 fused pass 527 us against 616, reduce 520 against 554; fp32
+// 528 against 539, 508 against 550).
+inline KtWindow kt_manyk_window(bool half, int K, int64_t ntiles, int64_t min_reads)
+{
+    if (K < (half ? 11 : 10)) return KtWindow{0, 0};
+    return kt_store_window(kt_manyk_period(half, K), ntiles, (min_reads + K - 1) / K);
+}
 
 // LDS to ask for beyond a kernel's own `own` bytes, so that `wgs` workgroups share a CU: the smallest
 // request of which one more does not fit.  A CU has 160 KiB and gives it out in granules of 1 280 bytes

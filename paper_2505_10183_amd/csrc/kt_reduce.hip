@@ -179,7 +179,7 @@ hipError_t launch_reduce_k(const KtTile *tiles, const int64_t *b_elems, int64_t 
 {
     const dim3 block(KT_BLOCK);
     if constexpr (K >= 7) {
-        const KtWindow win = kt_store_window(K, nt, KT_WINDOW_MIN_TILES_REDUCE, sizeof(T) == 4);
+        const KtWindow win = kt_store_window(sizeof(T) == 4 ? KT_PERIOD_14 : KT_PERIOD_12, nt, KT_WINDOW_MIN_TILES_REDUCE);
         if (win.width) {
             kt_reduce_kernel<T, K, DEVW, 1, sizeof(T) == 2><<<dim3((unsigned)nt), block, 0, s>>>(tiles, b_elems, peers, outs, win, FewWeights(w));
             return hipGetLastError();
@@ -203,7 +203,7 @@ hipError_t launch_reduce_t(const KtDeviceTables &tb, int64_t tile0, int64_t nt, 
         KT_CASE(1) KT_CASE(2) KT_CASE(3) KT_CASE(4) KT_CASE(5) KT_CASE(6) KT_CASE(7) KT_CASE(8)
 #undef KT_CASE
     }
-    const KtWindow win = kt_store_window(K, nt, (KT_WINDOW_MIN_READS_REDUCE_MANYK + K - 1) / K, sizeof(T) == 4);
+    const KtWindow win = kt_manyk_window(sizeof(T) == 2, K, nt, KT_WINDOW_MIN_READS_REDUCE_MANYK);
     const KtShape sh = win.width ? KtShape{1, 0} : reduce_manyk_shape(nt);
     const unsigned lds = kt_shape_lds(sh, 0);
     return launch_in_chunks(tiles, nt, sh.split, [&](const KtTile *t, dim3 grid) {

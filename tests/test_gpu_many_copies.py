@@ -1,4 +1,4 @@
-"""9 and more copies: quarter tiles and whole ones on both sides of the limits that choose them, every number
+"""9 and more copies: quarter tiles, whole ones and store windows at the limits that choose them, every number
 of copies left for the last chunk, device-resident weights; every kernel, every element, odd tensor sizes."""
 import sys
 
@@ -26,6 +26,8 @@ def announce(request):
     ("f32", 255, 9, 0, False), ("bf16", 258, 16, 36, True), ("f32", 600, 12, 4, True), ("bf16", 700, 11, 0, False),
     ("f32", 896, 12, 60, False), ("f32", 1152, 10, 4, True), ("bf16", 1152, 13, 0, False),
     ("f32", 2560, 16, 4, True), ("bf16", 2560, 9, 20, False),
+    # inside the store windows: the fused pass and the one-pass SGD, with 24 copies the reduce as well
+    ("f32", 8937, 11, 0, False), ("bf16", 12288, 16, 4, True), ("f32", 10923, 24, 36, True), ("bf16", 10923, 24, 0, False),
 ])
 def test_tiles_of_many_copies(dtype, tiles, K, shift, dense):
     n = -(-tiles * (16384 // (4 if dtype == "f32" else 2)) // 24) | 1
