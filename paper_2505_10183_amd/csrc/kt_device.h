@@ -257,6 +257,43 @@ struct GlobalView {
     const KT_GLOBAL uintptr_t *ptr2;
 };
 
+// The table slice of a tile with at most KT_REG_TENSORS tensors (where a large tensor ends and the next begins, with a
+// bias or a norm between them) in scalar registers: one more batch of scalar loads behind the tile record's,
+// where staging is a vector load, an LDS write, a barrier and a search ahead of the data loads.  Entries from nt on
+// repeat the last.  SGD on unpack of bf16 gradients only (kt_sgd.hip): pack, unpack and the fused passes gain 1 % at
+// most, small launches of pack lose 10 %.
+#define KT_REG_TENSORS 4
+template <typename P> struct Regs {
+    P a, b, c, d;
+    __device__ __forceinline__ P operator[](int i) const
+    {
+        // all four read first: a choice between their addresses would put them in scratch memory
+        const P p = a, q = b, r = c, s = d;
+        const P lo = i >= 1 ? q : p, hi = i >= 3 ? s : r;
+        return i >= 2 ? hi : lo;
+    }
+};
+struct RegView {
+    Regs<int64_t> off, numel;
+    Regs<uintptr_t> ptr, ptr2;
+};
+template <typename P, typename Q> __device__ __forceinline__ Regs<P> ld_regs(const Q *table, int t0, int nt)
+{
+    const Q *t = table + t0;
+    return Regs<P>{(P)ld_table(t), (P)ld_table(t + (nt > 1 ? 1 : 0)), (P)ld_table(t + (nt > 2 ? 2 : nt - 1)), (P)ld_table(t + nt - 1)};
+}
+__device__ __forceinline__ RegView reg_view(const int64_t *t_off, const int64_t *t_numel, const void *const *first,
+                                            const void *const *second, int t0, int nt)
+{
+    return RegView{ld_regs<int64_t>(t_off, t0, nt), ld_regs<int64_t>(t_numel, t0, nt), ld_regs<uintptr_t>(first, t0, nt),
+                   ld_regs<uintptr_t>(second, t0, nt)};
+}
+__device__ __forceinline__ int find_owner_v(const RegView &tv, int nt, int64_t e)
+{
+    const int n = (tv.off.a <= e) + (tv.off.b <= e) + (tv.off.c <= e) + (tv.off.d <= e);
+    return (n < nt ? n : nt) - 1;
+}
+
 template <typename V> __device__ __forceinline__ int find_owner_v(const V &tv, int nt, int64_t e)
 {
     int lo = 0, hi = nt;

@@ -11,23 +11,28 @@ namespace {
 // and 78 % (fp32) with two quads.  Every tensor may lie at any element address: the
 // quads of a full tile are laid out from a 64-byte boundary of the parameters
 // (rot_vec), which the system-scope stores of the bf16 form need.  45.1 M bf16
-// elements in 600 tensors of odd sizes, with the model copy: unpack 200 -> 178 us
+// elements in 600 tensors of odd sizes, with the model copy: unpack 200 -> 178 us.
+// bf16: a full tile whose parameters start elsewhere in their 64 bytes takes non-temporal stores although all of its
+// stores but two fill whole pieces (the same set, dense layout: 180 -> 149 us without the model copy), mixed tiles system-scope ones
+// wherever they lie (600 tensors of 75 208 elements 146 -> 139 us).
 template <typename T> struct SgdShape {
     static constexpr int SPLIT = (int)(KT_TILE_VECS * Elem<T>::VE / 4 / KT_BLOCK);   // workgroups per tile
     static constexpr int PBYTES = KT_TILE_VECS * Elem<T>::VE * 4;                     // bytes of p in a tile
 };
 
 // The quads of a lane's turn: parameters p, momentum v, model copy m (bf16, or NULL).
-template <typename T, bool MASTER>
+// MASTER: 0 no model copy, 1 non-temporal stores of it, 2 system-scope ones.
+template <typename T, int MASTER>
 __device__ __forceinline__ void sgd_store(float *p, float *v, uint16_t *m, u32x4 pr, u32x4 vr, bool p64, bool v64)
 {
-    // with bf16 gradients 44 % of the bytes are written: system-scope stores where they fill whole 64-byte pieces
+    // with bf16 gradients 44 % of the bytes are written: system-scope stores where the tile starts on 64 bytes and in
+    // mixed tiles
     if (sizeof(T) == 2 && p64) st_vec_copy<true>(p, pr); else st_vec(p, pr);
     if (sizeof(T) == 2 && v64) st_vec_copy<true>(v, vr); else st_vec(v, vr);
-    if (MASTER) st_model_quad<true>(m, pr);
+    if (MASTER) st_model_quad<MASTER == 2>(m, pr);
 }
 
-template <typename T, bool MASTER>
+template <typename T, int MASTER>
 __device__ __forceinline__ void sgd_one(const T *g, float *p, float *v, uint16_t *m, const KtSgd &a)
 {
     float pv = ld_elem(p), vv = ld_elem(a.first ? p : v);
@@ -38,39 +43,52 @@ __device__ __forceinline__ void sgd_one(const T *g, float *p, float *v, uint16_t
 }
 
 // Mixed tile: tv.ptr = parameters, tv.ptr2 = momentum of the owning tensor; model (MASTER only) =
-// the model-parameter pointers of the tile's tensors, from the global pointer table.  Quads wholly
-// inside one tensor one per lane, the elements of the others one per lane (each_cut_elem).
-template <typename T, bool MASTER, typename V>
+// the model-parameter pointers of the tile's tensors, in registers or in the global pointer table.  Quads wholly
+// inside one tensor one per lane, the elements of the others one per lane (each_cut_elem): with bf16
+// gradients between the quads' loads and their stores, which are system-scope at any address here and waited for.
+template <typename T, int MASTER, typename V, typename M>
 __device__ __forceinline__ void sgd_mixed(const V &tv, int nt, const TileGeom &g, const T *src, const KtSgd &a, int part,
-                                          void *const *model)
+                                          const M &model)
 {
     const int len = (int)(g.end - g.start);
     const int q = part * KT_BLOCK + threadIdx.x;
+    auto cut = [&] {
+        each_cut_elem<4>(tv, nt, g.start, len, q, SgdShape<T>::SPLIT * KT_BLOCK, [&](int i, int64_t r, int e) {
+            sgd_one<T, MASTER>(src + g.start + e, reinterpret_cast<float *>(tv.ptr[i]) + r, reinterpret_cast<float *>(tv.ptr2[i]) + r,
+                               MASTER ? reinterpret_cast<uint16_t *>(model[i]) + r : nullptr, a);
+        });
+    };
+    float *p = nullptr, *v = nullptr;
+    uint16_t *m = nullptr;
+    Quad<T> gq;
+    u32x4 pr, vr;
+    auto update = [&] {
+        sgd_quad(gq, pr, vr, a);
+        sgd_store<T, MASTER>(p, v, m, pr, vr, true, true);
+    };
     if (q < len / 4) {
         const int64_t e0 = g.start + 4 * (int64_t)q;
         const int i = find_owner_v(tv, nt, e0);
         const int64_t r = i >= 0 ? e0 - tv.off[i] : -1;
         if (r >= 0 && r + 4 <= tv.numel[i]) {
-            float *p = reinterpret_cast<float *>(tv.ptr[i]) + r, *v = reinterpret_cast<float *>(tv.ptr2[i]) + r;
-            const Quad<T> gq = ld_quad(reinterpret_cast<const Quad<T> *>(src + e0));
-            u32x4 pr = ld_vec(p), vr = ld_vec(a.first ? p : v);
-            sgd_quad(gq, pr, vr, a);
-            const int lane = (threadIdx.x & 3) * 4;      // the lane that starts the 64-byte piece
-            sgd_store<T, MASTER>(p, v, MASTER ? reinterpret_cast<uint16_t *>(model[i]) + r : nullptr, pr, vr,
-                                 off64(p - lane) == 0, off64(v - lane) == 0);
+            p = reinterpret_cast<float *>(tv.ptr[i]) + r;
+            v = reinterpret_cast<float *>(tv.ptr2[i]) + r;
+            if (MASTER) m = reinterpret_cast<uint16_t *>(model[i]) + r;
+            gq = ld_quad(reinterpret_cast<const Quad<T> *>(src + e0));
+            pr = ld_vec(p);
+            vr = ld_vec(a.first ? p : v);
+            if (sizeof(T) == 4) update();
         }
     }
-    each_cut_elem<4>(tv, nt, g.start, len, q, SgdShape<T>::SPLIT * KT_BLOCK, [&](int i, int64_t r, int e) {
-        sgd_one<T, MASTER>(src + g.start + e, reinterpret_cast<float *>(tv.ptr[i]) + r, reinterpret_cast<float *>(tv.ptr2[i]) + r,
-                           MASTER ? reinterpret_cast<uint16_t *>(model[i]) + r : nullptr, a);
-    });
+    cut();
+    if (sizeof(T) == 2 && p) update();
 }
 
 // DEVS: the four optimizer scalars come from device memory (uniform scalar loads, issued with
 // the tile-table load) instead of the kernel-argument block, so that a recorded launch follows
 // a learning-rate schedule.  A separate instantiation: launches with scalars by value run the
 // code they always ran.
-template <typename T, bool MASTER, bool DEVS>
+template <typename T, int MASTER, bool DEVS>
 __global__ __launch_bounds__(KT_BLOCK) void kt_unpack_sgd_kernel(const KtTile *tiles, const int64_t *b_elems,
                                                                  const int64_t *t_offs, const void *const *bucket_ptrs,
                                                                  void *const *param_ptrs, void *const *mom_ptrs,
@@ -119,7 +137,7 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_unpack_sgd_kernel(const KtTile *t
                 const Quad<T> gq = ld_quad(reinterpret_cast<const Quad<T> *>(src + e));
                 u32x4 pr = ld_vec(p + e), vr = ld_vec((a.first ? p : v) + e);
                 sgd_quad(gq, pr, vr, a);
-                sgd_store<T, MASTER>(p + e, v + e, MASTER ? m + e : nullptr, pr, vr, true, off64(v) == o);
+                sgd_store<T, MASTER>(p + e, v + e, MASTER ? m + e : nullptr, pr, vr, o == 0, o == 0 && off64(v) == 0);
             }
             if ((o & 15) && part == 0 && tid < 4) {
                 const int e = edge_elem<PBYTES>(tid, 4, o) / 4;
@@ -142,7 +160,10 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_unpack_sgd_kernel(const KtTile *t
     const void *const *pp = reinterpret_cast<const void *const *>(param_ptrs);
     const void *const *mp = reinterpret_cast<const void *const *>(mom_ptrs);
     void *const *model = MASTER ? model_ptrs + tl.t0 : nullptr;
-    if (tl.nt <= KT_LDS_TENSORS) {
+    if (sizeof(T) == 2 && tl.nt <= KT_REG_TENSORS) {
+        const Regs<uintptr_t> mr = ld_regs<uintptr_t>(MASTER ? model_ptrs : mom_ptrs, tl.t0, tl.nt);
+        sgd_mixed<T, MASTER>(reg_view(t_offs, t_numel, pp, mp, tl.t0, tl.nt), tl.nt, g, src, a, part, mr);
+    } else if (tl.nt <= KT_LDS_TENSORS) {
         const LdsView tv = stage_lds(lds, t_offs, t_numel, pp, mp, tl.t0, tl.nt);
         sgd_mixed<T, MASTER>(tv, tl.nt, g, src, a, part, model);
     } else {
@@ -177,11 +198,15 @@ int kt_launch_unpack_sgd(const KtDeviceTables &tb, kt_dtype dt, int64_t tile0, i
     kt_unpack_sgd_kernel<TT, MM, DD><<<grid, block, lds, s>>>(tiles, tb.b_elems, tb.t_off, d_bucket_ptrs, d_param_ptrs, \
                                                               d_mom_ptrs, d_model_ptrs, a, tb.t_numel)
         if (dt == KT_F32) {
-            if (d_model_ptrs) { if (a.dev) KT_SGD_LAUNCH(float, true, true); else KT_SGD_LAUNCH(float, true, false); }
-            else { if (a.dev) KT_SGD_LAUNCH(float, false, true); else KT_SGD_LAUNCH(float, false, false); }
+            if (d_model_ptrs) { if (a.dev) KT_SGD_LAUNCH(float, 2, true); else KT_SGD_LAUNCH(float, 2, false); }
+            else { if (a.dev) KT_SGD_LAUNCH(float, 0, true); else KT_SGD_LAUNCH(float, 0, false); }
         } else {
-            if (d_model_ptrs) { if (a.dev) KT_SGD_LAUNCH(uint16_t, true, true); else KT_SGD_LAUNCH(uint16_t, true, false); }
-            else { if (a.dev) KT_SGD_LAUNCH(uint16_t, false, true); else KT_SGD_LAUNCH(uint16_t, false, false); }
+            // model copy of 2 bytes per element: half pieces wherever p starts on an odd 64 bytes.  Non-temporal (19 837 tiles
+            // 517 -> 506 us, 59 899 tiles 1 530 -> 1 507, odd tensors 15 770 tiles 475 -> 438) below 98 304 tiles (120 061 tiles 1 %
+            // slower); fp32 keeps system scope (20 000 tiles 300 -> 295 us without, odd tensors 11 007 tiles 160 -> 168)
+            if (d_model_ptrs && ntiles >= 98304) { if (a.dev) KT_SGD_LAUNCH(uint16_t, 2, true); else KT_SGD_LAUNCH(uint16_t, 2, false); }
+            else if (d_model_ptrs) { if (a.dev) KT_SGD_LAUNCH(uint16_t, 1, true); else KT_SGD_LAUNCH(uint16_t, 1, false); }
+            else { if (a.dev) KT_SGD_LAUNCH(uint16_t, 0, true); else KT_SGD_LAUNCH(uint16_t, 0, false); }
         }
 #undef KT_SGD_LAUNCH
     });

@@ -65,7 +65,7 @@ __device__ __forceinline__ void sgd_quad(const Quad<uint16_t> &g, u32x4 &p, u32x
 
 // Mixed precision: the four updated binary32 master values of a quad are also
 // written, rounded to nearest-even, as four bf16 model parameters (8 bytes).
-// SYS: system-scope store (SGD on unpack: +1-2 points of 8 TB/s), else non-temporal.
+// SYS: system-scope store, else non-temporal.
 template <bool SYS = false> __device__ __forceinline__ void st_model_quad(void *m, u32x4 p)
 {
     u32x2 o;
