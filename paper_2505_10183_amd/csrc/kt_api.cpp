@@ -112,6 +112,24 @@ KtWindow kt_store_window(KtPeriod kind, int64_t ntiles, int64_t min_tiles)
 
 // ---- plan object -----------------------------------------------------------
 
+// What tells two streams apart: the handle, and for hipStreamPerThread, which names another stream in
+// every host thread, the thread.
+struct StreamKey {
+    hipStream_t handle = nullptr;
+    uint64_t id = 0;
+    bool operator==(const StreamKey &o) const { return handle == o.handle && id == o.id; }
+    bool operator!=(const StreamKey &o) const { return !(*this == o); }
+};
+
+static uint64_t thread_id()
+{
+    static std::atomic<uint64_t> next{1};
+    static thread_local const uint64_t mine = next.fetch_add(1);      // never given again
+    return mine;
+}
+
+static StreamKey key_of(hipStream_t s) { return StreamKey{s, s == hipStreamPerThread ? thread_id() : 0}; }
+
 // A per-call table of device pointers (tensor/bucket or peer/out pointers)
 // lives in a small ring of device buffers.  A call whose pointers equal a
 // resident table reuses it, so a steady training loop uploads nothing.
@@ -121,8 +139,8 @@ struct PtrSlot {
     size_t cap = 0;               // capacity in entries
     size_t n = 0;                 // entries in use
     hipEvent_t uploaded = nullptr;
-    hipStream_t upload_stream = nullptr;
-    hipStream_t use_stream = nullptr;   // stream of the last launch that read the table
+    StreamKey upload_stream;
+    StreamKey use_stream;               // stream of the last launch that read the table
     uint64_t last_seq = 0;              // plan-wide sequence number of that launch
     uint64_t upload_seq = 0;            // launches issued through the plan before the upload
     bool multi_stream = false;
@@ -315,7 +333,9 @@ static hipError_t wait_retired(kt_plan *p, const PtrSlot *v)
         for (const PtrSlot &s : p->slots)
             if (s.valid && s.upload_stream == v->use_stream && s.upload_seq >= v->last_seq && (!best || s.upload_seq < best->upload_seq))
                 best = &s;
-        e = best ? hipEventSynchronize(best->uploaded) : hipStreamSynchronize(v->use_stream);
+        if (best) e = hipEventSynchronize(best->uploaded);
+        else if (v->use_stream == key_of(v->use_stream.handle)) e = hipStreamSynchronize(v->use_stream.handle);
+        else return hipDeviceSynchronize();        // another thread's stream: no handle of this thread names it
     }
     if (e != hipSuccess) {
         // e.g. the caller destroyed the stream of that launch: the targeted wait is
@@ -332,6 +352,7 @@ static kt_status stage_pointers(kt_plan *p, const uint64_t *vals, size_t n, hipS
 {
     hipError_t e;
     const bool cap = capturing(stream);
+    const StreamKey key = key_of(stream);
     for (PtrSlot *g : p->graph_tables) {
         if (g->n == n && memcmp(g->pinned, vals, n * 8) == 0) {
             // its upload was waited for when it was moved here
@@ -356,7 +377,7 @@ static kt_status stage_pointers(kt_plan *p, const uint64_t *vals, size_t n, hipS
             *slot_out = g;
             return KT_OK;
         }
-        if (hit->upload_stream != stream) {
+        if (hit->upload_stream != key) {
             e = hipStreamWaitEvent(stream, hit->uploaded, 0);
             if (e != hipSuccess) return hip_fail("hipStreamWaitEvent", e);
         }
@@ -376,7 +397,7 @@ static kt_status stage_pointers(kt_plan *p, const uint64_t *vals, size_t n, hipS
     if (victim->valid) {
         // the upload must have left the staging copy; the launches that read the table must have
         // finished, or stand before the new upload on its stream
-        const bool ordered = victim->cap >= n && victim->use_stream == stream && !victim->multi_stream;
+        const bool ordered = victim->cap >= n && victim->use_stream == key && !victim->multi_stream;
         e = ordered ? hipEventSynchronize(victim->uploaded) : wait_retired(p, victim);
         if (e != hipSuccess) return hip_fail("waiting for a pointer table to retire", e);
     } else if (victim->dev) {        // an upload into it failed: who still reads it is not known
@@ -405,9 +426,9 @@ static kt_status stage_pointers(kt_plan *p, const uint64_t *vals, size_t n, hipS
     e = hipEventRecord(victim->uploaded, stream);
     if (e != hipSuccess) return hip_fail("hipEventRecord", e);
     victim->n = n;
-    victim->upload_stream = stream;
+    victim->upload_stream = key;
     victim->upload_seq = p->seq;
-    victim->use_stream = stream;
+    victim->use_stream = key;
     victim->last_seq = 0;
     victim->multi_stream = false;
     victim->valid = true;
@@ -420,9 +441,9 @@ static kt_status stage_pointers(kt_plan *p, const uint64_t *vals, size_t n, hipS
 static kt_status mark_used(kt_plan *p, PtrSlot *s, hipStream_t stream)
 {
     if (s->in_graph) return KT_OK;   // the table stays resident until the plan is destroyed
-    // (the per-thread handle names another stream in every thread)
-    if ((s->last_seq > 0 && s->use_stream != stream) || stream == hipStreamPerThread) s->multi_stream = true;
-    s->use_stream = stream;
+    const StreamKey key = key_of(stream);
+    if (s->last_seq > 0 && s->use_stream != key) s->multi_stream = true;
+    s->use_stream = key;
     s->last_seq = ++p->seq;
     return KT_OK;
 }

@@ -1,0 +1,88 @@
+// The library's pointer tables on streams, threads and destroyed streams (fake_hip.h).  usage: pointer_tables CASE
+#include <thread>
+
+#include "fake_hip.h"
+
+static const int KEPT = 8;          // tables that a plan keeps
+static const int T = 3;
+
+#define CHECK(x)                                                        \
+    do {                                                                \
+        if (!(x)) { printf("line %d: %s\n", __LINE__, #x); exit(1); }   \
+    } while (0)
+
+struct Plan {
+    kt_plan *p = nullptr;
+    Plan()
+    {
+        const int64_t numel[T] = {40, 7, 100};
+        CHECK(kt_plan_create(numel, T, KT_F32, 0, 16, &p) == KT_OK);
+    }
+    ~Plan() { CHECK(kt_plan_destroy(p) == KT_OK); }
+    // one call with the pointers of set `set`
+    kt_status pack(int set, hipStream_t s)
+    {
+        const void *t[T];
+        void *b = reinterpret_cast<void *>(0x900000000ull + (uint64_t)set * 4096);
+        fake::want.assign(T + 1, reinterpret_cast<uintptr_t>(b));
+        for (int i = 0; i < T; ++i) {
+            t[i] = reinterpret_cast<const void *>(0x100000000ull + (uint64_t)set * 4096 + (uint64_t)i * 512);
+            fake::want[(size_t)i] = reinterpret_cast<uintptr_t>(t[i]);
+        }
+        return kt_bucket_pack(p, KT_ALL_BUCKETS, t, &b, s);
+    }
+    void call(int set, hipStream_t s) { CHECK(pack(set, s) == KT_OK); }
+};
+template <typename F> static void in_thread(F f) { std::thread(f).join(); }
+static void end(int launches)
+{
+    fake::finish();
+    CHECK(fake::launched == launches);
+    CHECK(fake::wrong == 0);
+}
+
+// hipStreamPerThread names another stream in every thread: a table that one thread's stream is still uploading is
+// not read by another's
+static void per_thread_hit()
+{
+    Plan p;
+    fake::of(hipStreamPerThread)->held = true;
+    p.call(0, hipStreamPerThread);
+    in_thread([&] { p.call(0, hipStreamPerThread); });
+    end(2);
+}
+static void per_thread_eviction()
+{
+    Plan p;
+    fake::of(hipStreamPerThread)->held = true;
+    for (int r = 0; r < KEPT; ++r) p.call(r, hipStreamPerThread);
+    in_thread([&] { for (int r = 0; r < 2 * KEPT; ++r) p.call(100 + r, hipStreamPerThread); });
+    for (int r = 0; r < KEPT; ++r) p.call(r, hipStreamPerThread);
+    end(4 * KEPT);
+}
+// one thread on its per-thread stream is one stream: new pointers on every call wait for no device
+static void per_thread_new_pointers()
+{
+    Plan p;
+    fake::of(hipStreamPerThread)->held = true;
+    for (int r = 0; r < 8 * KEPT; ++r) p.call(r, hipStreamPerThread);
+    CHECK(fake::device_syncs == 0 && fake::stream_syncs == 0);
+    end(8 * KEPT);
+}
+
+int main(int argc, char **argv)
+{
+    const struct { const char *name; void (*run)(); } cases[] = {
+        {"per_thread_hit", per_thread_hit},
+        {"per_thread_eviction", per_thread_eviction},
+        {"per_thread_new_pointers", per_thread_new_pointers},
+    };
+    for (const auto &c : cases)
+        if (argc > 1 && strcmp(argv[1], c.name) == 0) {
+            c.run();
+            printf("ok\n");
+            return 0;
+        }
+    printf("no such case\n");
+    return 2;
+}

@@ -1,6 +1,7 @@
 """Pointer tables overwritten while the launches that read them are still queued: more pointer sets than
 the plan keeps, enqueued without a wait behind work that keeps the GPU busy; every result is checked."""
 import sys
+import threading
 
 import pytest
 import torch
@@ -64,3 +65,40 @@ def test_a_table_that_grows_while_its_launch_is_queued():
     torch.cuda.synchronize()
     for K, o in outs:
         assert all(bool((t == K * (K + 1) / 2).all()) for t in o), K
+
+
+PER_THREAD = 2        # hipStreamPerThread: one handle, another stream in every thread
+
+
+def test_equal_pointers_on_two_per_thread_streams():
+    """Two threads call with the same pointers and with their own, each on its per-thread stream, the first
+    behind work that keeps the GPU busy."""
+    numels = [3, 4099, 17, 70001, 5]
+    plan = kt.Plan(numels, "f32", 0, 16)
+    n = plan.bucket_elems()[0]
+    offs = [plan.tensor_info(t)[1] for t in range(len(numels))]
+    sets = 3 * KEPT
+    grads = [[torch.full((m,), float(100 * r + t), device=DEV) for t, m in enumerate(numels)] for r in range(2 * sets)]
+    out = [torch.full((n,), -1.0, device=DEV) for _ in range(2 * sets)]
+    both = [torch.full((n,), -1.0, device=DEV) for _ in range(KEPT // 2)]
+    large = kt.Plan([1 << 25], "f32", 0, 16)
+    a, b = torch.zeros(1 << 25, device=DEV), torch.zeros(large.bucket_elems()[0], device=DEV)
+    torch.cuda.synchronize()
+
+    def calls(which):
+        for r in range(KEPT // 2):
+            plan.kt_bucket_pack(-1, grads[r], [both[r]], stream=PER_THREAD)
+        for r in range(which * sets, (which + 1) * sets):
+            plan.kt_bucket_pack(-1, grads[r], [out[r]], stream=PER_THREAD)
+            plan.kt_bucket_pack(-1, grads[r % (KEPT // 2)], [both[r % (KEPT // 2)]], stream=PER_THREAD)
+
+    for _ in range(100):
+        large.kt_bucket_pack(-1, [a], [b], stream=PER_THREAD)
+    calls(0)
+    other = threading.Thread(target=calls, args=(1,))
+    other.start()
+    other.join()
+    torch.cuda.synchronize()
+    for r, o in [*enumerate(out), *enumerate(both)]:
+        for t, m in enumerate(numels):
+            assert bool((o[offs[t]:offs[t] + m] == float(100 * r + t)).all()), (r, t)

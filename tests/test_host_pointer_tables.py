@@ -1,0 +1,34 @@
+"""The pointer tables of a plan on several streams and threads, on the CPU: kt_api.cpp built against a stand-in
+for the HIP runtime (host/fake_hip.h) that runs whatever is not ordered in the worst order, with
+AddressSanitizer and UBSan."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2505_10183_amd", "csrc")
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir("/opt/rocm/include/hip"),
+                                reason="needs g++ and the HIP headers")
+
+
+@pytest.fixture(scope="module")
+def exe(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("tables") / "pointer_tables")
+    subprocess.check_call(
+        ["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-static-libasan",
+         "-static-libubsan", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+         os.path.join(ROOT, "tests", "host", "pointer_tables.cpp"), os.path.join(CSRC, "kt_api.cpp"),
+         os.path.join(CSRC, "kt_plan.cpp"), "-rdynamic", "-ldl", "-pthread", "-o", out])
+    return out
+
+
+def run(exe, case):
+    got = subprocess.run([exe, case], capture_output=True, text=True, timeout=120)
+    assert got.returncode == 0 and got.stdout == "ok\n", got.stdout + got.stderr
+
+
+@pytest.mark.parametrize("case", ["per_thread_hit", "per_thread_eviction", "per_thread_new_pointers"])
+def test_the_per_thread_stream(exe, case):
+    run(exe, case)
