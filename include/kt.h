@@ -67,7 +67,10 @@
  *    Results do not depend on it.
  *  - Streams passed to device calls should outlive the plan.  If the stream of
  *    an earlier call has been destroyed, the library waits for the whole
- *    device instead of that stream when it recycles a pointer table.
+ *    device instead of that stream when it recycles a pointer table.  It knows
+ *    a new stream at the same handle from the old one where the HIP runtime
+ *    has hipStreamGetId (7.1); before, it relies on hipStreamDestroy to
+ *    return only when the stream's work is done, as measured on 7.0.
  */
 #ifndef KT_H
 #define KT_H

@@ -1,5 +1,6 @@
 // C ABI of the library: plan objects, argument checks, per-call pointer tables
 // and kernel launches.  Host code; the kernels live in the .hip files beside it.
+#include <dlfcn.h>
 #include <hip/hip_runtime_api.h>
 
 #include <atomic>
@@ -112,13 +113,18 @@ KtWindow kt_store_window(KtPeriod kind, int64_t ntiles, int64_t min_tiles)
 
 // ---- plan object -----------------------------------------------------------
 
-// What tells two streams apart: the handle, and for hipStreamPerThread, which names another stream in
-// every host thread, the thread.
+// What tells two streams apart: the handle; for hipStreamPerThread, which names another stream in every host
+// thread, the thread; and the runtime's id of the stream, because the handle of a destroyed stream is given to the
+// next one created (three times in three) and HIP leaves it open whether destroying a stream waits for what is
+// queued on it.  Runtimes before 7.1 have no ids; there equal handles count as one stream, which holds as
+// long as hipStreamDestroy drains: with 50 ms of work queued it returned after 50.1 ms, the work
+// done, on 7.0 and on 7.2.
 struct StreamKey {
     hipStream_t handle = nullptr;
     uint64_t id = 0;
-    bool operator==(const StreamKey &o) const { return handle == o.handle && id == o.id; }
+    bool operator==(const StreamKey &o) const { return handle == o.handle && id == o.id && id != GONE; }
     bool operator!=(const StreamKey &o) const { return !(*this == o); }
+    static const uint64_t GONE = ~0ull;      // no such stream (any more): unlike every other
 };
 
 static uint64_t thread_id()
@@ -128,7 +134,17 @@ static uint64_t thread_id()
     return mine;
 }
 
-static StreamKey key_of(hipStream_t s) { return StreamKey{s, s == hipStreamPerThread ? thread_id() : 0}; }
+static StreamKey key_of(hipStream_t s)
+{
+    typedef hipError_t (*IdFn)(hipStream_t, unsigned long long *);
+    static const IdFn get_id = reinterpret_cast<IdFn>(dlsym(RTLD_DEFAULT, "hipStreamGetId"));
+    if (s == hipStreamPerThread) return StreamKey{s, thread_id()};
+    if (!s || s == hipStreamLegacy || !get_id) return StreamKey{s, 0};
+    unsigned long long id = 0;
+    if (get_id(s, &id) == hipSuccess) return StreamKey{s, id};
+    (void)hipGetLastError();
+    return StreamKey{s, StreamKey::GONE};
+}
 
 // A per-call table of device pointers (tensor/bucket or peer/out pointers)
 // lives in a small ring of device buffers.  A call whose pointers equal a
@@ -335,7 +351,7 @@ static hipError_t wait_retired(kt_plan *p, const PtrSlot *v)
                 best = &s;
         if (best) e = hipEventSynchronize(best->uploaded);
         else if (v->use_stream == key_of(v->use_stream.handle)) e = hipStreamSynchronize(v->use_stream.handle);
-        else return hipDeviceSynchronize();        // another thread's stream: no handle of this thread names it
+        else return hipDeviceSynchronize();        // another thread's stream, or a destroyed one: no handle names it
     }
     if (e != hipSuccess) {
         // e.g. the caller destroyed the stream of that launch: the targeted wait is

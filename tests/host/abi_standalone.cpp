@@ -195,6 +195,34 @@ int main()
         }
     }
 
+    // more pointer sets than the plan keeps, each on a stream that is destroyed behind the call (the next stream gets
+    // its handle); some of the pointers twice
+    const int sets = 20;
+    std::vector<std::vector<void *>> packed(sets, std::vector<void *>(nb, nullptr));
+    for (auto &set : packed)
+        for (int b = 0; b < nb; ++b) {
+            HIP_OK(hipMalloc(&set[b], (size_t)belems[b] * 4));
+            HIP_OK(hipMemset(set[b], 0xFF, (size_t)belems[b] * 4));
+        }
+    HIP_OK(hipDeviceSynchronize());
+    for (int r = 0; r < 2 * sets; ++r) {
+        const int i = r % 3 == 2 ? r / 2 % sets : r % sets;
+        hipStream_t brief;
+        HIP_OK(hipStreamCreateWithFlags(&brief, hipStreamNonBlocking));
+        KT_OKAY(kt_bucket_pack(plan, KT_ALL_BUCKETS, dg[i % K].data(), packed[i].data(), brief));
+        HIP_OK(hipStreamDestroy(brief));
+    }
+    HIP_OK(hipDeviceSynchronize());
+    for (int i = 0; i < sets; ++i)
+        for (int t = 0; t < T; ++t) {
+            int b;
+            int64_t off;
+            KT_OKAY(kt_plan_tensor_info(plan, t, &b, &off));
+            std::vector<float> got((size_t)numel[t]);
+            HIP_OK(hipMemcpy(got.data(), static_cast<float *>(packed[i][b]) + off, (size_t)numel[t] * 4, hipMemcpyDeviceToHost));
+            if (!same(got, hg[i % K][t], "pack on destroyed streams", t)) ++bad;
+        }
+
     // errors come back as codes, with a message, and leave the plan usable
     if (kt_weighted_reduce(plan, nb, peers.data(), K, w, red.data(), nullptr) != KT_EINVAL || !*kt_last_error()) { printf("bad bucket not refused\n"); ++bad; }
     KT_OKAY(kt_weighted_reduce(plan, 0, peers.data(), K, w, red.data(), nullptr));

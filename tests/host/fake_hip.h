@@ -192,6 +192,15 @@ hipError_t hipStreamSynchronize(hipStream_t st)
     fake::run(*s, true);
     return hipSuccess;
 }
+#ifdef FAKE_STREAM_IDS                   // newer runtimes have it
+hipError_t hipStreamGetId(hipStream_t st, unsigned long long *id)
+{
+    fake::Stream *s = fake::of(st);
+    if (!s) return hipErrorInvalidHandle;
+    *id = s->id;
+    return hipSuccess;
+}
+#endif
 hipError_t hipDeviceSynchronize(void)
 {
     ++fake::device_syncs;

@@ -70,12 +70,49 @@ static void per_thread_new_pointers()
     end(8 * KEPT);
 }
 
+// A stream destroyed with its launches queued, and a new one at the same handle: the new one's uploads are not
+// ordered behind those launches, nor its launches behind the old one's uploads.  Without stream ids the runtime
+// drains a stream that it destroys.
+static void destroyed_stream(bool drains)
+{
+    fake::destroy_drains = drains;
+    Plan p;
+    hipStream_t a = fake::create();
+    fake::of(a)->held = true;
+    for (int r = 0; r < KEPT; ++r) p.call(r, a);
+    fake::destroy(a);
+    hipStream_t b = fake::create();
+    CHECK(a == b);
+    for (int r = 0; r < 2 * KEPT; ++r) p.call(r < 3 ? r + 1 : 100 + r, b);      // some of the old pointers, then new ones
+    end(3 * KEPT);
+}
+static void destroyed_stream_undrained() { destroyed_stream(false); }
+static void destroyed_stream_drained() { destroyed_stream(true); }
+// the stream behind a later table's upload is not the one of the launch that is waited for
+static void destroyed_stream_later_upload()
+{
+    fake::destroy_drains = false;
+    Plan p;
+    hipStream_t a = fake::create(), c = fake::create();
+    fake::of(a)->held = true;
+    for (int r = 0; r < KEPT - 1; ++r) p.call(r, a);
+    fake::destroy(a);
+    hipStream_t b = fake::create();
+    CHECK(a == b);
+    p.call(50, b);
+    for (int r = 0; r < 2 * KEPT; ++r) p.call(100 + r, c);
+    end(3 * KEPT);
+}
+
 int main(int argc, char **argv)
 {
     const struct { const char *name; void (*run)(); } cases[] = {
         {"per_thread_hit", per_thread_hit},
         {"per_thread_eviction", per_thread_eviction},
         {"per_thread_new_pointers", per_thread_new_pointers},
+        {"destroyed_stream_undrained", destroyed_stream_undrained},
+        {"destroyed_stream_drained", destroyed_stream_drained},
+        {"destroyed_stream_later_upload", destroyed_stream_later_upload},
     };
     for (const auto &c : cases)
         if (argc > 1 && strcmp(argv[1], c.name) == 0) {

@@ -13,15 +13,24 @@ pytestmark = pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir
                                 reason="needs g++ and the HIP headers")
 
 
-@pytest.fixture(scope="module")
-def exe(tmp_path_factory):
-    out = str(tmp_path_factory.mktemp("tables") / "pointer_tables")
+def build(out, *flags):
     subprocess.check_call(
         ["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-static-libasan",
-         "-static-libubsan", "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+         "-static-libubsan", *flags, "-D__HIP_PLATFORM_AMD__", "-I", "/opt/rocm/include", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
          os.path.join(ROOT, "tests", "host", "pointer_tables.cpp"), os.path.join(CSRC, "kt_api.cpp"),
          os.path.join(CSRC, "kt_plan.cpp"), "-rdynamic", "-ldl", "-pthread", "-o", out])
     return out
+
+
+@pytest.fixture(scope="module")
+def exe(tmp_path_factory):
+    """With the runtime's ids of streams."""
+    return build(str(tmp_path_factory.mktemp("tables") / "pointer_tables"), "-DFAKE_STREAM_IDS")
+
+
+@pytest.fixture(scope="module")
+def exe_no_ids(tmp_path_factory):
+    return build(str(tmp_path_factory.mktemp("tables_no_ids") / "pointer_tables"))
 
 
 def run(exe, case):
@@ -32,3 +41,13 @@ def run(exe, case):
 @pytest.mark.parametrize("case", ["per_thread_hit", "per_thread_eviction", "per_thread_new_pointers"])
 def test_the_per_thread_stream(exe, case):
     run(exe, case)
+
+
+@pytest.mark.parametrize("case", ["destroyed_stream_undrained", "destroyed_stream_drained", "destroyed_stream_later_upload"])
+def test_a_destroyed_streams_handle_given_again(exe, case):
+    run(exe, case)
+
+
+def test_a_runtime_without_stream_ids(exe_no_ids):
+    for case in ("per_thread_hit", "per_thread_eviction", "destroyed_stream_drained"):
+        run(exe_no_ids, case)
