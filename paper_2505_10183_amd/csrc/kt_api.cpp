@@ -175,11 +175,21 @@ static void release_slot(PtrSlot &s)
 
 // Before a table is overwritten, the launches that read it must have finished.  Streams run in
 // order, so an upload on the stream of those launches needs no wait but for its pinned staging; an
-// upload on another stream waits for the event behind a later table's upload on theirs, or for their stream.
-// No event is recorded behind launches: a marker between two kernels costs the stream 4.7 us
-// (200 empty kernels 1.6 us each, 2.7 with a marker after every fourth, as there was here; ViT-B/16
+// upload on another stream waits for an event behind them on theirs, or for their stream.  The events are those
+// of later uploads on that stream and, once a table has been taken from another stream, one behind
+// every fourth of the next launches: such plans wait for a few launches of the other stream then, not for all that
+// its program has queued there.  Other plans have no events behind their launches: a marker between two kernels
+// costs the stream 4.7 us (200 empty kernels 1.6 us each, 2.7 with a marker after every fourth; ViT-B/16
 // bucket by bucket, 48 launches: 888 us with, 854 without; MLP step 16.5, 14.3).
+struct Mark {
+    hipEvent_t ev = nullptr;
+    StreamKey stream;
+    uint64_t seq = 0;              // the launch before it
+};
 static const int KT_SLOTS = 8;
+static const int KT_MARKS = 16;
+static const uint64_t KT_MARK_EVERY = 4;
+static const uint64_t KT_MARK_FOR = 1024;      // launches after a table was taken from another stream
 static const int KT_WSTAGE = 4;
 
 struct kt_plan {
@@ -204,6 +214,9 @@ struct kt_plan {
     float *w_stage = nullptr;                 // KT_WSTAGE * KT_MAX_PEERS floats, pinned
     hipEvent_t w_done[4] = {nullptr, nullptr, nullptr, nullptr};
     int w_head = 0;
+    Mark marks[KT_MARKS];
+    int mark_head = 0;
+    uint64_t mark_until = 0;
     uint64_t seq = 0;      // launches issued through this plan
     uint64_t clock = 0;
 };
@@ -247,6 +260,8 @@ extern "C" kt_status kt_plan_destroy(kt_plan *p)
         if (e != hipSuccess) st = hip_fail("kt_plan_destroy: hipDeviceSynchronize", e);
         for (PtrSlot &s : p->slots) release_slot(s);
         for (PtrSlot *g : p->graph_tables) { release_slot(*g); delete g; }
+        for (Mark &m : p->marks)
+            if (m.ev) (void)hipEventDestroy(m.ev);
         if (p->dev_w) (void)hipFree(p->dev_w);
         if (p->dev_sgd) (void)hipFree(p->dev_sgd);
         if (p->w_stage) (void)hipHostFree(p->w_stage);
@@ -345,11 +360,16 @@ static hipError_t wait_retired(kt_plan *p, const PtrSlot *v)
     } else if (v->multi_stream) {
         return hipDeviceSynchronize();
     } else {
-        const PtrSlot *best = nullptr;
+        hipEvent_t best = nullptr;                 // the first event behind that launch on its stream
+        uint64_t best_seq = 0;
+        auto offer = [&](hipEvent_t ev, const StreamKey &on, uint64_t seq) {
+            if (on == v->use_stream && seq >= v->last_seq && (!best || seq < best_seq)) { best = ev; best_seq = seq; }
+        };
         for (const PtrSlot &s : p->slots)
-            if (s.valid && s.upload_stream == v->use_stream && s.upload_seq >= v->last_seq && (!best || s.upload_seq < best->upload_seq))
-                best = &s;
-        if (best) e = hipEventSynchronize(best->uploaded);
+            if (s.valid) offer(s.uploaded, s.upload_stream, s.upload_seq);
+        for (const Mark &m : p->marks)
+            if (m.seq) offer(m.ev, m.stream, m.seq);
+        if (best) e = hipEventSynchronize(best);
         else if (v->use_stream == key_of(v->use_stream.handle)) e = hipStreamSynchronize(v->use_stream.handle);
         else return hipDeviceSynchronize();        // another thread's stream, or a destroyed one: no handle names it
     }
@@ -414,6 +434,7 @@ static kt_status stage_pointers(kt_plan *p, const uint64_t *vals, size_t n, hipS
         // the upload must have left the staging copy; the launches that read the table must have
         // finished, or stand before the new upload on its stream
         const bool ordered = victim->cap >= n && victim->use_stream == key && !victim->multi_stream;
+        if (!ordered && victim->use_stream != key) p->mark_until = p->seq + KT_MARK_FOR;
         e = ordered ? hipEventSynchronize(victim->uploaded) : wait_retired(p, victim);
         if (e != hipSuccess) return hip_fail("waiting for a pointer table to retire", e);
     } else if (victim->dev) {        // an upload into it failed: who still reads it is not known
@@ -461,6 +482,18 @@ static kt_status mark_used(kt_plan *p, PtrSlot *s, hipStream_t stream)
     if (s->last_seq > 0 && s->use_stream != key) s->multi_stream = true;
     s->use_stream = key;
     s->last_seq = ++p->seq;
+    if (p->seq < p->mark_until && p->seq % KT_MARK_EVERY == 0) {
+        Mark &m = p->marks[p->mark_head];
+        p->mark_head = (p->mark_head + 1) % KT_MARKS;
+        hipError_t e = hipSuccess;
+        if (!m.ev) e = hipEventCreateWithFlags(&m.ev, hipEventDisableTiming);
+        if (e != hipSuccess) return hip_fail("hipEventCreate", e);
+        m.seq = 0;
+        e = hipEventRecord(m.ev, stream);
+        if (e != hipSuccess) return hip_fail("hipEventRecord", e);
+        m.stream = key;
+        m.seq = p->seq;
+    }
     return KT_OK;
 }
 

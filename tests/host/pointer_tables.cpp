@@ -104,12 +104,45 @@ static void destroyed_stream_later_upload()
     end(3 * KEPT);
 }
 
+// Two streams with new pointers: from the second round on, what one stream's program has queued behind its launches
+// is not waited for when the other takes its tables.
+static void other_streams_queue()
+{
+    Plan p;
+    hipStream_t a = fake::create(), b = fake::create();
+    fake::of(a)->held = true;
+    int calls = 0;
+    for (int round = 0; round < 3; ++round) {
+        for (int r = 0; r < 8; ++r, ++calls) p.call(r % 4, a);      // every table again after the last upload
+        for (int r = 0; r < 4; ++r, ++calls) p.call(3, a);
+        fake::work(a);
+        for (int r = 0; r < KEPT - 1; ++r, ++calls) p.call(100 * (round + 1) + r, b);      // all but a's last
+        CHECK(round == 0 || fake::work_done <= round);
+    }
+    CHECK(fake::device_syncs == 0);
+    end(calls);
+}
+// one stream alone: no event but the uploads'
+static void one_stream_marks_nothing()
+{
+    Plan p;
+    hipStream_t a = fake::create();
+    for (int r = 0; r < 4 * KEPT; ++r) p.call(r, a);
+    const size_t n = fake::events.size();
+    for (int r = 0; r < 4 * KEPT; ++r) p.call(r % 3, a);
+    CHECK(n == (size_t)KEPT && fake::events.size() == n);
+    CHECK(fake::device_syncs == 0 && fake::stream_syncs == 0);
+    end(8 * KEPT);
+}
+
 int main(int argc, char **argv)
 {
     const struct { const char *name; void (*run)(); } cases[] = {
         {"per_thread_hit", per_thread_hit},
         {"per_thread_eviction", per_thread_eviction},
         {"per_thread_new_pointers", per_thread_new_pointers},
+        {"other_streams_queue", other_streams_queue},
+        {"one_stream_marks_nothing", one_stream_marks_nothing},
         {"destroyed_stream_undrained", destroyed_stream_undrained},
         {"destroyed_stream_drained", destroyed_stream_drained},
         {"destroyed_stream_later_upload", destroyed_stream_later_upload},

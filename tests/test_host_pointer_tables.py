@@ -48,6 +48,11 @@ def test_a_destroyed_streams_handle_given_again(exe, case):
     run(exe, case)
 
 
+@pytest.mark.parametrize("case", ["other_streams_queue", "one_stream_marks_nothing"])
+def test_what_a_new_table_waits_for(exe, case):
+    run(exe, case)
+
+
 def test_a_runtime_without_stream_ids(exe_no_ids):
-    for case in ("per_thread_hit", "per_thread_eviction", "destroyed_stream_drained"):
+    for case in ("per_thread_hit", "per_thread_eviction", "destroyed_stream_drained", "other_streams_queue"):
         run(exe_no_ids, case)
