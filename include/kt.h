@@ -31,9 +31,10 @@
  *    device copy instead of uploading it again.
  *  - HIP graphs: a device call may be recorded under stream capture once the
  *    same call (same plan, same pointer arrays) has been made outside capture,
- *    so that the plan's tables and the pointer table are resident; under
- *    capture the library enqueues its kernel and nothing else.  Otherwise the
- *    call returns KT_EUNSUPPORTED.  A pointer table read by a recorded call is
+ *    so that the plan's tables and the pointer table are resident (on any
+ *    stream, the one captured later included; it need not have finished);
+ *    into the capture the library enqueues its kernel and nothing else.
+ *    Otherwise the call returns KT_EUNSUPPORTED.  A pointer table read by a recorded call is
  *    set aside for the graph and stays resident until the plan is destroyed
  *    (one table per distinct pointer set: a chained step records three, pack,
  *    reduce and unpack; tables of eager calls are not affected).

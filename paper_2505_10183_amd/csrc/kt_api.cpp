@@ -47,13 +47,21 @@ static kt_status hip_fail(const char *what, hipError_t e)
     return e == hipErrorOutOfMemory ? KT_ENOMEM : KT_EHIP;
 }
 
-// True while `s` is recording into a HIP graph.  Under capture the library only
-// enqueues kernels: it uploads nothing, allocates nothing and records no events.
+// True while `s` is recording into a HIP graph.  Under capture the library only enqueues kernels on `s`: what a
+// table needs before it can be recorded (stage_pointers) is done beside the capture.
 static bool capturing(hipStream_t s)
 {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     return hipStreamIsCapturing(s, &st) == hipSuccess && st == hipStreamCaptureStatusActive;
 }
+
+// While it lives, calls of this thread that are refused beside a capture in the default modes (waits for streams and
+// events that are not captured, allocations) neither fail nor end the capture.
+struct BesideCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    BesideCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~BesideCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
 
 // No exception may cross the C boundary.
 #define KT_GUARD_BEGIN try {
@@ -204,6 +212,7 @@ struct kt_plan {
     // (so that eager calls keep all KT_SLOTS tables) and kept until the plan
     // is destroyed, because a graph may be replayed at any time.
     std::vector<PtrSlot *> graph_tables;
+    std::vector<void *> replaced;          // device buffers that graph tables had before
     // device-resident weights (kt_plan_set_weights): one array of KT_MAX_PEERS floats on the
     // device, a small ring of pinned staging copies so that successive updates do not wait
     float *dev_w = nullptr;
@@ -260,6 +269,7 @@ extern "C" kt_status kt_plan_destroy(kt_plan *p)
         if (e != hipSuccess) st = hip_fail("kt_plan_destroy: hipDeviceSynchronize", e);
         for (PtrSlot &s : p->slots) release_slot(s);
         for (PtrSlot *g : p->graph_tables) { release_slot(*g); delete g; }
+        for (void *d : p->replaced) (void)hipFree(d);
         for (Mark &m : p->marks)
             if (m.ev) (void)hipEventDestroy(m.ev);
         if (p->dev_w) (void)hipFree(p->dev_w);
@@ -382,6 +392,27 @@ static hipError_t wait_retired(kt_plan *p, const PtrSlot *v)
     return e;
 }
 
+// A new device copy of a table whose upload was enqueued on a stream that is being captured now: neither that stream nor
+// an event recorded on it can be waited for before the capture ends.
+static hipError_t upload_again(kt_plan *p, PtrSlot *v)
+{
+    p->replaced.reserve(p->replaced.size() + 1);
+    void *dev = nullptr;
+    hipStream_t side = nullptr;
+    hipError_t e = hipMalloc(&dev, v->cap * 8);
+    if (e == hipSuccess) e = hipStreamCreateWithFlags(&side, hipStreamNonBlocking);
+    if (e == hipSuccess) e = hipMemcpyAsync(dev, v->pinned, v->n * 8, hipMemcpyHostToDevice, side);
+    if (e == hipSuccess) e = hipStreamSynchronize(side);
+    if (side) (void)hipStreamDestroy(side);
+    if (e != hipSuccess) {
+        if (dev) (void)hipFree(dev);
+        return e;
+    }
+    p->replaced.push_back(v->dev);         // launches that read it may be queued
+    v->dev = dev;
+    return hipSuccess;
+}
+
 // Make `vals[0..n)` resident on the device for a launch on `stream`.
 // Caller holds p->mu.  On success *slot_out is the slot to mark after launch.
 static kt_status stage_pointers(kt_plan *p, const uint64_t *vals, size_t n, hipStream_t stream, PtrSlot **slot_out)
@@ -404,8 +435,12 @@ static kt_status stage_pointers(kt_plan *p, const uint64_t *vals, size_t n, hipS
         if (cap) {
             // A graph keeps using this table for as long as it is replayed: take
             // it out of the ring, whose slot becomes free for eager calls again.
-            e = hipEventSynchronize(hit->uploaded);
-            if (e != hipSuccess) return hip_fail("hipEventSynchronize", e);
+            BesideCapture beside;
+            const StreamKey &up = hit->upload_stream;
+            // (the null stream is never captured, and asking leaves an error behind while a stream that it waits for is)
+            const bool held = up.handle && up.handle != hipStreamLegacy && up == key_of(up.handle) && capturing(up.handle);
+            e = held ? upload_again(p, hit) : hipEventSynchronize(hit->uploaded);
+            if (e != hipSuccess) return hip_fail("upload of a pointer table for a graph", e);
             PtrSlot *g = new PtrSlot(*hit);
             g->in_graph = true;
             p->graph_tables.push_back(g);

@@ -14,6 +14,7 @@
 #include <cstring>
 #include <deque>
 #include <memory>
+#include <utility>
 #include <vector>
 
 #include "kt_internal.h"
@@ -46,6 +47,7 @@ inline std::vector<std::unique_ptr<Event>> events;
 inline std::vector<std::unique_ptr<Handle>> handles;
 inline std::vector<Handle *> free_handles;
 inline std::vector<uint64_t> want;               // table that the next launch is meant to read
+inline std::vector<Op> recorded;                 // launches under capture
 inline int wrong = 0, launched = 0, device_syncs = 0, stream_syncs = 0, work_done = 0;
 inline bool destroy_drains = true;
 
@@ -106,13 +108,31 @@ inline void finish()
     for (auto &s : all) s->held = false;
     for (auto it = all.rbegin(); it != all.rend(); ++it) run(**it, true);
 }
-// Waiting for anything of a stream under capture, or for the device, ends the capture.
+// Waiting for anything of a stream under capture, or for the device, ends the capture; so do waits for other streams
+// (but the null stream) and allocations, unless the thread has exchanged its mode for the relaxed one.
+inline thread_local hipStreamCaptureMode mode = hipStreamCaptureModeGlobal;
 inline bool breaks_capture(Stream *s)
 {
     bool broken = false;
     for (auto &x : all)
-        if (x->capturing && (!s || x.get() == s)) x->invalidated = broken = true;
+        if (x->capturing && (!s || x.get() == s || (mode != hipStreamCaptureModeRelaxed && s != null_stream())))
+            x->invalidated = broken = true;
     return broken;
+}
+inline hipError_t last = hipSuccess;             // what a launch reports
+inline bool refused()
+{
+    bool any = false;
+    if (mode != hipStreamCaptureModeRelaxed)
+        for (auto &x : all)
+            if (x->capturing) x->invalidated = any = true;
+    return any;
+}
+inline void begin_capture(hipStream_t s) { of(s)->capturing = true; }
+inline bool end_capture(hipStream_t s)
+{
+    of(s)->capturing = false;
+    return !of(s)->invalidated;
 }
 
 inline hipStream_t create()
@@ -144,8 +164,17 @@ hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) { *v = 10000
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
 hipError_t hipSetDevice(int) { return hipSuccess; }
 const char *hipGetErrorString(hipError_t) { return "error"; }
-hipError_t hipGetLastError(void) { return hipSuccess; }
-hipError_t hipMalloc(void **p, size_t n) { *p = calloc(1, n); return hipSuccess; }
+hipError_t hipGetLastError(void) { return std::exchange(fake::last, hipSuccess); }
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode *m) { std::swap(*m, fake::mode); return hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = fake::create(); return hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t s) { fake::destroy(s); return hipSuccess; }
+hipError_t hipMalloc(void **p, size_t n)
+{
+    *p = nullptr;
+    if (fake::refused()) return hipErrorStreamCaptureUnsupported;
+    *p = calloc(1, n);
+    return hipSuccess;
+}
 hipError_t hipFree(void *p) { free(p); return hipSuccess; }
 hipError_t hipHostMalloc(void **p, size_t n, unsigned) { *p = calloc(1, n); return hipSuccess; }
 hipError_t hipHostFree(void *p) { free(p); return hipSuccess; }
@@ -211,6 +240,9 @@ hipError_t hipDeviceSynchronize(void)
 hipError_t hipStreamIsCapturing(hipStream_t st, hipStreamCaptureStatus *c)
 {
     fake::Stream *s = fake::of(st);
+    if (!st)                                      // the streams here are ones that the null stream waits for
+        for (auto &x : fake::all)
+            if (x->capturing) return fake::last = hipErrorStreamCaptureImplicit;
     *c = s && s->capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
     return hipSuccess;
 }
@@ -220,8 +252,9 @@ int kt_launch_pack(const KtDeviceTables &, kt_dtype, int64_t, int64_t, const voi
 {
     ++fake::launched;
     fake::Stream *s = fake::of(static_cast<hipStream_t>(stream));
-    if (!s->capturing) fake::push(s, fake::Op{fake::Op::LAUNCH, nullptr, table, 0, fake::want, nullptr, 0});
-    return 0;
+    fake::Op op{fake::Op::LAUNCH, nullptr, table, 0, fake::want, nullptr, 0};
+    if (s->capturing) fake::recorded.push_back(op); else fake::push(s, op);
+    return (int)hipGetLastError();
 }
 int kt_launch_unpack(const KtDeviceTables &, kt_dtype, int64_t, int64_t, const void *const *, float, void *const *, void *) { return 0; }
 int kt_launch_reduce(const KtDeviceTables &, kt_dtype, int64_t, int64_t, const void *const *, int, const KtWeights &, void *const *, void *) { return 0; }

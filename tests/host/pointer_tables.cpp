@@ -135,6 +135,27 @@ static void one_stream_marks_nothing()
     end(8 * KEPT);
 }
 
+// A call recorded after the same call was made on the stream that is captured, on another one, on the null
+// stream; the recorded launch runs before anything else that is queued.
+static void recorded_after(int where)
+{
+    Plan p;
+    hipStream_t a = fake::create(), b = fake::create();
+    hipStream_t eager = where == 0 ? a : where == 1 ? b : nullptr;
+    fake::of(eager)->held = true;
+    for (int r = 0; r < 3; ++r) p.call(r, eager);
+    fake::begin_capture(a);
+    for (int r = 0; r < 3; ++r) p.call(r, a);
+    CHECK(fake::end_capture(a));
+    CHECK(fake::recorded.size() == 3);
+    for (const fake::Op &op : fake::recorded) fake::push(fake::of(fake::create()), op);
+    for (int r = 0; r < 2 * KEPT; ++r) p.call(100 + r, b);
+    end(6 + 2 * KEPT);
+}
+static void recorded_after_captured_stream() { recorded_after(0); }
+static void recorded_after_other_stream() { recorded_after(1); }
+static void recorded_after_null_stream() { recorded_after(2); }
+
 int main(int argc, char **argv)
 {
     const struct { const char *name; void (*run)(); } cases[] = {
@@ -143,6 +164,9 @@ int main(int argc, char **argv)
         {"per_thread_new_pointers", per_thread_new_pointers},
         {"other_streams_queue", other_streams_queue},
         {"one_stream_marks_nothing", one_stream_marks_nothing},
+        {"recorded_after_captured_stream", recorded_after_captured_stream},
+        {"recorded_after_other_stream", recorded_after_other_stream},
+        {"recorded_after_null_stream", recorded_after_null_stream},
         {"destroyed_stream_undrained", destroyed_stream_undrained},
         {"destroyed_stream_drained", destroyed_stream_drained},
         {"destroyed_stream_later_upload", destroyed_stream_later_upload},

@@ -121,6 +121,41 @@ def test_capture_refuses_unprepared_calls():
     assert torch.equal(b2[0][:5000], a[0])
 
 
+@pytest.mark.parametrize("eager", ["captured", "other", "default"])
+@pytest.mark.parametrize("sync", [False, True])
+def test_recorded_after_an_eager_call_on_a_stream_of_its_own(eager, sync):
+    """The eager call may have run on the stream that is captured afterwards, or on another one, and need not have
+    finished; the tables of later calls do not disturb the graph."""
+    numels = [4096, 17, 70001]
+    plan = kt.Plan(numels, "f32", 0, 16)
+    n = plan.bucket_elems()[0]
+    offs = [plan.tensor_info(t)[1] for t in range(len(numels))]
+    src = [torch.randn(m, device=DEV) for m in numels]
+    buf, out = [torch.zeros(n, device=DEV)], [torch.zeros(m, device=DEV) for m in numels]
+    cap, other = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream({"captured": cap, "other": other, "default": torch.cuda.default_stream()}[eager]):
+        plan.kt_bucket_pack(-1, src, buf)
+        plan.kt_bucket_unpack_scale(-1, buf, 2.0, out)
+    if sync:
+        torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=cap):
+        plan.kt_bucket_pack(-1, src, buf)
+        plan.kt_bucket_unpack_scale(-1, buf, 2.0, out)
+    for r in range(4):
+        for t, x in enumerate(src):
+            x.fill_(float(10 * r + t))
+        for _ in range(10):                      # more tables than the plan keeps
+            plan.kt_bucket_pack(-1, src, [torch.zeros(n, device=DEV)])
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        for t, m in enumerate(numels):
+            assert bool((buf[0][offs[t]:offs[t] + m] == float(10 * r + t)).all()), (r, t)
+            assert bool((out[t] == 2.0 * (10 * r + t)).all()), (r, t)
+
+
 def test_tables_used_by_graphs_do_not_consume_the_eager_ring():
     """A pointer table read by a recorded call is set aside for the graph (kept
     until the plan is destroyed) and frees its place in the ring of 8 tables

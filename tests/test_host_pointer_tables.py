@@ -53,6 +53,12 @@ def test_what_a_new_table_waits_for(exe, case):
     run(exe, case)
 
 
+@pytest.mark.parametrize("where", ["captured", "other", "null"])
+def test_a_call_recorded_after_the_same_call_on(exe, exe_no_ids, where):
+    run(exe, "recorded_after_%s_stream" % where)
+    run(exe_no_ids, "recorded_after_%s_stream" % where)
+
+
 def test_a_runtime_without_stream_ids(exe_no_ids):
     for case in ("per_thread_hit", "per_thread_eviction", "destroyed_stream_drained", "other_streams_queue"):
         run(exe_no_ids, case)
