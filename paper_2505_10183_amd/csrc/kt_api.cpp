@@ -154,6 +154,13 @@ static StreamKey key_of(hipStream_t s)
     return StreamKey{s, StreamKey::GONE};
 }
 
+// True while the stream of an earlier call is being captured.  The null stream never is, and asking leaves an error
+// behind while a stream that it waits for is.
+static bool captured(const StreamKey &k)
+{
+    return k.handle && k.handle != hipStreamLegacy && k == key_of(k.handle) && capturing(k.handle);
+}
+
 // A per-call table of device pointers (tensor/bucket or peer/out pointers)
 // lives in a small ring of device buffers.  A call whose pointers equal a
 // resident table reuses it, so a steady training loop uploads nothing.
@@ -436,10 +443,7 @@ static kt_status stage_pointers(kt_plan *p, const uint64_t *vals, size_t n, hipS
             // A graph keeps using this table for as long as it is replayed: take
             // it out of the ring, whose slot becomes free for eager calls again.
             BesideCapture beside;
-            const StreamKey &up = hit->upload_stream;
-            // (the null stream is never captured, and asking leaves an error behind while a stream that it waits for is)
-            const bool held = up.handle && up.handle != hipStreamLegacy && up == key_of(up.handle) && capturing(up.handle);
-            e = held ? upload_again(p, hit) : hipEventSynchronize(hit->uploaded);
+            e = captured(hit->upload_stream) ? upload_again(p, hit) : hipEventSynchronize(hit->uploaded);
             if (e != hipSuccess) return hip_fail("upload of a pointer table for a graph", e);
             PtrSlot *g = new PtrSlot(*hit);
             g->in_graph = true;
@@ -461,9 +465,25 @@ static kt_status stage_pointers(kt_plan *p, const uint64_t *vals, size_t n, hipS
                      "make the same call once outside stream capture first");
         return KT_EUNSUPPORTED;
     }
-    for (PtrSlot &s : p->slots) {
-        if (!s.valid) { victim = &s; break; }
-        if (!victim || s.stamp < victim->stamp) victim = &s;
+    // the table used least recently, but none that a stream under capture has to be waited for: that would end the capture
+    BesideCapture beside;
+    bool passed[KT_SLOTS] = {};
+    for (;;) {
+        victim = nullptr;
+        for (int i = 0; i < KT_SLOTS; ++i) {
+            PtrSlot &s = p->slots[i];
+            if (passed[i]) continue;
+            if (!s.valid) { victim = &s; break; }
+            if (!victim || s.stamp < victim->stamp) victim = &s;
+        }
+        if (!victim) {
+            kt_set_error("all %d resident pointer tables were last used on a stream that is being captured; make the call "
+                         "after the capture", KT_SLOTS);
+            return KT_EUNSUPPORTED;
+        }
+        auto in_capture = [&](const StreamKey &k) { return k != key && captured(k); };
+        if (!victim->valid || !(in_capture(victim->upload_stream) || in_capture(victim->use_stream))) break;
+        passed[victim - p->slots] = true;
     }
     if (victim->valid) {
         // the upload must have left the staging copy; the launches that read the table must have

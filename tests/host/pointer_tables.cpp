@@ -156,6 +156,25 @@ static void recorded_after_captured_stream() { recorded_after(0); }
 static void recorded_after_other_stream() { recorded_after(1); }
 static void recorded_after_null_stream() { recorded_after(2); }
 
+// New pointers on one stream while another, which used some of the tables last, is being captured
+static void new_pointers_beside_a_capture()
+{
+    Plan p;
+    hipStream_t a = fake::create(), b = fake::create();
+    fake::of(a)->held = true;
+    for (int r = 0; r < 2 * KEPT - 3; ++r) p.call(r, r < KEPT ? b : a);      // 5 tables of a, 3 of b
+    fake::begin_capture(a);
+    p.call(2 * KEPT - 4, a);
+    for (int r = 0; r < 3 * KEPT; ++r) p.call(100 + r, b);
+    CHECK(fake::end_capture(a));
+    for (int r = 0; r < KEPT; ++r) p.call(200 + r, a);
+    fake::begin_capture(a);
+    CHECK(p.pack(300, b) == KT_EUNSUPPORTED);
+    CHECK(fake::end_capture(a));
+    p.call(300, b);
+    end(2 * KEPT - 3 + 1 + 3 * KEPT + KEPT + 1);
+}
+
 int main(int argc, char **argv)
 {
     const struct { const char *name; void (*run)(); } cases[] = {
@@ -167,6 +186,7 @@ int main(int argc, char **argv)
         {"recorded_after_captured_stream", recorded_after_captured_stream},
         {"recorded_after_other_stream", recorded_after_other_stream},
         {"recorded_after_null_stream", recorded_after_null_stream},
+        {"new_pointers_beside_a_capture", new_pointers_beside_a_capture},
         {"destroyed_stream_undrained", destroyed_stream_undrained},
         {"destroyed_stream_drained", destroyed_stream_drained},
         {"destroyed_stream_later_upload", destroyed_stream_later_upload},

@@ -59,6 +59,11 @@ def test_a_call_recorded_after_the_same_call_on(exe, exe_no_ids, where):
     run(exe_no_ids, "recorded_after_%s_stream" % where)
 
 
+def test_new_pointers_beside_a_capture(exe, exe_no_ids):
+    run(exe, "new_pointers_beside_a_capture")
+    run(exe_no_ids, "new_pointers_beside_a_capture")
+
+
 def test_a_runtime_without_stream_ids(exe_no_ids):
     for case in ("per_thread_hit", "per_thread_eviction", "destroyed_stream_drained", "other_streams_queue"):
         run(exe_no_ids, case)
