@@ -42,7 +42,7 @@ def equal(dev, want, what):
     ("bf16", 8192, 3, 16, False),
     ("f32", 4096, 16, 4, False),        # fused pass of many copies inside the store windows (65 536 tiles read)
     ("bf16", 4096, 16, 0, False),
-    ("bf16", 8192, 8, 4, True),         # and of 8
+    ("bf16", 8192, 8, 4, True),         # and of 8: half tiles (fused pass) and quarter tiles, held
 ])
 def test_large_launches(dtype, tiles, K, shift, dense):
     n = -(-tiles * (16384 // (4 if dtype == "f32" else 2)) // 24) | 1

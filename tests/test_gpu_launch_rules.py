@@ -1,5 +1,6 @@
-"""Which launches hold back workgroups per CU (they ask for LDS beyond the kernel's own): read from
-the kernel nodes of a recorded graph, around the limits of the launch rules."""
+"""Which launches hold back workgroups per CU (they ask for LDS beyond the kernel's own), share tiles between
+workgroups or store in windows (whole tiles, nothing held): read from the kernel nodes of a recorded
+graph, around the limits of the launch rules."""
 import ctypes
 import os
 import subprocess
@@ -36,8 +37,8 @@ def hip():
     return ctypes.CDLL("libamdhip64.so")       # the runtime the process already holds
 
 
-def recorded_lds(call):
-    """The dynamic LDS of the one kernel that `call(stream)` launches (its tables are on the device already)."""
+def recorded_launch(call):
+    """Workgroups and dynamic LDS of the one kernel that `call(stream)` launches (its tables are on the device already)."""
     h, s = hip(), torch.cuda.Stream()
     graph = ctypes.c_void_p()
     assert h.hipStreamBeginCapture(ctypes.c_void_p(s.cuda_stream), 0) == 0
@@ -57,13 +58,13 @@ def recorded_lds(call):
             p = KernelNodeParams()
             assert h.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
             assert p.blockDim.x == 256
-            got.append(p.sharedMemBytes)
+            got.append((p.gridDim.x, p.sharedMemBytes))
     assert h.hipGraphDestroy(graph) == 0
     assert len(got) == 1, got
     return got[0]
 
 
-def dynamic_lds(op, dtype, K, tiles):
+def launch(op, dtype, K, tiles):
     es, td = (4, torch.float32) if dtype == "f32" else (2, torch.bfloat16)
     numels = [tiles * (16384 // es)]
     plan = kt.Plan(numels, dtype, 0, 16)
@@ -87,7 +88,11 @@ def dynamic_lds(op, dtype, K, tiles):
 
     call()
     torch.cuda.synchronize()
-    return recorded_lds(call)
+    return recorded_launch(call)
+
+
+def dynamic_lds(op, dtype, K, tiles):
+    return launch(op, dtype, K, tiles)[1]
 
 
 @pytest.mark.parametrize("op,dtype,K,least", [
@@ -127,3 +132,39 @@ def test_nothing_held_where_the_gpu_is_shared(op, dtype, K):
     r = subprocess.run([sys.executable, "-c", code], env=env, capture_output=True, text=True, timeout=100)
     assert r.returncode == 0, r.stderr[-2000:]
     assert "LDS 0" in r.stdout.splitlines(), r.stdout
+
+
+@pytest.mark.parametrize("op,dtype,K,least", [
+    ("reduce", "f32", 7, 65536), ("reduce", "f32", 8, 65536), ("reduce", "bf16", 7, 65536), ("reduce", "bf16", 8, 65536),
+    ("reduce", "f32", 10, 26215), ("reduce", "f32", 16, 16384), ("reduce", "bf16", 11, 23832), ("reduce", "bf16", 24, 10923),
+    ("fused", "f32", 7, 65536), ("fused", "f32", 8, 16384), ("fused", "bf16", 7, 131072), ("fused", "bf16", 8, 131072),
+    ("fused", "f32", 10, 6554), ("fused", "f32", 16, 4096), ("fused", "bf16", 11, 5958), ("fused", "bf16", 16, 4096),
+    ("fused_sgd", "f32", 11, 8937), ("fused_sgd", "f32", 16, 6144), ("fused_sgd", "bf16", 14, 14044),
+])
+def test_store_windows_from_a_launch_size_on(op, dtype, K, least):
+    """Inside the windows a launch has one workgroup per tile and holds none; just below it shares tiles and holds."""
+    below, lds = launch(op, dtype, K, least - 1)
+    assert below > least - 1 and lds > 0
+    assert launch(op, dtype, K, least) == (least, 0)
+
+
+@pytest.mark.parametrize("op,dtype,K", [("reduce", "f32", 9), ("reduce", "bf16", 10), ("fused", "f32", 9), ("fused", "bf16", 10),
+                                        ("fused_sgd", "f32", 10), ("fused_sgd", "bf16", 13), ("reduce", "f32", 6), ("fused", "bf16", 6)])
+def test_no_store_windows_with_fewer_copies(op, dtype, K):
+    grid, lds = launch(op, dtype, K, 32768)
+    assert grid > 32768 and lds > 0
+
+
+@pytest.mark.parametrize("op,dtype,K,tiles,split", [
+    # nearly full rounds of whole tiles, uneven ones, and where sharing begins
+    ("reduce", "f32", 2, 12287, 1), ("reduce", "f32", 2, 12288, 4), ("reduce", "bf16", 3, 8192, 4), ("reduce", "f32", 4, 8191, 1),
+    ("reduce", "f32", 4, 8192, 4), ("reduce", "bf16", 4, 12287, 1), ("reduce", "f32", 5, 4095, 1), ("reduce", "f32", 6, 2048, 4),
+    ("reduce", "bf16", 7, 2047, 1), ("reduce", "f32", 7, 4096, 4), ("reduce", "f32", 8, 3071, 1), ("reduce", "bf16", 8, 2048, 4),
+    ("reduce", "f32", 8, 512, 1), ("reduce", "f32", 8, 551, 4), ("reduce", "bf16", 16, 256, 4), ("reduce", "f32", 12, 2559, 1),
+    ("reduce", "f32", 12, 2560, 4),
+    ("fused", "bf16", 4, 1023, 2), ("fused", "bf16", 4, 1024, 1), ("fused", "bf16", 5, 5120, 2), ("fused", "f32", 4, 8191, 1),
+    ("fused", "f32", 4, 8192, 4), ("fused", "f32", 6, 4096, 4), ("fused", "bf16", 6, 100, 2), ("fused", "f32", 12, 100, 4),
+    ("fused_sgd", "f32", 12, 896, 4), ("fused_sgd", "f32", 12, 897, 1), ("fused_sgd", "bf16", 9, 641, 1), ("fused_sgd", "f32", 9, 2560, 4),
+])
+def test_workgroups_per_tile(op, dtype, K, tiles, split):
+    assert launch(op, dtype, K, tiles)[0] == split * tiles

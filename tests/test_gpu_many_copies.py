@@ -54,3 +54,39 @@ def test_zeros_keep_their_signs(dtype, K):
     torch.cuda.synchronize()
     assert bool(torch.signbit(out[0::2]).all()) and not bool(torch.signbit(out[1::2]).any())
     assert bool((out == 0).all()) and bool((torch.signbit(out) == torch.signbit(out_dev)).all())
+
+
+@pytest.mark.parametrize("dtype,tiles,K", [("f32", 20, 12), ("bf16", 700, 16), ("f32", 2560, 9), ("bf16", 2560, 16), ("f32", 8937, 11),
+                                           ("bf16", 551, 6), ("f32", 4096, 8)])
+def test_resident_weights(dtype, tiles, K):
+    """Weights and optimizer scalars from device memory: the bits of the same calls by value, in shared tiles, in whole
+    ones and inside the store windows."""
+    td, es = (torch.float32, 4) if dtype == "f32" else (torch.bfloat16, 2)
+    n = -(-tiles * (16384 // es) // 24) | 1
+    numels = [n + 2 * t for t in range(24)]
+    plan = kt.Plan(numels, dtype, 0 if tiles < 2000 else 64 << 20, 16)
+    elems, nb = plan.bucket_elems(), plan.num_buckets
+    _, weights = kt.kt_plan_shares([1.0 - 0.01 * k for k in range(K)], 4096)
+    gen = torch.Generator("cuda").manual_seed(5)
+    copies = [[torch.empty(m, dtype=td, device="cuda").normal_(0, 1e-3, generator=gen) for m in elems] for _ in range(K)]
+    grads = [torch.empty(m, dtype=td, device="cuda").normal_(0, 1e-3, generator=gen) for m in numels]
+    p0 = [torch.empty(m, device="cuda").normal_(0, 1, generator=gen) for m in numels]
+    flat = [copies[k][b] for b in range(nb) for k in range(K)]
+    others = [copies[k][b] for b in range(nb) for k in range(1, K)]
+    plan.kt_plan_set_weights(weights)
+    plan.kt_plan_set_sgd(0.37, 0.1, 0.9, 5e-4)
+    got = []
+    for resident in (False, True):
+        red, out = [torch.zeros(m, dtype=td, device="cuda") for m in elems], [torch.zeros_like(g) for g in grads]
+        p, v, m = [t.clone() for t in p0], [t * 0.1 for t in p0], [torch.zeros(t.numel(), dtype=torch.bfloat16, device="cuda") for t in p0]
+        plan.kt_weighted_reduce(-1, flat, K, None if resident else weights, red)
+        plan.kt_fused_step(-1, grads, others, K, None if resident else weights, 0.37, out)
+        if resident:
+            plan.kt_fused_step_sgd_resident(-1, grads, others, K, p, v, m, False)
+        else:
+            plan.kt_fused_step_sgd(-1, grads, others, K, weights, 0.37, p, v, m, 0.1, 0.9, 5e-4, False)
+        torch.cuda.synchronize()
+        got.append([*red, *out, *p, *v, *m])
+    for i, (a, b) in enumerate(zip(*got)):
+        kind = torch.int32 if a.element_size() == 4 else torch.int16
+        assert torch.equal(a.view(kind), b.view(kind)), i

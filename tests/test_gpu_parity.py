@@ -528,18 +528,19 @@ def check_large_reduce(dtype, K, tiles):
         list(pool.map(bucket, range(nb)))
 
 
-# the reduce holds its stores back until the chip-wide store window from 65 536 tiles on with 5 to 8
-# copies and from 262 144 tiles read on with more
-@pytest.mark.parametrize("dtype,K,tiles", [("f32", 5, 65536), ("bf16", 6, 65536), ("f32", 16, 16384), ("bf16", 16, 16384)])
+# the reduce holds its stores back until the chip-wide store window from 65 536 tiles on with 7 and 8
+# copies and from 262 144 tiles read on with more (fp32 10, bf16 11 and more)
+@pytest.mark.parametrize("dtype,K,tiles", [("f32", 7, 65536), ("f32", 8, 65536), ("bf16", 7, 65536), ("f32", 16, 16384),
+                                           ("bf16", 16, 16384)])
 def test_reduce_large_launch_with_store_windows(dtype, K, tiles):
-    assert K >= 5 and (tiles >= 65536 if K <= 8 else tiles * K >= 262144)
+    assert K >= 7 and (tiles >= 65536 if K <= 8 else tiles * K >= 262144)
     check_large_reduce(dtype, K, tiles)
 
 
-@pytest.mark.parametrize("dtype,K", [("f32", 3), ("bf16", 4)])
-def test_reduce_large_launch_with_held_workgroups(dtype, K):
-    """Three to five copies without a window: two workgroups per CU."""
-    check_large_reduce(dtype, K, 16384)
+@pytest.mark.parametrize("dtype,K,tiles", [("f32", 3, 16384), ("bf16", 4, 16384), ("f32", 5, 65536), ("bf16", 6, 65536)])
+def test_reduce_large_launch_with_held_workgroups(dtype, K, tiles):
+    """Three to six copies use no window: quarter tiles, three to five workgroups per CU."""
+    check_large_reduce(dtype, K, tiles)
 
 
 def test_two_host_threads_share_a_plan():
