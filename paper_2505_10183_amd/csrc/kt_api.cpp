@@ -144,10 +144,11 @@ static uint64_t thread_id()
 
 static StreamKey key_of(hipStream_t s)
 {
+    if (!s || s == hipStreamLegacy) return StreamKey{s, 0};
+    if (s == hipStreamPerThread) return StreamKey{s, thread_id()};
     typedef hipError_t (*IdFn)(hipStream_t, unsigned long long *);
     static const IdFn get_id = reinterpret_cast<IdFn>(dlsym(RTLD_DEFAULT, "hipStreamGetId"));
-    if (s == hipStreamPerThread) return StreamKey{s, thread_id()};
-    if (!s || s == hipStreamLegacy || !get_id) return StreamKey{s, 0};
+    if (!get_id) return StreamKey{s, 0};
     unsigned long long id = 0;
     if (get_id(s, &id) == hipSuccess) return StreamKey{s, id};
     (void)hipGetLastError();
