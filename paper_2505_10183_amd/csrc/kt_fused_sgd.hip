@@ -66,7 +66,7 @@ template <int N, bool SYS> __device__ __forceinline__ void st_quads(u32x4 *p4, u
         st_vec_copy<SYS>(p4 + j * KT_BLOCK, pr[j]);
         st_vec_copy<SYS>(v4 + j * KT_BLOCK, vr[j]);
     }
-    if (m2) {      // non-temporal beside system-scope ones too (1.3B set 7.54 -> 7.49 ms, 33 106 tiles 1 600 -> 1 564 us, 44 137 even)
+    if (m2) {      // non-temporal beside system-scope ones too (1.3B set, 8 placements of its memory: 0 to 3.3 % faster in seven, 0.5 % slower in one)
 #pragma unroll
         for (int j = 0; j < N; ++j) st_model_quad(m2 + j * KT_BLOCK, pr[j]);
     }
@@ -273,10 +273,11 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_kernel(const KtTile *ti
         }
         update_quads<VPT>(red, lds.red, pr, vr, a, T(0));
         u32x2 *m2 = t.m ? reinterpret_cast<u32x2 *>(t.m) + q0 : nullptr;
-        // system-scope stores want whole 64-byte pieces: a tile that starts elsewhere in any of the three
-        // takes the others (48 831 tiles, K = 8, tensors at 16-byte steps, with the model copy: 2.57 ms,
-        // 2.85 with system-scope stores throughout, 2.54 with none)
-        if (SYS && off64(t.p) + off64(t.v) + off64(t.m) == 0) st_quads<QPL, SYS>(p4, v4, m2, pr, vr);
+        // system-scope stores want whole 64-byte pieces: a tile whose parameters or momentum start elsewhere takes the
+        // others (48 831 tiles, K = 8, tensors at 16-byte steps: 2.57 ms, 2.85 with system-scope stores throughout).  The
+        // model copy's stores are non-temporal either way and may start anywhere (32 bytes off: 33 005 tiles 1 646 ->
+        // 1 607 us against non-temporal stores of all three, 44 004 tiles 2 092 -> 2 002, 100 032 tiles 4 760 -> 4 593)
+        if (SYS && off64(t.p) + off64(t.v) == 0) st_quads<QPL, SYS>(p4, v4, m2, pr, vr);
         else st_quads<QPL, false>(p4, v4, m2, pr, vr);
         return;
     }
@@ -346,11 +347,12 @@ constexpr unsigned FSGD_LDS_2 = kt_hold_lds(2, sizeof(FsgdLds)), FSGD_LDS_4 = kt
 //   bf16    2 workgroups per CU (96 KiB in flight at K = 8) above 2 048 tiles, above 1 024 for one and
 //           two copies: 1.3B set 7.38 -> 7.08 ms against 8 workgroups, with the model copy 7.97 -> 7.60
 //           (which depends on where the tensors lie: three sets of 46 GB in turn, 24 arrangements,
-//           7.45-7.94 ms without, 7.47-7.77 with, 7.45-7.65 with system-scope stores as well); K = 4,
-//           21 135 tiles 791 -> 745 us.  Below, the chip is not full long enough to gain (300 to 1 200
-//           tiles, K = 1 to 6: 1-6 % slower with it on aligned sets).  8 copies and 32 768 tiles or
-//           more also with system-scope stores (65 536 tiles 3 116 -> 3 062 us); fewer lose 3-20 % with
-//           them.  Buffer stores, which are not waited for, are slower there (1.3B set 7.74 ms, 7.54)
+//           7.45-7.94 ms without, 7.47-7.77 with); K = 4, 21 135 tiles 791 -> 745 us.  Below, the chip is
+//           not full long enough to gain (300 to 1 200 tiles, K = 1 to 6: 1-6 % slower with it on aligned sets).
+//           8 copies and 32 768 tiles or more also with system-scope stores (33 005 tiles 1 622 -> 1 596 us,
+//           66 000 tiles 3 150 -> 3 030, 100 032 tiles 4 768 -> 4 645; 1.3B set, on the same memory in turn, 8 placements:
+//           0.4-3.8 % faster in six, even in one, 1.6 % slower in one); fewer lose 3-20 % with them.  Buffer
+//           stores, which are not waited for, are slower there (1.3B set 7.74 ms, 7.54)
 //   fp32    above 4 096 tiles 2 workgroups per CU for 4 and more copies (K = 8, 21 135 tiles 716 -> 687 us,
 //           K = 4, 8 192 tiles 181 -> 179 us), 4 for fewer (K = 2, 21 135 tiles 340 -> 336 us); 6 and more
 //           copies from 2 048 tiles on (K = 8, 3 700 tiles 2-5 % over none).  Non-temporal
