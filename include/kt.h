@@ -49,19 +49,20 @@
  *    weight_decay with kt_plan_set_sgd.
  *    A recorded first_step != 0 would reset the momentum on every replay, so
  *    the SGD calls refuse it under capture (KT_EUNSUPPORTED).
- *  - Large launches of 7 and more copies issue their stores in bursts that every
+ *  - Large launches of many copies issue their stores in bursts that every
  *    workgroup times by the device-wide clock, which the memory system rewards
- *    when the launch has the GPU to itself: kt_fused_step from 1 GiB read in all
- *    copies together (7 and 8 copies from 256 MiB to 2 GiB per copy),
- *    kt_weighted_reduce from 1 GiB per copy (7 and 8 copies) or 4 GiB in all
- *    copies together (more), kt_fused_step_sgd of 11 and more copies from 1.5
- *    to 3 GiB.  1.2 us in every 12 us, or 6 % of a period of 14 to 24 us that
- *    grows with the number of copies.
+ *    when the launch has the GPU to itself: kt_weighted_reduce of 7 and 8
+ *    copies from 1 GiB per copy; kt_fused_step of 8 copies from 256 MiB (F32)
+ *    or 2 GiB (BF16) per copy, of 7 from 1 or 2 GiB; of 10 (F32), 11 (BF16) and
+ *    more copies kt_weighted_reduce from 4 GiB and kt_fused_step from 1 GiB
+ *    read in all copies together; kt_fused_step_sgd of 11 (F32) and more copies
+ *    from 1.5 GiB, of 14 (BF16) from 3 GiB.  1.2 us in every 12 us, or 6 % of a
+ *    period of 14 to 24 us that grows with the number of copies.
  *  - Other large launches ask for more LDS than they use, so that only 2 to 5 of
  *    their workgroups share a CU (22 to 52 KiB of its LDS stay free):
- *    kt_fused_step and kt_weighted_reduce without bursts from 16 to 192 MiB per
- *    copy on, unpack fused with SGD from 64 MiB, and kt_fused_step_sgd above 16
- *    to 64 MiB.
+ *    kt_fused_step and kt_weighted_reduce of 3 and more copies without bursts
+ *    from 16 to 128 MiB per copy on, unpack fused with SGD from 64 MiB, and
+ *    kt_fused_step_sgd from 16 to 64 MiB.
  *  - The environment variable KT_STORE_WINDOW_NS, read once per process, sets the
  *    period of the bursts in nanoseconds; 0, for programs whose other kernels
  *    run beside these calls, switches both the bursts and the LDS requests off.

@@ -133,7 +133,7 @@ template <int BYTES> __device__ __forceinline__ int edge_elem(int q, int es, int
 __device__ __forceinline__ int off64(const void *p) { return (int)(reinterpret_cast<uintptr_t>(p) & 63u); }
 
 // Holds a wave back until the store window opens (KtWindow).  Bounded twice over: the clock
-// always advances, so the condition comes true within one period (12 or 14 us), and the
+// always advances, so the condition comes true within one period (12 to 24 us), and the
 // iteration count ends the loop in any case.  (The low 32 bits of the clock wrap every 43 s at
 // 100 MHz; one period is then irregular.)
 __device__ __forceinline__ void kt_wait_store_window(const KtWindow &w)

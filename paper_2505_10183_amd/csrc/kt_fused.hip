@@ -274,8 +274,9 @@ template <typename T> KtShape fused_shape(int K, int64_t nt)
 
 // 9 and more copies outside the store window: quarter tiles, whose mixed tiles are shared too (a vector with a
 // serial loop over the copies decides small launches: K = 16 fp32 29 tiles 18.3 -> 6.3 us, 222 tiles 22.1 -> 13.0, 763 tiles
-// 41 -> 37.5, bf16 508 tiles 32.6 -> 27.2), held at two per CU above 1 152 (K = 12 fp32 2 713 tiles 5 % faster than whole
-// ones, 1 200 to 1 800 tiles within 2 %; K = 9 there up to 4 % behind).
+// 41 -> 37.5, bf16 508 tiles 32.6 -> 27.2), held at two per CU above 1 152 (against whole ones, two types, K = 9 to 16, 1 141 to
+// 3 006 tiles: 0-8 % faster, K = 9 to 14 up to 2 % slower where whole tiles make full rounds: fp32 K = 9 1 228 tiles
+// 36.7 -> 35.9 us, 1 692 tiles 46.5 -> 46.9, K = 14 1 228 tiles 52.6 -> 53.6, K = 12 2 172 tiles 84.4 -> 79.6).
 inline KtShape fused_manyk_shape(int64_t nt) { return {4, nt > 1152 ? 2u : 0u}; }
 
 template <typename T, int K, bool DEVW>

@@ -68,15 +68,15 @@ int kt_launch_pack(const KtDeviceTables &tb, kt_dtype dt, int64_t tile0,
 int kt_launch_unpack(const KtDeviceTables &tb, kt_dtype dt, int64_t tile0,
                      int64_t ntiles, const void *const *d_bucket_ptrs,
                      float scale, void *const *d_tensor_ptrs, void *stream);
-// Store window of the read-dominated kernels (reduce, fused pass) on large launches: every wave
+// Store window of the read-dominated kernels (reduce, fused pass, one-pass SGD of many copies) on large launches: every wave
 // holds its finished results back until the device-wide constant-rate clock, masked to a period
-// of 12 or 14 us, is inside the first `width` ticks, so that the whole chip alternates between
+// of 12 to 24 us, is inside the first `width` ticks, so that the whole chip alternates between
 // reading and writing instead of sprinkling one written line among eight read ones.  Measured on
 // 8 peers: 72-73 % -> 77-78 % of 8 TB/s, the same within a point for periods of 10-14 us, and a steep
 // loss once the period exceeds the time the resident workgroups need for their loads (about 14-19 us
 // at K = 8; the 14 us period leaves 0-5 us, the 12 us one 2-7), which is why it is used only where
-// that time is known to be longer (K >= 5, many tiles).  Launches of 7 and 8 copies below the limits
-// here, and all of fewer, do better with few workgroups per CU that share tiles (KtShape).
+// that time is known to be longer (7 and more copies, many tiles).  Launches below the limits here, all of up to 6
+// copies, and those of 9 (bf16: and 10) do better with few workgroups per CU that share tiles (KtShape).
 // width == 0: no window.
 struct KtWindow {
     uint32_t period;  // clock ticks
@@ -109,9 +109,13 @@ KtWindow kt_store_window(KtPeriod period, int64_t ntiles, int64_t min_tiles);
 // (K = 16: 8 192 tiles 399 -> 371 us, 4 096 tiles 212 -> 199 us), the fp32 one of 8 is even with quarter
 // tiles from 10 331 to 20 623 tiles and better above (39 522 tiles 923 us, 935), the bf16 one from 131 072 on.  The reduce of 7 and 8 copies
 // is 6-9 % slower with the window at 40 000 tiles and 2-5 % faster at 85 000 (K = 8, fp32 1 984 us against
-// 2 066, bf16 2 016 against 2 075).  With more copies, in the step between pack and unpack, from 262 144
-// tiles read on the step is even or faster (K = 16, 32 768 tiles: 1 927 -> 1 888 us fp32, 1 952 ->
-// 1 862 bf16) and the reduce alone gains 6-10 % (K = 16, 21 135 tiles: 1 040 -> 983 us, 1 032 -> 943).
+// 2 066, bf16 2 016 against 2 075).  With more copies, from 262 144
+// tiles read on, the reduce alone gains 2-8 % over held quarter tiles (fp32 K = 12, 29 439 tiles 1 046 -> 1 008 us; K = 16, 20 749
+// tiles 956 -> 915; K = 24, 29 439 tiles 2 048 -> 1 894; bf16 K = 16, 20 449 tiles 946 -> 907), bf16 of 12 copies loses 1-2 % (30 030
+// tiles 995 -> 1 012).  Inside the step, where the reduce displaces what pack wrote last, the window costs up to 6 % below 1 GiB
+// per copy and 24 copies (fp32 K = 16, 16 574 tiles 929 -> 983 us, 39 661 tiles 2 204 -> 2 249; bf16 K = 12, 39 712 tiles
+// 1 681 -> 1 791, K = 16, 20 449 tiles 1 143 -> 1 168, 30 030 even) and gains 1-2 % there (K = 24, 39 661 tiles 3 106 -> 3 072,
+// bf16 3 170 -> 3 103); it is even with or faster than the whole tiles without a window that the limit was set against.
 #ifndef KT_WINDOW_MIN_READS_FUSED
 #define KT_WINDOW_MIN_READS_FUSED 65536
 #endif

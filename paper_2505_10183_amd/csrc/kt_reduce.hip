@@ -136,11 +136,13 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_reduce_manyk_kernel(const KtTile 
 // the launches had them before (two per CU for 3 to 5 copies), flat out:
 //   K   fp32                                             bf16
 //   2   23 912 tiles 187.7 -> 180.0 us, 14 767 even (not held; held at 3 to 5: 2-10 % slower)   60 883 tiles 487 -> 463 us
-//   3   23 912 tiles 250.5 -> 244.2 us                   18 043 tiles 191.8 -> 185.7 us
+//   3   8 459 tiles 88.5 -> 87.7 us, 23 912 250.5 -> 244.2   8 682 tiles 91.6 -> 89.7 us, 18 043 191.8 -> 185.7
+//       (below, shared and held: 5 416 tiles even, 2 435 3 % slower than whole tiles not held, 7 907 2.5 % faster)
 //   4   36 090 tiles 485 -> 467 us, 7 052 even           11 956 tiles 156.1 -> 153.3 us, 9 081 1 % slower
 //   5   7 052 tiles 113.8 -> 109.7 us, 3 563 2 % slower  18 043 tiles 291.7 -> 280.2 us, 3 526 2 % slower
 //   6   42 203 tiles 832 -> 761 us, 1 957 even           42 502 tiles 837 -> 741 us, 1 528 1 % slower
-//   7   42 203 tiles 958 -> 889 us, 1 957 4 % slower     18 043 tiles 407 -> 375 us, 2 055 even
+//   7   5 877 tiles 128.9 -> 125.5 us, 42 203 958 -> 889,    18 043 tiles 407 -> 375 us, 2 055 even
+//       4 149 1 % slower, 2 047 to 3 472 1-2 % slower
 //   8   39 522 tiles 1 006 -> 920 us, 1 957 1 % slower   39 961 tiles 1 020 -> 942 us, 2 055 55.7 -> 50.5 us
 //       (two per CU; three: 931 us)
 // Below, a launch is a few rounds of workgroups: quarter tiles only where whole ones would leave a sixth of

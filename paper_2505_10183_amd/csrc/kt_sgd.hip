@@ -202,8 +202,8 @@ int kt_launch_unpack_sgd(const KtDeviceTables &tb, kt_dtype dt, int64_t tile0, i
             else { if (a.dev) KT_SGD_LAUNCH(float, 0, true); else KT_SGD_LAUNCH(float, 0, false); }
         } else {
             // model copy of 2 bytes per element: half pieces wherever p starts on an odd 64 bytes.  Non-temporal (19 837 tiles
-            // 517 -> 506 us, 59 899 tiles 1 530 -> 1 507, odd tensors 15 770 tiles 475 -> 438) below 98 304 tiles (120 061 tiles 1 %
-            // slower); fp32 keeps system scope (20 000 tiles 300 -> 295 us without, odd tensors 11 007 tiles 160 -> 168)
+            // 517 -> 506 us, 59 899 tiles 1 526 -> 1 505, odd tensors 15 770 tiles 475 -> 438; 69 818 to 97 261 tiles within 1 % either way)
+            // below 98 304 tiles (104 124 to 138 759 tiles 0.3-0.8 % slower, 158 785 2.5 %); fp32 keeps system scope (20 000 tiles 300 -> 295 us without, odd tensors 11 007 tiles 160 -> 168)
             if (d_model_ptrs && ntiles >= 98304) { if (a.dev) KT_SGD_LAUNCH(uint16_t, 2, true); else KT_SGD_LAUNCH(uint16_t, 2, false); }
             else if (d_model_ptrs) { if (a.dev) KT_SGD_LAUNCH(uint16_t, 1, true); else KT_SGD_LAUNCH(uint16_t, 1, false); }
             else { if (a.dev) KT_SGD_LAUNCH(uint16_t, 0, true); else KT_SGD_LAUNCH(uint16_t, 0, false); }
