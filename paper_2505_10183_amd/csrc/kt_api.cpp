@@ -467,6 +467,7 @@ static kt_status stage_pointers(kt_plan *p, const uint64_t *vals, size_t n, hipS
         return KT_EUNSUPPORTED;
     }
     // the table used least recently, but none that a stream under capture has to be waited for: that would end the capture
+    // (one that several streams have used is waited for with the device, which ends every capture: those are not told apart)
     BesideCapture beside;
     bool passed[KT_SLOTS] = {};
     for (;;) {
