@@ -6,9 +6,9 @@ namespace {
 
 // SPLIT workgroups share a 16 KiB tile, each with KT_TILE_VECS / KT_BLOCK / SPLIT vectors of all K copies per
 // lane in flight together.  The kernel is bound by how well the memory system takes K read streams and
-// one write stream: few bytes in flight (48-96 KB per CU), in workgroups that the dispatcher starts
-// in order, so that the chip sweeps every stream over a narrow front, do best (reduce_shape); persistent
-// workgroups with the same bytes in flight lose 5-10 %.  Copies and output may lie at any element
+// one write stream: few bytes in flight (40-96 KB per CU), in workgroups that the dispatcher starts
+// in order, so that the chip sweeps every stream over a narrow front, each XCD on runs of neighbouring
+// pieces (kt_piece), do best (reduce_shape); persistent workgroups with the same bytes in flight lose 5-10 %.  Copies and output may lie at any element
 // address; the stores are not moved to 64-byte boundaries as pack and unpack do: it costs more
 // than the 3 % of a misaligned non-temporal store stream.  INT: bf16 narrowing in integer instructions
 // (f32_to_bf16_int).  Whole tiles test the window's width whether it is zero or not: without
@@ -16,14 +16,15 @@ namespace {
 template <typename T, int K, bool DEVW, int SPLIT, bool INT>
 __global__ __launch_bounds__(KT_BLOCK) void kt_reduce_kernel(const KtTile *tiles, const int64_t *b_elems,
                                                              const void *const *peer_ptrs, void *const *out_ptrs,
-                                                             KtWindow win, FewWeights wts)
+                                                             uint32_t order, KtWindow win, FewWeights wts)
 {
     constexpr int VE = Elem<T>::VE;
     constexpr int64_t TILE_ELEMS = (int64_t)KT_TILE_VECS * VE;
     constexpr int VPT = KT_TILE_VECS / KT_BLOCK / SPLIT;   // vectors per lane, K loads each, all in flight at once
 
-    const int part = SPLIT == 1 ? 0 : (int)(blockIdx.x % SPLIT);
-    const KtTile tl = ld_tile(tiles + blockIdx.x / SPLIT);
+    const unsigned piece = SPLIT == 1 ? blockIdx.x : kt_piece(order);
+    const int part = (int)(piece % SPLIT);
+    const KtTile tl = ld_tile(tiles + piece / SPLIT);
     const int64_t b_n = ld_table(b_elems + tl.bucket);
     T *out = reinterpret_cast<T *>(ld_table(out_ptrs + tl.bucket));
     const T *x[K];
@@ -88,13 +89,14 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_reduce_kernel(const KtTile *tiles
 template <typename T, bool DEVW, int SPLIT>
 __global__ __launch_bounds__(KT_BLOCK) void kt_reduce_manyk_kernel(const KtTile *tiles, const int64_t *b_elems,
                                                                    const void *const *peer_ptrs, void *const *out_ptrs,
-                                                                   int K, KtWindow win, AllWeights wts)
+                                                                   int K, uint32_t order, KtWindow win, AllWeights wts)
 {
     constexpr int VE = Elem<T>::VE;
     constexpr int64_t TILE_ELEMS = (int64_t)KT_TILE_VECS * VE;
     constexpr int VPT = KT_TILE_VECS / KT_BLOCK / SPLIT;
-    const int part = SPLIT == 1 ? 0 : (int)(blockIdx.x % SPLIT);
-    const KtTile tl = ld_tile(tiles + blockIdx.x / SPLIT);
+    const unsigned piece = SPLIT == 1 ? blockIdx.x : kt_piece(order);
+    const int part = (int)(piece % SPLIT);
+    const KtTile tl = ld_tile(tiles + piece / SPLIT);
     const TileGeom g = tile_geom(tl, ld_table(b_elems + tl.bucket), TILE_ELEMS);
     const int tid = threadIdx.x;
     const void *const *pp = peer_ptrs + (int64_t)g.bucket * K;
@@ -148,17 +150,24 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_reduce_manyk_kernel(const KtTile 
 // Below, a launch is a few rounds of workgroups: quarter tiles only where whole ones would leave a sixth of
 // the last round idle (551 tiles of bf16: K = 8 17.8 -> 15.4 us against 16.3, K = 4 10.5 -> 8.9 against
 // 9.3; 491 tiles, 96 % of two rounds: whole tiles 4-8 % faster).
+// Shared tiles go in runs of 64 KiB per XCD, of 128 KiB up to 3 copies (kt_order), which is 2-6 % faster than launch order
+// (K = 4 fp32 19 993 tiles 259 -> 248 us, 63 057 tiles 825 -> 799; K = 5 fp32 63 057 tiles 1 014 -> 959; K = 6 bf16 31 528 tiles
+// 585 -> 553; K = 7 bf16 698 -> 647; K = 8 fp32 19 993 tiles 480 -> 460, bf16 31 528 tiles 790 -> 742; uneven launches:
+// bf16 596 tiles, K = 5 10.9 -> 10.5).  With runs 3 copies do best with 4 workgroups per CU (fp32 19 993 tiles 201 us with 5,
+// 199 with 4; bf16 31 528 tiles 322, 318) and fp32 of 6 and 7 copies with 2 from 6 144 tiles on (K = 7 19 993 tiles 424 us with 3, 410
+// with 2; K = 6 351, 348; 5 412 tiles even).  Whole tiles stay in launch order: runs are 1 % faster for 4 and more copies at
+// 1 600 to 5 400 tiles and 1-5 % slower below.
 template <typename T> KtShape reduce_shape(int K, int64_t nt)
 {
     const bool half = sizeof(T) == 2;
     switch (K) {
     case 1: break;
     case 2: if (nt >= 12288) return {4, 0}; break;
-    case 3: if (nt >= 8192) return {4, 5}; break;
+    case 3: if (nt >= 8192) return {4, 4}; break;
     case 4: if (nt >= 4096) return nt >= (half ? 12288 : 8192) ? KtShape{4, 3} : KtShape{1, 2}; break;
     case 5: if (nt >= 4096) return {4, 3}; break;
-    case 6: if (nt >= 2048) return {4, 3}; break;
-    case 7: if (nt >= (half ? 2048 : 4096)) return {4, 3}; break;
+    case 6: if (nt >= 2048) return {4, half || nt < 6144 ? 3u : 2u}; break;
+    case 7: if (nt >= (half ? 2048 : 4096)) return {4, half || nt < 6144 ? 3u : 2u}; break;
     default: if (nt >= (half ? 2048 : 3072)) return {4, half ? 3u : 2u}; break;
     }
     return {K >= 2 && kt_uneven(nt) ? 4 : 1, 0};
@@ -167,7 +176,8 @@ template <typename T> KtShape reduce_shape(int K, int64_t nt)
 // 9 and more copies outside the store window.  Up to one tile per CU, and where whole tiles would leave a sixth of
 // two or three rounds idle, quarter tiles (K = 16: 29 tiles fp32 8.6 -> 5.6 us, 111 tiles bf16 14.2 -> 8.0, 577 tiles
 // bf16 28.9 -> 23.7; a workgroup's serial chunks and its own table reads are a quarter); even or 2-10 % slower
-// than whole tiles on full rounds.  From 2 560 tiles on quarter tiles held at two per CU (64 KB in flight; K = 12 fp32
+// than whole tiles on full rounds.  Shared tiles in runs of 64 KiB per XCD (K = 9 fp32 3 243 tiles 87.5 -> 83.1 us, bf16 31 528
+// tiles 882 -> 808; K = 16 bf16 2 706 tiles 124 -> 117).  From 2 560 tiles on quarter tiles held at two per CU (64 KB in flight; K = 12 fp32
 // 2 713 tiles even, 4 149 tiles 4 % faster, 20 749 tiles 769 -> 704 us; bf16 K = 16 7 896 tiles 378 -> 361).
 inline KtShape reduce_manyk_shape(int64_t nt)
 {
@@ -183,15 +193,16 @@ hipError_t launch_reduce_k(const KtTile *tiles, const int64_t *b_elems, int64_t 
     if constexpr (K >= 7) {
         const KtWindow win = kt_store_window(sizeof(T) == 4 ? KT_PERIOD_14 : KT_PERIOD_12, nt, KT_WINDOW_MIN_TILES_REDUCE);
         if (win.width) {
-            kt_reduce_kernel<T, K, DEVW, 1, sizeof(T) == 2><<<dim3((unsigned)nt), block, 0, s>>>(tiles, b_elems, peers, outs, win, FewWeights(w));
+            kt_reduce_kernel<T, K, DEVW, 1, sizeof(T) == 2><<<dim3((unsigned)nt), block, 0, s>>>(tiles, b_elems, peers, outs, 0u, win, FewWeights(w));
             return hipGetLastError();
         }
     }
     const KtShape sh = reduce_shape<T>(K, nt);
     const unsigned lds = kt_shape_lds(sh, 0);
     return launch_in_chunks(tiles, nt, sh.split, [&](const KtTile *t, dim3 grid) {
-        if (sh.split == 1) kt_reduce_kernel<T, K, DEVW, 1, false><<<grid, block, lds, s>>>(t, b_elems, peers, outs, KtWindow{0, 0}, FewWeights(w));
-        else if constexpr (K > 1) kt_reduce_kernel<T, K, DEVW, 4, (sizeof(T) == 2 && K >= 6)><<<grid, block, lds, s>>>(t, b_elems, peers, outs, KtWindow{0, 0}, FewWeights(w));
+        const uint32_t order = kt_order(grid.x, KT_TILE_BYTES / sh.split, sh.split == 1 ? 0 : K <= 3 ? 131072 : 65536);
+        if (sh.split == 1) kt_reduce_kernel<T, K, DEVW, 1, false><<<grid, block, lds, s>>>(t, b_elems, peers, outs, order, KtWindow{0, 0}, FewWeights(w));
+        else if constexpr (K > 1) kt_reduce_kernel<T, K, DEVW, 4, (sizeof(T) == 2 && K >= 6)><<<grid, block, lds, s>>>(t, b_elems, peers, outs, order, KtWindow{0, 0}, FewWeights(w));
     });
 }
 
@@ -209,8 +220,9 @@ hipError_t launch_reduce_t(const KtDeviceTables &tb, int64_t tile0, int64_t nt, 
     const KtShape sh = win.width ? KtShape{1, 0} : reduce_manyk_shape(nt);
     const unsigned lds = kt_shape_lds(sh, 0);
     return launch_in_chunks(tiles, nt, sh.split, [&](const KtTile *t, dim3 grid) {
-        if (sh.split == 1) kt_reduce_manyk_kernel<T, DEVW, 1><<<grid, dim3(KT_BLOCK), lds, s>>>(t, tb.b_elems, peers, outs, K, win, AllWeights(w));
-        else kt_reduce_manyk_kernel<T, DEVW, 4><<<grid, dim3(KT_BLOCK), lds, s>>>(t, tb.b_elems, peers, outs, K, win, AllWeights(w));
+        const uint32_t order = kt_order(grid.x, KT_TILE_BYTES / sh.split, sh.split == 1 ? 0 : 65536);
+        if (sh.split == 1) kt_reduce_manyk_kernel<T, DEVW, 1><<<grid, dim3(KT_BLOCK), lds, s>>>(t, tb.b_elems, peers, outs, K, order, win, AllWeights(w));
+        else kt_reduce_manyk_kernel<T, DEVW, 4><<<grid, dim3(KT_BLOCK), lds, s>>>(t, tb.b_elems, peers, outs, K, order, win, AllWeights(w));
     });
 }
 

@@ -1,0 +1,42 @@
+"""Launches whose workgroups take runs of neighbouring pieces per XCD: pieces in whole groups and left over."""
+import sys
+
+import pytest
+import torch
+
+import oracle
+import paper_2505_10183_amd as kt
+from paper_2505_10183_amd import workloads as wl
+from test_gpu_parity import DEV, host, raw, tdtype
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def announce(request):
+    print("\n[gpu-case] %s" % request.node.nodeid, file=sys.stderr, flush=True)
+    yield
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+
+
+def inputs(dtype, K, elems):
+    plan = kt.Plan([elems], dtype, 0, 16)
+    _, weights = kt.kt_plan_shares([1.0 - 0.05 * k for k in range(K)], 1024)
+    copies = [wl.flat_normal(elems, dtype, 1e-3, 900 + k, DEV) for k in range(K)]
+    want = oracle.weighted_reduce([host(c) for c in copies], weights, dtype, "S")
+    return plan, weights, copies, want
+
+
+# tiles shared by four workgroups: 300 tiles are 1 200 pieces (4 groups of 256 in runs of 128 KiB and 176 pieces in launch order, 9 of
+# 128 in runs of 64 KiB and 48), 320 are whole groups only, 321 leave one tile over
+@pytest.mark.parametrize("dtype,K,tiles,tail", [
+    ("f32", 2, 300, 0), ("f32", 3, 320, 0), ("f32", 8, 321, 4), ("bf16", 4, 300, 8), ("bf16", 7, 320, 0), ("f32", 9, 33, 0),
+    ("f32", 12, 255, 4), ("bf16", 16, 64, 8),
+])
+def test_reduce_in_runs(dtype, K, tiles, tail):
+    plan, weights, copies, want = inputs(dtype, K, tiles * (16384 // (4 if dtype == "f32" else 2)) + tail)
+    out = torch.empty_like(copies[0])
+    plan.kt_weighted_reduce(-1, copies, K, weights, [out])
+    torch.cuda.synchronize()
+    assert raw(host(out)).tobytes() == raw(want).tobytes()
