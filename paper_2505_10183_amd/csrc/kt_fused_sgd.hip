@@ -219,7 +219,7 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_kernel(const KtTile *ti
                                                                 const int64_t *t_offs, const void *const *local_ptrs,
                                                                 const void *const *peer_ptrs, void *const *param_ptrs,
                                                                 void *const *mom_ptrs, void *const *model_ptrs,
-                                                                const int64_t *t_numel, KtSgd a_in,
+                                                                const int64_t *t_numel, uint32_t order, KtSgd a_in,
                                                                 FewWeights wts)
 {
     const FsgdArgs f{local_ptrs, peer_ptrs, param_ptrs, mom_ptrs, model_ptrs};
@@ -229,8 +229,9 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_kernel(const KtTile *ti
     constexpr int KP = K > 1 ? K - 1 : 1;
     __shared__ FsgdLds lds;
 
-    const int part = SPLIT == 1 ? 0 : (int)(blockIdx.x % SPLIT);
-    const KtTile tl = ld_tile(tiles + blockIdx.x / SPLIT);
+    const unsigned piece = SPLIT == 1 ? blockIdx.x : kt_piece(order);
+    const int part = (int)(piece % SPLIT);
+    const KtTile tl = ld_tile(tiles + piece / SPLIT);
     const int64_t b_n = ld_table(b_elems + tl.bucket), t_off = ld_table(t_offs + tl.t0);
     const void *const *pp = f.peer_ptrs + (int64_t)tl.bucket * (K - 1);   // peers 1..K-1 of this bucket
     const T *x[KP];
@@ -292,7 +293,7 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_manyk_kernel(const KtTi
                                                                       const int64_t *t_offs, const void *const *local_ptrs,
                                                                       const void *const *peer_ptrs, void *const *param_ptrs,
                                                                       void *const *mom_ptrs, void *const *model_ptrs,
-                                                                      int K, const int64_t *t_numel, KtSgd a_in,
+                                                                      int K, const int64_t *t_numel, uint32_t order, KtSgd a_in,
                                                                       KtWindow win, AllWeights wts)
 {
     const FsgdArgs f{local_ptrs, peer_ptrs, param_ptrs, mom_ptrs, model_ptrs};
@@ -301,8 +302,9 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_manyk_kernel(const KtTi
     constexpr int VPT = KT_TILE_VECS / KT_BLOCK / SPLIT, QPL = VPT * FsgdShape<T>::QPV;
     __shared__ FsgdLds lds;
 
-    const int part = SPLIT == 1 ? 0 : (int)(blockIdx.x % SPLIT);
-    const KtTile tl = ld_tile(tiles + blockIdx.x / SPLIT);
+    const unsigned piece = SPLIT == 1 ? blockIdx.x : kt_piece(order);
+    const int part = (int)(piece % SPLIT);
+    const KtTile tl = ld_tile(tiles + piece / SPLIT);
     const int64_t b_n = ld_table(b_elems + tl.bucket), t_off = ld_table(t_offs + tl.t0);
     TensorSide<T> t(f, tl.t0);
     const KtSgd a = resolve_sgd(a_in);
@@ -359,6 +361,10 @@ constexpr unsigned FSGD_LDS_2 = kt_hold_lds(2, sizeof(FsgdLds)), FSGD_LDS_4 = kt
 //           stores throughout: system-scope ones gain 2-10 % up to 4 096 tiles where a call finds p and v
 //           of the call before in the last-level cache and lose 2-5 % (64-byte aligned) to 13 % (odd
 //           addresses, 2 700 tiles) where it does not, which is the state a training step is called in
+// Runs of 128 KiB of gradient per XCD (kt_order) but with system-scope stores: fp32 K = 4 1 191 tiles 28.2 -> 26.2 us, 3 243 tiles 71.9 ->
+// 68.2, 63 057 tiles 1 395 -> 1 333; K = 8 2 141 -> 2 030; bf16 K = 6 2 706 tiles 111.9 -> 108.3, K = 8 9 996 tiles 468 -> 459 (one and
+// two copies even there and 2 % faster below).  Not below 640 tiles, where the few slow tiles that hold many tensors
+// come to lie on one XCD (MobileNetV2, 547 tiles 13.2 -> 13.5 us; 197 tiles of odd tensors 13.1 -> 13.7).  With system-scope stores 1 % faster (160 640 tiles) to 5 % slower (76 849).
 struct FsgdLaunch {
     unsigned lds;
     bool sys;
@@ -402,8 +408,11 @@ hipError_t launch_fused_sgd_t(const KtDeviceTables &tb, int64_t tile0, int64_t n
         const KtShape sh = win.width ? KtShape{1, 0} : fsgd_manyk_shape(K, ntiles);
         const unsigned lds = kt_shape_lds(sh, (unsigned)sizeof(FsgdLds));
         return launch_in_chunks(tb.tiles + tile0, ntiles, sh.split, [&](const KtTile *tiles, dim3 grid) {
+            // runs of 64 KiB per XCD for shared tiles (K = 12 bf16 2 706 tiles 161 -> 153 us, K = 9 bf16 31 528 tiles 1 611 -> 1 534);
+            // fp32 of 9 and 10 copies 1 % slower with them (K = 9 19 993 tiles 676 us, 687)
+            const uint32_t order = kt_order(grid.x, KT_TILE_BYTES / sh.split, sh.split == 1 || ntiles < 640 || (sizeof(T) == 4 && K < 11) ? 0 : 65536);
 #define KT_ARGS \
-    tiles, tb.b_elems, tb.t_off, f.local_ptrs, f.peer_ptrs, f.param_ptrs, f.mom_ptrs, f.model_ptrs, K, tb.t_numel, a, win, AllWeights(w)
+    tiles, tb.b_elems, tb.t_off, f.local_ptrs, f.peer_ptrs, f.param_ptrs, f.mom_ptrs, f.model_ptrs, K, tb.t_numel, order, a, win, AllWeights(w)
             if (sh.split == 1) kt_fused_sgd_manyk_kernel<T, DEVW, 1><<<grid, block, lds, s>>>(KT_ARGS);
             else kt_fused_sgd_manyk_kernel<T, DEVW, 4><<<grid, block, lds, s>>>(KT_ARGS);
 #undef KT_ARGS
@@ -412,8 +421,9 @@ hipError_t launch_fused_sgd_t(const KtDeviceTables &tb, int64_t tile0, int64_t n
     FsgdLaunch how = fsgd_launch<T>(K, ntiles);
     if (!kt_may_hold()) how.lds = 0;
     return launch_in_chunks(tb.tiles + tile0, ntiles, FsgdShape<T>::SPLIT, [&](const KtTile *tiles, dim3 grid) {
+        const uint32_t order = kt_order(grid.x, KT_TILE_BYTES / FsgdShape<T>::SPLIT, how.sys || ntiles < 640 ? 0 : 131072);
 #define KT_ARGS \
-    tiles, tb.b_elems, tb.t_off, f.local_ptrs, f.peer_ptrs, f.param_ptrs, f.mom_ptrs, f.model_ptrs, tb.t_numel, a, FewWeights(w)
+    tiles, tb.b_elems, tb.t_off, f.local_ptrs, f.peer_ptrs, f.param_ptrs, f.mom_ptrs, f.model_ptrs, tb.t_numel, order, a, FewWeights(w)
         switch (K) {
 #define KT_CASE(KK)                                                                                                     \
     case KK:                                                                                                            \

@@ -40,3 +40,23 @@ def test_reduce_in_runs(dtype, K, tiles, tail):
     plan.kt_weighted_reduce(-1, copies, K, weights, [out])
     torch.cuda.synchronize()
     assert raw(host(out)).tobytes() == raw(want).tobytes()
+
+
+@pytest.mark.parametrize("dtype,K,tiles,tail", [
+    ("f32", 1, 640, 0), ("f32", 4, 660, 4), ("f32", 8, 641, 0), ("bf16", 2, 641, 8), ("bf16", 8, 640, 0), ("bf16", 12, 704, 8), ("f32", 16, 641, 0),
+])
+def test_one_pass_sgd_in_runs(dtype, K, tiles, tail):
+    plan, weights, copies, want = inputs(dtype, K, tiles * (16384 // (4 if dtype == "f32" else 2)) + tail)
+    n = copies[0].numel()
+    p, v = wl.flat_normal(n, "f32", 2e-2, 1, DEV), wl.flat_normal(n, "f32", 1e-3, 2, DEV)
+    p2, v2 = p.clone(), v.clone()
+    m, m2 = (torch.zeros(n, dtype=torch.bfloat16, device=DEV) for _ in range(2))
+    plan.kt_fused_step_sgd(-1, copies[:1], copies[1:], K, weights, 0.5, [p], [v], [m], 0.05, 0.9, 5e-4, False)
+    # the update of the oracle's sum, in the kernel that other tests compare with the oracle
+    red = torch.empty_like(copies[0])
+    kind = torch.int32 if dtype == "f32" else torch.int16
+    red.view(kind).copy_(torch.from_numpy(raw(want).view("i4" if dtype == "f32" else "i2")))
+    plan.kt_bucket_unpack_sgd_master(-1, [red], 0.5, [p2], [v2], [m2], 0.05, 0.9, 5e-4, False)
+    torch.cuda.synchronize()
+    assert torch.equal(p.view(torch.int32), p2.view(torch.int32)) and torch.equal(v.view(torch.int32), v2.view(torch.int32))
+    assert torch.equal(m.view(torch.int16), m2.view(torch.int16))
