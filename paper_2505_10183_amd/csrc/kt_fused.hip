@@ -88,8 +88,10 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_kernel(const KtTile *tiles,
     constexpr int KP = K > 1 ? K - 1 : 1;
     __shared__ LdsTable lds;
 
-    const int part = SPLIT == 1 ? 0 : (int)(blockIdx.x % SPLIT);
-    const KtTile tl = ld_tile(tiles + blockIdx.x / SPLIT);
+    // launches without a window have their order in the place of its period (one argument more would no longer arrive in registers)
+    const unsigned piece = SPLIT > 1 || K == 4 || K == 5 ? kt_piece(win.period) : blockIdx.x;      // fused_run
+    const int part = (int)(piece % SPLIT);
+    const KtTile tl = ld_tile(tiles + piece / SPLIT);
     const int64_t b_n = ld_table(b_elems + tl.bucket), t_off = ld_table(t_offs + tl.t0);
     const T *src = reinterpret_cast<const T *>(ld_table(local_ptrs + tl.t0));
     T *dst = reinterpret_cast<T *>(ld_table(out_ptrs + tl.t0));
@@ -193,7 +195,7 @@ template <typename T, bool DEVW, int SPLIT>
 __global__ __launch_bounds__(KT_BLOCK) void kt_fused_manyk_kernel(const KtTile *tiles, const int64_t *b_elems,
                                                                   const int64_t *t_offs, const void *const *local_ptrs,
                                                                   const void *const *peer_ptrs, void *const *out_ptrs,
-                                                                  float scale, int K, KtWindow win,
+                                                                  uint32_t order, int K, float scale, KtWindow win,
                                                                   const int64_t *t_numel, AllWeights wts)
 {
     constexpr int VE = Elem<T>::VE;
@@ -201,8 +203,9 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_manyk_kernel(const KtTile *
     constexpr int VPT = KT_TILE_VECS / KT_BLOCK / SPLIT;
     __shared__ LdsTable lds;
 
-    const int part = SPLIT == 1 ? 0 : (int)(blockIdx.x % SPLIT);
-    const KtTile tl = ld_tile(tiles + blockIdx.x / SPLIT);
+    const unsigned piece = SPLIT == 1 ? blockIdx.x : kt_piece(order);
+    const int part = (int)(piece % SPLIT);
+    const KtTile tl = ld_tile(tiles + piece / SPLIT);
     const int64_t b_n = ld_table(b_elems + tl.bucket), t_off = ld_table(t_offs + tl.t0);
     const T *src = reinterpret_cast<const T *>(ld_table(local_ptrs + tl.t0));
     T *dst = reinterpret_cast<T *>(ld_table(out_ptrs + tl.t0));
@@ -264,7 +267,7 @@ template <typename T> KtShape fused_shape(int K, int64_t nt)
     } else {
         if (K == 4 && nt >= 8192) return {S, 3};
         if (K == 5 && nt >= 6144) return {S, 3};
-        if (K >= 6 && nt >= 4096) return {S, K == 8 ? 2u : 3u};
+        if (K >= 6 && nt >= 4096) return {S, K == 8 || (K == 7 && nt >= 6144) ? 2u : 3u};
         if (K >= 4 && kt_uneven(nt)) return {S, 0};
     }
     // whole tiles, two per CU for 3 to 5 copies (2 729 tiles, K = 4: 38.0 -> 37.7 us against none held; 3 copies,
@@ -272,9 +275,22 @@ template <typename T> KtShape fused_shape(int K, int64_t nt)
     return {1, K >= 3 && K <= 5 && nt >= (K == 3 ? 8192 : 2048) ? 2u : 0u};
 }
 
+// Bytes of a copy that an XCD takes in a run (kt_order; 0: launch order): 64 KiB on shared tiles (fp32 K = 4 19 993 tiles 266 -> 252 us,
+// 63 057 tiles 843 -> 806, K = 5 1 020 -> 983; bf16 K = 6 31 528 tiles 587 -> 562, K = 7 677 -> 655; fp32 K = 7 with 2 workgroups per CU
+// instead of 3 19 993 tiles 436 -> 419), 128 KiB on the half tiles of 4 and 5 copies and where whole tiles of these are held (K = 5
+// fp32 3 243 tiles 53.0 -> 51.6 us, bf16 9 996 tiles 159 -> 155).  Launches that hold nothing stay in launch
+// order (whole tiles, K = 4 fp32 1 950 tiles 2 % slower in runs), and the whole tiles of other numbers of copies do not look for an order at
+// all (K = 3 bf16, 596 tiles 9.7 us, 9.9 when they do).
+template <typename T> int fused_run(int K, int64_t nt, const KtShape &sh)
+{
+    if (!sh.wgs || nt < 1024) return 0;
+    return sh.split == 1 || (sizeof(T) == 2 && K < 6) ? 131072 : 65536;
+}
+
 // 9 and more copies outside the store window: quarter tiles, whose mixed tiles are shared too (a vector with a
 // serial loop over the copies decides small launches: K = 16 fp32 29 tiles 18.3 -> 6.3 us, 222 tiles 22.1 -> 13.0, 763 tiles
-// 41 -> 37.5, bf16 508 tiles 32.6 -> 27.2), held at two per CU above 1 152 (against whole ones, two types, K = 9 to 16, 1 141 to
+// 41 -> 37.5, bf16 508 tiles 32.6 -> 27.2) in runs of 64 KiB per XCD from 640 tiles on (K = 9 fp32 3 243 tiles 87.5 -> 84.8 us, bf16 31 528
+// tiles 889 -> 851; K = 16 bf16 975 tiles 48.3 -> 45.7), held at two per CU above 1 152 (against whole ones, two types, K = 9 to 16, 1 141 to
 // 3 006 tiles: 0-8 % faster, K = 9 to 14 up to 2 % slower where whole tiles make full rounds: fp32 K = 9 1 228 tiles
 // 36.7 -> 35.9 us, 1 692 tiles 46.5 -> 46.9, K = 14 1 228 tiles 52.6 -> 53.6, K = 12 2 172 tiles 84.4 -> 79.6).
 inline KtShape fused_manyk_shape(int64_t nt) { return {4, nt > 1152 ? 2u : 0u}; }
@@ -295,8 +311,8 @@ hipError_t launch_fused_k(const KtDeviceTables &tb, const KtTile *tiles, int64_t
     }
     const KtShape sh = fused_shape<T>(K, nt);
     const unsigned lds = kt_shape_lds(sh, (unsigned)sizeof(LdsTable));
-    const KtWindow off{0, 0};
     return launch_in_chunks(tiles, nt, sh.split, [&](const KtTile *t, dim3 grid) {
+        const KtWindow off{kt_order(grid.x, KT_TILE_BYTES / sh.split, fused_run<T>(K, nt, sh)), 0};
         if constexpr (K >= 4) {
             if (sh.split > 1) { kt_fused_kernel<T, K, DEVW, FusedSplit<T>::N, (sizeof(T) == 2 && K >= 6)><<<grid, block, lds, s>>>(KT_ARGS(t, off)); return; }
         }
@@ -320,7 +336,8 @@ hipError_t launch_fused_t(const KtDeviceTables &tb, int64_t tile0, int64_t nt, c
     const KtShape sh = win.width ? KtShape{1, 0} : fused_manyk_shape(nt);
     const unsigned lds = kt_shape_lds(sh, (unsigned)sizeof(LdsTable));
     return launch_in_chunks(tiles, nt, sh.split, [&](const KtTile *t, dim3 grid) {
-#define KT_ARGS t, tb.b_elems, tb.t_off, locals, peers, outs, scale, K, win, tb.t_numel, AllWeights(w)
+        const uint32_t order = kt_order(grid.x, KT_TILE_BYTES / sh.split, sh.split == 1 || nt < 640 ? 0 : 65536);
+#define KT_ARGS t, tb.b_elems, tb.t_off, locals, peers, outs, order, K, scale, win, tb.t_numel, AllWeights(w)
         if (sh.split == 1) kt_fused_manyk_kernel<T, DEVW, 1><<<grid, dim3(KT_BLOCK), lds, s>>>(KT_ARGS);
         else kt_fused_manyk_kernel<T, DEVW, 4><<<grid, dim3(KT_BLOCK), lds, s>>>(KT_ARGS);
 #undef KT_ARGS

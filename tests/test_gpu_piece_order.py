@@ -60,3 +60,15 @@ def test_one_pass_sgd_in_runs(dtype, K, tiles, tail):
     torch.cuda.synchronize()
     assert torch.equal(p.view(torch.int32), p2.view(torch.int32)) and torch.equal(v.view(torch.int32), v2.view(torch.int32))
     assert torch.equal(m.view(torch.int16), m2.view(torch.int16))
+
+
+@pytest.mark.parametrize("dtype,K,tiles,tail", [
+    ("f32", 4, 2048, 0), ("f32", 5, 2067, 4), ("f32", 6, 4097, 0), ("bf16", 5, 2049, 8), ("bf16", 6, 1024, 0), ("bf16", 8, 1061, 8),
+    ("f32", 9, 640, 4), ("bf16", 12, 673, 0),
+])
+def test_fused_pass_in_runs(dtype, K, tiles, tail):
+    plan, weights, copies, want = inputs(dtype, K, tiles * (16384 // (4 if dtype == "f32" else 2)) + tail)
+    out = torch.empty_like(copies[0])
+    plan.kt_fused_step(-1, copies[:1], copies[1:], K, weights, 1.0, [out])       # scale 1: the sum itself
+    torch.cuda.synchronize()
+    assert raw(host(out)).tobytes() == raw(want).tobytes()
