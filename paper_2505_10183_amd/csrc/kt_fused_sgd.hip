@@ -218,8 +218,8 @@ template <typename T, int K, bool DEVW, bool SYS>
 __global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_kernel(const KtTile *tiles, const int64_t *b_elems,
                                                                 const int64_t *t_offs, const void *const *local_ptrs,
                                                                 const void *const *peer_ptrs, void *const *param_ptrs,
-                                                                void *const *mom_ptrs, void *const *model_ptrs,
-                                                                const int64_t *t_numel, uint32_t order, KtSgd a_in,
+                                                                uint32_t order, void *const *mom_ptrs,
+                                                                void *const *model_ptrs, const int64_t *t_numel, KtSgd a_in,
                                                                 FewWeights wts)
 {
     const FsgdArgs f{local_ptrs, peer_ptrs, param_ptrs, mom_ptrs, model_ptrs};
@@ -291,9 +291,9 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_kernel(const KtTile *ti
 template <typename T, bool DEVW, int SPLIT>
 __global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_manyk_kernel(const KtTile *tiles, const int64_t *b_elems,
                                                                       const int64_t *t_offs, const void *const *local_ptrs,
-                                                                      const void *const *peer_ptrs, void *const *param_ptrs,
+                                                                      const void *const *peer_ptrs, void *const *param_ptrs, uint32_t order, int K,
                                                                       void *const *mom_ptrs, void *const *model_ptrs,
-                                                                      int K, const int64_t *t_numel, uint32_t order, KtSgd a_in,
+                                                                      const int64_t *t_numel, KtSgd a_in,
                                                                       KtWindow win, AllWeights wts)
 {
     const FsgdArgs f{local_ptrs, peer_ptrs, param_ptrs, mom_ptrs, model_ptrs};
@@ -412,7 +412,7 @@ hipError_t launch_fused_sgd_t(const KtDeviceTables &tb, int64_t tile0, int64_t n
             // fp32 of 9 and 10 copies 1 % slower with them (K = 9 19 993 tiles 676 us, 687)
             const uint32_t order = kt_order(grid.x, KT_TILE_BYTES / sh.split, sh.split == 1 || ntiles < 640 || (sizeof(T) == 4 && K < 11) ? 0 : 65536);
 #define KT_ARGS \
-    tiles, tb.b_elems, tb.t_off, f.local_ptrs, f.peer_ptrs, f.param_ptrs, f.mom_ptrs, f.model_ptrs, K, tb.t_numel, order, a, win, AllWeights(w)
+    tiles, tb.b_elems, tb.t_off, f.local_ptrs, f.peer_ptrs, f.param_ptrs, order, K, f.mom_ptrs, f.model_ptrs, tb.t_numel, a, win, AllWeights(w)
             if (sh.split == 1) kt_fused_sgd_manyk_kernel<T, DEVW, 1><<<grid, block, lds, s>>>(KT_ARGS);
             else kt_fused_sgd_manyk_kernel<T, DEVW, 4><<<grid, block, lds, s>>>(KT_ARGS);
 #undef KT_ARGS
@@ -423,7 +423,7 @@ hipError_t launch_fused_sgd_t(const KtDeviceTables &tb, int64_t tile0, int64_t n
     return launch_in_chunks(tb.tiles + tile0, ntiles, FsgdShape<T>::SPLIT, [&](const KtTile *tiles, dim3 grid) {
         const uint32_t order = kt_order(grid.x, KT_TILE_BYTES / FsgdShape<T>::SPLIT, how.sys || ntiles < 640 ? 0 : 131072);
 #define KT_ARGS \
-    tiles, tb.b_elems, tb.t_off, f.local_ptrs, f.peer_ptrs, f.param_ptrs, f.mom_ptrs, f.model_ptrs, tb.t_numel, order, a, FewWeights(w)
+    tiles, tb.b_elems, tb.t_off, f.local_ptrs, f.peer_ptrs, f.param_ptrs, order, f.mom_ptrs, f.model_ptrs, tb.t_numel, a, FewWeights(w)
         switch (K) {
 #define KT_CASE(KK)                                                                                                     \
     case KK:                                                                                                            \
