@@ -92,7 +92,7 @@ template <typename T, int MASTER, bool DEVS>
 __global__ __launch_bounds__(KT_BLOCK) void kt_unpack_sgd_kernel(const KtTile *tiles, const int64_t *b_elems,
                                                                  const int64_t *t_offs, const void *const *bucket_ptrs,
                                                                  void *const *param_ptrs, void *const *mom_ptrs,
-                                                                 void *const *model_ptrs, KtSgd a,
+                                                                 uint32_t order, void *const *model_ptrs, KtSgd a,
                                                                  const int64_t *t_numel)
 {
     constexpr int VE = Elem<T>::VE;
@@ -100,8 +100,9 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_unpack_sgd_kernel(const KtTile *t
     constexpr int SPLIT = SgdShape<T>::SPLIT, PBYTES = SgdShape<T>::PBYTES;
     __shared__ LdsTable lds;
 
-    const int part = SPLIT == 1 ? 0 : (int)(blockIdx.x % SPLIT);
-    const KtTile tl = ld_tile(tiles + blockIdx.x / SPLIT);
+    const unsigned piece = kt_piece(order);
+    const int part = (int)(piece % SPLIT);
+    const KtTile tl = ld_tile(tiles + piece / SPLIT);
     const int64_t b_n = ld_table(b_elems + tl.bucket), t_off = ld_table(t_offs + tl.t0);
     const T *src = reinterpret_cast<const T *>(ld_table(bucket_ptrs + tl.bucket));
     float *p = reinterpret_cast<float *>(ld_table(param_ptrs + tl.t0));
@@ -183,6 +184,14 @@ static unsigned sgd_lds(kt_dtype dt, int64_t ntiles)
     return kt_hold_lds(dt == KT_F32 ? 4 : 5, (unsigned)sizeof(LdsTable));
 }
 
+// Bytes of gradient that an XCD takes in a run (kt_order; 0: launch order).  fp32 from 1 024 tiles on (5 412 tiles 72.9 -> 69.9 us,
+// 19 993 tiles 264.5 -> 262; 63 057 tiles 1 % either way); bf16, whose stores are system-scope ones, from 640 to 4 095 (with the
+// model copy 975 tiles 27.5 -> 27.1 us, 1 622 tiles 47.2 -> 46.5, odd tensors 1 519 tiles 49.5 -> 45.5; 9 996 tiles 257 us, 265 in runs).
+static int sgd_run(kt_dtype dt, int64_t ntiles)
+{
+    return (dt == KT_F32 ? ntiles >= 1024 && ntiles < 32768 : ntiles >= 640 && ntiles < 4096) ? 131072 : 0;
+}
+
 }  // namespace
 
 int kt_launch_unpack_sgd(const KtDeviceTables &tb, kt_dtype dt, int64_t tile0, int64_t ntiles,
@@ -194,9 +203,10 @@ int kt_launch_unpack_sgd(const KtDeviceTables &tb, kt_dtype dt, int64_t tile0, i
     const int split = dt == KT_F32 ? SgdShape<float>::SPLIT : SgdShape<uint16_t>::SPLIT;
     const unsigned lds = sgd_lds(dt, ntiles);
     return (int)launch_in_chunks(tb.tiles + tile0, ntiles, split, [&](const KtTile *tiles, dim3 grid) {
+        const uint32_t order = kt_order(grid.x, KT_TILE_BYTES / split, sgd_run(dt, ntiles));
 #define KT_SGD_LAUNCH(TT, MM, DD)                                                                                    \
     kt_unpack_sgd_kernel<TT, MM, DD><<<grid, block, lds, s>>>(tiles, tb.b_elems, tb.t_off, d_bucket_ptrs, d_param_ptrs, \
-                                                              d_mom_ptrs, d_model_ptrs, a, tb.t_numel)
+                                                              d_mom_ptrs, order, d_model_ptrs, a, tb.t_numel)
         if (dt == KT_F32) {
             if (d_model_ptrs) { if (a.dev) KT_SGD_LAUNCH(float, 2, true); else KT_SGD_LAUNCH(float, 2, false); }
             else { if (a.dev) KT_SGD_LAUNCH(float, 0, true); else KT_SGD_LAUNCH(float, 0, false); }

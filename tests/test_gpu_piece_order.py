@@ -72,3 +72,29 @@ def test_fused_pass_in_runs(dtype, K, tiles, tail):
     plan.kt_fused_step(-1, copies[:1], copies[1:], K, weights, 1.0, [out])       # scale 1: the sum itself
     torch.cuda.synchronize()
     assert raw(host(out)).tobytes() == raw(want).tobytes()
+
+
+@pytest.mark.parametrize("dtype,tiles,tail,master", [
+    ("f32", 1024, 0, False), ("f32", 1061, 4, True), ("bf16", 640, 0, False), ("bf16", 703, 8, True), ("bf16", 4095, 0, True),
+])
+def test_sgd_on_unpack_in_runs(dtype, tiles, tail, master):
+    n = tiles * (16384 // (4 if dtype == "f32" else 2)) + tail
+    g = wl.flat_normal(n, dtype, 1e-3, 7, DEV)
+    p, v = wl.flat_normal(n, "f32", 2e-2, 1, DEV), wl.flat_normal(n, "f32", 1e-3, 2, DEV)
+    want_p, want_v, want_m = p.clone(), v.clone(), torch.zeros(n, dtype=torch.bfloat16, device=DEV)
+    m = torch.zeros_like(want_m)
+
+    def update(grad, params, momenta, models):
+        plan = kt.Plan([grad.numel()], dtype, 0, 16)
+        if master:
+            plan.kt_bucket_unpack_sgd_master(-1, [grad], 0.5, [params], [momenta], [models], 0.05, 0.9, 5e-4, False)
+        else:
+            plan.kt_bucket_unpack_sgd(-1, [grad], 0.5, [params], [momenta], 0.05, 0.9, 5e-4, False)
+        torch.cuda.synchronize()
+
+    update(g, p, v, m)
+    part = 512 * (16384 // (4 if dtype == "f32" else 2))       # launches in launch order, which other tests compare with the checker
+    for at in range(0, n, part):
+        update(*[t[at:at + part] for t in (g, want_p, want_v, want_m)])
+    assert torch.equal(p.view(torch.int32), want_p.view(torch.int32)) and torch.equal(v.view(torch.int32), want_v.view(torch.int32))
+    assert torch.equal(m.view(torch.int16), want_m.view(torch.int16))
