@@ -1,19 +1,26 @@
-"""Thin ctypes binding over libkt.so: argument marshalling only.
+"""Thin binding over libkt.so: argument marshalling only.
 
 Every step of the path (share planning, bucket layout, pack, reduce, unpack)
 runs inside the C-ABI library; this module converts Python lists / torch
 tensors to the pointers and sizes the C functions take and raises on a non-zero
 status.  There is no fallback: if the library is missing, loading fails.
+
+The device calls that a training step makes go through _kt_marshal.so where their arguments have
+the plain forms (lists of tensors, marshalled arrays) and torch is there; everything
+else goes through ctypes.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
+import sys
 from array import array
 from typing import List, Optional, Sequence, Tuple
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libkt.so")
+MARSHAL_PATH = os.path.join(_HERE, "_kt_marshal.so")
 
 KT_F32, KT_BF16 = 0, 1
 KT_ALL_BUCKETS = -1
@@ -21,6 +28,7 @@ KT_MAX_PEERS = 64
 _DTYPES = {"f32": KT_F32, "bf16": KT_BF16}
 
 _lib = None
+_calls = None
 
 
 class KtError(RuntimeError):
@@ -101,6 +109,27 @@ def lib() -> ctypes.CDLL:
             getattr(L, n).restype = i32
         _lib = L
     return _lib
+
+
+def _native():
+    """The plain device calls in native code; None while torch is not there (addresses as ints, host calls)."""
+    global _calls
+    if _calls is None and "torch" in sys.modules:
+        if not os.path.exists(MARSHAL_PATH):
+            raise RuntimeError(
+                "_kt_marshal.so is not built (%s); run __graft_entry__.build() or "
+                "python paper_2505_10183_amd/build.py" % MARSHAL_PATH)
+        import torch        # complete before the module that is linked against it
+        if not hasattr(torch._C, "_cuda_getCurrentRawStream"):
+            return None
+        spec = importlib.util.spec_from_file_location("_kt_marshal", MARSHAL_PATH)
+        m = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(m)
+        L = lib()
+        _calls = m.Calls(*[ctypes.cast(f, ctypes.c_void_p).value for f in (
+            L.kt_bucket_pack, L.kt_weighted_reduce, L.kt_bucket_unpack_scale, L.kt_fused_step, L.kt_bucket_unpack_sgd,
+            L.kt_bucket_unpack_sgd_master, L.kt_fused_step_sgd)])
+    return _calls
 
 
 def _check(status: int):
@@ -212,11 +241,12 @@ class Plan:
         _check(lib().kt_plan_create(arr, T, _DTYPES[dtype], int(cap_bytes), int(align_bytes), ctypes.byref(h)))
         self._h = h
         self._nb = lib().kt_plan_num_buckets(h)
+        self._id = (h.value, T, self._nb)       # what the native calls start with
 
     def close(self):
         if getattr(self, "_h", None):
             _check(lib().kt_plan_destroy(self._h))
-            self._h = None
+            self._h = self._id = None
 
     def __del__(self):
         try:
@@ -257,7 +287,17 @@ class Plan:
     # -- device calls: marshal pointers, call, raise on error ---------------
     # The library copies whole arrays (T tensor pointers, num_buckets bucket
     # pointers, num_buckets * K peer pointers) whatever bucket is selected, so
-    # every array's length is checked here before its address crosses the ABI.
+    # every array's length is checked here (or in the native calls) before its address crosses the ABI.
+
+    def _plainly(self, name: str, *args) -> bool:
+        """Make the call natively; False where an argument is of a form that is left to ctypes."""
+        calls = _calls or _native()
+        if calls is None or self._id is None:
+            return False
+        status = getattr(calls, name)(*self._id, *args)
+        if status:
+            _check(status)
+        return status is not None
 
     def marshal(self, items: Sequence) -> ctypes.Array:
         """Pre-marshalled pointer array (reusable across calls)."""
@@ -287,12 +327,16 @@ class Plan:
         _check(lib().kt_plan_set_weights(self._h, w, K, _stream(stream)))
 
     def kt_bucket_pack(self, bucket: int, tensors, bucket_bufs, stream=None):
+        if self._plainly("pack", bucket, tensors, bucket_bufs, stream):
+            return
         T, nb = len(self.numels), self.num_buckets
         _check(lib().kt_bucket_pack(self._h, bucket, self._arr(tensors, T, "tensor_ptrs"),
                                     self._arr(bucket_bufs, nb, "bucket_bufs"), _stream(stream)))
 
     def kt_weighted_reduce(self, bucket: int, peer_bufs, K: int, weights, out_bufs, stream=None):
         """peer_bufs: flat sequence, entry [b * K + k]."""
+        if self._plainly("reduce", bucket, K, peer_bufs, weights, out_bufs, stream):
+            return
         nb = self.num_buckets
         if not 1 <= K <= KT_MAX_PEERS:      # the library rejects K before it reads any array
             _check(lib().kt_weighted_reduce(self._h, bucket, None, K, None, None, _stream(stream)))
@@ -301,6 +345,8 @@ class Plan:
                                         _stream(stream)))
 
     def kt_bucket_unpack_scale(self, bucket: int, bucket_bufs, scale: float, tensors, stream=None):
+        if self._plainly("unpack", bucket, bucket_bufs, scale, tensors, stream):
+            return
         T, nb = len(self.numels), self.num_buckets
         _check(lib().kt_bucket_unpack_scale(self._h, bucket, self._arr(bucket_bufs, nb, "bucket_bufs"), float(scale),
                                             self._arr(tensors, T, "tensor_ptrs"), _stream(stream)))
@@ -316,6 +362,8 @@ class Plan:
     def kt_fused_step(self, bucket: int, local_tensors, peer_bufs, K: int, weights, scale: float, out_tensors,
                       stream=None):
         """peer_bufs: flat sequence over peers 1..K-1, entry [b * (K-1) + (k-1)]."""
+        if self._plainly("fused", bucket, K, local_tensors, peer_bufs, weights, scale, out_tensors, stream):
+            return
         self._fused(lib().kt_fused_step, bucket, local_tensors, peer_bufs, K, weights, scale, out_tensors, stream)
 
     def kt_fused_step_noalloc(self, bucket: int, local_tensors, peer_bufs, K: int, weights, scale: float,
@@ -326,6 +374,8 @@ class Plan:
 
     def kt_bucket_unpack_sgd(self, bucket: int, bucket_bufs, scale: float, params, momenta, lr: float,
                              momentum: float, weight_decay: float, first_step: bool, stream=None):
+        if self._plainly("sgd", bucket, bucket_bufs, scale, params, momenta, lr, momentum, weight_decay, first_step, stream):
+            return
         T, nb = len(self.numels), self.num_buckets
         _check(lib().kt_bucket_unpack_sgd(self._h, bucket, self._arr(bucket_bufs, nb, "bucket_bufs"), float(scale),
                                           self._arr(params, T, "tensor_ptrs (parameters)"),
@@ -336,6 +386,9 @@ class Plan:
     def kt_bucket_unpack_sgd_master(self, bucket: int, bucket_bufs, scale: float, masters, momenta, models,
                                     lr: float, momentum: float, weight_decay: float, first_step: bool, stream=None):
         """Mixed precision: binary32 master parameters and momentum updated in place, bf16 model copy written."""
+        if self._plainly("master", bucket, bucket_bufs, scale, masters, momenta, models, lr, momentum, weight_decay,
+                         first_step, stream):
+            return
         T, nb = len(self.numels), self.num_buckets
         _check(lib().kt_bucket_unpack_sgd_master(self._h, bucket, self._arr(bucket_bufs, nb, "bucket_bufs"),
                                                  float(scale), self._arr(masters, T, "tensor_ptrs (master parameters)"),
@@ -348,6 +401,9 @@ class Plan:
                           models, lr: float, momentum: float, weight_decay: float, first_step: bool, stream=None):
         """K gradient copies -> updated parameters in one pass.  peer_bufs: flat sequence, entry
         [b * (K-1) + (k-1)] for k = 1..K-1; models=None: no bf16 model copy."""
+        if self._plainly("fused_sgd", bucket, K, local_tensors, peer_bufs, weights, scale, params, momenta, models, lr,
+                         momentum, weight_decay, first_step, stream):
+            return
         T, nb = len(self.numels), self.num_buckets
         if not 1 <= K <= KT_MAX_PEERS:
             _check(lib().kt_fused_step_sgd(self._h, bucket, None, None, K, None, 1.0, None, None, None, 0.0, 0.0, 0.0, 0,

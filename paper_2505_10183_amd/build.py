@@ -52,6 +52,28 @@ def build(verbose: bool = False, extra_defines=(), out: str = LIB) -> str:
     return out
 
 
+MARSHAL_LIB = os.path.join(HERE, "_kt_marshal.so")
+
+
+def build_marshal(verbose: bool = False) -> str:
+    """Compile the native half of the Python binding (host code only, against the installed torch)."""
+    import sysconfig
+    import torch
+    base = os.path.dirname(torch.__file__)
+    tmp = MARSHAL_LIB + ".tmp%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+           "-I", os.path.join(ROOT, "include"), "-isystem", os.path.join(base, "include"),
+           "-isystem", os.path.join(base, "include", "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"], os.path.join(CSRC, "kt_marshal.cpp"), "-o", tmp,
+           "-L", os.path.join(base, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    os.replace(tmp, MARSHAL_LIB)
+    return MARSHAL_LIB
+
+
 PROBE_SRC = os.path.join(ROOT, "bench_probe.hip")
 PROBE_LIB = os.path.join(ROOT, "libkt_bench_probe.so")
 
@@ -78,4 +100,5 @@ if __name__ == "__main__":
         del args[i:i + 2]
     print(build(verbose=True, extra_defines=args, out=target))
     if target == LIB:
+        print(build_marshal(verbose=True))
         print(build_bench_probe(verbose=True))
