@@ -4,6 +4,13 @@
 
 namespace {
 
+// Vector `v` of a full tile at `out`.  SYS: system-scope stores (reduce_sys), where the tile starts on 64 bytes.
+template <bool SYS, typename T> __device__ __forceinline__ void st_reduced(T *out, int v, u32x4 r)
+{
+    if (SYS && off64(out) == 0) st_tile_wt(tile_rsrc(out, KT_TILE_BYTES), v * KT_VEC_BYTES, r);
+    else st_vec(reinterpret_cast<u32x4 *>(out) + v, r);
+}
+
 // SPLIT workgroups share a 16 KiB tile, each with KT_TILE_VECS / KT_BLOCK / SPLIT vectors of all K copies per
 // lane in flight together.  The kernel is bound by how well the memory system takes K read streams and
 // one write stream: few bytes in flight (40-96 KB per CU), in workgroups that the dispatcher starts
@@ -13,7 +20,7 @@ namespace {
 // than the 3 % of a misaligned non-temporal store stream.  INT: bf16 narrowing in integer instructions
 // (f32_to_bf16_int).  Whole tiles test the window's width whether it is zero or not: without
 // that test between loads and stores they are 1-3 % slower.
-template <typename T, int K, bool DEVW, int SPLIT, bool INT>
+template <typename T, int K, bool DEVW, int SPLIT, bool INT, bool SYS>
 __global__ __launch_bounds__(KT_BLOCK) void kt_reduce_kernel(const KtTile *tiles, const int64_t *b_elems,
                                                              const void *const *peer_ptrs, void *const *out_ptrs,
                                                              uint32_t order, KtWindow win, FewWeights wts)
@@ -61,7 +68,7 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_reduce_kernel(const KtTile *tiles
         }
         if (SPLIT == 1) kt_wait_store_window(win);     // large launches: the chip writes in bursts (KtWindow)
 #pragma unroll
-        for (int u = 0; u < VPT; ++u) st_vec(reinterpret_cast<u32x4 *>(out) + u * KT_BLOCK + v0, res[u]);
+        for (int u = 0; u < VPT; ++u) st_reduced<SYS>(out, u * KT_BLOCK + v0, res[u]);
     } else {
         for (int v = part * KT_BLOCK + tid; v < nvec; v += SPLIT * KT_BLOCK) {
             u32x4 r[K];
@@ -86,7 +93,7 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_reduce_kernel(const KtTile *tiles
 
 // K > 8: peers in chunks, accumulators in registers across chunks (whole tiles: sum_in_chunks; quarter tiles, SPLIT 4:
 // sum_rolling).
-template <typename T, bool DEVW, int SPLIT>
+template <typename T, bool DEVW, int SPLIT, bool SYS>
 __global__ __launch_bounds__(KT_BLOCK) void kt_reduce_manyk_kernel(const KtTile *tiles, const int64_t *b_elems,
                                                                    const void *const *peer_ptrs, void *const *out_ptrs,
                                                                    int K, uint32_t order, KtWindow win, AllWeights wts)
@@ -114,7 +121,7 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_reduce_manyk_kernel(const KtTile 
         for (int u = 0; u < VPT; ++u) res[u] = acc[u].finish();
         if (SPLIT == 1) kt_wait_store_window(win);
 #pragma unroll
-        for (int u = 0; u < VPT; ++u) st_vec(reinterpret_cast<u32x4 *>(out) + u * KT_BLOCK + v0, res[u]);
+        for (int u = 0; u < VPT; ++u) st_reduced<SYS>(out, u * KT_BLOCK + v0, res[u]);
         return;
     }
     // the ragged last tile of a bucket: one vector at a time
@@ -185,6 +192,15 @@ inline KtShape reduce_manyk_shape(int64_t nt)
     return {nt <= 256 || (nt <= 640 && kt_uneven(nt)) ? 4 : 1, 0};
 }
 
+// System-scope stores, not waited for, where the reduced buckets are 17 to 96 MiB: the L2s have nothing to write back when the
+// kernel ends, and the next call reads the buckets out of the last-level cache.  Pack, reduce and unpack together: K = 8 fp32
+// 1 191 tiles 46.4 -> 45.2 us, 3 243 tiles 110.8 -> 107.7 (116.0 -> 110.6 where nine sets of buffers take turns), 5 412 tiles 182 -> 175;
+// K = 4 bf16 2 706 tiles 65.8 -> 63.6; K = 12 fp32 5 412 tiles 6 % faster; ViT-B/16 bucket by bucket (1 154 tiles each) 837 -> 799.  Alone, in place
+// over the first copy, 1 950 to 5 600 tiles 2-8 % faster, 1 200 even.  Below, steps are 2-5 % slower (434 tiles), above 16 384 tiles as well
+// (19 993 tiles, K = 8 fp32 5 %); between 7 600 and 11 300 the reduce alone is 2-6 % slower where a step is 4 % faster, as is one of 5 and
+// more copies at 1 038 tiles (2 %; a step 2 % faster).  More than 8 copies from 1 536 tiles on (K = 12 fp32 1 191 tiles alone 3 % slower).
+inline bool reduce_sys(int K, int64_t nt) { return K > 1 && nt >= (K > 8 ? 1536 : 1100) && nt < 6144; }
+
 template <typename T, int K, bool DEVW>
 hipError_t launch_reduce_k(const KtTile *tiles, const int64_t *b_elems, int64_t nt, const void *const *peers,
                            const KtWeights &w, void *const *outs, hipStream_t s)
@@ -193,16 +209,22 @@ hipError_t launch_reduce_k(const KtTile *tiles, const int64_t *b_elems, int64_t 
     if constexpr (K >= 7) {
         const KtWindow win = kt_store_window(sizeof(T) == 4 ? KT_PERIOD_14 : KT_PERIOD_12, nt, KT_WINDOW_MIN_TILES_REDUCE);
         if (win.width) {
-            kt_reduce_kernel<T, K, DEVW, 1, sizeof(T) == 2><<<dim3((unsigned)nt), block, 0, s>>>(tiles, b_elems, peers, outs, 0u, win, FewWeights(w));
+            kt_reduce_kernel<T, K, DEVW, 1, sizeof(T) == 2, false><<<dim3((unsigned)nt), block, 0, s>>>(tiles, b_elems, peers, outs, 0u, win, FewWeights(w));
             return hipGetLastError();
         }
     }
     const KtShape sh = reduce_shape<T>(K, nt);
+    const bool sys = reduce_sys(K, nt);
     const unsigned lds = kt_shape_lds(sh, 0);
     return launch_in_chunks(tiles, nt, sh.split, [&](const KtTile *t, dim3 grid) {
         const uint32_t order = kt_order(grid.x, KT_TILE_BYTES / sh.split, sh.split == 1 ? 0 : K <= 3 ? 131072 : 65536);
-        if (sh.split == 1) kt_reduce_kernel<T, K, DEVW, 1, false><<<grid, block, lds, s>>>(t, b_elems, peers, outs, order, KtWindow{0, 0}, FewWeights(w));
-        else if constexpr (K > 1) kt_reduce_kernel<T, K, DEVW, 4, (sizeof(T) == 2 && K >= 6)><<<grid, block, lds, s>>>(t, b_elems, peers, outs, order, KtWindow{0, 0}, FewWeights(w));
+#define KT_LAUNCH(SPLIT, INT, SYS) \
+    kt_reduce_kernel<T, K, DEVW, SPLIT, INT, SYS><<<grid, block, lds, s>>>(t, b_elems, peers, outs, order, KtWindow{0, 0}, FewWeights(w))
+        constexpr bool INT = sizeof(T) == 2 && K >= 6;
+        if constexpr (K == 1) KT_LAUNCH(1, false, false);
+        else if (sys) { if (sh.split == 1) KT_LAUNCH(1, false, true); else KT_LAUNCH(4, INT, true); }
+        else { if (sh.split == 1) KT_LAUNCH(1, false, false); else KT_LAUNCH(4, INT, false); }
+#undef KT_LAUNCH
     });
 }
 
@@ -218,11 +240,15 @@ hipError_t launch_reduce_t(const KtDeviceTables &tb, int64_t tile0, int64_t nt, 
     }
     const KtWindow win = kt_manyk_window(sizeof(T) == 2, K, nt, KT_WINDOW_MIN_READS_REDUCE_MANYK);
     const KtShape sh = win.width ? KtShape{1, 0} : reduce_manyk_shape(nt);
+    const bool sys = reduce_sys(K, nt);
     const unsigned lds = kt_shape_lds(sh, 0);
     return launch_in_chunks(tiles, nt, sh.split, [&](const KtTile *t, dim3 grid) {
         const uint32_t order = kt_order(grid.x, KT_TILE_BYTES / sh.split, sh.split == 1 ? 0 : 65536);
-        if (sh.split == 1) kt_reduce_manyk_kernel<T, DEVW, 1><<<grid, dim3(KT_BLOCK), lds, s>>>(t, tb.b_elems, peers, outs, K, order, win, AllWeights(w));
-        else kt_reduce_manyk_kernel<T, DEVW, 4><<<grid, dim3(KT_BLOCK), lds, s>>>(t, tb.b_elems, peers, outs, K, order, win, AllWeights(w));
+#define KT_LAUNCH(SPLIT, SYS) \
+    kt_reduce_manyk_kernel<T, DEVW, SPLIT, SYS><<<grid, dim3(KT_BLOCK), lds, s>>>(t, tb.b_elems, peers, outs, K, order, win, AllWeights(w))
+        if (sys) { if (sh.split == 1) KT_LAUNCH(1, true); else KT_LAUNCH(4, true); }
+        else { if (sh.split == 1) KT_LAUNCH(1, false); else KT_LAUNCH(4, false); }
+#undef KT_LAUNCH
     });
 }
 

@@ -98,3 +98,21 @@ def test_sgd_on_unpack_in_runs(dtype, tiles, tail, master):
         update(*[t[at:at + part] for t in (g, want_p, want_v, want_m)])
     assert torch.equal(p.view(torch.int32), want_p.view(torch.int32)) and torch.equal(v.view(torch.int32), want_v.view(torch.int32))
     assert torch.equal(m.view(torch.int16), want_m.view(torch.int16))
+
+
+# system-scope stores from 1 100 (many copies: 1 536) to 6 143 tiles, where the output starts on 64 bytes, and outputs that start elsewhere
+@pytest.mark.parametrize("dtype,K,tiles,tail,off", [
+    ("f32", 2, 1100, 0, 0), ("bf16", 3, 1099, 8, 0), ("f32", 8, 1101, 4, 0), ("f32", 8, 1100, 4, 1), ("bf16", 8, 2048, 8, 1), ("bf16", 8, 2048, 8, 8),
+    ("f32", 4, 6143, 0, 0), ("bf16", 12, 1536, 0, 0), ("f32", 9, 2560, 4, 0), ("bf16", 9, 2560, 8, 3),
+])
+def test_reduce_store_scopes(dtype, K, tiles, tail, off):
+    plan, weights, copies, want = inputs(dtype, K, tiles * (16384 // (4 if dtype == "f32" else 2)) + tail)
+    n = copies[0].numel()
+    memory = torch.full((n + off + 64,), 7.0, dtype=tdtype(dtype), device=DEV)
+    out = memory[off:off + n]
+    plan.kt_weighted_reduce(-1, copies, K, weights, [out])
+    in_place = copies[0].clone()
+    plan.kt_weighted_reduce(-1, [in_place] + copies[1:], K, weights, [in_place])
+    torch.cuda.synchronize()
+    assert raw(host(out)).tobytes() == raw(want).tobytes() and raw(host(in_place)).tobytes() == raw(want).tobytes()
+    assert bool((memory[:off] == 7).all()) and bool((memory[off + n:] == 7).all())
