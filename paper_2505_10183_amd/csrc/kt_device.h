@@ -66,8 +66,8 @@ __device__ __forceinline__ void st_vec(void *p, u32x4 v)
 // unpack with bf16 gradients: 44-50 % of their bytes are written): a system-scope store, which
 // the L2 writes through at once instead of holding the line, measured 1-4 points of 8 TB/s
 // better there than the non-temporal store, and 1-3 points worse in the kernels that write a
-// quarter of their bytes or less (reduce, fused pass, K copies -> parameters), which keep
-// st_vec (the last one but for large bf16 launches, FsgdLaunch).  KT_WT_STORE=0 builds these
+// quarter of their bytes or less (reduce but for middling launches, fused pass, K copies -> parameters), which keep
+// st_vec.  KT_WT_STORE=0 builds these
 // kernels with st_vec as well, for measurement.
 #ifndef KT_WT_STORE
 #define KT_WT_STORE 1
@@ -392,10 +392,11 @@ __device__ __forceinline__ u32x4 gather_vec(const V &tv, int nt, int i, int64_t 
     return join(x);
 }
 // `second` may be NULL for kernels with one tensor set (ptr2 then mirrors ptr).
+template <int LANES = KT_BLOCK>
 __device__ __forceinline__ LdsView stage_lds(LdsTable &lds, const int64_t *t_off, const int64_t *t_numel,
                                              const void *const *first, const void *const *second, int t0, int nt)
 {
-    for (int i = threadIdx.x; i < nt; i += KT_BLOCK) {
+    for (int i = threadIdx.x; i < nt; i += LANES) {
         lds.off[i] = t_off[t0 + i];
         lds.numel[i] = t_numel[t0 + i];
         lds.ptr[i] = reinterpret_cast<uintptr_t>(first[t0 + i]);
@@ -622,10 +623,10 @@ inline uint32_t kt_order(unsigned pieces, int piece_bytes, int run)
 }
 
 // A grid may not hold 2^32 or more lanes: very large plans go in several launches.  `split`
-// workgroups share a tile; launch(tiles, grid) launches one part.
-template <typename F> hipError_t launch_in_chunks(const KtTile *tiles, int64_t ntiles, int split, F launch)
+// workgroups of `lanes` share a tile; launch(tiles, grid) launches one part.
+template <typename F> hipError_t launch_in_chunks(const KtTile *tiles, int64_t ntiles, int split, F launch, int lanes = KT_BLOCK)
 {
-    const int64_t per_launch = (((int64_t)1 << 32) / KT_BLOCK - 1) / split;
+    const int64_t per_launch = (((int64_t)1 << 32) / lanes - 1) / split;
     for (int64_t done = 0; done < ntiles; done += per_launch) {
         const int64_t now = ntiles - done < per_launch ? ntiles - done : per_launch;
         launch(tiles + done, dim3((unsigned)(now * split)));

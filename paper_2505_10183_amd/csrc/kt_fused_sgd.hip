@@ -57,25 +57,25 @@ template <typename T> struct TensorSide {
     }
 };
 
-// Stores of a lane's N updated quads (quad j at q4 + j * KT_BLOCK): parameters, momentum and, for
+// Stores of a lane's N updated quads (quad j at q4 + j * LANES): parameters, momentum and, for
 // mixed precision, the model copy.
-template <int N, bool SYS> __device__ __forceinline__ void st_quads(u32x4 *p4, u32x4 *v4, u32x2 *m2, const u32x4 *pr, const u32x4 *vr)
+template <int N, int LANES> __device__ __forceinline__ void st_quads(u32x4 *p4, u32x4 *v4, u32x2 *m2, const u32x4 *pr, const u32x4 *vr)
 {
 #pragma unroll
     for (int j = 0; j < N; ++j) {
-        st_vec_copy<SYS>(p4 + j * KT_BLOCK, pr[j]);
-        st_vec_copy<SYS>(v4 + j * KT_BLOCK, vr[j]);
+        st_vec(p4 + j * LANES, pr[j]);
+        st_vec(v4 + j * LANES, vr[j]);
     }
-    if (m2) {      // non-temporal beside system-scope ones too (1.3B set, 8 placements of its memory: 0 to 3.3 % faster in seven, 0.5 % slower in one)
+    if (m2) {
 #pragma unroll
-        for (int j = 0; j < N; ++j) st_model_quad(m2 + j * KT_BLOCK, pr[j]);
+        for (int j = 0; j < N; ++j) st_model_quad(m2 + j * LANES, pr[j]);
     }
 }
 
 // The quads of a lane against their gradients.  bf16: a lane's 16-byte vector holds 8 elements =
 // 32 bytes of p; the reduced values go through LDS once and come back in quads of 4 elements, so
 // that every access to p and v is one coalesced 16 bytes per lane.  binary32: a vector is a quad.
-template <int VPT> __device__ __forceinline__ void update_quads(const u32x4 *red, u32x4 *, u32x4 *pr, u32x4 *vr, const KtSgd &a, float)
+template <int VPT, int LANES> __device__ __forceinline__ void update_quads(const u32x4 *red, u32x4 *, u32x4 *pr, u32x4 *vr, const KtSgd &a, float)
 {
 #pragma unroll
     for (int u = 0; u < VPT; ++u) {
@@ -84,16 +84,16 @@ template <int VPT> __device__ __forceinline__ void update_quads(const u32x4 *red
         sgd_quad(q, pr[u], vr[u], a);
     }
 }
-template <int VPT> __device__ __forceinline__ void update_quads(const u32x4 *red, u32x4 *lds, u32x4 *pr, u32x4 *vr, const KtSgd &a, uint16_t)
+template <int VPT, int LANES> __device__ __forceinline__ void update_quads(const u32x4 *red, u32x4 *lds, u32x4 *pr, u32x4 *vr, const KtSgd &a, uint16_t)
 {
     const int tid = threadIdx.x;
 #pragma unroll
-    for (int u = 0; u < VPT; ++u) lds[u * KT_BLOCK + tid] = red[u];
+    for (int u = 0; u < VPT; ++u) lds[u * LANES + tid] = red[u];
     __syncthreads();
     const u32x2 *l2 = reinterpret_cast<const u32x2 *>(lds);
 #pragma unroll
     for (int j = 0; j < 2 * VPT; ++j) {
-        const u32x2 t = l2[j * KT_BLOCK + tid];
+        const u32x2 t = l2[j * LANES + tid];
         Quad<uint16_t> q;
         q.d[0] = t[0];
         q.d[1] = t[1];
@@ -101,17 +101,10 @@ template <int VPT> __device__ __forceinline__ void update_quads(const u32x4 *red
     }
 }
 
-// How a 16 KiB tile is shared out (K <= 8): one 16-byte vector of every copy per lane and
-// workgroup, i.e. 4 workgroups per tile.  KT_FSGD_VPT overrides it for measurement.
-#ifndef KT_FSGD_VPT
-#define KT_FSGD_VPT 1
-#endif
+// How a 16 KiB tile is shared out (K <= 8): one 16-byte vector of every copy per lane, i.e. 4 workgroups of 256 lanes
+// per tile or 16 of 64.
 template <typename T> struct FsgdShape {
-    static constexpr int TILE_VPT = KT_TILE_VECS / KT_BLOCK;
-    static constexpr int VPT = KT_FSGD_VPT;                      // vectors per lane and workgroup
-    static constexpr int SPLIT = TILE_VPT / VPT;                 // workgroups per tile
     static constexpr int QPV = Elem<T>::VE / 4;                  // quads per vector
-    static_assert(VPT >= 1 && TILE_VPT % VPT == 0, "a tile is shared out in equal parts");
 };
 
 // Everything that is not a full solid tile: vectors wholly inside one tensor one per lane with the
@@ -119,7 +112,7 @@ template <typename T> struct FsgdShape {
 // the others one per lane (each_cut_elem).  tv.ptr = local gradients, tv.ptr2 = parameters;
 // momentum and model pointers come from the global pointer table (mom, model: already advanced to
 // the tile's first tensor).  KC: K at compile time, or 0.
-template <typename T, int KC, bool DEVW, typename V, typename W>
+template <typename T, int KC, bool DEVW, int LANES, typename V, typename W>
 __device__ __forceinline__ void fsgd_mixed(const V &tv, int nt, const TileGeom &g, const void *const *pp, int K_,
                                            const W &wts, const KtSgd &a, void *const *mom, void *const *model,
                                            int part, int parts)
@@ -130,7 +123,7 @@ __device__ __forceinline__ void fsgd_mixed(const V &tv, int nt, const TileGeom &
     const int nvec = (int)((g.end - g.start) / VE);
     auto peer = [&](int k) { return reinterpret_cast<const T *>(ld_table(pp + k - 1)) + g.start; };
 #pragma unroll 1
-    for (int v = part * KT_BLOCK + threadIdx.x; v < nvec; v += parts * KT_BLOCK) {
+    for (int v = part * LANES + threadIdx.x; v < nvec; v += parts * LANES) {
         const int64_t e0 = g.start + (int64_t)v * VE;
         const int i = find_owner_v(tv, nt, e0);
         const int64_t r = i >= 0 ? e0 - tv.off[i] : -1;
@@ -165,7 +158,7 @@ __device__ __forceinline__ void fsgd_mixed(const V &tv, int nt, const TileGeom &
             if (model) st_model_quad(reinterpret_cast<uint16_t *>(model[i]) + r + 4 * h, pr[h]);
         }
     }
-    each_cut_elem<VE>(tv, nt, g.start, (int)(g.end - g.start), part * KT_BLOCK + threadIdx.x, parts * KT_BLOCK,
+    each_cut_elem<VE>(tv, nt, g.start, (int)(g.end - g.start), part * LANES + threadIdx.x, parts * LANES,
                       [&](int i, int64_t r, int e) {
                           float *pe = reinterpret_cast<float *>(tv.ptr2[i]) + r;
                           float *ve = reinterpret_cast<float *>(mom[i]) + r;
@@ -191,7 +184,7 @@ union FsgdLds {
     u32x4 red[KT_TILE_VECS];
 };
 
-template <typename T, int KC, bool DEVW, typename W>
+template <typename T, int KC, bool DEVW, int LANES, typename W>
 __device__ __forceinline__ void fsgd_other_tile(LdsTable &lds, const int64_t *t_offs, const int64_t *t_numel, const KtTile &tl,
                                                 const TileGeom &g, const FsgdArgs &f, const void *const *pp, int K,
                                                 const W &wts, const KtSgd &a, int part, int parts)
@@ -201,21 +194,20 @@ __device__ __forceinline__ void fsgd_other_tile(LdsTable &lds, const int64_t *t_
     void *const *mom = f.mom_ptrs + tl.t0;
     void *const *model = f.model_ptrs ? f.model_ptrs + tl.t0 : nullptr;
     if (nt <= KT_LDS_TENSORS) {
-        const LdsView tv = stage_lds(lds, t_offs, t_numel, f.local_ptrs, prm, tl.t0, nt);
-        fsgd_mixed<T, KC, DEVW>(tv, nt, g, pp, K, wts, a, mom, model, part, parts);
+        const LdsView tv = stage_lds<LANES>(lds, t_offs, t_numel, f.local_ptrs, prm, tl.t0, nt);
+        fsgd_mixed<T, KC, DEVW, LANES>(tv, nt, g, pp, K, wts, a, mom, model, part, parts);
     } else {
         const GlobalView tv = global_view(t_offs, t_numel, f.local_ptrs, prm, tl.t0);
-        fsgd_mixed<T, KC, DEVW>(tv, nt, g, pp, K, wts, a, mom, model, part, parts);
+        fsgd_mixed<T, KC, DEVW, LANES>(tv, nt, g, pp, K, wts, a, mom, model, part, parts);
     }
 }
 
 // K = 1..8.  SPLIT workgroups share a tile; on a full solid tile the loads of all copies, of p and
 // of v are in flight together.  The kernel reads K * s + 8 bytes (24 and 40 at K = 8) and writes
 // 8 or 10 per element, and what bounds it is how well the memory system mixes the two: the fewer
-// bytes the chip has in flight beyond what hides the latency the better (FsgdLaunch).  SYS:
-// system-scope stores.
-template <typename T, int K, bool DEVW, bool SYS>
-__global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_kernel(const KtTile *tiles, const int64_t *b_elems,
+// bytes the chip has in flight beyond what hides the latency the better, in small workgroups (FsgdLaunch).
+template <typename T, int K, bool DEVW, int LANES>
+__global__ __launch_bounds__(LANES) void kt_fused_sgd_kernel(const KtTile *tiles, const int64_t *b_elems,
                                                                 const int64_t *t_offs, const void *const *local_ptrs,
                                                                 const void *const *peer_ptrs, void *const *param_ptrs,
                                                                 uint32_t order, void *const *mom_ptrs,
@@ -225,11 +217,11 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_kernel(const KtTile *ti
     const FsgdArgs f{local_ptrs, peer_ptrs, param_ptrs, mom_ptrs, model_ptrs};
     constexpr int VE = Elem<T>::VE;
     constexpr int64_t TILE_ELEMS = (int64_t)KT_TILE_VECS * VE;
-    constexpr int VPT = FsgdShape<T>::VPT, SPLIT = FsgdShape<T>::SPLIT, QPL = VPT * FsgdShape<T>::QPV;
+    constexpr int VPT = 1, SPLIT = KT_TILE_VECS / LANES, QPL = VPT * FsgdShape<T>::QPV;
     constexpr int KP = K > 1 ? K - 1 : 1;
     __shared__ FsgdLds lds;
 
-    const unsigned piece = SPLIT == 1 ? blockIdx.x : kt_piece(order);
+    const unsigned piece = kt_piece(order);
     const int part = (int)(piece % SPLIT);
     const KtTile tl = ld_tile(tiles + piece / SPLIT);
     const int64_t b_n = ld_table(b_elems + tl.bucket), t_off = ld_table(t_offs + tl.t0);
@@ -244,22 +236,22 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_kernel(const KtTile *ti
 
     if (tl.nt == 0 && g.end - g.start == TILE_ELEMS) {
         t.advance(g.start - t_off);
-        const int v0 = part * VPT * KT_BLOCK + tid;       // the lane's first vector in the tile
-        const int q0 = part * QPL * KT_BLOCK + tid;       // and its first quad of p, v and the model copy
+        const int v0 = part * VPT * LANES + tid;       // the lane's first vector in the tile
+        const int q0 = part * QPL * LANES + tid;       // and its first quad of p, v and the model copy
         u32x4 r[VPT][K], pr[QPL], vr[QPL];
         u32x4 *p4 = reinterpret_cast<u32x4 *>(t.p) + q0, *v4 = reinterpret_cast<u32x4 *>(t.v) + q0;
         u32x4 *vs = a.first ? p4 : v4;                     // a first step does not read the momentum
 #pragma unroll
         for (int u = 0; u < VPT; ++u) {
-            r[u][0] = ld_vec(reinterpret_cast<const u32x4 *>(t.src) + v0 + u * KT_BLOCK);
+            r[u][0] = ld_vec(reinterpret_cast<const u32x4 *>(t.src) + v0 + u * LANES);
 #pragma unroll
             for (int k = 1; k < K; ++k)
-                r[u][k] = ld_vec(reinterpret_cast<const u32x4 *>(x[k - 1] + g.start) + v0 + u * KT_BLOCK);
+                r[u][k] = ld_vec(reinterpret_cast<const u32x4 *>(x[k - 1] + g.start) + v0 + u * LANES);
         }
 #pragma unroll
         for (int j = 0; j < QPL; ++j) {
-            pr[j] = ld_vec(p4 + j * KT_BLOCK);
-            vr[j] = ld_vec(vs + j * KT_BLOCK);
+            pr[j] = ld_vec(p4 + j * LANES);
+            vr[j] = ld_vec(vs + j * LANES);
         }
         // keep every load above the arithmetic: all of them are in flight together
         __builtin_amdgcn_sched_barrier(0);
@@ -272,17 +264,12 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_kernel(const KtTile *ti
             for (int k = 1; k < K; ++k) acc.add(r[u][k], kt_weight<DEVW>(wts, k));
             red[u] = acc.finish();
         }
-        update_quads<VPT>(red, lds.red, pr, vr, a, T(0));
+        update_quads<VPT, LANES>(red, lds.red, pr, vr, a, T(0));
         u32x2 *m2 = t.m ? reinterpret_cast<u32x2 *>(t.m) + q0 : nullptr;
-        // system-scope stores want whole 64-byte pieces: a tile whose parameters or momentum start elsewhere takes the
-        // others (48 831 tiles, K = 8, tensors at 16-byte steps: 2.57 ms, 2.85 with system-scope stores throughout).  The
-        // model copy's stores are non-temporal either way and may start anywhere (32 bytes off: 33 005 tiles 1 646 ->
-        // 1 607 us against non-temporal stores of all three, 44 004 tiles 2 092 -> 2 002, 100 032 tiles 4 760 -> 4 593)
-        if (SYS && off64(t.p) + off64(t.v) == 0) st_quads<QPL, SYS>(p4, v4, m2, pr, vr);
-        else st_quads<QPL, false>(p4, v4, m2, pr, vr);
+        st_quads<QPL, LANES>(p4, v4, m2, pr, vr);
         return;
     }
-    fsgd_other_tile<T, K, DEVW>(lds.table, t_offs, t_numel, tl, g, f, pp, K, wts, a, part, SPLIT);
+    fsgd_other_tile<T, K, DEVW, LANES>(lds.table, t_offs, t_numel, tl, g, f, pp, K, wts, a, part, SPLIT);
 }
 
 // K = 9..64: full solid tiles take the peers in chunks with the accumulators in registers; every other
@@ -333,47 +320,50 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_manyk_kernel(const KtTi
 #pragma unroll
         for (int u = 0; u < VPT; ++u) red[u] = acc[u].finish();
         if (SPLIT == 1) load_state();
-        update_quads<VPT>(red, lds.red, pr, vr, a, T(0));
+        update_quads<VPT, KT_BLOCK>(red, lds.red, pr, vr, a, T(0));
         if (SPLIT == 1) kt_wait_store_window(win);
-        st_quads<QPL, false>(p4, v4, t.m ? reinterpret_cast<u32x2 *>(t.m) + q0 : nullptr, pr, vr);
+        st_quads<QPL, KT_BLOCK>(p4, v4, t.m ? reinterpret_cast<u32x2 *>(t.m) + q0 : nullptr, pr, vr);
         return;
     }
-    fsgd_other_tile<T, 0, DEVW>(lds.table, t_offs, t_numel, tl, g, f, pp, K, wts, a, part, SPLIT);
+    fsgd_other_tile<T, 0, DEVW, KT_BLOCK>(lds.table, t_offs, t_numel, tl, g, f, pp, K, wts, a, part, SPLIT);
 }
 
 // Bytes of LDS asked for beyond the kernel's own, to hold the number of workgroups per CU at 2 or 4;
 // without, registers allow 7 or 8.
 constexpr unsigned FSGD_LDS_2 = kt_hold_lds(2, sizeof(FsgdLds)), FSGD_LDS_4 = kt_hold_lds(4, sizeof(FsgdLds));
 
-// Bytes in flight and store scope by the size of the launch:
+// Workgroups, bytes in flight and order by the size of the launch.  Stores are non-temporal throughout.
 //   bf16    2 workgroups per CU (96 KiB in flight at K = 8) above 2 048 tiles, above 1 024 for one and
 //           two copies: 1.3B set 7.38 -> 7.08 ms against 8 workgroups, with the model copy 7.97 -> 7.60
 //           (which depends on where the tensors lie: three sets of 46 GB in turn, 24 arrangements,
 //           7.45-7.94 ms without, 7.47-7.77 with); K = 4, 21 135 tiles 791 -> 745 us.  Below, the chip is
 //           not full long enough to gain (300 to 1 200 tiles, K = 1 to 6: 1-6 % slower with it on aligned sets).
-//           8 copies and 32 768 tiles or more also with system-scope stores (33 005 tiles 1 622 -> 1 596 us,
-//           66 000 tiles 3 150 -> 3 030, 100 032 tiles 4 768 -> 4 645; 1.3B set, on the same memory in turn, 8 placements:
-//           0.4-3.8 % faster in six, even in one, 1.6 % slower in one); fewer lose 3-20 % with them.  Buffer
-//           stores, which are not waited for, are slower there (1.3B set 7.74 ms, 7.54)
+//           8 copies and 32 768 tiles or more: 4 workgroups of 64 lanes per CU (48 KiB in flight), which against system-scope stores
+//           from workgroups of 256 lanes in launch order is 0-5.7 % faster, 2.6 % in the mean (18 launches of 33 813 to 160 640 tiles,
+//           three placements each: 1.3B set 7 516 -> 7 366, 7 527 -> 7 128, 7 782 -> 7 603 us; 33 813 tiles 1 610 -> 1 544; one
+//           launch even).  256 lanes in runs of 64 KiB: 2.4 % faster to 3.3 % slower on the same launches
 //   fp32    above 4 096 tiles 2 workgroups per CU for 4 and more copies (K = 8, 21 135 tiles 716 -> 687 us,
 //           K = 4, 8 192 tiles 181 -> 179 us), 4 for fewer (K = 2, 21 135 tiles 340 -> 336 us); 6 and more
-//           copies from 2 048 tiles on (K = 8, 3 700 tiles 2-5 % over none).  Non-temporal
-//           stores throughout: system-scope ones gain 2-10 % up to 4 096 tiles where a call finds p and v
-//           of the call before in the last-level cache and lose 2-5 % (64-byte aligned) to 13 % (odd
-//           addresses, 2 700 tiles) where it does not, which is the state a training step is called in
-// Runs of 128 KiB of gradient per XCD (kt_order) but with system-scope stores: fp32 K = 4 1 191 tiles 28.2 -> 26.2 us, 3 243 tiles 71.9 ->
+//           copies from 2 048 tiles on (K = 8, 3 700 tiles 2-5 % over none).  System-scope stores gain 2-12 % up to 2 700
+//           tiles where a call finds p and v of the call before in the last-level cache and lose 1-5 % where it does not (1 950
+//           tiles, K = 2 and 4, nine sets of buffers in turn), which is the state a training step is called in
+// Runs of 128 KiB of gradient per XCD (kt_order), 64 KiB for workgroups of 64 lanes: fp32 K = 4 1 191 tiles 28.2 -> 26.2 us, 3 243 tiles 71.9 ->
 // 68.2, 63 057 tiles 1 395 -> 1 333; K = 8 2 141 -> 2 030; bf16 K = 6 2 706 tiles 111.9 -> 108.3, K = 8 9 996 tiles 468 -> 459 (one and
 // two copies even there and 2 % faster below).  Not below 640 tiles, where the few slow tiles that hold many tensors
-// come to lie on one XCD (MobileNetV2, 547 tiles 13.2 -> 13.5 us; 197 tiles of odd tensors 13.1 -> 13.7).  With system-scope stores 1 % faster (160 640 tiles) to 5 % slower (76 849).
+// come to lie on one XCD (MobileNetV2, 547 tiles 13.2 -> 13.5 us; 197 tiles of odd tensors 13.1 -> 13.7).
 struct FsgdLaunch {
     unsigned lds;
-    bool sys;
+    int lanes, run;
 };
 template <typename T> FsgdLaunch fsgd_launch(int K, int64_t ntiles)
 {
-    if (sizeof(T) == 2) return FsgdLaunch{ntiles > (K <= 2 ? 1024 : 2048) ? FSGD_LDS_2 : 0u, K >= 8 && ntiles >= 32768};
-    if (ntiles <= (K >= 6 ? 2048 : 4096)) return FsgdLaunch{0u, false};
-    return FsgdLaunch{K >= 4 ? FSGD_LDS_2 : FSGD_LDS_4, false};
+    const int run = ntiles < 640 ? 0 : 131072;
+    if (sizeof(T) == 2) {
+        if (K >= 8 && ntiles >= 32768) return FsgdLaunch{FSGD_LDS_4, 64, 65536};
+        return FsgdLaunch{ntiles > (K <= 2 ? 1024 : 2048) ? FSGD_LDS_2 : 0u, KT_BLOCK, run};
+    }
+    if (ntiles <= (K >= 6 ? 2048 : 4096)) return FsgdLaunch{0u, KT_BLOCK, run};
+    return FsgdLaunch{K >= 4 ? FSGD_LDS_2 : FSGD_LDS_4, KT_BLOCK, run};
 }
 
 // 9 and more copies.  Small launches take quarter tiles (K = 16: 29 tiles fp32 18.9 -> 6.6 us, 249 tiles bf16
@@ -402,7 +392,6 @@ template <typename T, bool DEVW>
 hipError_t launch_fused_sgd_t(const KtDeviceTables &tb, int64_t tile0, int64_t ntiles, const FsgdArgs &f, int K,
                               const KtWeights &w, const KtSgd &a, hipStream_t s)
 {
-    const dim3 block(KT_BLOCK);
     if (K > 8) {
         const KtWindow win = fsgd_manyk_window<T>(K, ntiles);
         const KtShape sh = win.width ? KtShape{1, 0} : fsgd_manyk_shape(K, ntiles);
@@ -413,28 +402,28 @@ hipError_t launch_fused_sgd_t(const KtDeviceTables &tb, int64_t tile0, int64_t n
             const uint32_t order = kt_order(grid.x, KT_TILE_BYTES / sh.split, sh.split == 1 || ntiles < 640 || (sizeof(T) == 4 && K < 11) ? 0 : 65536);
 #define KT_ARGS \
     tiles, tb.b_elems, tb.t_off, f.local_ptrs, f.peer_ptrs, f.param_ptrs, order, K, f.mom_ptrs, f.model_ptrs, tb.t_numel, a, win, AllWeights(w)
-            if (sh.split == 1) kt_fused_sgd_manyk_kernel<T, DEVW, 1><<<grid, block, lds, s>>>(KT_ARGS);
-            else kt_fused_sgd_manyk_kernel<T, DEVW, 4><<<grid, block, lds, s>>>(KT_ARGS);
+            if (sh.split == 1) kt_fused_sgd_manyk_kernel<T, DEVW, 1><<<grid, dim3(KT_BLOCK), lds, s>>>(KT_ARGS);
+            else kt_fused_sgd_manyk_kernel<T, DEVW, 4><<<grid, dim3(KT_BLOCK), lds, s>>>(KT_ARGS);
 #undef KT_ARGS
         });
     }
     FsgdLaunch how = fsgd_launch<T>(K, ntiles);
     if (!kt_may_hold()) how.lds = 0;
-    return launch_in_chunks(tb.tiles + tile0, ntiles, FsgdShape<T>::SPLIT, [&](const KtTile *tiles, dim3 grid) {
-        const uint32_t order = kt_order(grid.x, KT_TILE_BYTES / FsgdShape<T>::SPLIT, how.sys || ntiles < 640 ? 0 : 131072);
-#define KT_ARGS \
-    tiles, tb.b_elems, tb.t_off, f.local_ptrs, f.peer_ptrs, f.param_ptrs, order, f.mom_ptrs, f.model_ptrs, tb.t_numel, a, FewWeights(w)
+    return launch_in_chunks(tb.tiles + tile0, ntiles, KT_TILE_VECS / how.lanes, [&](const KtTile *tiles, dim3 grid) {
+        const uint32_t order = kt_order(grid.x, how.lanes * KT_VEC_BYTES, how.run);
+#define KT_LAUNCH(KK, LANES)                                                                                              \
+    kt_fused_sgd_kernel<T, KK, DEVW, LANES><<<grid, dim3(LANES), how.lds, s>>>(tiles, tb.b_elems, tb.t_off, f.local_ptrs, \
+        f.peer_ptrs, f.param_ptrs, order, f.mom_ptrs, f.model_ptrs, tb.t_numel, a, FewWeights(w))
+        if constexpr (sizeof(T) == 2) {
+            if (how.lanes == 64) { KT_LAUNCH(8, 64); return; }
+        }
         switch (K) {
-#define KT_CASE(KK)                                                                                                     \
-    case KK:                                                                                                            \
-        if (how.sys) kt_fused_sgd_kernel<T, KK, DEVW, sizeof(T) == 2 && KK >= 8><<<grid, block, how.lds, s>>>(KT_ARGS); \
-        else kt_fused_sgd_kernel<T, KK, DEVW, false><<<grid, block, how.lds, s>>>(KT_ARGS);                             \
-        break;
+#define KT_CASE(KK) case KK: KT_LAUNCH(KK, KT_BLOCK); break;
             KT_CASE(1) KT_CASE(2) KT_CASE(3) KT_CASE(4) KT_CASE(5) KT_CASE(6) KT_CASE(7) KT_CASE(8)
 #undef KT_CASE
-#undef KT_ARGS
+#undef KT_LAUNCH
         }
-    });
+    }, how.lanes);
 }
 
 }  // namespace
