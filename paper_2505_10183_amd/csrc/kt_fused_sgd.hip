@@ -338,28 +338,31 @@ constexpr unsigned FSGD_LDS_2 = kt_hold_lds(2, sizeof(FsgdLds)), FSGD_LDS_4 = kt
 //           (which depends on where the tensors lie: three sets of 46 GB in turn, 24 arrangements,
 //           7.45-7.94 ms without, 7.47-7.77 with); K = 4, 21 135 tiles 791 -> 745 us.  Below, the chip is
 //           not full long enough to gain (300 to 1 200 tiles, K = 1 to 6: 1-6 % slower with it on aligned sets).
-//           8 copies and 32 768 tiles or more: 4 workgroups of 64 lanes per CU (48 KiB in flight), which against system-scope stores
-//           from workgroups of 256 lanes in launch order is 0-5.7 % faster, 2.6 % in the mean (18 launches of 33 813 to 160 640 tiles,
-//           three placements each: 1.3B set 7 516 -> 7 366, 7 527 -> 7 128, 7 782 -> 7 603 us; 33 813 tiles 1 610 -> 1 544; one
-//           launch even).  256 lanes in runs of 64 KiB: 2.4 % faster to 3.3 % slower on the same launches
+//           From 12 288 tiles on (8 copies: 8 192) workgroups of 64 lanes in runs of 64 KiB, 4 per CU for 6 and more copies (48 KiB in flight at K = 8),
+//           5 for 3 to 5, 6 for fewer, against 2 of 256 lanes in launch order (to 32 767 tiles) or with system-scope stores (8 copies
+//           above), mean and range over four or three placements of the buffers: K = 8 9 996 tiles -3.1 % (-6.9 to -0.1), 15 619
+//           -4.5 (-5.9 to -3.6), 26 914 -5.4 (-6.0 to -5.0), 33 813 -3.8, 95 293 -1.7, 1.3B set -3.2 (7 516 -> 7 366, 7 527 -> 7 128,
+//           7 782 -> 7 603 us); K = 4 26 914 -4.1; K = 2 -1.4; K = 1 15 619 even;
+//           odd tensors 15 645 tiles -8.1; K = 1, 3 and 6 8 458 tiles 1-4 % slower, which is where the line comes from.  256 lanes
+//           in runs are 1-2 % faster than launch order at 5 300 and 9 996 tiles and 1-3 % slower at 15 619 and 26 914
 //   fp32    above 4 096 tiles 2 workgroups per CU for 4 and more copies (K = 8, 21 135 tiles 716 -> 687 us,
 //           K = 4, 8 192 tiles 181 -> 179 us), 4 for fewer (K = 2, 21 135 tiles 340 -> 336 us); 6 and more
 //           copies from 2 048 tiles on (K = 8, 3 700 tiles 2-5 % over none).  System-scope stores gain 2-12 % up to 2 700
 //           tiles where a call finds p and v of the call before in the last-level cache and lose 1-5 % where it does not (1 950
 //           tiles, K = 2 and 4, nine sets of buffers in turn), which is the state a training step is called in
-// Runs of 128 KiB of gradient per XCD (kt_order), 64 KiB for workgroups of 64 lanes: fp32 K = 4 1 191 tiles 28.2 -> 26.2 us, 3 243 tiles 71.9 ->
-// 68.2, 63 057 tiles 1 395 -> 1 333; K = 8 2 141 -> 2 030; bf16 K = 6 2 706 tiles 111.9 -> 108.3, K = 8 9 996 tiles 468 -> 459 (one and
-// two copies even there and 2 % faster below).  Not below 640 tiles, where the few slow tiles that hold many tensors
-// come to lie on one XCD (MobileNetV2, 547 tiles 13.2 -> 13.5 us; 197 tiles of odd tensors 13.1 -> 13.7).
+// Runs (kt_order) of 64 KiB of gradient per XCD for fp32 of 4 and more copies and workgroups of 64 lanes, else of 128: fp32 K = 4 1 191 tiles
+// 28.2 -> 26.2 us, 3 243 tiles 71.9 -> 68.2, 44 601 tiles 6.5 % faster (four placements, 6.0 with 128 KiB); K = 2 44 601 tiles 3.3 %;
+// K = 8 63 057 tiles 2 141 -> 2 030 us; bf16 K = 6 2 706 tiles 111.9 -> 108.3.  Not below 640 tiles, where the few slow tiles that hold
+// many tensors come to lie on one XCD (MobileNetV2, 547 tiles 13.2 -> 13.5 us; 197 tiles of odd tensors 13.1 -> 13.7).
 struct FsgdLaunch {
     unsigned lds;
     int lanes, run;
 };
 template <typename T> FsgdLaunch fsgd_launch(int K, int64_t ntiles)
 {
-    const int run = ntiles < 640 ? 0 : 131072;
+    const int run = ntiles < 640 ? 0 : sizeof(T) == 4 && K >= 4 ? 65536 : 131072;
     if (sizeof(T) == 2) {
-        if (K >= 8 && ntiles >= 32768) return FsgdLaunch{FSGD_LDS_4, 64, 65536};
+        if (ntiles >= (K >= 8 ? 8192 : 12288)) return FsgdLaunch{kt_hold_lds(K >= 6 ? 4 : K >= 3 ? 5 : 6, sizeof(FsgdLds)), 64, 65536};
         return FsgdLaunch{ntiles > (K <= 2 ? 1024 : 2048) ? FSGD_LDS_2 : 0u, KT_BLOCK, run};
     }
     if (ntiles <= (K >= 6 ? 2048 : 4096)) return FsgdLaunch{0u, KT_BLOCK, run};
@@ -414,11 +417,14 @@ hipError_t launch_fused_sgd_t(const KtDeviceTables &tb, int64_t tile0, int64_t n
 #define KT_LAUNCH(KK, LANES)                                                                                              \
     kt_fused_sgd_kernel<T, KK, DEVW, LANES><<<grid, dim3(LANES), how.lds, s>>>(tiles, tb.b_elems, tb.t_off, f.local_ptrs, \
         f.peer_ptrs, f.param_ptrs, order, f.mom_ptrs, f.model_ptrs, tb.t_numel, a, FewWeights(w))
-        if constexpr (sizeof(T) == 2) {
-            if (how.lanes == 64) { KT_LAUNCH(8, 64); return; }
-        }
         switch (K) {
-#define KT_CASE(KK) case KK: KT_LAUNCH(KK, KT_BLOCK); break;
+#define KT_CASE(KK)                                                              \
+    case KK:                                                                     \
+        if constexpr (sizeof(T) == 2) {                                          \
+            if (how.lanes == 64) { KT_LAUNCH(KK, 64); break; }                   \
+        }                                                                        \
+        KT_LAUNCH(KK, KT_BLOCK);                                                 \
+        break;
             KT_CASE(1) KT_CASE(2) KT_CASE(3) KT_CASE(4) KT_CASE(5) KT_CASE(6) KT_CASE(7) KT_CASE(8)
 #undef KT_CASE
 #undef KT_LAUNCH

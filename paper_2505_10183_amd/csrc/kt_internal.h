@@ -152,7 +152,7 @@ constexpr bool kt_holds(unsigned wgs)
     const unsigned bytes = kt_hold_lds(wgs, 0);
     return bytes % KT_LDS_GRANULE == 0 && bytes <= 65536 && KT_CU_LDS / bytes == wgs;
 }
-static_assert(kt_holds(2) && kt_holds(3) && kt_holds(4) && kt_holds(5), "the counts that launches ask for");
+static_assert(kt_holds(2) && kt_holds(3) && kt_holds(4) && kt_holds(5) && kt_holds(6), "the counts that launches ask for");
 
 // false where the caller shares the GPU (KT_STORE_WINDOW_NS=0): held workgroups keep the LDS of every
 // CU from kernels that run beside them.

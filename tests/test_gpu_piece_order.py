@@ -44,6 +44,7 @@ def test_reduce_in_runs(dtype, K, tiles, tail):
 
 @pytest.mark.parametrize("dtype,K,tiles,tail", [
     ("f32", 1, 640, 0), ("f32", 4, 660, 4), ("f32", 8, 641, 0), ("bf16", 2, 641, 8), ("bf16", 8, 640, 0), ("bf16", 12, 704, 8), ("f32", 16, 641, 0),
+    ("bf16", 1, 12288, 0), ("bf16", 3, 12289, 8), ("bf16", 8, 8251, 8),       # workgroups of 64 lanes
 ])
 def test_one_pass_sgd_in_runs(dtype, K, tiles, tail):
     plan, weights, copies, want = inputs(dtype, K, tiles * (16384 // (4 if dtype == "f32" else 2)) + tail)
