@@ -140,6 +140,17 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_reduce_manyk_kernel(const KtTile 
     }
 }
 
+// Shared tiles go in runs of 64 KiB per XCD, of 128 KiB up to 3 copies (kt_order), which is 2-6 % faster than launch order
+// (K = 4 fp32 19 993 tiles 259 -> 248 us; K = 5 fp32 315 -> 299; K = 6 bf16 31 528 tiles
+// 585 -> 553; K = 7 bf16 698 -> 647; K = 8 fp32 19 993 tiles 480 -> 460, bf16 31 528 tiles 790 -> 742; uneven launches:
+// bf16 596 tiles, K = 5 10.9 -> 10.5).  With runs 3 copies do best with 4 workgroups per CU (fp32 19 993 tiles 201 us with 5,
+// 199 with 4; bf16 31 528 tiles 322, 318) and fp32 of 7 copies with 2 from 6 144 tiles on (19 993 tiles 424 us with 3, 410
+// with 2; 5 412 tiles even; 6 copies alone 351 and 348 us, but a step of them 2 % slower than before with 2).  Whole tiles stay in launch order: runs are 1 % faster for 4 and more copies at
+// 1 600 to 5 400 tiles and 1-5 % slower below; so do launches of 32 768 tiles and more: alone they would gain 3-5 %, but between pack and unpack
+// runs are even there (46 696 tiles, -0.3 to 0.9 %; 38 449 tiles, K = 7 -1.4, K = 4 1.4) or slower (K = 4 107 589 tiles, the whole step 3.2 % at three
+// placements of its buffers, K = 6 fp32 4.7).
+inline bool reduce_runs(int64_t nt) { return nt < 32768; }
+
 // Workgroups per tile and per CU (0: as many as fit) by type, copies and tiles, where no store window
 // is open.  Quarter tiles held at 2 to 5 workgroups per CU (40-96 KB in flight) against whole tiles as
 // the launches had them before (two per CU for 3 to 5 copies), flat out:
@@ -157,24 +168,17 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_reduce_manyk_kernel(const KtTile 
 // Below, a launch is a few rounds of workgroups: quarter tiles only where whole ones would leave a sixth of
 // the last round idle (551 tiles of bf16: K = 8 17.8 -> 15.4 us against 16.3, K = 4 10.5 -> 8.9 against
 // 9.3; 491 tiles, 96 % of two rounds: whole tiles 4-8 % faster).
-// Shared tiles go in runs of 64 KiB per XCD, of 128 KiB up to 3 copies (kt_order), which is 2-6 % faster than launch order
-// (K = 4 fp32 19 993 tiles 259 -> 248 us, 63 057 tiles 825 -> 799; K = 5 fp32 63 057 tiles 1 014 -> 959; K = 6 bf16 31 528 tiles
-// 585 -> 553; K = 7 bf16 698 -> 647; K = 8 fp32 19 993 tiles 480 -> 460, bf16 31 528 tiles 790 -> 742; uneven launches:
-// bf16 596 tiles, K = 5 10.9 -> 10.5).  With runs 3 copies do best with 4 workgroups per CU (fp32 19 993 tiles 201 us with 5,
-// 199 with 4; bf16 31 528 tiles 322, 318) and fp32 of 6 and 7 copies with 2 from 6 144 tiles on (K = 7 19 993 tiles 424 us with 3, 410
-// with 2; K = 6 351, 348; 5 412 tiles even).  Whole tiles stay in launch order: runs are 1 % faster for 4 and more copies at
-// 1 600 to 5 400 tiles and 1-5 % slower below.
 template <typename T> KtShape reduce_shape(int K, int64_t nt)
 {
     const bool half = sizeof(T) == 2;
     switch (K) {
     case 1: break;
     case 2: if (nt >= 12288) return {4, 0}; break;
-    case 3: if (nt >= 8192) return {4, 4}; break;
+    case 3: if (nt >= 8192) return {4, reduce_runs(nt) ? 4u : 5u}; break;
     case 4: if (nt >= 4096) return nt >= (half ? 12288 : 8192) ? KtShape{4, 3} : KtShape{1, 2}; break;
     case 5: if (nt >= 4096) return {4, 3}; break;
-    case 6: if (nt >= 2048) return {4, half || nt < 6144 ? 3u : 2u}; break;
-    case 7: if (nt >= (half ? 2048 : 4096)) return {4, half || nt < 6144 ? 3u : 2u}; break;
+    case 6: if (nt >= 2048) return {4, 3}; break;
+    case 7: if (nt >= (half ? 2048 : 4096)) return {4, half || nt < 6144 || !reduce_runs(nt) ? 3u : 2u}; break;
     default: if (nt >= (half ? 2048 : 3072)) return {4, half ? 3u : 2u}; break;
     }
     return {K >= 2 && kt_uneven(nt) ? 4 : 1, 0};
@@ -217,7 +221,7 @@ hipError_t launch_reduce_k(const KtTile *tiles, const int64_t *b_elems, int64_t 
     const bool sys = reduce_sys(K, nt);
     const unsigned lds = kt_shape_lds(sh, 0);
     return launch_in_chunks(tiles, nt, sh.split, [&](const KtTile *t, dim3 grid) {
-        const uint32_t order = kt_order(grid.x, KT_TILE_BYTES / sh.split, sh.split == 1 ? 0 : K <= 3 ? 131072 : 65536);
+        const uint32_t order = kt_order(grid.x, KT_TILE_BYTES / sh.split, sh.split == 1 || !reduce_runs(nt) ? 0 : K <= 3 ? 131072 : 65536);
 #define KT_LAUNCH(SPLIT, INT, SYS) \
     kt_reduce_kernel<T, K, DEVW, SPLIT, INT, SYS><<<grid, block, lds, s>>>(t, b_elems, peers, outs, order, KtWindow{0, 0}, FewWeights(w))
         constexpr bool INT = sizeof(T) == 2 && K >= 6;
@@ -243,7 +247,7 @@ hipError_t launch_reduce_t(const KtDeviceTables &tb, int64_t tile0, int64_t nt, 
     const bool sys = reduce_sys(K, nt);
     const unsigned lds = kt_shape_lds(sh, 0);
     return launch_in_chunks(tiles, nt, sh.split, [&](const KtTile *t, dim3 grid) {
-        const uint32_t order = kt_order(grid.x, KT_TILE_BYTES / sh.split, sh.split == 1 ? 0 : 65536);
+        const uint32_t order = kt_order(grid.x, KT_TILE_BYTES / sh.split, sh.split == 1 || !reduce_runs(nt) ? 0 : 65536);
 #define KT_LAUNCH(SPLIT, SYS) \
     kt_reduce_manyk_kernel<T, DEVW, SPLIT, SYS><<<grid, dim3(KT_BLOCK), lds, s>>>(t, tb.b_elems, peers, outs, K, order, win, AllWeights(w))
         if (sys) { if (sh.split == 1) KT_LAUNCH(1, true); else KT_LAUNCH(4, true); }
