@@ -28,7 +28,8 @@ KT_MAX_PEERS = 64
 _DTYPES = {"f32": KT_F32, "bf16": KT_BF16}
 
 _lib = None
-_calls = None
+_native_of = {}         # the native calls of each loaded library that a plan has made one with
+_calls = None           # those made last
 
 
 class KtError(RuntimeError):
@@ -111,10 +112,14 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
-def _native():
-    """The plain device calls in native code; None while torch is not there (addresses as ints, host calls)."""
+def _native(L: Optional[ctypes.CDLL] = None):
+    """The plain device calls of a library (default: the current one) in native code; None while torch is not there (addresses
+    as ints, host calls)."""
     global _calls
-    if _calls is None and "torch" in sys.modules:
+    if L is None:
+        L = lib()
+    calls = _native_of.get(L)
+    if calls is None and "torch" in sys.modules:
         if not os.path.exists(MARSHAL_PATH):
             raise RuntimeError(
                 "_kt_marshal.so is not built (%s); run __graft_entry__.build() or "
@@ -125,16 +130,15 @@ def _native():
         spec = importlib.util.spec_from_file_location("_kt_marshal", MARSHAL_PATH)
         m = importlib.util.module_from_spec(spec)
         spec.loader.exec_module(m)
-        L = lib()
-        _calls = m.Calls(*[ctypes.cast(f, ctypes.c_void_p).value for f in (
+        _calls = _native_of[L] = calls = m.Calls(*[ctypes.cast(f, ctypes.c_void_p).value for f in (
             L.kt_bucket_pack, L.kt_weighted_reduce, L.kt_bucket_unpack_scale, L.kt_fused_step, L.kt_bucket_unpack_sgd,
             L.kt_bucket_unpack_sgd_master, L.kt_fused_step_sgd)])
-    return _calls
+    return calls
 
 
-def _check(status: int):
+def _check(status: int, L: Optional[ctypes.CDLL] = None):
     if status != 0:
-        L = lib()
+        L = L or lib()
         raise KtError(status, L.kt_status_string(status).decode(), L.kt_last_error().decode())
 
 
@@ -230,7 +234,7 @@ def kt_sampler_epoch(N: int, B: int, shares: Sequence[int], seed: int, epoch: in
 
 
 class Plan:
-    """Owner of a kt_plan handle."""
+    """Owner of a kt_plan handle.  Two libraries may be loaded in one process: every call goes to the one that made the handle."""
 
     def __init__(self, numels: Sequence[int], dtype: str, cap_bytes: int, align_bytes: int = 16):
         self.dtype = dtype
@@ -238,14 +242,19 @@ class Plan:
         T = len(self.numels)
         arr = (ctypes.c_int64 * max(1, T))(*self.numels)
         h = ctypes.c_void_p()
-        _check(lib().kt_plan_create(arr, T, _DTYPES[dtype], int(cap_bytes), int(align_bytes), ctypes.byref(h)))
+        self._lib, self._calls = lib(), None
+        self._check(self._lib.kt_plan_create(arr, T, _DTYPES[dtype], int(cap_bytes), int(align_bytes), ctypes.byref(h)))
         self._h = h
-        self._nb = lib().kt_plan_num_buckets(h)
+        self._nb = self._lib.kt_plan_num_buckets(h)
         self._id = (h.value, T, self._nb)       # what the native calls start with
+
+    def _check(self, status: int):
+        if status:
+            _check(status, self._lib)
 
     def close(self):
         if getattr(self, "_h", None):
-            _check(lib().kt_plan_destroy(self._h))
+            self._check(self._lib.kt_plan_destroy(self._h))
             self._h = self._id = None
 
     def __del__(self):
@@ -260,25 +269,25 @@ class Plan:
 
     @property
     def num_tensors(self) -> int:
-        return lib().kt_plan_num_tensors(self._h)
+        return self._lib.kt_plan_num_tensors(self._h)
 
     def bucket_info(self, b: int) -> Tuple[int, int, int]:
         n, f, c = ctypes.c_int64(), ctypes.c_int(), ctypes.c_int()
-        _check(lib().kt_plan_bucket_info(self._h, b, ctypes.byref(n), ctypes.byref(f), ctypes.byref(c)))
+        self._check(self._lib.kt_plan_bucket_info(self._h, b, ctypes.byref(n), ctypes.byref(f), ctypes.byref(c)))
         return n.value, f.value, c.value
 
     def tensor_info(self, t: int) -> Tuple[int, int]:
         b, o = ctypes.c_int(), ctypes.c_int64()
-        _check(lib().kt_plan_tensor_info(self._h, t, ctypes.byref(b), ctypes.byref(o)))
+        self._check(self._lib.kt_plan_tensor_info(self._h, t, ctypes.byref(b), ctypes.byref(o)))
         return b.value, o.value
 
     @property
     def num_tiles(self) -> int:
-        return lib().kt_plan_num_tiles(self._h)
+        return self._lib.kt_plan_num_tiles(self._h)
 
     def tile_info(self, i: int) -> Tuple[int, int, int, int]:
         b, k, f, c = ctypes.c_int(), ctypes.c_int64(), ctypes.c_int(), ctypes.c_int()
-        _check(lib().kt_plan_tile_info(self._h, i, ctypes.byref(b), ctypes.byref(k), ctypes.byref(f), ctypes.byref(c)))
+        self._check(self._lib.kt_plan_tile_info(self._h, i, ctypes.byref(b), ctypes.byref(k), ctypes.byref(f), ctypes.byref(c)))
         return b.value, k.value, f.value, c.value
 
     def bucket_elems(self) -> List[int]:
@@ -291,12 +300,14 @@ class Plan:
 
     def _plainly(self, name: str, *args) -> bool:
         """Make the call natively; False where an argument is of a form that is left to ctypes."""
-        calls = _calls or _native()
+        calls = self._calls
+        if calls is None:
+            calls = self._calls = _native(self._lib)
         if calls is None or self._id is None:
             return False
         status = getattr(calls, name)(*self._id, *args)
         if status:
-            _check(status)
+            self._check(status)
         return status is not None
 
     def marshal(self, items: Sequence) -> ctypes.Array:
@@ -324,14 +335,14 @@ class Plan:
         """Copy the weights into the plan's device memory; device calls with weights=None read them there."""
         K = len(weights)
         w = weights if isinstance(weights, ctypes.Array) else (ctypes.c_float * max(1, K))(*[float(x) for x in weights])
-        _check(lib().kt_plan_set_weights(self._h, w, K, _stream(stream)))
+        self._check(self._lib.kt_plan_set_weights(self._h, w, K, _stream(stream)))
 
     def kt_bucket_pack(self, bucket: int, tensors, bucket_bufs, stream=None):
         if self._plainly("pack", bucket, tensors, bucket_bufs, stream):
             return
         T, nb = len(self.numels), self.num_buckets
-        _check(lib().kt_bucket_pack(self._h, bucket, self._arr(tensors, T, "tensor_ptrs"),
-                                    self._arr(bucket_bufs, nb, "bucket_bufs"), _stream(stream)))
+        self._check(self._lib.kt_bucket_pack(self._h, bucket, self._arr(tensors, T, "tensor_ptrs"),
+                                             self._arr(bucket_bufs, nb, "bucket_bufs"), _stream(stream)))
 
     def kt_weighted_reduce(self, bucket: int, peer_bufs, K: int, weights, out_bufs, stream=None):
         """peer_bufs: flat sequence, entry [b * K + k]."""
@@ -339,37 +350,37 @@ class Plan:
             return
         nb = self.num_buckets
         if not 1 <= K <= KT_MAX_PEERS:      # the library rejects K before it reads any array
-            _check(lib().kt_weighted_reduce(self._h, bucket, None, K, None, None, _stream(stream)))
-        _check(lib().kt_weighted_reduce(self._h, bucket, self._arr(peer_bufs, nb * K, "peer_bufs"), K,
-                                        self._weights(weights, K), self._arr(out_bufs, nb, "bucket_bufs (outputs)"),
-                                        _stream(stream)))
+            self._check(self._lib.kt_weighted_reduce(self._h, bucket, None, K, None, None, _stream(stream)))
+        self._check(self._lib.kt_weighted_reduce(self._h, bucket, self._arr(peer_bufs, nb * K, "peer_bufs"), K,
+                                                 self._weights(weights, K), self._arr(out_bufs, nb, "bucket_bufs (outputs)"),
+                                                 _stream(stream)))
 
     def kt_bucket_unpack_scale(self, bucket: int, bucket_bufs, scale: float, tensors, stream=None):
         if self._plainly("unpack", bucket, bucket_bufs, scale, tensors, stream):
             return
         T, nb = len(self.numels), self.num_buckets
-        _check(lib().kt_bucket_unpack_scale(self._h, bucket, self._arr(bucket_bufs, nb, "bucket_bufs"), float(scale),
-                                            self._arr(tensors, T, "tensor_ptrs"), _stream(stream)))
+        self._check(self._lib.kt_bucket_unpack_scale(self._h, bucket, self._arr(bucket_bufs, nb, "bucket_bufs"), float(scale),
+                                                     self._arr(tensors, T, "tensor_ptrs"), _stream(stream)))
 
     def _fused(self, fn, bucket, local_tensors, peer_bufs, K, weights, scale, out_tensors, stream):
         T, nb = len(self.numels), self.num_buckets
         if not 1 <= K <= KT_MAX_PEERS:      # the library rejects K before it reads any array
-            _check(fn(self._h, bucket, None, None, K, None, float(scale), None, _stream(stream)))
-        _check(fn(self._h, bucket, self._arr(local_tensors, T, "tensor_ptrs (local)"),
-                  self._arr(peer_bufs, nb * (K - 1), "peer_bufs"), K, self._weights(weights, K), float(scale),
-                  self._arr(out_tensors, T, "tensor_ptrs (outputs)"), _stream(stream)))
+            self._check(fn(self._h, bucket, None, None, K, None, float(scale), None, _stream(stream)))
+        self._check(fn(self._h, bucket, self._arr(local_tensors, T, "tensor_ptrs (local)"),
+                       self._arr(peer_bufs, nb * (K - 1), "peer_bufs"), K, self._weights(weights, K), float(scale),
+                       self._arr(out_tensors, T, "tensor_ptrs (outputs)"), _stream(stream)))
 
     def kt_fused_step(self, bucket: int, local_tensors, peer_bufs, K: int, weights, scale: float, out_tensors,
                       stream=None):
         """peer_bufs: flat sequence over peers 1..K-1, entry [b * (K-1) + (k-1)]."""
         if self._plainly("fused", bucket, K, local_tensors, peer_bufs, weights, scale, out_tensors, stream):
             return
-        self._fused(lib().kt_fused_step, bucket, local_tensors, peer_bufs, K, weights, scale, out_tensors, stream)
+        self._fused(self._lib.kt_fused_step, bucket, local_tensors, peer_bufs, K, weights, scale, out_tensors, stream)
 
     def kt_fused_step_noalloc(self, bucket: int, local_tensors, peer_bufs, K: int, weights, scale: float,
                               out_tensors, stream=None):
         """kt_fused_step through the entry point that allocates nothing."""
-        self._fused(lib().kt_fused_step_noalloc, bucket, local_tensors, peer_bufs, K, weights, scale, out_tensors,
+        self._fused(self._lib.kt_fused_step_noalloc, bucket, local_tensors, peer_bufs, K, weights, scale, out_tensors,
                     stream)
 
     def kt_bucket_unpack_sgd(self, bucket: int, bucket_bufs, scale: float, params, momenta, lr: float,
@@ -377,11 +388,11 @@ class Plan:
         if self._plainly("sgd", bucket, bucket_bufs, scale, params, momenta, lr, momentum, weight_decay, first_step, stream):
             return
         T, nb = len(self.numels), self.num_buckets
-        _check(lib().kt_bucket_unpack_sgd(self._h, bucket, self._arr(bucket_bufs, nb, "bucket_bufs"), float(scale),
-                                          self._arr(params, T, "tensor_ptrs (parameters)"),
-                                          self._arr(momenta, T, "tensor_ptrs (momentum)"), float(lr),
-                                          float(momentum), float(weight_decay), int(bool(first_step)),
-                                          _stream(stream)))
+        self._check(self._lib.kt_bucket_unpack_sgd(self._h, bucket, self._arr(bucket_bufs, nb, "bucket_bufs"), float(scale),
+                                                   self._arr(params, T, "tensor_ptrs (parameters)"),
+                                                   self._arr(momenta, T, "tensor_ptrs (momentum)"), float(lr),
+                                                   float(momentum), float(weight_decay), int(bool(first_step)),
+                                                   _stream(stream)))
 
     def kt_bucket_unpack_sgd_master(self, bucket: int, bucket_bufs, scale: float, masters, momenta, models,
                                     lr: float, momentum: float, weight_decay: float, first_step: bool, stream=None):
@@ -390,12 +401,12 @@ class Plan:
                          first_step, stream):
             return
         T, nb = len(self.numels), self.num_buckets
-        _check(lib().kt_bucket_unpack_sgd_master(self._h, bucket, self._arr(bucket_bufs, nb, "bucket_bufs"),
-                                                 float(scale), self._arr(masters, T, "tensor_ptrs (master parameters)"),
-                                                 self._arr(momenta, T, "tensor_ptrs (momentum)"),
-                                                 self._arr(models, T, "tensor_ptrs (model parameters)"), float(lr),
-                                                 float(momentum), float(weight_decay), int(bool(first_step)),
-                                                 _stream(stream)))
+        self._check(self._lib.kt_bucket_unpack_sgd_master(self._h, bucket, self._arr(bucket_bufs, nb, "bucket_bufs"),
+                                                          float(scale), self._arr(masters, T, "tensor_ptrs (master parameters)"),
+                                                          self._arr(momenta, T, "tensor_ptrs (momentum)"),
+                                                          self._arr(models, T, "tensor_ptrs (model parameters)"), float(lr),
+                                                          float(momentum), float(weight_decay), int(bool(first_step)),
+                                                          _stream(stream)))
 
     def kt_fused_step_sgd(self, bucket: int, local_tensors, peer_bufs, K: int, weights, scale: float, params, momenta,
                           models, lr: float, momentum: float, weight_decay: float, first_step: bool, stream=None):
@@ -406,33 +417,33 @@ class Plan:
             return
         T, nb = len(self.numels), self.num_buckets
         if not 1 <= K <= KT_MAX_PEERS:
-            _check(lib().kt_fused_step_sgd(self._h, bucket, None, None, K, None, 1.0, None, None, None, 0.0, 0.0, 0.0, 0,
-                                           _stream(stream)))
+            self._check(self._lib.kt_fused_step_sgd(self._h, bucket, None, None, K, None, 1.0, None, None, None, 0.0, 0.0, 0.0, 0,
+                                                    _stream(stream)))
         m = None if models is None else self._arr(models, T, "tensor_ptrs (model parameters)")
-        _check(lib().kt_fused_step_sgd(self._h, bucket, self._arr(local_tensors, T, "tensor_ptrs (local gradients)"),
-                                       self._arr(peer_bufs, nb * (K - 1), "peer_bufs"), K, self._weights(weights, K),
-                                       float(scale), self._arr(params, T, "tensor_ptrs (parameters)"),
-                                       self._arr(momenta, T, "tensor_ptrs (momentum)"), m, float(lr), float(momentum),
-                                       float(weight_decay), int(bool(first_step)), _stream(stream)))
+        self._check(self._lib.kt_fused_step_sgd(self._h, bucket, self._arr(local_tensors, T, "tensor_ptrs (local gradients)"),
+                                                self._arr(peer_bufs, nb * (K - 1), "peer_bufs"), K, self._weights(weights, K),
+                                                float(scale), self._arr(params, T, "tensor_ptrs (parameters)"),
+                                                self._arr(momenta, T, "tensor_ptrs (momentum)"), m, float(lr), float(momentum),
+                                                float(weight_decay), int(bool(first_step)), _stream(stream)))
 
     def kt_fused_step_sgd_resident(self, bucket: int, local_tensors, peer_bufs, K: int, params, momenta, models,
                                    first_step: bool, stream=None):
         """kt_fused_step_sgd with the weights of kt_plan_set_weights and the scalars of kt_plan_set_sgd."""
         T, nb = len(self.numels), self.num_buckets
         if not 1 <= K <= KT_MAX_PEERS:
-            _check(lib().kt_fused_step_sgd_resident(self._h, bucket, None, None, K, None, None, None, 0, _stream(stream)))
+            self._check(self._lib.kt_fused_step_sgd_resident(self._h, bucket, None, None, K, None, None, None, 0, _stream(stream)))
         m = None if models is None else self._arr(models, T, "tensor_ptrs (model parameters)")
-        _check(lib().kt_fused_step_sgd_resident(self._h, bucket,
-                                                self._arr(local_tensors, T, "tensor_ptrs (local gradients)"),
-                                                self._arr(peer_bufs, nb * (K - 1), "peer_bufs"), K,
-                                                self._arr(params, T, "tensor_ptrs (parameters)"),
-                                                self._arr(momenta, T, "tensor_ptrs (momentum)"), m,
-                                                int(bool(first_step)), _stream(stream)))
+        self._check(self._lib.kt_fused_step_sgd_resident(self._h, bucket,
+                                                         self._arr(local_tensors, T, "tensor_ptrs (local gradients)"),
+                                                         self._arr(peer_bufs, nb * (K - 1), "peer_bufs"), K,
+                                                         self._arr(params, T, "tensor_ptrs (parameters)"),
+                                                         self._arr(momenta, T, "tensor_ptrs (momentum)"), m,
+                                                         int(bool(first_step)), _stream(stream)))
 
     def kt_plan_set_sgd(self, scale: float, lr: float, momentum: float, weight_decay: float, stream=None):
         """Copy the optimizer scalars into the plan's device memory (read by kt_bucket_unpack_sgd_resident)."""
-        _check(lib().kt_plan_set_sgd(self._h, float(scale), float(lr), float(momentum), float(weight_decay),
-                                     _stream(stream)))
+        self._check(self._lib.kt_plan_set_sgd(self._h, float(scale), float(lr), float(momentum), float(weight_decay),
+                                              _stream(stream)))
 
     def kt_bucket_unpack_sgd_resident(self, bucket: int, bucket_bufs, params, momenta, models, first_step: bool,
                                       stream=None):
@@ -440,7 +451,7 @@ class Plan:
         bf16 model copy."""
         T, nb = len(self.numels), self.num_buckets
         m = None if models is None else self._arr(models, T, "tensor_ptrs (model parameters)")
-        _check(lib().kt_bucket_unpack_sgd_resident(self._h, bucket, self._arr(bucket_bufs, nb, "bucket_bufs"),
-                                                   self._arr(params, T, "tensor_ptrs (parameters)"),
-                                                   self._arr(momenta, T, "tensor_ptrs (momentum)"), m,
-                                                   int(bool(first_step)), _stream(stream)))
+        self._check(self._lib.kt_bucket_unpack_sgd_resident(self._h, bucket, self._arr(bucket_bufs, nb, "bucket_bufs"),
+                                                            self._arr(params, T, "tensor_ptrs (parameters)"),
+                                                            self._arr(momenta, T, "tensor_ptrs (momentum)"), m,
+                                                            int(bool(first_step)), _stream(stream)))
