@@ -7,7 +7,8 @@ status.  There is no fallback: if the library is missing, loading fails.
 
 The device calls that a training step makes go through _kt_marshal.so where their arguments have
 the plain forms (lists of tensors, marshalled arrays) and torch is there; everything
-else goes through ctypes.
+else goes through ctypes, and so does every call where _kt_marshal.so is missing or was built for
+another torch or Python (with one warning: only the marshalling is slower).
 """
 from __future__ import annotations
 
@@ -15,6 +16,7 @@ import ctypes
 import importlib.util
 import os
 import sys
+import warnings
 from array import array
 from typing import List, Optional, Sequence, Tuple
 
@@ -28,6 +30,7 @@ KT_MAX_PEERS = 64
 _DTYPES = {"f32": KT_F32, "bf16": KT_BF16}
 
 _lib = None
+_marshal = None         # the module of the native calls; False: none for this torch and this Python
 _native_of = {}         # the native calls of each loaded library that a plan has made one with
 _calls = None           # those made last
 
@@ -112,24 +115,34 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+def _marshal_module():
+    global _marshal
+    if _marshal is None:
+        import torch            # complete before the module that is linked against it
+        _marshal = False
+        if hasattr(torch._C, "_cuda_getCurrentRawStream"):
+            try:
+                spec = importlib.util.spec_from_file_location("_kt_marshal", MARSHAL_PATH)
+                m = importlib.util.module_from_spec(spec)
+                spec.loader.exec_module(m)
+                _marshal = m
+            except ImportError as e:
+                warnings.warn("%s; lists of tensors are marshalled in Python, which takes 0.1 us a tensor: run "
+                              "__graft_entry__.build() or python paper_2505_10183_amd/build.py" % e, RuntimeWarning)
+    return _marshal
+
+
 def _native(L: Optional[ctypes.CDLL] = None):
-    """The plain device calls of a library (default: the current one) in native code; None while torch is not there (addresses
-    as ints, host calls)."""
+    """The plain device calls of a library (default: the current one) in native code; None while torch is not
+    there (addresses as ints, host calls) and where there is no module for it."""
     global _calls
     if L is None:
         L = lib()
     calls = _native_of.get(L)
     if calls is None and "torch" in sys.modules:
-        if not os.path.exists(MARSHAL_PATH):
-            raise RuntimeError(
-                "_kt_marshal.so is not built (%s); run __graft_entry__.build() or "
-                "python paper_2505_10183_amd/build.py" % MARSHAL_PATH)
-        import torch        # complete before the module that is linked against it
-        if not hasattr(torch._C, "_cuda_getCurrentRawStream"):
+        m = _marshal_module()
+        if not m:
             return None
-        spec = importlib.util.spec_from_file_location("_kt_marshal", MARSHAL_PATH)
-        m = importlib.util.module_from_spec(spec)
-        spec.loader.exec_module(m)
         _calls = _native_of[L] = calls = m.Calls(*[ctypes.cast(f, ctypes.c_void_p).value for f in (
             L.kt_bucket_pack, L.kt_weighted_reduce, L.kt_bucket_unpack_scale, L.kt_fused_step, L.kt_bucket_unpack_sgd,
             L.kt_bucket_unpack_sgd_master, L.kt_fused_step_sgd)])

@@ -62,6 +62,7 @@ def build_marshal(verbose: bool = False) -> str:
     base = os.path.dirname(torch.__file__)
     tmp = MARSHAL_LIB + ".tmp%d" % os.getpid()
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
+           '-DKT_TORCH_VERSION="%s"' % torch.__version__,          # it refuses to load beside another
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
            "-I", os.path.join(ROOT, "include"), "-isystem", os.path.join(base, "include"),
            "-isystem", os.path.join(base, "include", "torch", "csrc", "api", "include"),

@@ -12,6 +12,8 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <cstdint>
+#include <cstring>
+#include <string>
 #include <vector>
 
 #include "kt.h"
@@ -298,10 +300,28 @@ PyObject *attribute(const char *mod, const char *name)
     return v;
 }
 
+// What looks into a tensor here is inline code of torch's and Python's headers: the objects have to be those that it was
+// compiled for.
+bool built_for_these()
+{
+    const std::string python = std::to_string(PY_MAJOR_VERSION) + "." + std::to_string(PY_MINOR_VERSION) + ".";
+    const std::string now = std::string(Py_GetVersion()).substr(0, std::strcspn(Py_GetVersion(), " "));
+    PyObject *version = attribute("torch", "__version__");
+    const char *torch_now = version ? PyUnicode_AsUTF8(version) : nullptr;
+    if (!torch_now) return false;
+    const bool same = !std::strcmp(torch_now, KT_TORCH_VERSION) && now.compare(0, python.size(), python) == 0;
+    if (!same)
+        PyErr_Format(PyExc_ImportError, "_kt_marshal.so was built for torch %s and Python %s* and not for torch %s and Python %s",
+                     KT_TORCH_VERSION, python.c_str(), torch_now, now.c_str());
+    Py_DECREF(version);
+    return same;
+}
+
 }  // namespace
 
 PyMODINIT_FUNC PyInit__kt_marshal(void)
 {
+    if (!built_for_these()) return nullptr;
     ctypes_array = attribute("ctypes", "Array");
     get_device = ctypes_array ? attribute("torch._C", "_cuda_getDevice") : nullptr;
     get_stream = get_device ? attribute("torch._C", "_cuda_getCurrentRawStream") : nullptr;
