@@ -167,11 +167,14 @@ def _ptr(x) -> int:
 def _ptr_array(items: Sequence) -> ctypes.Array:
     # Lists of tensors, the usual case, go through one array of addresses: 158 tensors take 19 us
     # of which 12 are their data_ptr() calls, against 33 us item by item.
-    if len(items):
+    if len(items) and type(items[0]) is not int:
         try:
-            addresses = array("Q", [x.data_ptr() for x in items])
-        except AttributeError:
-            pass                # addresses or None among them
+            try:
+                addresses = array("Q", [x.data_ptr() for x in items])
+            except AttributeError:          # addresses or None among them
+                addresses = array("Q", [0 if x is None else x if isinstance(x, int) else x.data_ptr() for x in items])
+        except OverflowError:
+            pass                            # no address; c_void_p takes it all the same
         else:
             return (ctypes.c_void_p * len(items)).from_buffer(addresses)
     arr = (ctypes.c_void_p * max(1, len(items)))()

@@ -1,7 +1,7 @@
 // The hot half of the Python binding: the device calls of a plan with lists of tensors or marshalled pointer
-// arrays, straight to the C ABI.  Only the plainest forms are taken here (lists and tuples of plain tensors, c_void_p and c_float
-// arrays, lists of floats, streams that are None or an int); for every other form a call returns None and
-// the ctypes half of the binding, which raises every error of marshalling, makes the call.
+// arrays, straight to the C ABI.  Tensors and buffers are taken as lists and tuples of plain tensors or as c_void_p arrays;
+// weights, scalars and streams in every form that the ctypes half takes.  For anything else a call returns None and
+// that half, which raises every error of marshalling, makes the call.
 //
 // On small sets the host decides: a pack, reduce and unpack of 158 tensors handed over as lists asked 323 tensors
 // for their addresses through Python and copied them twice, 34.5 us a step where the kernels take 18 (18.5 now, the kernels
@@ -21,6 +21,7 @@
 namespace {
 
 PyObject *ctypes_array = nullptr;       // ctypes.Array
+PyObject *cuda_stream = nullptr;        // "cuda_stream"
 PyObject *get_device = nullptr, *get_stream = nullptr;      // torch._C._cuda_getDevice, _cuda_getCurrentRawStream
 
 // The entry points of one loaded library, as addresses: two libraries may be loaded in one process.
@@ -44,9 +45,10 @@ struct Calls {
 constexpr int MAX_ARRAYS = 5;
 
 // What one call has converted.  `ok` turns false at the first form that is not taken here; a Python error is never left set.
+// Scalars, weights and the stream may run Python (__float__, __index__, the collector with what it finalizes), and with it other
+// calls of this thread: they are asked for before the pointers, whose tables the thread has once.
 struct Args {
     PyObject *const *a;
-    int at = 0;
     bool ok = true;
     Py_buffer held[MAX_ARRAYS + 1];
     int nheld = 0;
@@ -65,41 +67,47 @@ struct Args {
         return ok = false;
     }
 
-    // an int that fits a C int
-    int integer()
+    // an int, or what stands for one, that fits a C int
+    int integer(int i)
     {
-        if (!ok || !PyLong_Check(a[at])) return fail(), 0;
+        if (!ok) return 0;
+        PyObject *x = a[i], *own = PyLong_CheckExact(x) ? nullptr : PyNumber_Index(x);
+        if (!PyLong_CheckExact(x) && !own) return fail(), 0;
         int over = 0;
-        const long v = PyLong_AsLongAndOverflow(a[at++], &over);
+        const long v = PyLong_AsLongAndOverflow(own ? own : x, &over);
+        Py_XDECREF(own);
         if (over || v != (int)v) return fail(), 0;
         return (int)v;
     }
     void *address(PyObject *x)
     {
-        if (!PyLong_CheckExact(x)) return fail(), nullptr;
+        if (!PyLong_Check(x)) return fail(), nullptr;
         void *p = PyLong_AsVoidPtr(x);
         if (!p && PyErr_Occurred()) fail();
         return p;
     }
-    float real()
+    // float(x)
+    float real(PyObject *x)
     {
-        if (!ok) return 0.0f;
-        if (PyFloat_CheckExact(a[at])) return (float)PyFloat_AS_DOUBLE(a[at++]);
-        if (!PyLong_CheckExact(a[at])) return fail(), 0.0f;
-        const double v = PyLong_AsDouble(a[at++]);
-        if (v == -1.0 && PyErr_Occurred()) fail();
+        if (PyFloat_CheckExact(x)) return (float)PyFloat_AS_DOUBLE(x);
+        PyObject *f = PyNumber_Float(x);
+        if (!f) return fail(), 0.0f;
+        const double v = PyFloat_AS_DOUBLE(f);
+        Py_DECREF(f);
         return (float)v;
     }
-    int flag()
+    float real(int i) { return ok ? real(a[i]) : 0.0f; }
+    // bool(x)
+    int flag(int i)
     {
-        if (!ok || !PyBool_Check(a[at])) return fail(), 0;
-        return a[at++] == Py_True;
+        const int v = ok ? PyObject_IsTrue(a[i]) : 0;
+        if (v < 0) fail();
+        return v > 0;
     }
 
     // `want` elements of a ctypes array whose items are of struct code `code`; marshal() pads an empty list to one entry
-    void *array(Py_ssize_t want, char code, Py_ssize_t size)
+    void *array(PyObject *x, Py_ssize_t want, char code, Py_ssize_t size)
     {
-        PyObject *x = a[at];
         if (!PyObject_TypeCheck(x, reinterpret_cast<PyTypeObject *>(ctypes_array))) return fail(), nullptr;
         Py_buffer &b = held[nheld];
         if (PyObject_GetBuffer(x, &b, PyBUF_FORMAT | PyBUF_ND) != 0) return fail(), nullptr;
@@ -107,51 +115,42 @@ struct Args {
         const char *f = b.format ? b.format : "";
         if (*f == '<' || *f == '=' || *f == '@') ++f;
         if (b.ndim != 1 || b.itemsize != size || f[0] != code || f[1] || b.shape[0] != (want > 0 ? want : 1)) return fail(), nullptr;
-        ++at;
         return b.buf;
     }
     // `want` device addresses
-    void *const *pointers(Py_ssize_t want)
+    void *const *pointers(int i, Py_ssize_t want)
     {
         if (!ok) return nullptr;
-        PyObject *x = a[at];
-        if (!PyList_CheckExact(x) && !PyTuple_CheckExact(x)) return static_cast<void *const *>(array(want, 'P', sizeof(void *)));
+        PyObject *x = a[i];
+        if (!PyList_CheckExact(x) && !PyTuple_CheckExact(x)) return static_cast<void *const *>(array(x, want, 'P', sizeof(void *)));
         const Py_ssize_t n = PySequence_Fast_GET_SIZE(x);
         if (n != want || at::impl::torch_function_mode_enabled()) return fail(), nullptr;
         static thread_local std::vector<void *> tables[MAX_ARRAYS];      // kept: no allocation per call
         try {
             std::vector<void *> &t = tables[arrays++];
             t.resize(n > 0 ? n : 1);
-            for (Py_ssize_t i = 0; i < n; ++i) {
-                PyObject *item = PySequence_Fast_GET_ITEM(x, i);
+            for (Py_ssize_t j = 0; j < n; ++j) {
+                PyObject *item = PySequence_Fast_GET_ITEM(x, j);
                 if (!THPVariable_CheckExact(item)) return fail(), nullptr;
-                t[i] = THPVariable_Unpack(item).data_ptr();
+                t[j] = THPVariable_Unpack(item).data_ptr();
             }
-            ++at;
             return t.data();
         } catch (...) {         // a tensor without memory of its own, say: asked again through Python, it raises its own error
             return fail(), nullptr;
         }
     }
-    const float *weights(int K)
+    const float *weights(int i, int K)
     {
-        if (!ok) return nullptr;
-        PyObject *x = a[at];
-        if (x == Py_None) {             // the plan's device-resident ones
-            ++at;
-            return nullptr;
-        }
-        if (!PyList_CheckExact(x) && !PyTuple_CheckExact(x)) return static_cast<const float *>(array(K, 'f', sizeof(float)));
-        if (PySequence_Fast_GET_SIZE(x) != K) return fail(), nullptr;
-        for (int k = 0; k < K; ++k) {
-            PyObject *item = PySequence_Fast_GET_ITEM(x, k);
-            if (!PyFloat_CheckExact(item)) return fail(), nullptr;
-            w[k] = (float)PyFloat_AS_DOUBLE(item);
-        }
-        ++at;
+        if (!ok || a[i] == Py_None) return nullptr;      // None: the plan's device-resident ones
+        if (PyObject_TypeCheck(a[i], reinterpret_cast<PyTypeObject *>(ctypes_array)))
+            return static_cast<const float *>(array(a[i], K, 'f', sizeof(float)));
+        if (PyObject_Size(a[i]) != K) return fail(), nullptr;
+        PyObject *t = PySequence_Tuple(a[i]);           // its own: __float__ of an item may change the list
+        if (!t || PyTuple_GET_SIZE(t) != K) fail();
+        for (int k = 0; ok && k < K; ++k) w[k] = real(PyTuple_GET_ITEM(t, k));
+        Py_XDECREF(t);
         return w;
     }
-    // Asked for first: it runs Python, and with it whatever the collector finds to finalize.
     void *stream(PyObject *x)
     {
         if (x == Py_None) {             // torch's current stream on the current device
@@ -163,11 +162,15 @@ struct Args {
             if (PyErr_Occurred()) fail();
             return s;
         }
-        return address(x);
+        if (PyLong_Check(x)) return address(x);
+        PyObject *raw = PyObject_GetAttr(x, cuda_stream);
+        void *s = raw ? address(raw) : (fail(), nullptr);
+        Py_XDECREF(raw);
+        return s;
     }
-    int copies()
+    int copies(int i)
     {
-        const int K = integer();
+        const int K = integer(i);
         if (ok && (K < 1 || K > KT_MAX_PEERS)) fail();
         return ok ? K : 1;
     }
@@ -179,10 +182,10 @@ struct Plan {
     int T, nb, bucket;
     explicit Plan(Args &x)
     {
-        p = static_cast<kt_plan *>(x.address(x.a[x.at++]));
-        T = x.integer();
-        nb = x.integer();
-        bucket = x.integer();
+        p = static_cast<kt_plan *>(x.address(x.a[0]));
+        T = x.integer(1);
+        nb = x.integer(2);
+        bucket = x.integer(3);
     }
 };
 
@@ -209,61 +212,54 @@ const Entries &entries(PyObject *self) { return reinterpret_cast<Calls *>(self)-
         const Plan p(x);
 
 KT_CALL(pack, 7)
-    void *const *t = x.pointers(p.T), *const *b = x.pointers(p.nb);
+    void *const *t = x.pointers(4, p.T), *const *b = x.pointers(5, p.nb);
     return finish(x, [&] { return f.pack(p.p, p.bucket, t, b, s); });
 }
 
 KT_CALL(reduce, 9)
-    const int K = x.copies();
-    void *const *in = x.pointers((Py_ssize_t)p.nb * K);
-    const float *w = x.weights(K);
-    void *const *out = x.pointers(p.nb);
+    const int K = x.copies(4);
+    const float *w = x.weights(6, K);
+    void *const *in = x.pointers(5, (Py_ssize_t)p.nb * K), *const *out = x.pointers(7, p.nb);
     return finish(x, [&] { return f.reduce(p.p, p.bucket, in, K, w, out, s); });
 }
 
 KT_CALL(unpack, 8)
-    void *const *b = x.pointers(p.nb);
-    const float scale = x.real();
-    void *const *t = x.pointers(p.T);
+    const float scale = x.real(5);
+    void *const *b = x.pointers(4, p.nb), *const *t = x.pointers(6, p.T);
     return finish(x, [&] { return f.unpack(p.p, p.bucket, b, scale, t, s); });
 }
 
 KT_CALL(fused, 11)
-    const int K = x.copies();
-    void *const *in = x.pointers(p.T), *const *peers = x.pointers((Py_ssize_t)p.nb * (K - 1));
-    const float *w = x.weights(K);
-    const float scale = x.real();
-    void *const *out = x.pointers(p.T);
+    const int K = x.copies(4);
+    const float *w = x.weights(7, K);
+    const float scale = x.real(8);
+    void *const *in = x.pointers(5, p.T), *const *peers = x.pointers(6, (Py_ssize_t)p.nb * (K - 1)), *const *out = x.pointers(9, p.T);
     return finish(x, [&] { return f.fused(p.p, p.bucket, in, peers, K, w, scale, out, s); });
 }
 
 KT_CALL(sgd, 13)
-    void *const *b = x.pointers(p.nb);
-    const float scale = x.real();
-    void *const *params = x.pointers(p.T), *const *momenta = x.pointers(p.T);
-    const float lr = x.real(), mu = x.real(), wd = x.real();
-    const int first = x.flag();
+    const float scale = x.real(5), lr = x.real(8), mu = x.real(9), wd = x.real(10);
+    const int first = x.flag(11);
+    void *const *b = x.pointers(4, p.nb), *const *params = x.pointers(6, p.T), *const *momenta = x.pointers(7, p.T);
     return finish(x, [&] { return f.sgd(p.p, p.bucket, b, scale, params, momenta, lr, mu, wd, first, s); });
 }
 
 KT_CALL(master, 14)
-    void *const *b = x.pointers(p.nb);
-    const float scale = x.real();
-    void *const *params = x.pointers(p.T), *const *momenta = x.pointers(p.T), *const *models = x.pointers(p.T);
-    const float lr = x.real(), mu = x.real(), wd = x.real();
-    const int first = x.flag();
+    const float scale = x.real(5), lr = x.real(9), mu = x.real(10), wd = x.real(11);
+    const int first = x.flag(12);
+    void *const *b = x.pointers(4, p.nb), *const *params = x.pointers(6, p.T), *const *momenta = x.pointers(7, p.T);
+    void *const *models = x.pointers(8, p.T);
     return finish(x, [&] { return f.master(p.p, p.bucket, b, scale, params, momenta, models, lr, mu, wd, first, s); });
 }
 
 KT_CALL(fused_sgd, 17)
-    const int K = x.copies();
-    void *const *in = x.pointers(p.T), *const *peers = x.pointers((Py_ssize_t)p.nb * (K - 1));
-    const float *w = x.weights(K);
-    const float scale = x.real();
-    void *const *params = x.pointers(p.T), *const *momenta = x.pointers(p.T), *const *models = nullptr;
-    if (x.ok && x.a[x.at] == Py_None) ++x.at; else models = x.pointers(p.T);
-    const float lr = x.real(), mu = x.real(), wd = x.real();
-    const int first = x.flag();
+    const int K = x.copies(4);
+    const float *w = x.weights(7, K);
+    const float scale = x.real(8), lr = x.real(12), mu = x.real(13), wd = x.real(14);
+    const int first = x.flag(15);
+    void *const *in = x.pointers(5, p.T), *const *peers = x.pointers(6, (Py_ssize_t)p.nb * (K - 1));
+    void *const *params = x.pointers(9, p.T), *const *momenta = x.pointers(10, p.T);
+    void *const *models = x.a[11] == Py_None ? nullptr : x.pointers(11, p.T);
     return finish(x, [&] { return f.fused_sgd(p.p, p.bucket, in, peers, K, w, scale, params, momenta, models, lr, mu, wd, first, s); });
 }
 
@@ -325,7 +321,8 @@ PyMODINIT_FUNC PyInit__kt_marshal(void)
     ctypes_array = attribute("ctypes", "Array");
     get_device = ctypes_array ? attribute("torch._C", "_cuda_getDevice") : nullptr;
     get_stream = get_device ? attribute("torch._C", "_cuda_getCurrentRawStream") : nullptr;
-    if (!get_stream) return nullptr;
+    cuda_stream = get_stream ? PyUnicode_InternFromString("cuda_stream") : nullptr;
+    if (!cuda_stream) return nullptr;
     calls_type.tp_name = "_kt_marshal.Calls";
     calls_type.tp_basicsize = sizeof(Calls);
     calls_type.tp_flags = Py_TPFLAGS_DEFAULT;

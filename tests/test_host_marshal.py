@@ -4,6 +4,7 @@ import ctypes
 import os
 import sys
 
+import numpy as np
 import pytest
 import torch
 
@@ -143,3 +144,75 @@ def test_references_are_left_as_they_were(native):
         calls.pack(1, T, NB, 0, a, b, 0)
         calls.pack(1, T, NB, 0, a, l, 0)
     assert [sys.getrefcount(x) for x in (l, b, a, *l, *b)] == before
+
+
+class Stream:
+    cuda_stream = 91
+
+
+class Real:
+    """float(x), which makes calls of its own meanwhile."""
+
+    def __init__(self, value, then):
+        self.value, self.then = value, then
+
+    def __float__(self):
+        self.then()
+        return self.value
+
+
+def sgd(calls, lr=0.1, first=True, stream=0):
+    return calls.sgd(1, T, NB, 0, tensors(NB), 1.0, tensors(T), tensors(T), lr, 0.9, 0.0, first, stream)
+
+
+@pytest.mark.parametrize("stream,want", [(Stream(), 91), (77, 77), (True, 1)])
+def test_streams(native, stream, want):
+    calls, seen, _ = native
+    del seen[:]
+    assert calls.pack(1, T, NB, 0, tensors(T), tensors(NB), stream) == 0 and sgd(calls, stream=stream) == 0
+    assert seen[0][-1] == want and seen[1][-1] == want
+
+
+@pytest.mark.parametrize("weights", [[1, 2], (1, 2.0), np.array([1, 2]), np.array([1, 2], "f4"), torch.tensor([1.0, 2.0]), [True, np.float32(2)],
+                                     {1: 0, 2: 0}, [Real(1.0, lambda: None), 2]])
+def test_weights(native, weights):
+    calls, seen, _ = native
+    del seen[:]
+    assert calls.reduce(1, T, NB, 0, 2, tensors(2 * NB), weights, tensors(NB), 0) == 0
+    assert calls.fused(1, T, NB, 0, np.int64(2), tensors(T), tensors(NB), weights, 1.0, tensors(T), 0) == 0
+    assert seen[0][5] == [1.0, 2.0] and seen[1][6] == [1.0, 2.0] and seen[0][4] == seen[1][5] == 2
+
+
+@pytest.mark.parametrize("value,want", [(3, 3.0), (True, 1.0), (np.float64(0.1), 0.1), (np.float32(0.5), 0.5), (np.int32(2), 2.0), (torch.tensor(0.25), 0.25),
+                                        (1e300, float("inf"))])
+def test_scalars(native, value, want):
+    calls, seen, _ = native
+    del seen[:]
+    assert sgd(calls, lr=value) == 0 and seen[0][7] == f32(want).value
+
+
+@pytest.mark.parametrize("value,want", [(True, 1), (False, 0), (0, 0), (1, 1), (7, 1), (np.bool_(True), 1), (None, 0), ("", 0), (torch.tensor(True), 1)])
+def test_flags(native, value, want):
+    calls, seen, _ = native
+    del seen[:]
+    assert sgd(calls, first=value) == 0 and seen[0][10] == want
+
+
+def test_calls_made_while_another_one_is_marshalled(native):
+    calls, seen, _ = native
+    other = tensors(T)
+    mine, momenta, bufs = tensors(T), tensors(T), tensors(NB)
+    inner = lambda: calls.fused_sgd(1, T, NB, 0, 1, other, [], [1.0], 1.0, other, other, other, 0.1, 0.9, 0.0, True, 0)
+    del seen[:]
+    assert calls.sgd(1, T, NB, 0, bufs, Real(0.5, inner), mine, momenta, Real(0.1, inner), Real(0.9, inner), 0.0, True, 0) == 0
+    assert [s[0] for s in seen] == ["fused_sgd"] * 3 + ["sgd"]
+    assert seen[3][3:7] == ([t.data_ptr() for t in bufs], 0.5, [t.data_ptr() for t in mine], [t.data_ptr() for t in momenta])
+
+
+def test_weights_that_change_while_they_are_read(native):
+    calls, seen, _ = native
+    w = []
+    w += [Real(0.5, w.clear), Real(0.25, w.clear)]
+    del seen[:]
+    assert calls.reduce(1, T, NB, 0, 2, tensors(2 * NB), w, tensors(NB), 0) == 0
+    assert seen[0][5] == [0.5, 0.25]
