@@ -411,7 +411,10 @@ hipError_t launch_fused_sgd_t(const KtDeviceTables &tb, int64_t tile0, int64_t n
         });
     }
     FsgdLaunch how = fsgd_launch<T>(K, ntiles);
-    if (!kt_may_hold()) how.lds = 0;
+    // nothing held: 64 lanes would still keep 146 KiB of LDS per CU (9 workgroups with the table of a mixed tile each) from kernels
+    // beside them, 256 lanes 112-130 (7 or 8); and these do better in launch order (no holds, bf16, 101 to 312 tensors
+    // of 1 Mi elements: K = 4 25 984 tiles 983 us, 1 001 in runs of 64 KiB; K = 8 15 616 tiles 760, 791; K = 1 39 936 tiles 1 194, 1 103)
+    if (!kt_may_hold()) how = FsgdLaunch{0u, KT_BLOCK, how.lanes == KT_BLOCK ? how.run : 0};
     return launch_in_chunks(tb.tiles + tile0, ntiles, KT_TILE_VECS / how.lanes, [&](const KtTile *tiles, dim3 grid) {
         const uint32_t order = kt_order(grid.x, how.lanes * KT_VEC_BYTES, how.run);
 #define KT_LAUNCH(KK, LANES)                                                                                              \

@@ -37,8 +37,8 @@ def hip():
     return ctypes.CDLL("libamdhip64.so")       # the runtime the process already holds
 
 
-def recorded_launch(call):
-    """Workgroups and dynamic LDS of the one kernel that `call(stream)` launches (its tables are on the device already)."""
+def recorded_kernel(call):
+    """Lanes, workgroups and dynamic LDS of the one kernel that `call(stream)` launches (its tables are on the device already)."""
     h, s = hip(), torch.cuda.Stream()
     graph = ctypes.c_void_p()
     assert h.hipStreamBeginCapture(ctypes.c_void_p(s.cuda_stream), 0) == 0
@@ -57,14 +57,19 @@ def recorded_launch(call):
         if kind.value == 0:                    # hipGraphNodeTypeKernel
             p = KernelNodeParams()
             assert h.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
-            assert p.blockDim.x == 256
-            got.append((p.gridDim.x, p.sharedMemBytes))
+            got.append((p.blockDim.x, p.gridDim.x, p.sharedMemBytes))
     assert h.hipGraphDestroy(graph) == 0
     assert len(got) == 1, got
     return got[0]
 
 
 def launch(op, dtype, K, tiles):
+    lanes, grid, lds = kernel(op, dtype, K, tiles)
+    assert lanes == 256
+    return grid, lds
+
+
+def kernel(op, dtype, K, tiles):
     es, td = (4, torch.float32) if dtype == "f32" else (2, torch.bfloat16)
     numels = [tiles * (16384 // es)]
     plan = kt.Plan(numels, dtype, 0, 16)
@@ -88,7 +93,7 @@ def launch(op, dtype, K, tiles):
 
     call()
     torch.cuda.synchronize()
-    return recorded_launch(call)
+    return recorded_kernel(call)
 
 
 def dynamic_lds(op, dtype, K, tiles):
@@ -132,6 +137,18 @@ def test_nothing_held_where_the_gpu_is_shared(op, dtype, K):
     r = subprocess.run([sys.executable, "-c", code], env=env, capture_output=True, text=True, timeout=100)
     assert r.returncode == 0, r.stderr[-2000:]
     assert "LDS 0" in r.stdout.splitlines(), r.stdout
+
+
+@pytest.mark.parametrize("K,tiles", [(1, 12288), (4, 12288), (8, 8192)])
+def test_full_workgroups_where_the_gpu_is_shared(K, tiles):
+    """Workgroups of 64 lanes, unheld, would keep nearly all LDS of a CU with few wavefronts."""
+    env = dict(os.environ, KT_STORE_WINDOW_NS="0")
+    here = os.path.dirname(os.path.abspath(__file__))
+    code = "import sys; sys.path[:0] = [%r, %r]; import test_gpu_launch_rules as t; print('GOT', t.kernel('fused_sgd', 'bf16', %d, %d))" \
+        % (os.path.dirname(here), here, K, tiles)
+    r = subprocess.run([sys.executable, "-c", code], env=env, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0, r.stderr[-2000:]
+    assert "GOT (256, %d, 0)" % (4 * tiles) in r.stdout.splitlines(), r.stdout
 
 
 @pytest.mark.parametrize("op,dtype,K,least", [
