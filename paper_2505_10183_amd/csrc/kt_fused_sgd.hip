@@ -328,45 +328,47 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_fused_sgd_manyk_kernel(const KtTi
     fsgd_other_tile<T, 0, DEVW, KT_BLOCK>(lds.table, t_offs, t_numel, tl, g, f, pp, K, wts, a, part, SPLIT);
 }
 
-// Bytes of LDS asked for beyond the kernel's own, to hold the number of workgroups per CU at 2 or 4;
-// without, registers allow 7 or 8.
+// Bytes of LDS asked for beyond the kernel's own, to hold the number of workgroups per CU.  Without, registers allow 7 or 8 of
+// 256 lanes and LDS 9 of 64 (each keeps the 16 KiB table of a mixed tile).
 constexpr unsigned FSGD_LDS_2 = kt_hold_lds(2, sizeof(FsgdLds)), FSGD_LDS_4 = kt_hold_lds(4, sizeof(FsgdLds));
 
 // Workgroups, bytes in flight and order by the size of the launch.  Stores are non-temporal throughout.
-//   bf16    2 workgroups per CU (96 KiB in flight at K = 8) above 2 048 tiles, above 1 024 for one and
-//           two copies: 1.3B set 7.38 -> 7.08 ms against 8 workgroups, with the model copy 7.97 -> 7.60
-//           (which depends on where the tensors lie: three sets of 46 GB in turn, 24 arrangements,
-//           7.45-7.94 ms without, 7.47-7.77 with); K = 4, 21 135 tiles 791 -> 745 us.  Below, the chip is
+//   bf16    2 workgroups of 256 lanes per CU (96 KiB in flight at K = 8) above 2 048 tiles, above 1 024 for one and
+//           two copies: K = 4, 21 135 tiles 791 -> 745 us.  Below, the chip is
 //           not full long enough to gain (300 to 1 200 tiles, K = 1 to 6: 1-6 % slower with it on aligned sets).
-//           From 12 288 tiles on (8 copies: 8 192) workgroups of 64 lanes in runs of 64 KiB, 4 per CU for 6 and more copies (48 KiB in flight at K = 8),
-//           5 for 3 to 5, 6 for fewer, against 2 of 256 lanes in launch order (to 32 767 tiles) or with system-scope stores (8 copies
-//           above), mean and range over four or three placements of the buffers: K = 8 9 996 tiles -3.1 % (-6.9 to -0.1), 15 619
-//           -4.5 (-5.9 to -3.6), 26 914 -5.4 (-6.0 to -5.0), 33 813 -3.8, 95 293 -1.7, 1.3B set -3.2 (7 516 -> 7 366, 7 527 -> 7 128,
-//           7 782 -> 7 603 us); K = 4 26 914 -4.1; K = 2 -1.4; K = 1 15 619 even;
-//           odd tensors 15 645 tiles -8.1; K = 1, 3 and 6 8 458 tiles 1-4 % slower, which is where the line comes from.  256 lanes
-//           in runs are 1-2 % faster than launch order at 5 300 and 9 996 tiles and 1-3 % slower at 15 619 and 26 914
+//           Of 3 and more copies from 12 288 tiles on (8 copies: 8 192) workgroups of 64 lanes, 4 per CU for 8 copies (48 KiB in
+//           flight), 5 for 5 to 7, 6 for 3 and 4.  Against 2 of 256 lanes, on the buffers of the call before / after 1 GiB of other reads
+//           (below): K = 8 9 686 tiles 467 -> 440 / 462 -> 441 us, 39 961 tiles 1 827 -> 1 755 / 1 802 -> 1 750, 1.3B set 7 311 -> 7 160 /
+//           7 315 -> 7 059; K = 6 13 725 tiles 576 -> 552 / 570 -> 543; K = 4 39 961 tiles 1 387 -> 1 305 / 1 356 -> 1 283; K = 3 13 725
+//           tiles 456 -> 430 / 440 -> 429, 9 686 tiles 304 -> 309 after other reads, which is where the line comes from.  One and two
+//           copies: 0-3 % faster, 2-4 % slower after other reads
 //   fp32    above 4 096 tiles 2 workgroups per CU for 4 and more copies (K = 8, 21 135 tiles 716 -> 687 us,
 //           K = 4, 8 192 tiles 181 -> 179 us), 4 for fewer (K = 2, 21 135 tiles 340 -> 336 us); 6 and more
 //           copies from 2 048 tiles on (K = 8, 3 700 tiles 2-5 % over none).  System-scope stores gain 2-12 % up to 2 700
 //           tiles where a call finds p and v of the call before in the last-level cache and lose 1-5 % where it does not (1 950
 //           tiles, K = 2 and 4, nine sets of buffers in turn), which is the state a training step is called in
-// Runs (kt_order) of 64 KiB of gradient per XCD for fp32 of 4 and more copies and workgroups of 64 lanes, else of 128: fp32 K = 4 1 191 tiles
-// 28.2 -> 26.2 us, 3 243 tiles 71.9 -> 68.2, 44 601 tiles 6.5 % faster (four placements, 6.0 with 128 KiB); K = 2 44 601 tiles 3.3 %;
-// K = 8 63 057 tiles 2 141 -> 2 030 us; bf16 K = 6 2 706 tiles 111.9 -> 108.3.  Not below 640 tiles, where the few slow tiles that hold
-// many tensors come to lie on one XCD (MobileNetV2, 547 tiles 13.2 -> 13.5 us; 197 tiles of odd tensors 13.1 -> 13.7).
+// Runs (kt_order) of 64 KiB of gradient per XCD for fp32 of 4 and more copies, else of 128, for launches that hold nothing, from 640
+// tiles on: fp32 K = 4 2 587 tiles 58.7 -> 56.8 us on the buffers of the call before, 59.6 -> 59.0 after other reads, bf16 K = 6 1 294 tiles
+// 57.0 -> 55.7 / 59.6 -> 57.8.  Held launches gain 1-5 % from runs on the buffers of the call before and lose up to 15 %, for the
+// whole launch, after 512 MiB and more of ordinary reads or writes of other data, as a backward pass makes (1.3B set in runs 7 474 / 7 912
+// us, in launch order 7 225 / 7 260; fp32 K = 4 19 375 tiles 414 -> 398 / 394 -> 425, K = 7 44 031 tiles 1 313 -> 1 269 / 1 253 -> 1 307; bf16
+// K = 6 94 645 tiles 3 856 -> 3 895 / 3 793 -> 4 378); one pass over the set ends that state.  Not below
+// 640 tiles, where the few slow tiles that hold many tensors come to lie on one XCD (MobileNetV2, 547 tiles 13.2 -> 13.5 us; 197
+// tiles of odd tensors 13.1 -> 13.7).
 struct FsgdLaunch {
     unsigned lds;
     int lanes, run;
 };
 template <typename T> FsgdLaunch fsgd_launch(int K, int64_t ntiles)
 {
-    const int run = ntiles < 640 ? 0 : sizeof(T) == 4 && K >= 4 ? 65536 : 131072;
     if (sizeof(T) == 2) {
-        if (ntiles >= (K >= 8 ? 8192 : 12288)) return FsgdLaunch{kt_hold_lds(K >= 6 ? 4 : K >= 3 ? 5 : 6, sizeof(FsgdLds)), 64, 65536};
-        return FsgdLaunch{ntiles > (K <= 2 ? 1024 : 2048) ? FSGD_LDS_2 : 0u, KT_BLOCK, run};
+        if (K >= 3 && ntiles >= (K >= 8 ? 8192 : 12288))
+            return FsgdLaunch{kt_hold_lds(K >= 8 ? 4 : K >= 5 ? 5 : 6, sizeof(FsgdLds)), 64, 0};
+        if (ntiles > (K <= 2 ? 1024 : 2048)) return FsgdLaunch{FSGD_LDS_2, KT_BLOCK, 0};
+    } else if (ntiles > (K >= 6 ? 2048 : 4096)) {
+        return FsgdLaunch{K >= 4 ? FSGD_LDS_2 : FSGD_LDS_4, KT_BLOCK, 0};
     }
-    if (ntiles <= (K >= 6 ? 2048 : 4096)) return FsgdLaunch{0u, KT_BLOCK, run};
-    return FsgdLaunch{K >= 4 ? FSGD_LDS_2 : FSGD_LDS_4, KT_BLOCK, run};
+    return FsgdLaunch{0u, KT_BLOCK, ntiles < 640 ? 0 : sizeof(T) == 4 && K >= 4 ? 65536 : 131072};
 }
 
 // 9 and more copies.  Small launches take quarter tiles (K = 16: 29 tiles fp32 18.9 -> 6.6 us, 249 tiles bf16
@@ -412,9 +414,8 @@ hipError_t launch_fused_sgd_t(const KtDeviceTables &tb, int64_t tile0, int64_t n
     }
     FsgdLaunch how = fsgd_launch<T>(K, ntiles);
     // nothing held: 64 lanes would still keep 146 KiB of LDS per CU (9 workgroups with the table of a mixed tile each) from kernels
-    // beside them, 256 lanes 112-130 (7 or 8); and these do better in launch order (no holds, bf16, 101 to 312 tensors
-    // of 1 Mi elements: K = 4 25 984 tiles 983 us, 1 001 in runs of 64 KiB; K = 8 15 616 tiles 760, 791; K = 1 39 936 tiles 1 194, 1 103)
-    if (!kt_may_hold()) how = FsgdLaunch{0u, KT_BLOCK, how.lanes == KT_BLOCK ? how.run : 0};
+    // beside them, 256 lanes 112-130 (7 or 8)
+    if (!kt_may_hold()) how = FsgdLaunch{0u, KT_BLOCK, how.run};
     return launch_in_chunks(tb.tiles + tile0, ntiles, KT_TILE_VECS / how.lanes, [&](const KtTile *tiles, dim3 grid) {
         const uint32_t order = kt_order(grid.x, how.lanes * KT_VEC_BYTES, how.run);
 #define KT_LAUNCH(KK, LANES)                                                                                              \
@@ -423,7 +424,7 @@ hipError_t launch_fused_sgd_t(const KtDeviceTables &tb, int64_t tile0, int64_t n
         switch (K) {
 #define KT_CASE(KK)                                                              \
     case KK:                                                                     \
-        if constexpr (sizeof(T) == 2) {                                          \
+        if constexpr (sizeof(T) == 2 && KK >= 3) {                               \
             if (how.lanes == 64) { KT_LAUNCH(KK, 64); break; }                   \
         }                                                                        \
         KT_LAUNCH(KK, KT_BLOCK);                                                 \

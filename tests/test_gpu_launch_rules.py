@@ -37,8 +37,9 @@ def hip():
     return ctypes.CDLL("libamdhip64.so")       # the runtime the process already holds
 
 
-def recorded_kernel(call):
-    """Lanes, workgroups and dynamic LDS of the one kernel that `call(stream)` launches (its tables are on the device already)."""
+def recorded_kernel(call, argument=None):
+    """Lanes, workgroups and dynamic LDS of the one kernel that `call(stream)` launches (its tables are on the device already),
+    and the 32 bits at the place `argument` of its arguments."""
     h, s = hip(), torch.cuda.Stream()
     graph = ctypes.c_void_p()
     assert h.hipStreamBeginCapture(ctypes.c_void_p(s.cuda_stream), 0) == 0
@@ -58,6 +59,9 @@ def recorded_kernel(call):
             p = KernelNodeParams()
             assert h.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
             got.append((p.blockDim.x, p.gridDim.x, p.sharedMemBytes))
+            if argument is not None:
+                where = ctypes.cast(p.kernelParams, ctypes.POINTER(ctypes.c_void_p))[argument]
+                got[-1] += (ctypes.cast(where, ctypes.POINTER(ctypes.c_uint32))[0],)
     assert h.hipGraphDestroy(graph) == 0
     assert len(got) == 1, got
     return got[0]
@@ -69,7 +73,7 @@ def launch(op, dtype, K, tiles):
     return grid, lds
 
 
-def kernel(op, dtype, K, tiles):
+def kernel(op, dtype, K, tiles, argument=None):
     es, td = (4, torch.float32) if dtype == "f32" else (2, torch.bfloat16)
     numels = [tiles * (16384 // es)]
     plan = kt.Plan(numels, dtype, 0, 16)
@@ -93,7 +97,18 @@ def kernel(op, dtype, K, tiles):
 
     call()
     torch.cuda.synchronize()
-    return recorded_kernel(call)
+    return recorded_kernel(call, argument)
+
+
+def run_bytes(op, dtype, K, tiles):
+    """Lanes, workgroups per tile, and bytes of a copy that an XCD takes in a run (0: launch order)."""
+    lanes, grid, _, order = kernel(op, dtype, K, tiles, ORDER[op])
+    split, g = grid // tiles, order & 7
+    assert grid == split * tiles and order >> 3 << 3 == (grid >> 3 + g << 3 + g if g else 0)
+    return lanes, split, (16384 // split << g if g else 0)
+
+
+ORDER = {"fused_sgd": 6}         # place of the order of the pieces among the kernel's arguments (up to 8 copies)
 
 
 def dynamic_lds(op, dtype, K, tiles):
@@ -137,6 +152,23 @@ def test_nothing_held_where_the_gpu_is_shared(op, dtype, K):
     r = subprocess.run([sys.executable, "-c", code], env=env, capture_output=True, text=True, timeout=100)
     assert r.returncode == 0, r.stderr[-2000:]
     assert "LDS 0" in r.stdout.splitlines(), r.stdout
+
+
+@pytest.mark.parametrize("dtype,K,tiles,lanes,run", [
+    ("bf16", 1, 1024, 256, 131072), ("bf16", 2, 1025, 256, 0), ("bf16", 3, 2048, 256, 131072), ("bf16", 6, 2049, 256, 0), ("bf16", 4, 9700, 256, 0),
+    ("bf16", 2, 12288, 256, 0), ("bf16", 3, 12287, 256, 0), ("bf16", 3, 12288, 64, 0), ("bf16", 7, 12288, 64, 0), ("bf16", 8, 8191, 256, 0),
+    ("bf16", 8, 8192, 64, 0), ("bf16", 8, 639, 256, 0), ("bf16", 8, 640, 256, 131072),
+    ("f32", 2, 639, 256, 0), ("f32", 2, 640, 256, 131072), ("f32", 4, 640, 256, 65536), ("f32", 4, 4096, 256, 65536), ("f32", 4, 4097, 256, 0),
+    ("f32", 3, 4097, 256, 0), ("f32", 8, 2048, 256, 65536), ("f32", 8, 2049, 256, 0), ("f32", 5, 44000, 256, 0),
+])
+def test_lanes_and_runs_of_the_one_pass_sgd(dtype, K, tiles, lanes, run):
+    assert run_bytes("fused_sgd", dtype, K, tiles) == (lanes, 16384 // (16 * lanes), run)
+
+
+@pytest.mark.parametrize("K,tiles,count", [(3, 12288, 6), (4, 12288, 6), (5, 12288, 5), (7, 12288, 5), (8, 8192, 4)])
+def test_held_workgroups_of_64_lanes(K, tiles, count):
+    lanes, grid, lds = kernel("fused_sgd", "bf16", K, tiles)
+    assert (lanes, grid) == (64, 16 * tiles) and 163840 // 1280 // -(-(16384 + lds) // 1280) == count
 
 
 @pytest.mark.parametrize("K,tiles", [(1, 12288), (4, 12288), (8, 8192)])
