@@ -265,9 +265,9 @@ template <typename T> KtShape fused_shape(int K, int64_t nt)
         if (K >= 4 && nt < 1024) return {S, 0};
         if (nt >= (K == 4 ? 32768 : 5120) && K >= 4) return {S, 2};
     } else {
-        if (K == 4 && nt >= 8192) return {S, 3};
+        if (K == 4 && nt >= 8192) return {S, nt < 32768 ? 4u : 3u};       // 4 in runs, fused_run
         if (K == 5 && nt >= 6144) return {S, 3};
-        if (K >= 6 && nt >= 4096) return {S, K == 8 || (K == 7 && nt >= 6144) ? 2u : 3u};
+        if (K >= 6 && nt >= 4096) return {S, K == 8 ? 2u : 3u};
         if (K >= 4 && kt_uneven(nt)) return {S, 0};
     }
     // whole tiles, two per CU for 3 to 5 copies (2 729 tiles, K = 4: 38.0 -> 37.7 us against none held; 3 copies,
@@ -275,25 +275,39 @@ template <typename T> KtShape fused_shape(int K, int64_t nt)
     return {1, K >= 3 && K <= 5 && nt >= (K == 3 ? 8192 : 2048) ? 2u : 0u};
 }
 
-// Bytes of a copy that an XCD takes in a run (kt_order; 0: launch order): 64 KiB on shared tiles (fp32 K = 4 19 993 tiles 266 -> 252 us,
-// 63 057 tiles 843 -> 806, K = 5 1 020 -> 983; bf16 K = 6 31 528 tiles 587 -> 562, K = 7 677 -> 655; fp32 K = 7 with 2 workgroups per CU
-// instead of 3 19 993 tiles 436 -> 419), 128 KiB on the half tiles of 4 and 5 copies and where whole tiles of these are held (K = 5
-// fp32 3 243 tiles 53.0 -> 51.6 us, bf16 9 996 tiles 159 -> 155).  Launches that hold nothing stay in launch
-// order (whole tiles, K = 4 fp32 1 950 tiles 2 % slower in runs), and the whole tiles of other numbers of copies do not look for an order at
-// all (K = 3 bf16, 596 tiles 9.7 us, 9.9 when they do).
+// Bytes of a copy that an XCD takes in a run (kt_order; 0: launch order), where launches with runs are no slower after 512 MiB and more
+// of ordinary reads or writes of other data, as a backward pass makes.  In us, launch order -> runs on the buffers of the call before / after
+// 1 GiB of other reads:
+//   bf16   4 to 7 copies 128 KiB: K = 4 94 645 tiles 1 285 -> 1 228 / 1 298 -> 1 254, K = 5 6 600 tiles 107.6 -> 103.3 / 105.8 -> 106.1 (19 772
+//          tiles 314 -> 308 / 295 -> 306), K = 6 32 824 tiles 644 -> 623 / 640 -> 623, K = 7 93 682 tiles 2 155 -> 2 073 / 2 144 -> 2 075 (64 KiB: even)
+//   fp32   4 copies 32 KiB on quarter tiles, 4 workgroups per CU, up to 32 767 tiles: 8 618 tiles 116.8 -> 112.8 / 117.9 -> 116.4, 19 993
+//          tiles 267 -> 257 / 264 -> 262, 44 031 tiles 570 -> 575 / 559 -> 569, 92 895 tiles 2 and 4 % slower; 4 and 5 copies 128 KiB where whole tiles
+//          are held (K = 5 2 587 tiles 44.0 -> 43.1 / 46.4 -> 45.6)
+// The others gain 1-4 % from runs on the buffers of the call before and lose 2-10 % after other reads (fp32 K = 6 44 031 tiles 817 -> 799 /
+// 769 -> 816, K = 8 9 892 tiles 236 -> 233 / 234 -> 244; bf16 K = 8 94 645 tiles 2 341 -> 2 306 / 2 133 -> 2 216).  Launches that hold nothing
+// stay in launch order (whole tiles, K = 4 fp32 1 950 tiles 2 % slower in runs), and the whole tiles of other numbers of copies do not look for
+// an order at all (K = 3 bf16, 596 tiles 9.7 us, 9.9 when they do).
 template <typename T> int fused_run(int K, int64_t nt, const KtShape &sh)
 {
-    if (!sh.wgs || nt < 1024) return 0;
-    return sh.split == 1 || (sizeof(T) == 2 && K < 6) ? 131072 : 65536;
+    if (!sh.wgs || !kt_may_hold() || nt < 1024) return 0;
+    if (sizeof(T) == 2) return K >= 4 && K <= 7 ? 131072 : 0;
+    if (sh.split == 1) return K == 4 || K == 5 ? 131072 : 0;
+    return K == 4 && nt < 32768 ? 32768 : 0;
 }
 
 // 9 and more copies outside the store window: quarter tiles, whose mixed tiles are shared too (a vector with a
 // serial loop over the copies decides small launches: K = 16 fp32 29 tiles 18.3 -> 6.3 us, 222 tiles 22.1 -> 13.0, 763 tiles
-// 41 -> 37.5, bf16 508 tiles 32.6 -> 27.2) in runs of 64 KiB per XCD from 640 tiles on (K = 9 fp32 3 243 tiles 87.5 -> 84.8 us, bf16 31 528
-// tiles 889 -> 851; K = 16 bf16 975 tiles 48.3 -> 45.7), held at two per CU above 1 152 (against whole ones, two types, K = 9 to 16, 1 141 to
+// 41 -> 37.5, bf16 508 tiles 32.6 -> 27.2) in runs of 64 KiB per XCD from 640 tiles on (K = 9 fp32 3 243 tiles 87.5 -> 84.8 us;
+// K = 16 bf16 975 tiles 48.3 -> 45.7; K = 12 5 322 tiles 1-3 % in every state; copies that have no window up to 4 095 tiles only: K = 9 fp32 19 375
+// tiles 509 -> 495 us on the buffers of the call before, 479 -> 511 after other reads), held at two per CU above 1 152 (against whole ones, two types, K = 9 to 16, 1 141 to
 // 3 006 tiles: 0-8 % faster, K = 9 to 14 up to 2 % slower where whole tiles make full rounds: fp32 K = 9 1 228 tiles
 // 36.7 -> 35.9 us, 1 692 tiles 46.5 -> 46.9, K = 14 1 228 tiles 52.6 -> 53.6, K = 12 2 172 tiles 84.4 -> 79.6).
 inline KtShape fused_manyk_shape(int64_t nt) { return {4, nt > 1152 ? 2u : 0u}; }
+template <typename T> int fused_manyk_run(int K, int64_t nt, const KtShape &sh)
+{
+    if (sh.split == 1 || nt < 640 || (nt > 1152 && !kt_may_hold())) return 0;
+    return nt < 4096 || K >= (sizeof(T) == 2 ? 11 : 10) ? 65536 : 0;
+}
 
 template <typename T, int K, bool DEVW>
 hipError_t launch_fused_k(const KtDeviceTables &tb, const KtTile *tiles, int64_t nt, const void *const *locals,
@@ -336,7 +350,7 @@ hipError_t launch_fused_t(const KtDeviceTables &tb, int64_t tile0, int64_t nt, c
     const KtShape sh = win.width ? KtShape{1, 0} : fused_manyk_shape(nt);
     const unsigned lds = kt_shape_lds(sh, (unsigned)sizeof(LdsTable));
     return launch_in_chunks(tiles, nt, sh.split, [&](const KtTile *t, dim3 grid) {
-        const uint32_t order = kt_order(grid.x, KT_TILE_BYTES / sh.split, sh.split == 1 || nt < 640 ? 0 : 65536);
+        const uint32_t order = kt_order(grid.x, KT_TILE_BYTES / sh.split, fused_manyk_run<T>(K, nt, sh));
 #define KT_ARGS t, tb.b_elems, tb.t_off, locals, peers, outs, order, K, scale, win, tb.t_numel, AllWeights(w)
         if (sh.split == 1) kt_fused_manyk_kernel<T, DEVW, 1><<<grid, dim3(KT_BLOCK), lds, s>>>(KT_ARGS);
         else kt_fused_manyk_kernel<T, DEVW, 4><<<grid, dim3(KT_BLOCK), lds, s>>>(KT_ARGS);

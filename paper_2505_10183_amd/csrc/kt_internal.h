@@ -77,7 +77,7 @@ int kt_launch_unpack(const KtDeviceTables &tb, kt_dtype dt, int64_t tile0,
 // at K = 8; the 14 us period leaves 0-5 us, the 12 us one 2-7), which is why it is used only where
 // that time is known to be longer (7 and more copies, many tiles).  Launches below the limits here, all of up to 6
 // copies, and those of 9 (bf16: and 10) do better with few workgroups per CU that share tiles (KtShape).
-// width == 0: no window.
+// width == 0: no window; the fused pass of up to 8 copies then finds the order of its pieces (kt_order) in `period`.
 struct KtWindow {
     uint32_t period;  // clock ticks
     uint32_t width;   // ticks at the start of each period in which stores are issued

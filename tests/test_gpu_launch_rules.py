@@ -102,13 +102,14 @@ def kernel(op, dtype, K, tiles, argument=None):
 
 def run_bytes(op, dtype, K, tiles):
     """Lanes, workgroups per tile, and bytes of a copy that an XCD takes in a run (0: launch order)."""
-    lanes, grid, _, order = kernel(op, dtype, K, tiles, ORDER[op])
+    lanes, grid, _, order = kernel(op, dtype, K, tiles, ORDER[op][K > 8])
     split, g = grid // tiles, order & 7
     assert grid == split * tiles and order >> 3 << 3 == (grid >> 3 + g << 3 + g if g else 0)
     return lanes, split, (16384 // split << g if g else 0)
 
 
-ORDER = {"fused_sgd": 6}         # place of the order of the pieces among the kernel's arguments (up to 8 copies)
+# place of the order of the pieces among the kernel's arguments: up to 8 copies and above
+ORDER = {"fused_sgd": (6, 6), "fused": (7, 6)}
 
 
 def dynamic_lds(op, dtype, K, tiles):
@@ -163,6 +164,23 @@ def test_nothing_held_where_the_gpu_is_shared(op, dtype, K):
 ])
 def test_lanes_and_runs_of_the_one_pass_sgd(dtype, K, tiles, lanes, run):
     assert run_bytes("fused_sgd", dtype, K, tiles) == (lanes, 16384 // (16 * lanes), run)
+
+
+@pytest.mark.parametrize("dtype,K,tiles,split,run", [
+    ("f32", 4, 2047, 1, 0), ("f32", 4, 2048, 1, 131072), ("f32", 4, 8191, 1, 131072), ("f32", 4, 8192, 4, 32768), ("f32", 4, 32767, 4, 32768),
+    ("f32", 4, 32768, 4, 0), ("f32", 5, 6143, 1, 131072), ("f32", 5, 6144, 4, 0), ("f32", 6, 4096, 4, 0), ("f32", 7, 20000, 4, 0), ("f32", 8, 9900, 4, 0),
+    ("f32", 3, 9000, 1, 0), ("bf16", 3, 9000, 1, 0), ("bf16", 4, 3000, 1, 131072), ("bf16", 4, 40000, 2, 131072), ("bf16", 5, 6000, 2, 131072),
+    ("bf16", 6, 1023, 2, 0), ("bf16", 6, 1024, 2, 131072), ("bf16", 7, 20000, 2, 131072), ("bf16", 8, 20000, 2, 0),
+    ("f32", 9, 639, 4, 0), ("f32", 9, 640, 4, 65536), ("f32", 9, 4095, 4, 65536), ("f32", 9, 4096, 4, 0), ("bf16", 10, 4096, 4, 0),
+    ("bf16", 12, 5000, 4, 65536),
+])
+def test_runs_of_the_fused_pass(dtype, K, tiles, split, run):
+    assert run_bytes("fused", dtype, K, tiles) == (256, split, run)
+
+
+@pytest.mark.parametrize("dtype,K,tiles,count", [("f32", 4, 8192, 4), ("f32", 4, 32768, 3), ("f32", 7, 9000, 3)])
+def test_held_workgroups_of_the_fused_pass(dtype, K, tiles, count):
+    assert 163840 // 1280 // -(-(16384 + kernel("fused", dtype, K, tiles)[2]) // 1280) == count
 
 
 @pytest.mark.parametrize("K,tiles,count", [(3, 12288, 6), (4, 12288, 6), (5, 12288, 5), (7, 12288, 5), (8, 8192, 4)])
