@@ -534,6 +534,7 @@ static kt_status stage_pointers(kt_plan *p, const uint64_t *vals, size_t n, hipS
 // Bookkeeping after a launch that read `s` on `stream`.  Caller holds p->mu.
 static kt_status mark_used(kt_plan *p, PtrSlot *s, hipStream_t stream)
 {
+    p->tb.packed = false;
     if (s->in_graph) return KT_OK;   // the table stays resident until the plan is destroyed
     const StreamKey key = key_of(stream);
     if (s->last_seq > 0 && s->use_stream != key) s->multi_stream = true;
@@ -644,7 +645,9 @@ extern "C" kt_status kt_bucket_pack(kt_plan *p, int bucket, const void *const *t
     void *const *d_b = reinterpret_cast<void *const *>(static_cast<uint64_t *>(slot->dev) + T);
     int e = kt_launch_pack(p->tb, p->hp.dt, tile0, ntiles, d_t, d_b, stream);
     if (e != 0) return hip_fail("kt_bucket_pack: launch", (hipError_t)e);
-    return mark_used(p, slot, s);
+    st = mark_used(p, slot, s);
+    p->tb.packed = true;
+    return st;
     KT_GUARD_END("kt_bucket_pack")
 }
 

@@ -58,6 +58,7 @@ struct KtDeviceTables {
     const int64_t *t_off;
     const int64_t *t_numel;
     const int64_t *b_elems;
+    bool packed = false;    // the launch before was this plan's pack (kt_launch_reduce)
 };
 
 // Launchers (defined next to their kernels in the .hip files).  `tile0`/`ntiles` select a contiguous tile range.

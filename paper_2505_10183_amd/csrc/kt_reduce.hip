@@ -140,16 +140,25 @@ __global__ __launch_bounds__(KT_BLOCK) void kt_reduce_manyk_kernel(const KtTile 
     }
 }
 
-// Shared tiles go in runs of 64 KiB per XCD, of 128 KiB up to 3 copies (kt_order), which is 2-6 % faster than launch order
-// (K = 4 fp32 19 993 tiles 259 -> 248 us; K = 5 fp32 315 -> 299; K = 6 bf16 31 528 tiles
-// 585 -> 553; K = 7 bf16 698 -> 647; K = 8 fp32 19 993 tiles 480 -> 460, bf16 31 528 tiles 790 -> 742; uneven launches:
-// bf16 596 tiles, K = 5 10.9 -> 10.5).  With runs 3 copies do best with 4 workgroups per CU (fp32 19 993 tiles 201 us with 5,
-// 199 with 4; bf16 31 528 tiles 322, 318) and fp32 of 7 copies with 2 from 6 144 tiles on (19 993 tiles 424 us with 3, 410
-// with 2; 5 412 tiles even; 6 copies alone 351 and 348 us, but a step of them 2 % slower than before with 2).  Whole tiles stay in launch order: runs are 1 % faster for 4 and more copies at
-// 1 600 to 5 400 tiles and 1-5 % slower below; so do launches of 32 768 tiles and more: alone they would gain 3-5 %, but between pack and unpack
-// runs are even there (46 696 tiles, -0.3 to 0.9 %; 38 449 tiles, K = 7 -1.4, K = 4 1.4) or slower (K = 4 107 589 tiles, the whole step 3.2 % at three
+// Bytes of a copy that an XCD takes in a run (kt_order; 0: launch order): 64 KiB on shared tiles of 3 and more copies.  `packed`: the
+// plan's pack is the launch before, which has just brought the buckets through the chip.  Then runs gain 2-6 % up to 32 767 tiles, whatever ran
+// before the pack (pack, reduce and unpack, in us, on the buffers of the step before / after 1 GiB of other reads: K = 8 fp32 19 993
+// tiles 666 -> 644 / 657 -> 636, bf16 30 055 tiles 1 029 -> 975 / 1 018 -> 958; K = 5 fp32 10 331 tiles 261 -> 253 / 258 -> 251; K = 12 fp32
+// 880 -> 851 / 872 -> 843; K = 16 fp32 10 331 tiles 1-2 % slower).  A reduce of buckets that other work has displaced loses with them
+// where few bytes are in flight (fp32 K = 4 19 375 tiles 250 -> 244 / 246 -> 260, K = 9 506 -> 486 / 477 -> 498; bf16 K = 5 308 -> 297 / 298 -> 305)
+// but for fp32 of 7 (19 992 tiles 435 -> 430 / 414 -> 407) and bf16 of 7 and 8 (19 772 tiles 466 -> 449 / 463 -> 447).  Smaller launches
+// gain in both states (uneven launches: bf16 596 tiles, K = 5 10.9 -> 10.5).  2 copies are even.  Whole tiles stay in launch order: runs
+// are 1 % faster for 4 and more copies at 1 600 to 5 400 tiles and 1-5 % slower below; so do launches of 32 768 tiles and more: between
+// pack and unpack runs are even there (46 696 tiles, -0.3 to 0.9 %) or slower (K = 4 107 589 tiles, the whole step 3.2 % at three
 // placements of its buffers, K = 6 fp32 4.7).
-inline bool reduce_runs(int64_t nt) { return nt < 32768; }
+template <typename T> int reduce_run(int K, int64_t nt, bool packed, const KtShape &sh)
+{
+    constexpr bool half = sizeof(T) == 2;
+    if (sh.split == 1 || K <= 2 || nt >= 32768 || (sh.wgs && !kt_may_hold())) return 0;
+    if (!half && K > 12 && nt >= 8192) return 0;
+    if (nt >= (half ? 8192 : 6144) && !packed && K != 7 && !(half && K == 8)) return 0;
+    return 65536;
+}
 
 // Workgroups per tile and per CU (0: as many as fit) by type, copies and tiles, where no store window
 // is open.  Quarter tiles held at 2 to 5 workgroups per CU (40-96 KB in flight) against whole tiles as
@@ -168,17 +177,18 @@ inline bool reduce_runs(int64_t nt) { return nt < 32768; }
 // Below, a launch is a few rounds of workgroups: quarter tiles only where whole ones would leave a sixth of
 // the last round idle (551 tiles of bf16: K = 8 17.8 -> 15.4 us against 16.3, K = 4 10.5 -> 8.9 against
 // 9.3; 491 tiles, 96 % of two rounds: whole tiles 4-8 % faster).
-template <typename T> KtShape reduce_shape(int K, int64_t nt)
+// fp32 of 7 copies holds 2 behind a pack (in runs: step of 19 993 tiles 611 -> 591 us, 601 with 3), else 3 (414 -> 407 after other reads, 437 with 2).
+template <typename T> KtShape reduce_shape(int K, int64_t nt, bool packed)
 {
     const bool half = sizeof(T) == 2;
     switch (K) {
     case 1: break;
     case 2: if (nt >= 12288) return {4, 0}; break;
-    case 3: if (nt >= 8192) return {4, reduce_runs(nt) ? 4u : 5u}; break;
+    case 3: if (nt >= 8192) return {4, 5}; break;
     case 4: if (nt >= 4096) return nt >= (half ? 12288 : 8192) ? KtShape{4, 3} : KtShape{1, 2}; break;
     case 5: if (nt >= 4096) return {4, 3}; break;
     case 6: if (nt >= 2048) return {4, 3}; break;
-    case 7: if (nt >= (half ? 2048 : 4096)) return {4, half || nt < 6144 || !reduce_runs(nt) ? 3u : 2u}; break;
+    case 7: if (nt >= (half ? 2048 : 4096)) return {4, !half && packed && nt >= 6144 && nt < 32768 ? 2u : 3u}; break;
     default: if (nt >= (half ? 2048 : 3072)) return {4, half ? 3u : 2u}; break;
     }
     return {K >= 2 && kt_uneven(nt) ? 4 : 1, 0};
@@ -187,8 +197,8 @@ template <typename T> KtShape reduce_shape(int K, int64_t nt)
 // 9 and more copies outside the store window.  Up to one tile per CU, and where whole tiles would leave a sixth of
 // two or three rounds idle, quarter tiles (K = 16: 29 tiles fp32 8.6 -> 5.6 us, 111 tiles bf16 14.2 -> 8.0, 577 tiles
 // bf16 28.9 -> 23.7; a workgroup's serial chunks and its own table reads are a quarter); even or 2-10 % slower
-// than whole tiles on full rounds.  Shared tiles in runs of 64 KiB per XCD (K = 9 fp32 3 243 tiles 87.5 -> 83.1 us, bf16 31 528
-// tiles 882 -> 808; K = 16 bf16 2 706 tiles 124 -> 117).  From 2 560 tiles on quarter tiles held at two per CU (64 KB in flight; K = 12 fp32
+// than whole tiles on full rounds.  Shared tiles in runs as above (K = 9 fp32 3 243 tiles 87.5 -> 83.1 us; K = 16 bf16 2 706
+// tiles 124 -> 117).  From 2 560 tiles on quarter tiles held at two per CU (64 KB in flight; K = 12 fp32
 // 2 713 tiles even, 4 149 tiles 4 % faster, 20 749 tiles 769 -> 704 us; bf16 K = 16 7 896 tiles 378 -> 361).
 inline KtShape reduce_manyk_shape(int64_t nt)
 {
@@ -199,17 +209,23 @@ inline KtShape reduce_manyk_shape(int64_t nt)
 // System-scope stores, not waited for, where the reduced buckets are 17 to 96 MiB: the L2s have nothing to write back when the
 // kernel ends, and the next call reads the buckets out of the last-level cache.  Pack, reduce and unpack together: K = 8 fp32
 // 1 191 tiles 46.4 -> 45.2 us, 3 243 tiles 110.8 -> 107.7 (116.0 -> 110.6 where nine sets of buffers take turns), 5 412 tiles 182 -> 175;
-// K = 4 bf16 2 706 tiles 65.8 -> 63.6; K = 12 fp32 5 412 tiles 6 % faster; ViT-B/16 bucket by bucket (1 154 tiles each) 837 -> 799.  Alone, in place
-// over the first copy, 1 950 to 5 600 tiles 2-8 % faster, 1 200 even.  Below, steps are 2-5 % slower (434 tiles), above 16 384 tiles as well
-// (19 993 tiles, K = 8 fp32 5 %); between 7 600 and 11 300 the reduce alone is 2-6 % slower where a step is 4 % faster, as is one of 5 and
-// more copies at 1 038 tiles (2 %; a step 2 % faster).  More than 8 copies from 1 536 tiles on (K = 12 fp32 1 191 tiles alone 3 % slower).
-inline bool reduce_sys(int K, int64_t nt) { return K > 1 && nt >= (K > 8 ? 1536 : 1100) && nt < 6144; }
+// K = 4 bf16 2 706 tiles 65.8 -> 63.6; K = 12 fp32 5 412 tiles 6 % faster; ViT-B/16 bucket by bucket (1 154 tiles each) 837 -> 799.  Below,
+// steps are 2-5 % slower (434 tiles), above 16 384 tiles as well (19 993 tiles, K = 8 fp32 5 %).  A reduce without a pack before it
+// (`packed`, as above) gains 2-12 % up to 6 copies (K = 5 fp32 5 322 tiles 84.9 -> 76.0 us, 2 % slower where 1 GiB of other data has just been
+// written); of 7 and more it is up to 10 % slower then (K = 8 fp32 5 322 tiles 126.9 -> 137.5, bf16 K = 12 5 393 tiles 186 -> 204), 4-9 %
+// faster on the buffers of the call before.  Between 7 600 and 11 300 tiles the reduce alone is 2-6 % slower where a step is 4 % faster.  More
+// than 8 copies from 1 536 tiles on (K = 12 fp32 1 191 tiles alone 3 % slower).
+inline bool reduce_sys(int K, int64_t nt, bool packed)
+{
+    return K > 1 && nt >= (K > 8 ? 1536 : 1100) && nt < 6144 && (packed || K <= 6);
+}
 
 template <typename T, int K, bool DEVW>
-hipError_t launch_reduce_k(const KtTile *tiles, const int64_t *b_elems, int64_t nt, const void *const *peers,
+hipError_t launch_reduce_k(const KtTile *tiles, const KtDeviceTables &tb, int64_t nt, const void *const *peers,
                            const KtWeights &w, void *const *outs, hipStream_t s)
 {
     const dim3 block(KT_BLOCK);
+    const int64_t *b_elems = tb.b_elems;
     if constexpr (K >= 7) {
         const KtWindow win = kt_store_window(sizeof(T) == 4 ? KT_PERIOD_14 : KT_PERIOD_12, nt, KT_WINDOW_MIN_TILES_REDUCE);
         if (win.width) {
@@ -217,11 +233,11 @@ hipError_t launch_reduce_k(const KtTile *tiles, const int64_t *b_elems, int64_t 
             return hipGetLastError();
         }
     }
-    const KtShape sh = reduce_shape<T>(K, nt);
-    const bool sys = reduce_sys(K, nt);
+    const KtShape sh = reduce_shape<T>(K, nt, tb.packed);
+    const bool sys = reduce_sys(K, nt, tb.packed);
     const unsigned lds = kt_shape_lds(sh, 0);
     return launch_in_chunks(tiles, nt, sh.split, [&](const KtTile *t, dim3 grid) {
-        const uint32_t order = kt_order(grid.x, KT_TILE_BYTES / sh.split, sh.split == 1 || !reduce_runs(nt) ? 0 : K <= 3 ? 131072 : 65536);
+        const uint32_t order = kt_order(grid.x, KT_TILE_BYTES / sh.split, reduce_run<T>(K, nt, tb.packed, sh));
 #define KT_LAUNCH(SPLIT, INT, SYS) \
     kt_reduce_kernel<T, K, DEVW, SPLIT, INT, SYS><<<grid, block, lds, s>>>(t, b_elems, peers, outs, order, KtWindow{0, 0}, FewWeights(w))
         constexpr bool INT = sizeof(T) == 2 && K >= 6;
@@ -238,16 +254,16 @@ hipError_t launch_reduce_t(const KtDeviceTables &tb, int64_t tile0, int64_t nt, 
 {
     const KtTile *tiles = tb.tiles + tile0;
     switch (K) {
-#define KT_CASE(KK) case KK: return launch_reduce_k<T, KK, DEVW>(tiles, tb.b_elems, nt, peers, w, outs, s);
+#define KT_CASE(KK) case KK: return launch_reduce_k<T, KK, DEVW>(tiles, tb, nt, peers, w, outs, s);
         KT_CASE(1) KT_CASE(2) KT_CASE(3) KT_CASE(4) KT_CASE(5) KT_CASE(6) KT_CASE(7) KT_CASE(8)
 #undef KT_CASE
     }
     const KtWindow win = kt_manyk_window(sizeof(T) == 2, K, nt, KT_WINDOW_MIN_READS_REDUCE_MANYK);
     const KtShape sh = win.width ? KtShape{1, 0} : reduce_manyk_shape(nt);
-    const bool sys = reduce_sys(K, nt);
+    const bool sys = reduce_sys(K, nt, tb.packed);
     const unsigned lds = kt_shape_lds(sh, 0);
     return launch_in_chunks(tiles, nt, sh.split, [&](const KtTile *t, dim3 grid) {
-        const uint32_t order = kt_order(grid.x, KT_TILE_BYTES / sh.split, sh.split == 1 || !reduce_runs(nt) ? 0 : 65536);
+        const uint32_t order = kt_order(grid.x, KT_TILE_BYTES / sh.split, reduce_run<T>(K, nt, tb.packed, sh));
 #define KT_LAUNCH(SPLIT, SYS) \
     kt_reduce_manyk_kernel<T, DEVW, SPLIT, SYS><<<grid, dim3(KT_BLOCK), lds, s>>>(t, tb.b_elems, peers, outs, K, order, win, AllWeights(w))
         if (sys) { if (sh.split == 1) KT_LAUNCH(1, true); else KT_LAUNCH(4, true); }

@@ -39,7 +39,7 @@ def hip():
 
 def recorded_kernel(call, argument=None):
     """Lanes, workgroups and dynamic LDS of the one kernel that `call(stream)` launches (its tables are on the device already),
-    and the 32 bits at the place `argument` of its arguments."""
+    and the 32 bits at the place `argument` of its arguments (-1: the address of its function)."""
     h, s = hip(), torch.cuda.Stream()
     graph = ctypes.c_void_p()
     assert h.hipStreamBeginCapture(ctypes.c_void_p(s.cuda_stream), 0) == 0
@@ -59,7 +59,9 @@ def recorded_kernel(call, argument=None):
             p = KernelNodeParams()
             assert h.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
             got.append((p.blockDim.x, p.gridDim.x, p.sharedMemBytes))
-            if argument is not None:
+            if argument == -1:
+                got[-1] += (p.func,)
+            elif argument is not None:
                 where = ctypes.cast(p.kernelParams, ctypes.POINTER(ctypes.c_void_p))[argument]
                 got[-1] += (ctypes.cast(where, ctypes.POINTER(ctypes.c_uint32))[0],)
     assert h.hipGraphDestroy(graph) == 0
@@ -85,7 +87,7 @@ def kernel(op, dtype, K, tiles, argument=None):
     w = [1.0 / K] * K
 
     def call(stream=None):
-        if op == "reduce":
+        if op.endswith("reduce"):
             plan.kt_weighted_reduce(-1, copies, K, w, out, stream=stream)
         elif op == "fused":
             plan.kt_fused_step(-1, grads, others, K, w, 1.0, out, stream=stream)
@@ -96,6 +98,8 @@ def kernel(op, dtype, K, tiles, argument=None):
                                    stream=stream)
 
     call()
+    if op == "packed reduce":
+        plan.kt_bucket_pack(-1, out, grads)
     torch.cuda.synchronize()
     return recorded_kernel(call, argument)
 
@@ -109,7 +113,7 @@ def run_bytes(op, dtype, K, tiles):
 
 
 # place of the order of the pieces among the kernel's arguments: up to 8 copies and above
-ORDER = {"fused_sgd": (6, 6), "fused": (7, 6)}
+ORDER = {"fused_sgd": (6, 6), "fused": (7, 6), "reduce": (4, 5), "packed reduce": (4, 5)}
 
 
 def dynamic_lds(op, dtype, K, tiles):
@@ -176,6 +180,56 @@ def test_lanes_and_runs_of_the_one_pass_sgd(dtype, K, tiles, lanes, run):
 ])
 def test_runs_of_the_fused_pass(dtype, K, tiles, split, run):
     assert run_bytes("fused", dtype, K, tiles) == (256, split, run)
+
+
+@pytest.mark.parametrize("dtype,K,tiles,run,packed_run", [
+    ("f32", 2, 590, 0, 0), ("f32", 2, 20000, 0, 0), ("f32", 3, 8192, 0, 65536), ("bf16", 3, 32767, 0, 65536), ("bf16", 3, 32768, 0, 0),
+    ("f32", 5, 590, 65536, 65536), ("f32", 6, 6143, 65536, 65536), ("f32", 6, 6144, 0, 65536), ("f32", 7, 6144, 65536, 65536), ("f32", 8, 32767, 0, 65536),
+    ("f32", 8, 32768, 0, 0), ("bf16", 5, 8191, 65536, 65536), ("bf16", 5, 8192, 0, 65536), ("bf16", 8, 20000, 65536, 65536), ("f32", 4, 8192, 0, 65536),
+    ("f32", 9, 6143, 65536, 65536), ("f32", 9, 6144, 0, 65536), ("f32", 12, 9000, 0, 65536), ("f32", 16, 8191, 0, 65536), ("f32", 16, 8192, 0, 0),
+    ("bf16", 16, 9000, 0, 65536),
+])
+def test_runs_of_the_reduce(dtype, K, tiles, run, packed_run):
+    assert run_bytes("reduce", dtype, K, tiles) == (256, 4, run)
+    assert run_bytes("packed reduce", dtype, K, tiles) == (256, 4, packed_run)
+
+
+@pytest.mark.parametrize("dtype,K,tiles,alike", [
+    ("f32", 7, 1099, True), ("f32", 7, 1100, False), ("bf16", 8, 6143, False), ("bf16", 8, 6144, True), ("f32", 6, 2000, True), ("bf16", 9, 1535, True),
+    ("bf16", 9, 1536, False),
+])
+def test_store_scope_of_the_reduce_behind_a_pack(dtype, K, tiles, alike):
+    """7 and more copies: another instantiation, with system-scope stores, between 1 100 (1 536) and 6 143 tiles behind a pack."""
+    assert (kernel("reduce", dtype, K, tiles, -1)[3] == kernel("packed reduce", dtype, K, tiles, -1)[3]) == alike
+
+
+def test_packed_ends_with_the_next_launch():
+    plan = kt.Plan([9000 * 4096], "f32", 0, 16)
+    mk = plan.marshal
+    keep = [torch.zeros(9000 * 4096, device=DEV) for _ in range(6)]
+    grads, copies, out, spare = mk(keep[:1]), mk(keep[1:5]), mk(keep[5:]), mk(keep[1:2])
+    pack = lambda stream=None: plan.kt_bucket_pack(-1, grads, spare, stream=stream)
+    reduce = lambda stream=None: plan.kt_weighted_reduce(-1, copies, 4, [0.25] * 4, out, stream=stream)
+    unpack = lambda stream=None: plan.kt_bucket_unpack_scale(-1, out, 1.0, grads, stream=stream)
+    order = lambda: recorded_kernel(reduce, 4)[3]
+    reduce(), pack(), unpack()
+    assert order() == 0
+    pack()
+    assert order() & 7 and order() == 0 and order() == 0
+    with pytest.raises(kt.KtError):
+        plan.kt_bucket_pack(5, grads, spare)       # refused: no launch
+    assert order() == 0
+    recorded_kernel(pack)
+    assert order() & 7
+    pack(), reduce()
+    assert order() == 0
+    torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("op,tiles,count", [("reduce", 6144, 3), ("packed reduce", 6143, 3), ("packed reduce", 6144, 2), ("packed reduce", 32767, 2),
+                                            ("packed reduce", 32768, 3)])
+def test_held_workgroups_of_the_reduce_of_7_copies(op, tiles, count):
+    assert 163840 // 1280 // -(-kernel(op, "f32", 7, tiles)[2] // 1280) == count
 
 
 @pytest.mark.parametrize("dtype,K,tiles,count", [("f32", 4, 8192, 4), ("f32", 4, 32768, 3), ("f32", 7, 9000, 3)])

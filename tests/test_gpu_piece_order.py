@@ -32,12 +32,17 @@ def inputs(dtype, K, elems):
 # 128 in runs of 64 KiB and 48), 320 are whole groups only, 321 leave one tile over
 @pytest.mark.parametrize("dtype,K,tiles,tail", [
     ("f32", 2, 300, 0), ("f32", 3, 320, 0), ("f32", 8, 321, 4), ("bf16", 4, 300, 8), ("bf16", 7, 320, 0), ("f32", 9, 33, 0),
-    ("f32", 12, 255, 4), ("bf16", 16, 64, 8),
+    ("f32", 12, 255, 4), ("bf16", 16, 64, 8), ("f32", 7, 6144, 4), ("f32", 9, 6145, 0), ("bf16", 5, 8200, 8), ("f32", 3, 8195, 4),   # the last four: behind a pack only, or with another hold
 ])
 def test_reduce_in_runs(dtype, K, tiles, tail):
     plan, weights, copies, want = inputs(dtype, K, tiles * (16384 // (4 if dtype == "f32" else 2)) + tail)
     out = torch.empty_like(copies[0])
     plan.kt_weighted_reduce(-1, copies, K, weights, [out])
+    torch.cuda.synchronize()
+    assert raw(host(out)).tobytes() == raw(want).tobytes()
+    packed = torch.zeros_like(copies[0])
+    plan.kt_bucket_pack(-1, copies[:1], [packed])
+    plan.kt_weighted_reduce(-1, [packed] + copies[1:], K, weights, [out.zero_()])
     torch.cuda.synchronize()
     assert raw(host(out)).tobytes() == raw(want).tobytes()
 
@@ -112,7 +117,12 @@ def test_reduce_store_scopes(dtype, K, tiles, tail, off):
     memory = torch.full((n + off + 64,), 7.0, dtype=tdtype(dtype), device=DEV)
     out = memory[off:off + n]
     plan.kt_weighted_reduce(-1, copies, K, weights, [out])
-    in_place = copies[0].clone()
+    torch.cuda.synchronize()
+    assert raw(host(out)).tobytes() == raw(want).tobytes() and bool((memory[:off] == 7).all()) and bool((memory[off + n:] == 7).all())
+    in_place = torch.zeros_like(copies[0])         # behind a pack: 7 and more copies take another scope there
+    plan.kt_bucket_pack(-1, copies[:1], [in_place])
+    plan.kt_weighted_reduce(-1, [in_place] + copies[1:], K, weights, [out.zero_()])
+    plan.kt_bucket_pack(-1, copies[:1], [in_place])
     plan.kt_weighted_reduce(-1, [in_place] + copies[1:], K, weights, [in_place])
     torch.cuda.synchronize()
     assert raw(host(out)).tobytes() == raw(want).tobytes() and raw(host(in_place)).tobytes() == raw(want).tobytes()
