@@ -184,12 +184,13 @@ static unsigned sgd_lds(kt_dtype dt, int64_t ntiles)
     return kt_hold_lds(dt == KT_F32 ? 4 : 5, (unsigned)sizeof(LdsTable));
 }
 
-// Bytes of gradient that an XCD takes in a run (kt_order; 0: launch order).  fp32 from 1 024 tiles on (5 412 tiles 72.9 -> 69.9 us,
-// 19 993 tiles 264.5 -> 262; 63 057 tiles 1 % either way); bf16, whose stores are system-scope ones, from 640 to 4 095 (with the
-// model copy 975 tiles 27.5 -> 27.1 us, 1 622 tiles 47.2 -> 46.5, odd tensors 1 519 tiles 49.5 -> 45.5; 9 996 tiles 257 us, 265 in runs).
+// Bytes of gradient that an XCD takes in a run (kt_order; 0: launch order).  Behind pack and reduce: fp32 from 1 024 tiles on (whole step of
+// 6 332 tiles 197 -> 192 us, 16 337 tiles of odd tensors 502 -> 494, others 0-2 %, also after 1 GiB of other reads or writes; 63 057
+// tiles 1 % either way); bf16, whose stores are system-scope ones, from 1 792 to 4 095 (1 916 tiles with the model copy 84.8 -> 83.2, 3 177 tiles of
+// odd tensors 150.7 -> 147.7; 883 to 1 320 tiles 2-5 % slower in runs, 9 996 tiles 257 us, 265 in runs).
 static int sgd_run(kt_dtype dt, int64_t ntiles)
 {
-    return (dt == KT_F32 ? ntiles >= 1024 && ntiles < 32768 : ntiles >= 640 && ntiles < 4096) ? 131072 : 0;
+    return (dt == KT_F32 ? ntiles >= 1024 && ntiles < 32768 : ntiles >= 1792 && ntiles < 4096) ? 131072 : 0;
 }
 
 }  // namespace

@@ -113,7 +113,7 @@ def run_bytes(op, dtype, K, tiles):
 
 
 # place of the order of the pieces among the kernel's arguments: up to 8 copies and above
-ORDER = {"fused_sgd": (6, 6), "fused": (7, 6), "reduce": (4, 5), "packed reduce": (4, 5)}
+ORDER = {"fused_sgd": (6, 6), "fused": (7, 6), "reduce": (4, 5), "packed reduce": (4, 5), "sgd": (6, 6)}
 
 
 def dynamic_lds(op, dtype, K, tiles):
@@ -192,6 +192,14 @@ def test_runs_of_the_fused_pass(dtype, K, tiles, split, run):
 def test_runs_of_the_reduce(dtype, K, tiles, run, packed_run):
     assert run_bytes("reduce", dtype, K, tiles) == (256, 4, run)
     assert run_bytes("packed reduce", dtype, K, tiles) == (256, 4, packed_run)
+
+
+@pytest.mark.parametrize("dtype,tiles,run", [
+    ("f32", 1023, 0), ("f32", 1024, 131072), ("f32", 32767, 131072), ("f32", 32768, 0), ("bf16", 1791, 0), ("bf16", 1792, 131072), ("bf16", 4095, 131072),
+    ("bf16", 4096, 0),
+])
+def test_runs_of_sgd_on_unpack(dtype, tiles, run):
+    assert run_bytes("sgd", dtype, 1, tiles) == (256, 4 if dtype == "f32" else 8, run)
 
 
 @pytest.mark.parametrize("dtype,K,tiles,alike", [

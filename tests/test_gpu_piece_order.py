@@ -81,7 +81,7 @@ def test_fused_pass_in_runs(dtype, K, tiles, tail):
 
 
 @pytest.mark.parametrize("dtype,tiles,tail,master", [
-    ("f32", 1024, 0, False), ("f32", 1061, 4, True), ("bf16", 640, 0, False), ("bf16", 703, 8, True), ("bf16", 4095, 0, True),
+    ("f32", 1024, 0, False), ("f32", 1061, 4, True), ("bf16", 640, 0, False), ("bf16", 1792, 0, False), ("bf16", 1855, 8, True), ("bf16", 4095, 0, True),
 ])
 def test_sgd_on_unpack_in_runs(dtype, tiles, tail, master):
     n = tiles * (16384 // (4 if dtype == "f32" else 2)) + tail
