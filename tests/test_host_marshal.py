@@ -46,9 +46,9 @@ def tensors(n):
     return [torch.zeros(5)[1:] for _ in range(n)]
 
 
-def arguments(name, K, form):
-    """Arguments in the order of the native call, and what has to arrive."""
-    got, want, k_at = [], [], None
+def arguments(name, K, form, first=True):
+    """Arguments in the order of the native call, no two alike, and what has to arrive."""
+    got, want, reals = [], [], iter([0.1, -0.2, 3.0, 0.4])
     for c in SIGNATURES[name]:
         if c in "TNPQ":
             l = tensors({"T": T, "N": NB, "P": NB * K, "Q": NB * (K - 1)}[c])
@@ -62,11 +62,11 @@ def arguments(name, K, form):
             want.append([f32(x).value for x in l])
             got.append((f32 * K)(*l) if form == "marshalled" else l)
         elif c == "f":
-            want.append(f32(0.1).value)
-            got.append(0.1)
+            got.append(next(reals))
+            want.append(f32(got[-1]).value)
         elif c == "i":
-            want.append(1)
-            got.append(True)
+            want.append(int(first))
+            got.append(first)
         else:
             want.append(77)
             got.append(77)
@@ -77,16 +77,55 @@ arguments.keep = []
 
 
 @pytest.mark.parametrize("form", ["list", "tuple", "marshalled"])
-@pytest.mark.parametrize("K", [1, 2, 64])
+@pytest.mark.parametrize("K,bucket,first", [(1, -1, True), (2, 1, False), (64, 0, True)])
 @pytest.mark.parametrize("name", list(SIGNATURES))
-def test_what_arrives(native, name, K, form):
+def test_what_arrives(native, name, K, bucket, first, form):
     calls, seen, _ = native
-    args, want = arguments(name, K, form)
+    args, want = arguments(name, K, form, first)
     if K == 1 and "Q" in SIGNATURES[name]:      # no peers: an array of one unused entry
         want[SIGNATURES[name].index("Q")] = []
     del seen[:]
-    assert getattr(calls, name)(1234, T, NB, -1, *args) == 0
-    assert seen == [(name, 1234, -1) + tuple(want)]
+    assert getattr(calls, name)(1234, T, NB, bucket, *args) == 0
+    assert seen == [(name, 1234, bucket) + tuple(want)]
+
+
+class Undecided:
+    def __bool__(self):
+        raise ValueError
+
+
+REFUSED = {
+    "K": [0, 65, -1, 2.0, "2", None, 1 << 40], "w": [[0.5], [0.5] * 3, [0.5, "x"], (vp * 2)(), (f32 * 3)(), 0.5, (x for x in (0.5, 0.5))],
+    "f": ["x", None, 1j, [0.1], 10 ** 400], "i": [Undecided(), torch.zeros(2)], "s": ["x", 1.0, object(), 1 << 80],
+    **{c: [[], None, 7, (f32 * 6)(), torch.zeros(6)] for c in "TNPQ"},
+}
+
+
+@pytest.mark.parametrize("name,at", [(n, i) for n, codes in SIGNATURES.items() for i in range(len(codes))])
+def test_what_every_call_refuses(native, name, at):
+    """One argument at a time in a form that is not taken: no call is made."""
+    calls, seen, _ = native
+    code = SIGNATURES[name][at]
+    bad = list(REFUSED[code])
+    size = {"T": T, "N": NB, "P": 2 * NB, "Q": NB}.get(code)
+    if size:
+        l = tensors(size)
+        arguments.keep.append(l)
+        bad += [l[:-1], l + l[:1], l[:-1] + [l[-1].data_ptr()], l[:-1] + [None], [l[0].as_subclass(Sub)] + l[1:], (vp * (size + 1))()]
+        if name == "fused_sgd" and at == SIGNATURES[name].rindex("T"):
+            bad.remove(None)            # no model copy
+    elif code == "w":
+        bad = [b for b in bad if b is not None]
+    for value in bad:
+        args, _ = arguments(name, 2, "list")
+        places = [i for i, c in enumerate(SIGNATURES[name]) if c != "K"] if "K" in SIGNATURES[name] else list(range(len(SIGNATURES[name])))
+        where = 0 if code == "K" else places.index(at) + ("K" in SIGNATURES[name])
+        args[where] = value
+        del seen[:]
+        assert getattr(calls, name)(1, T, NB, 0, *args) is None, (name, at, value)
+        assert seen == []
+    for bucket in (1 << 40, 1.0, "0", None):
+        assert getattr(calls, name)(1, T, NB, bucket, *arguments(name, 2, "list")[0]) is None and seen == []
 
 
 class Sub(torch.Tensor):
