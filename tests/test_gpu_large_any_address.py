@@ -33,7 +33,7 @@ def equal(dev, want, what):
 # tiles: just above a limit of the launch rules.  shift: bytes from a 64-byte boundary to the first
 # element of the gradients and parameters (the others lie elsewhere).
 @pytest.mark.parametrize("dtype,tiles,K,shift,dense", [
-    ("bf16", 32768, 8, 36, False),      # one-pass SGD: system-scope stores where a tile starts on 64 bytes
+    ("bf16", 32768, 8, 36, False),      # one-pass SGD: workgroups of 64 lanes
     ("bf16", 32768, 8, 0, False),
     ("f32", 4096, 2, 4, True),          # one-pass SGD with workgroups held per CU
     ("f32", 4096, 4, 36, False),        # and the held reduce, fused pass and SGD on unpack

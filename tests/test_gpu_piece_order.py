@@ -1,4 +1,5 @@
 """Launches whose workgroups take runs of neighbouring pieces per XCD: pieces in whole groups and left over."""
+import random
 import sys
 
 import pytest
@@ -49,7 +50,8 @@ def test_reduce_in_runs(dtype, K, tiles, tail):
 
 @pytest.mark.parametrize("dtype,K,tiles,tail", [
     ("f32", 1, 640, 0), ("f32", 4, 660, 4), ("f32", 8, 641, 0), ("bf16", 2, 641, 8), ("bf16", 8, 640, 0), ("bf16", 12, 704, 8), ("f32", 16, 641, 0),
-    ("bf16", 1, 12288, 0), ("bf16", 3, 12289, 8), ("bf16", 8, 8251, 8),       # workgroups of 64 lanes
+    ("bf16", 1, 12288, 0), ("bf16", 2, 12288, 0), ("bf16", 3, 12289, 8), ("bf16", 5, 12288, 8), ("bf16", 6, 12289, 0), ("bf16", 7, 12288, 0),
+    ("bf16", 8, 8251, 8),       # from 3 copies on workgroups of 64 lanes
 ])
 def test_one_pass_sgd_in_runs(dtype, K, tiles, tail):
     plan, weights, copies, want = inputs(dtype, K, tiles * (16384 // (4 if dtype == "f32" else 2)) + tail)
@@ -70,7 +72,7 @@ def test_one_pass_sgd_in_runs(dtype, K, tiles, tail):
 
 @pytest.mark.parametrize("dtype,K,tiles,tail", [
     ("f32", 4, 2048, 0), ("f32", 5, 2067, 4), ("f32", 6, 4097, 0), ("bf16", 5, 2049, 8), ("bf16", 6, 1024, 0), ("bf16", 8, 1061, 8),
-    ("f32", 9, 640, 4), ("bf16", 12, 673, 0),
+    ("f32", 9, 640, 4), ("bf16", 12, 673, 0), ("f32", 4, 8195, 4), ("bf16", 7, 1031, 8),
 ])
 def test_fused_pass_in_runs(dtype, K, tiles, tail):
     plan, weights, copies, want = inputs(dtype, K, tiles * (16384 // (4 if dtype == "f32" else 2)) + tail)
@@ -127,3 +129,43 @@ def test_reduce_store_scopes(dtype, K, tiles, tail, off):
     torch.cuda.synchronize()
     assert raw(host(out)).tobytes() == raw(want).tobytes() and raw(host(in_place)).tobytes() == raw(want).tobytes()
     assert bool((memory[:off] == 7).all()) and bool((memory[off + n:] == 7).all())
+
+
+# Workgroups of 64 lanes on large tensors of odd sizes with hundreds of very small ones between them (tiles of one tensor, of a few and of
+# more than their table in LDS holds), gradients, parameters, momentum and model copy at odd addresses, and (the same launches) with device-resident weights
+# and scalars, against pack, reduce and SGD on unpack of the same sets.
+@pytest.mark.parametrize("K,tiles,resident", [(3, 12288, False), (3, 12288, True), (4, 12300, False), (5, 12288, True), (5, 12301, False), (6, 12288, False),
+                                              (7, 12295, False), (7, 12288, True), (8, 8192, False), (8, 8200, True)])
+def test_one_pass_sgd_of_64_lanes_on_mixed_tiles(K, tiles, resident):
+    rng = random.Random(K * tiles + resident)
+    numels = []
+    for i in range(16):
+        numels += [tiles * 512 + rng.randint(1, 40)] + [rng.randint(1, 60) for _ in range(100)] + [rng.randint(1, 12) for _ in range(900)]
+    total = sum(numels)
+    plan = kt.Plan(numels, "bf16", 0, 2)
+    assert plan.num_tiles >= tiles and max(plan.tile_info(i)[3] for i in range(plan.num_tiles)) > 512
+    starts = [0]
+    for n in numels[:-1]:
+        starts.append(starts[-1] + n)
+    flats = [wl.flat_normal(total + 3, "bf16", 1e-3, 50, DEV)] + [wl.flat_normal(total + 3, "f32", 2e-2, 51 + i, DEV) for i in range(2)]
+    flats.append(torch.zeros(total + 3, dtype=torch.bfloat16, device=DEV))
+    views = lambda f, off: [f[off + s:off + s + n] for s, n in zip(starts, numels)]
+    grads, params, momenta, models = (views(f, off) for f, off in zip(flats, (1, 3, 2, 1)))
+    mine = [f.clone() for f in flats[1:]]
+    _, weights = kt.kt_plan_shares([1.0 - 0.05 * k for k in range(K)], 1024)
+    peers = [wl.flat_normal(plan.bucket_elems()[0], "bf16", 1e-3, 60 + k, DEV) for k in range(1, K)]
+    slot = torch.zeros_like(peers[0])
+    if resident:
+        plan.kt_plan_set_weights(weights)
+        plan.kt_plan_set_sgd(0.5, 0.05, 0.9, 5e-4)
+        plan.kt_fused_step_sgd_resident(-1, grads, peers, K, params, momenta, models, False)
+    else:
+        plan.kt_fused_step_sgd(-1, grads, peers, K, weights, 0.5, params, momenta, models, 0.05, 0.9, 5e-4, False)
+    plan.kt_bucket_pack(-1, grads, [slot])
+    plan.kt_weighted_reduce(-1, [slot] + peers, K, weights, [slot])
+    plan.kt_bucket_unpack_sgd_master(-1, [slot], 0.5, views(mine[0], 3), views(mine[1], 2), views(mine[2], 1), 0.05, 0.9, 5e-4, False)
+    torch.cuda.synchronize()
+    for got, want in zip(flats[1:], mine):          # whole memory: what lies beside the tensors as well
+        kind = torch.int32 if got.dtype == torch.float32 else torch.int16
+        assert torch.equal(got.view(kind), want.view(kind))
+    assert not torch.equal(flats[1], wl.flat_normal(total + 3, "f32", 2e-2, 51, DEV))
