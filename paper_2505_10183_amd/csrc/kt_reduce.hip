@@ -14,11 +14,11 @@ template <bool SYS, typename T> __device__ __forceinline__ void st_reduced(T *ou
 // SPLIT workgroups share a 16 KiB tile, each with KT_TILE_VECS / KT_BLOCK / SPLIT vectors of all K copies per
 // lane in flight together.  The kernel is bound by how well the memory system takes K read streams and
 // one write stream: few bytes in flight (40-96 KB per CU), in workgroups that the dispatcher starts
-// in order, so that the chip sweeps every stream over a narrow front, each XCD on runs of neighbouring
-// pieces (kt_piece), do best (reduce_shape); persistent workgroups with the same bytes in flight lose 5-10 %.  Copies and output may lie at any element
-// address; the stores are not moved to 64-byte boundaries as pack and unpack do: it costs more
-// than the 3 % of a misaligned non-temporal store stream.  INT: bf16 narrowing in integer instructions
-// (f32_to_bf16_int).  Whole tiles test the window's width whether it is zero or not: without
+// in order, so that the chip sweeps every stream over a narrow front, in part of the launches each XCD on runs of
+// neighbouring pieces (reduce_run), do best (reduce_shape); persistent workgroups with the same bytes in flight
+// lose 5-10 %.  Copies and output may lie at any element address; the stores are not moved to 64-byte boundaries as pack and
+// unpack do: it costs more than the 3 % of a misaligned non-temporal store stream.  INT: bf16 narrowing in integer
+// instructions (f32_to_bf16_int).  Whole tiles test the window's width whether it is zero or not: without
 // that test between loads and stores they are 1-3 % slower.
 template <typename T, int K, bool DEVW, int SPLIT, bool INT, bool SYS>
 __global__ __launch_bounds__(KT_BLOCK) void kt_reduce_kernel(const KtTile *tiles, const int64_t *b_elems,
@@ -242,8 +242,9 @@ hipError_t launch_reduce_k(const KtTile *tiles, const KtDeviceTables &tb, int64_
     kt_reduce_kernel<T, K, DEVW, SPLIT, INT, SYS><<<grid, block, lds, s>>>(t, b_elems, peers, outs, order, KtWindow{0, 0}, FewWeights(w))
         constexpr bool INT = sizeof(T) == 2 && K >= 6;
         if constexpr (K == 1) KT_LAUNCH(1, false, false);
-        else if (sys) { if (sh.split == 1) KT_LAUNCH(1, false, true); else KT_LAUNCH(4, INT, true); }
-        else { if (sh.split == 1) KT_LAUNCH(1, false, false); else KT_LAUNCH(4, INT, false); }
+        else if (sh.split == 1) { if (sys) KT_LAUNCH(1, false, true); else KT_LAUNCH(1, false, false); }
+        else if constexpr (K <= 4) KT_LAUNCH(4, INT, false);      // shared above and below the sizes of reduce_sys only
+        else { if (sys) KT_LAUNCH(4, INT, true); else KT_LAUNCH(4, INT, false); }
 #undef KT_LAUNCH
     });
 }

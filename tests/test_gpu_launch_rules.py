@@ -173,7 +173,8 @@ def test_lanes_and_runs_of_the_one_pass_sgd(dtype, K, tiles, lanes, run):
 @pytest.mark.parametrize("dtype,K,tiles,split,run", [
     ("f32", 4, 2047, 1, 0), ("f32", 4, 2048, 1, 131072), ("f32", 4, 8191, 1, 131072), ("f32", 4, 8192, 4, 32768), ("f32", 4, 32767, 4, 32768),
     ("f32", 4, 32768, 4, 0), ("f32", 5, 6143, 1, 131072), ("f32", 5, 6144, 4, 0), ("f32", 6, 4096, 4, 0), ("f32", 7, 20000, 4, 0), ("f32", 8, 9900, 4, 0),
-    ("f32", 3, 9000, 1, 0), ("bf16", 3, 9000, 1, 0), ("bf16", 4, 3000, 1, 131072), ("bf16", 4, 40000, 2, 131072), ("bf16", 5, 6000, 2, 131072),
+    ("f32", 3, 9000, 1, 0), ("bf16", 3, 9000, 1, 0), ("bf16", 4, 3000, 1, 131072), ("bf16", 4, 40000, 2, 131072), ("bf16", 5, 5119, 1, 131072),
+    ("bf16", 5, 5120, 2, 0), ("bf16", 5, 70000, 2, 0),
     ("bf16", 6, 1023, 2, 0), ("bf16", 6, 1024, 2, 131072), ("bf16", 7, 20000, 2, 131072), ("bf16", 8, 20000, 2, 0),
     ("f32", 9, 639, 4, 0), ("f32", 9, 640, 4, 65536), ("f32", 9, 4095, 4, 65536), ("f32", 9, 4096, 4, 0), ("bf16", 10, 4096, 4, 0),
     ("bf16", 12, 5000, 4, 65536),
