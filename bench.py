@@ -32,8 +32,8 @@ HBM_PEAK_GBS = 8000.0
 # sources the figure is reported as null until the counters are taken again.
 KERNEL_SOURCES = ("kt_internal.h", "kt_device.h", "kt_sgd_device.h", "kt_pack_unpack.hip", "kt_reduce.hip", "kt_fused.hip",
                   "kt_sgd.hip", "kt_fused_sgd.hip")
-TRAFFIC_SOURCES_SHA = "25716f30f410676e"
-TRAFFIC_BYTES = {"decoder_1p3b": 23705710893, "vit_b16": 3121828035}
+TRAFFIC_SOURCES_SHA = "15fdb01adb9a6958"
+TRAFFIC_BYTES = {"decoder_1p3b": 23705903405, "vit_b16": 3118121520}
 
 
 def measured_traffic(workload):

@@ -604,7 +604,7 @@ template <> __device__ __forceinline__ uint16_t narrow<uint16_t>(float a) { retu
 // sweeps every stream over a front of half a megabyte or one.  The memory system takes a mix of reads and few writes 3-6 %
 // faster that way (flat buffers, 8 reads and one write, two workgroups of 4 KiB of each per CU: 5.80 TB/s in
 // launch order, 6.12 with runs of 16 KiB, 6.32 with 64 KiB and more); reads alone and copies are even, and which XCD has which
-// run makes no difference.  Launches of few bytes in flight are slower with runs instead, for as long as they last, when 512 MiB or more
+// run makes no difference.  Launches of few bytes in flight are slower with runs instead, for as long as they last, when 320 MiB or more
 // of ordinary reads or writes of other data came before them (non-temporal reads do not count; one pass over the same buffers ends
 // it): each kernel's rule says where runs hold in both states.  `order`: pieces in whole groups in the upper bits, g in the lower three; 0 is launch
 // order.  The remainder of a launch keeps the launch order.

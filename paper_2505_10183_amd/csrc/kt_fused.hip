@@ -278,8 +278,9 @@ template <typename T> KtShape fused_shape(int K, int64_t nt)
 // Bytes of a copy that an XCD takes in a run (kt_order; 0: launch order), where launches with runs are no slower after 512 MiB and more
 // of ordinary reads or writes of other data, as a backward pass makes.  In us, launch order -> runs on the buffers of the call before / after
 // 1 GiB of other reads:
-//   bf16   4, 6 and 7 copies 128 KiB, 5 on whole tiles only: K = 4 94 645 tiles 1 285 -> 1 228 / 1 298 -> 1 254, K = 5 half
-//          tiles 19 772 tiles 314 -> 308 / 295 -> 306, K = 6 32 824 tiles 644 -> 623 / 640 -> 623, K = 7 93 682 tiles 2 155 -> 2 073 / 2 144 -> 2 075 (64 KiB: even)
+//   bf16   4, 6 and 7 copies 128 KiB, 5 on whole tiles only: K = 4 94 645 tiles 1 285 -> 1 228 / 1 298 -> 1 254, K = 6 32 824 tiles
+//          644 -> 623 / 640 -> 623, K = 7 93 682 tiles 2 155 -> 2 073 / 2 144 -> 2 075 (64 KiB: even); K = 5 on half tiles 19 772 tiles
+//          314 -> 308 / 295 -> 306
 //   fp32   4 copies 32 KiB on quarter tiles, 4 workgroups per CU, up to 32 767 tiles: 8 618 tiles 116.8 -> 112.8 / 117.9 -> 116.4, 19 993
 //          tiles 267 -> 257 / 264 -> 262, 44 031 tiles 570 -> 575 / 559 -> 569, 92 895 tiles 2 and 4 % slower; 4 and 5 copies 128 KiB where whole tiles
 //          are held (K = 5 2 587 tiles 44.0 -> 43.1 / 46.4 -> 45.6)

@@ -350,7 +350,7 @@ constexpr unsigned FSGD_LDS_2 = kt_hold_lds(2, sizeof(FsgdLds)), FSGD_LDS_4 = kt
 // Runs (kt_order) of 64 KiB of gradient per XCD for fp32 of 4 and more copies, else of 128, for launches that hold nothing, from 640
 // tiles on: fp32 K = 4 2 587 tiles 58.7 -> 56.8 us on the buffers of the call before, 59.6 -> 59.0 after other reads, bf16 K = 6 1 294 tiles
 // 57.0 -> 55.7 / 59.6 -> 57.8.  Held launches gain 1-5 % from runs on the buffers of the call before and lose up to 15 %, for the
-// whole launch, after 512 MiB and more of ordinary reads or writes of other data, as a backward pass makes (1.3B set in runs 7 474 / 7 912
+// whole launch, after 320 MiB and more of ordinary reads or writes of other data, as a backward pass makes (1.3B set in runs 7 474 / 7 912
 // us, in launch order 7 225 / 7 260; fp32 K = 4 19 375 tiles 414 -> 398 / 394 -> 425, K = 7 44 031 tiles 1 313 -> 1 269 / 1 253 -> 1 307; bf16
 // K = 6 94 645 tiles 3 856 -> 3 895 / 3 793 -> 4 378); one pass over the set ends that state.  Not below
 // 640 tiles, where the few slow tiles that hold many tensors come to lie on one XCD (MobileNetV2, 547 tiles 13.2 -> 13.5 us; 197
