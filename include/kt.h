@@ -58,14 +58,18 @@
  *    read in all copies together; kt_fused_step_sgd of 11 (F32) and more copies
  *    from 1.5 GiB, of 14 (BF16) from 3 GiB.  1.2 us in every 12 us, or 6 % of a
  *    period of 14 to 24 us that grows with the number of copies.
- *  - Other large launches ask for more LDS than they use, so that only 2 to 5 of
- *    their workgroups share a CU (22 to 52 KiB of its LDS stay free):
+ *  - Other large launches ask for more LDS than they use, so that only 2 to 6 of
+ *    their workgroups share a CU (17 to 52 KiB of its LDS stay free):
  *    kt_fused_step and kt_weighted_reduce of 3 and more copies without bursts
  *    from 16 to 128 MiB per copy on, unpack fused with SGD from 64 MiB, and
  *    kt_fused_step_sgd from 16 to 64 MiB.
  *  - The environment variable KT_STORE_WINDOW_NS, read once per process, sets the
  *    period of the bursts in nanoseconds; 0, for programs whose other kernels
  *    run beside these calls, switches both the bursts and the LDS requests off.
+ *    Results do not depend on it.
+ *  - kt_weighted_reduce orders its workgroups and its stores by whether the plan's
+ *    launch before was kt_bucket_pack, which brings the buckets through the chip;
+ *    the same holds for calls recorded into a graph, in the order of recording.
  *    Results do not depend on it.
  *  - Streams passed to device calls should outlive the plan.  If the stream of
  *    an earlier call has been destroyed, the library waits for the whole
